@@ -57,6 +57,7 @@ struct pg_ctx {
     float **d_gs = nullptr;
     std::vector<const float *> gs_cached;
     bool mcol_stage = true;  // matrix-core Q-sweep: Phat of a tile's row block staged in LDS
+    bool lazy = true;  // runs write the parameters every second round where that pays
     bool profiling = false;
     // Passes alternate direction through the parameters: each starts where the one before it
     // (also the last one of an earlier call) ended, on data still in the memory-side cache.
@@ -144,6 +145,26 @@ constexpr int kPrefetchSteps = 1;
 constexpr int kMfmaRowPrefetch = 1;
 constexpr int kMfmaColPrefetch = 2;
 
+// Whether a run writes the parameters every second round only (see run_lazy).
+// Measured on VGG-16 shapes, ring of 16, ten rounds a call: rank 1 (2 stacked columns) 5.55 -> 4.50 ms;
+// rank 2 (4 columns) gains 7 % with 4 rows per lane group and loses 12 % with 8, whose coefficients
+// for two updates no longer fit the registers.
+constexpr int kLazyCols = 4;
+constexpr size_t kLazyColLds = 64 * 1024;
+size_t lazy_col_lds(const ColClass &cc) {
+    return (size_t)(cc.max_rows + 2) * cc.RC * (sizeof(float) + sizeof(double)) + 16;
+}
+bool runs_lazily(const Plan &P) {
+    if (P.light || P.steps != 1 || P.max_groups > 1) return false;
+    // the second Phat buffer lies in the column-by-column Gram-Schmidt's scratch
+    if (P.ws_ph - P.ws_pd < P.pstate_floats * sizeof(float)) return false;
+    for (const RowClass &rc : P.row_classes)
+        if (rc.RC > kLazyCols || rc.vec) return false;
+    for (const ColClass &cc : P.col_classes)
+        if (cc.RC > kLazyCols || cc.vec || lazy_col_lds(cc) > kLazyColLds) return false;
+    return true;
+}
+
 struct Launcher {
     pg_ctx *c;
     hipStream_t st;
@@ -154,6 +175,9 @@ struct Launcher {
     // vectors (length p) the sweeps and the update read, when they are not the state / Phat
     const float *rhs = nullptr;
     const float *lhs = nullptr;
+    // the update before the latest one, for passes that apply two or peek (see run_lazy)
+    const float *phat1 = nullptr;
+    const float *q1 = nullptr;
     bool quiet = false;  // never record timing events (creating an event allocates)
     int status = PG_OK;
 
@@ -165,6 +189,9 @@ struct Launcher {
     double *qw() const { return (double *)(ws + c->plan.ws_qw); }
     double *pdb() const { return (double *)(ws + c->plan.ws_pd); }
     float *ph() const { return (float *)(ws + c->plan.ws_ph); }
+    float *ph2() const { return (float *)(ws + c->plan.ws_pd); }  // runs only (r <= 8 there: scratch unused)
+    float *ph_out = nullptr;  // where orth_p leaves Phat, when not in ph()
+    float *phw() const { return ph_out ? ph_out : ph(); }
     int32_t *flags() const { return (int32_t *)(ws + c->plan.ws_flag); }
     double *gpart() const { return (double *)(ws + c->plan.ws_gpart); }
 
@@ -203,10 +230,10 @@ struct Launcher {
                     tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
             else if (c->plan.light)
                 row_kernel<RC, kRowsPerGroupLight, kPrefetchSteps, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
-                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
+                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, nullptr, nullptr);
             else
                 row_kernel<RC, kRowsPerGroup, kPrefetchSteps, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
-                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
+                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, nullptr, nullptr);
         } else if (rc.mfma) {
 #define PG_MROW(VV) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD> \
                 <<<dim3((unsigned)n), dim3(kThreads), kMrowLdsBytes, st>>>( \
@@ -270,6 +297,27 @@ struct Launcher {
         }
         turn();
     }
+    // Row pass of a run that writes every second round (narrow classes only): PEND as in row_body.
+    template <int PEND, bool SWP>
+    void rows_pending() {
+        if (status) return;
+        const auto &classes = c->plan.row_classes;
+        for (size_t k = 0; k < classes.size(); ++k) {
+            const RowClass &rc = classes[c->reverse ? classes.size() - 1 - k : k];
+            if (rc.tiles.empty()) continue;
+            const int n = (int)rc.tiles.size();
+            begin(SWP ? K_UPDATE_SWEEP_P : K_UPDATE, rc.elems * 4.0 * (PEND == kPeek ? 1.0 : 2.0));
+#define PG_ROWP(RC, M) row_kernel<RC, M, kPrefetchSteps, true, SWP, false, PEND><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
+                c->d_row_tiles + rc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, phat1, q1)
+            if (rc.RC == 1) PG_ROWP(1, kRowsPerGroup);
+            else if (rc.RC == 2) PG_ROWP(2, kRowsPerGroup);
+            else PG_ROWP(4, kRowsPerGroupLight);
+#undef PG_ROWP
+            check();
+            end();
+        }
+        turn();
+    }
     // The next pass walks the parameters the other way.
     void turn() {
         if (c->alternate) c->reverse ^= 1;
@@ -294,11 +342,15 @@ struct Launcher {
                               (size_t)(kThreads / 64 - 1) * 64 * 4 * sizeof(double));
 #define PG_COL(VV) col_kernel<VV, RC, U><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
             c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, \
-            c->d_xs, left(), qw())
+            c->d_xs, left(), qw(), nullptr, nullptr)
         if constexpr (RC < kWideCols) {
             if (cc.vec)
                 vec_col_kernel<RC><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw());
+            else if (RC <= kLazyCols && phat1)
+                col_kernel<0, RC <= kLazyCols ? RC : 1, U, true><<<dim3((unsigned)n), dim3(kThreads),
+                                                                 std::max(lds, lazy_col_lds(cc)), st>>>(
+                    c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw(), phat1, q1);
             else
                 PG_COL(0);
         } else if (c->plan.mfma_cols) {
@@ -350,12 +402,12 @@ struct Launcher {
         const Plan &P = c->plan;
         if (P.orth_tiles.empty()) {
             orth_gram_kernel<NT, RMAX><<<dim3((unsigned)P.els.size()), dim3(NT), 0, st>>>(
-                c->d_els, pw(), ph(), flags());
+                c->d_els, pw(), phw(), flags());
         } else {
             dim3 grid((unsigned)P.orth_tiles.size());
             orth_gram_part_kernel<NT, RMAX><<<grid, dim3(NT), 0, st>>>(c->d_orth, c->d_els, pw(), gpart(), nullptr);
             orth_gram_apply_kernel<NT, RMAX><<<grid, dim3(NT), 0, st>>>(c->d_orth, c->d_els, pw(), gpart(),
-                                                                        ph(), flags(), nullptr);
+                                                                        phw(), flags(), nullptr);
         }
     }
     void orth_p() {
@@ -414,11 +466,11 @@ struct Launcher {
         check();
         end();
     }
-    void combine_q() {
+    void combine_q(float *hist = nullptr) {
         if (status || c->plan.comb_tiles.empty()) return;
         begin(K_COMBINE_Q, 0.0);
         comb_kernel<<<dim3((unsigned)c->plan.comb_tiles.size()), dim3(kThreads), 0, st>>>(
-            c->d_comb, c->d_els, qw(), flags(), qstate);
+            c->d_comb, c->d_els, qw(), flags(), qstate, hist);
         check();
         end();
     }
@@ -461,6 +513,52 @@ int prepare_grads(pg_ctx *c, const float *const *worker_grads, hipStream_t st) {
     return PG_OK;
 }
 
+// All rounds of a run with s = 1, writing the parameters every second round.  The passes are
+// bound by memory, and with few stacked columns the vector ALUs have time to spare, so a pass may
+// read parameters that are one update behind and apply that update to the values in registers
+// (rounded as it would be if stored: results are bit for bit those of the plain run).
+//   round t odd:   P-sweep fused with the two pending updates, stored; Q-sweep on what was stored
+//   round t even:  P-sweep and Q-sweep with the one pending update in registers, nothing written
+// 20 bytes per parameter for two rounds instead of 24, and one pass in two fewer whose write-backs
+// the next pass has to wait for.
+void run_lazy(Launcher &L, int rounds) {
+    float *const buf[2] = {L.ph(), L.ph2()};
+    for (int t = 1; t <= rounds; ++t) {
+        float *now = buf[(rounds - t) & 1], *before = buf[(rounds - t + 1) & 1];  // the last round's in ph()
+        const bool behind = (t & 1) == 0;  // X lags one update during this round
+        L.phat1 = L.q1 = nullptr;
+        if (t == 1) {
+            L.rows(false, true);
+        } else if (behind) {
+            L.lhs = before;
+            L.rows_pending<kPeek, true>();
+        } else {
+            L.lhs = before;
+            L.phat1 = now;  // two rounds ago
+            L.q1 = L.uq();
+            L.rows_pending<kApplyTwo, true>();
+        }
+        L.ph_out = now;
+        L.orth_p();
+        L.lhs = now;
+        L.phat1 = behind ? before : nullptr;
+        L.q1 = behind ? L.qstate : nullptr;
+        L.sweep_q();
+        L.combine_q(behind ? L.uq() : nullptr);
+    }
+    L.phat1 = L.q1 = nullptr;
+    L.lhs = buf[0];
+    if (rounds & 1) {
+        L.rows(true, false);
+    } else {
+        L.phat1 = buf[1];
+        L.q1 = L.uq();
+        L.rows_pending<kApplyTwo, false>();
+    }
+    L.phat1 = L.q1 = L.lhs = nullptr;
+    L.ph_out = nullptr;
+}
+
 int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *workspace,
                void *hip_stream, int rounds, bool fuse, bool may_allocate = true) {
     hipStream_t st = (hipStream_t)hip_stream;
@@ -476,6 +574,10 @@ int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *wor
     // Measured: with the passes that write (update + sweep) walking forwards and the Q-sweeps
     // backwards a run of fused rounds is 4 % faster than its mirror image, so a run starts forwards.
     if (fuse) c->reverse = 0;
+    if (c->lazy && fuse && rounds > 1 && runs_lazily(c->plan)) {
+        run_lazy(L, rounds);
+        return L.status;
+    }
     for (int t = 0; t < rounds; ++t) {
         for (int step = 0; step < s; ++step) {
             // the first product of a later round was already formed by the fused update pass
@@ -523,6 +625,7 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     if (const char *e = getenv("PG_MFMA_ROWS")) tune.mfma_rows = atoi(e) != 0;
     if (const char *e = getenv("PG_MFMA_COLS")) tune.mfma_cols = atoi(e) != 0;
     if (const char *e = getenv("PG_MCOL_STAGE")) c->mcol_stage = atoi(e) != 0;
+    if (const char *e = getenv("PG_LAZY")) c->lazy = atoi(e) != 0;
     if (const char *e = getenv("PG_LIGHT")) tune.light = atoi(e) != 0;
     if (const char *e = getenv("PG_VEC_KERNELS")) tune.vec_kernels = std::min(2, std::max(0, atoi(e)));
     if (const char *e = getenv("PG_MFMA_ROW_COLS")) tune.mfma_row_cols = atoi(e) <= 8 ? 8 : 16;

@@ -114,13 +114,22 @@ __device__ __forceinline__ void group_sum_all(double (&v)[N], int width) {
 //   UPDATE: X[row, c] -= sum_j coef_j * Phat_j[row] * Q'_j[c] (Eq. (2) summed over the edges)
 //   both  : the update, then the next round's sweep on the updated values -- the next
 //           round's right-hand side is exactly the Q' just applied (warm start).
+//   PEND  : which updates `UPDATE` applies and whether it stores the result.  A run of rounds
+//           writes the parameters every second round only (see run_lazy in the launch code):
+//           kApply -- the latest update, stored; kPeek -- the latest update, in registers only;
+//           kApplyTwo -- the update before (phat1, q1), rounded, then the latest one, stored.
+//           Every element goes through the same operations and roundings as with kApply alone.
 // ---------------------------------------------------------------------------------------
-template <int V, int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD>
+enum Pending { kApply = 0, kPeek = 1, kApplyTwo = 2 };
+
+template <int V, int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND>
 __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                                          const ColDesc *__restrict__ cols, float *X,
                                          const float *__restrict__ qstate,
                                          const float *__restrict__ phat, double *__restrict__ pw,
-                                         const float *Gp, double eta) {
+                                         const float *Gp, double eta, const float *__restrict__ phat1,
+                                         const float *__restrict__ q1) {
+    constexpr bool TWO = UPDATE && PEND == kApplyTwo;
     typedef typename VecT<V>::T vec;
     const int lane = threadIdx.x;
     const int lpr = pd.lpr;
@@ -134,14 +143,18 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
     const int row_end = t.row0 + t.nrows;
     const int step = lpr * V;
 
-    const float *qcol[RC];
-    const float *phc[RC];
+    const float *qcol[RC], *qcol1[TWO ? RC : 1];
+    const float *phc[RC], *phc1[TWO ? RC : 1];
     float coef[RC];
 #pragma unroll
     for (int j = 0; j < RC; ++j) {
         const ColDesc cd = cols[pd.col0 + min(j, R - 1)];
         qcol[j] = qstate + cd.q_off;
         phc[j] = phat + cd.ph_off;
+        if (TWO) {
+            qcol1[TWO ? j : 0] = q1 + cd.q_off;
+            phc1[TWO ? j : 0] = phat1 + cd.ph_off;
+        }
         coef[j] = (j < R) ? cd.coef : 0.0f;
     }
 
@@ -157,13 +170,15 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
             xrow[m] = X + (int64_t)rowi[m] * pd.ld;
             grow[m] = GRAD ? Gp + (int64_t)rowi[m] * pd.ld : nullptr;
         }
-        double cp[M][RC];
+        double cp[M][RC], cp1[TWO ? M : 1][RC];
         if (UPDATE) {
 #pragma unroll
             for (int m = 0; m < M; ++m)
 #pragma unroll
-                for (int j = 0; j < RC; ++j)
+                for (int j = 0; j < RC; ++j) {
                     cp[m][j] = (double)coef[j] * (double)ldg1(phc[j] + rowi[m]);
+                    if (TWO) cp1[TWO ? m : 0][j] = (double)coef[j] * (double)ldg1(phc1[TWO ? j : 0] + rowi[m]);
+                }
         }
         double acc[M][RC];
 #pragma unroll
@@ -171,9 +186,13 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
 #pragma unroll
             for (int j = 0; j < RC; ++j) acc[m][j] = 0.0;
 
-        auto load = [&](int c, vec(&xv)[M], vec(&qv)[RC], vec(&gv)[GRAD ? M : 1]) {
+        constexpr int NQ = TWO ? 2 * RC : RC;
+        auto load = [&](int c, vec(&xv)[M], vec(&qv)[NQ], vec(&gv)[GRAD ? M : 1]) {
 #pragma unroll
-            for (int j = 0; j < RC; ++j) qv[j] = ldg<V>(qcol[j] + c);
+            for (int j = 0; j < RC; ++j) {
+                qv[j] = ldg<V>(qcol[j] + c);
+                if (TWO) qv[TWO ? RC + j : 0] = ldg<V>(qcol1[TWO ? j : 0] + c);
+            }
 #pragma unroll
             for (int m = 0; m < M; ++m) xv[m] = ldg<V>(xrow[m] + c);
             if (GRAD) {
@@ -181,10 +200,10 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                 for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldg<V>(grow[m] + c);
             }
         };
-        auto process = [&](int c, vec(&xv)[M], vec(&qv)[RC], vec(&gv)[GRAD ? M : 1]) {
-            double qd[RC][V];
+        auto process = [&](int c, vec(&xv)[M], vec(&qv)[NQ], vec(&gv)[GRAD ? M : 1]) {
+            double qd[NQ][V];
 #pragma unroll
-            for (int j = 0; j < RC; ++j)
+            for (int j = 0; j < NQ; ++j)
 #pragma unroll
                 for (int v = 0; v < V; ++v) qd[j][v] = (double)qv[j][v];
 #pragma unroll
@@ -195,13 +214,18 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                 if (UPDATE) {
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
+                        if (TWO) {
+#pragma unroll
+                            for (int j = 0; j < RC; ++j) xd[v] = fma(-cp1[TWO ? m : 0][j], qd[TWO ? RC + j : 0][v], xd[v]);
+                            xd[v] = (double)(float)xd[v];
+                        }
 #pragma unroll
                         for (int j = 0; j < RC; ++j) xd[v] = fma(-cp[m][j], qd[j][v], xd[v]);
                         if (GRAD) xd[v] = fma(-eta, (double)gv[GRAD ? m : 0][v], xd[v]);
                         xv[m][v] = (float)xd[v];
                         xd[v] = (double)xv[m][v];  // the sweep uses the stored (rounded) value
                     }
-                    if (ok[m]) stg<V>(xrow[m] + c, xv[m]);
+                    if (PEND != kPeek && ok[m]) stg<V>(xrow[m] + c, xv[m]);
                 }
                 if (SWEEP) {
 #pragma unroll
@@ -219,7 +243,7 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
             // compile-time after unrolling).  PG_FENCE keeps the compiler from sinking a prefetch
             // below the arithmetic it overlaps.
             constexpr int NB = D + 1;
-            vec xb[NB][M], qb[NB][RC], gb[NB][GRAD ? M : 1];
+            vec xb[NB][M], qb[NB][NQ], gb[NB][GRAD ? M : 1];
             const int nsteps = (c_end - c0 - 1) / step + 1;
 #pragma unroll
             for (int k = 0; k < D; ++k)
@@ -264,23 +288,29 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
 // floats next to each other in memory, so lanes take consecutive rows (coalesced) instead of one
 // lane group per row; every product is a scalar multiple, with the same operations in the same
 // order as the general body performs for q = 1.
-template <int RC, bool UPDATE, bool SWEEP, bool GRAD>
+template <int RC, bool UPDATE, bool SWEEP, bool GRAD, int PEND>
 __device__ __forceinline__ void vec_row_body(const RowTile &t, const PairDesc &pd,
                                              const ColDesc *__restrict__ cols, float *X,
                                              const float *__restrict__ qstate,
                                              const float *__restrict__ phat, double *__restrict__ pw,
-                                             const float *Gp, double eta) {
+                                             const float *Gp, double eta, const float *__restrict__ phat1,
+                                             const float *__restrict__ q1) {
+    constexpr bool TWO = UPDATE && PEND == kApplyTwo;
     constexpr int U = 4;  // rows in flight per lane
     const int R = pd.R;
     const int row_end = t.row0 + t.nrows;
-    double qd[RC];
-    const float *phc[RC];
+    double qd[RC], qd1[TWO ? RC : 1];
+    const float *phc[RC], *phc1[TWO ? RC : 1];
     float coef[RC];
 #pragma unroll
     for (int j = 0; j < RC; ++j) {
         const ColDesc cd = cols[pd.col0 + min(j, R - 1)];
         qd[j] = (double)ldg1(qstate + cd.q_off);
         phc[j] = phat + cd.ph_off;
+        if (TWO) {
+            qd1[TWO ? j : 0] = (double)ldg1(q1 + cd.q_off);
+            phc1[TWO ? j : 0] = phat1 + cd.ph_off;
+        }
         coef[j] = (j < R) ? cd.coef : 0.0f;
     }
     for (int base = t.row0 + (int)threadIdx.x; base < row_end; base += 64 * U) {
@@ -294,20 +324,29 @@ __device__ __forceinline__ void vec_row_body(const RowTile &t, const PairDesc &p
             x[u] = (double)ldg1(X + row[u]);
         }
         if (UPDATE) {
-            float ph[U][RC], g[U];
+            float ph[U][RC], ph1[TWO ? U : 1][RC], g[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
 #pragma unroll
-                for (int j = 0; j < RC; ++j) ph[u][j] = ldg1(phc[j] + row[u]);
+                for (int j = 0; j < RC; ++j) {
+                    ph[u][j] = ldg1(phc[j] + row[u]);
+                    if (TWO) ph1[TWO ? u : 0][j] = ldg1(phc1[TWO ? j : 0] + row[u]);
+                }
                 g[u] = GRAD ? ldg1(Gp + row[u]) : 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (TWO) {
+#pragma unroll
+                    for (int j = 0; j < RC; ++j)
+                        x[u] = fma(-((double)coef[j] * (double)ph1[TWO ? u : 0][j]), qd1[TWO ? j : 0], x[u]);
+                    x[u] = (double)(float)x[u];
+                }
 #pragma unroll
                 for (int j = 0; j < RC; ++j) x[u] = fma(-((double)coef[j] * (double)ph[u][j]), qd[j], x[u]);
                 if (GRAD) x[u] = fma(-eta, (double)g[u], x[u]);
                 const float xf = (float)x[u];
-                if (ok[u]) *(PG_GLOBAL float *)(X + row[u]) = xf;
+                if (PEND != kPeek && ok[u]) *(PG_GLOBAL float *)(X + row[u]) = xf;
                 x[u] = (double)xf;  // the sweep uses the stored (rounded) value
             }
         }
@@ -324,21 +363,22 @@ __device__ __forceinline__ void vec_row_body(const RowTile &t, const PairDesc &p
 // One wavefront per tile; `reverse` walks the tile list backwards so that a pass can start on
 // the data the previous pass touched last (still resident in the memory-side cache).
 //   GRAD  : (with UPDATE) also subtract eta * G[row, c]: the update step of Algorithm 1 in one pass.
-template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD>
+template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND = kApply>
 __global__ void __launch_bounds__(kRowThreads)
 row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
            const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
            float *const *__restrict__ xs, const float *__restrict__ qstate,
            const float *__restrict__ phat, double *__restrict__ pw,
-           const float *const *__restrict__ gs, double eta) {
+           const float *const *__restrict__ gs, double eta,
+           const float *__restrict__ phat1, const float *__restrict__ q1) {
     const RowTile t = tiles[tile_index(ntiles, reverse)];
     const PairDesc pd = pairs[t.pair];
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
-    if (pd.q == 1) vec_row_body<RC, UPDATE, SWEEP, GRAD>(t, pd, cols, X, qstate, phat, pw, Gp, eta);
-    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD>(t, pd, cols, X, qstate, phat, pw, Gp, eta);
-    else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD>(t, pd, cols, X, qstate, phat, pw, Gp, eta);
-    else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD>(t, pd, cols, X, qstate, phat, pw, Gp, eta);
+    if (pd.q == 1) vec_row_body<RC, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
 }
 
 // The row passes over vector layers alone (one wavefront per tile): the same arithmetic as the
@@ -355,7 +395,7 @@ vec_row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     const PairDesc pd = pairs[t.pair];
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
-    vec_row_body<RC, UPDATE, SWEEP, GRAD>(t, pd, cols, X, qstate, phat, pw, Gp, eta);
+    vec_row_body<RC, UPDATE, SWEEP, GRAD, kApply>(t, pd, cols, X, qstate, phat, pw, Gp, eta, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1067,12 +1107,15 @@ sgd_only_kernel(const int32_t *__restrict__ pair_ids, const PairDesc *__restrict
 // arithmetic of the current U rows.
 //   Qw[blk][j][c] = sum_{row in blk} X[row, c] * Phat_j[row]   (Algorithm 2, even iteration:
 //   the product with X^T, for every incident edge in one read of X_i)
+//   PEEK: X is one update (phat1, q1) behind; the update is applied to the loaded values,
+//   rounded as the row kernels round it, and not stored.
 // ---------------------------------------------------------------------------------------
-template <int V, int RC, int U>
+template <int V, int RC, int U, bool PEEK>
 __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
                                          const ColDesc *__restrict__ cols, const float *X,
                                          const float *__restrict__ phat, double *__restrict__ qw,
-                                         float *sT) {
+                                         float *sT, const float *__restrict__ phat1,
+                                         const float *__restrict__ q1) {
     typedef typename VecT<V>::T vec;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lg = pd.lg;
@@ -1097,6 +1140,22 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
 #pragma unroll
         for (int j = 0; j < RC; ++j) sT[rr * RC + j] = (j < R && rr < nrows) ? ldg1(src[j] + rr) : 0.0f;
     }
+    // the pending update: coef * Phat1 of the block as doubles behind sT, Q' of this lane's columns in
+    // registers
+    double *sC = reinterpret_cast<double *>(sT + (((nrows + 1) * RC + 1) & ~1));
+    double q1d[PEEK ? RC : 1][V];
+    if (PEEK) {
+#pragma unroll
+        for (int j = 0; j < RC; ++j) {
+            const ColDesc cd = cols[pd.col0 + min(j, R - 1)];
+            const double cf = (j < R) ? (double)cd.coef : 0.0;
+            for (int rr = threadIdx.x; rr <= nrows; rr += kThreads)
+                sC[rr * RC + j] = cf * (double)ldg1(phat1 + cd.ph_off + rb + min(rr, nrows - 1));
+            const vec qv = ldg<V>(q1 + cd.q_off + c);
+#pragma unroll
+            for (int v = 0; v < V; ++v) q1d[PEEK ? j : 0][v] = (double)qv[v];
+        }
+    }
 
     double acc[RC][V];
 #pragma unroll
@@ -1119,6 +1178,16 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
             double xd[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) xd[v] = (double)xv[u][v];
+            if (PEEK) {
+#pragma unroll
+                for (int j = 0; j < RC; ++j) {
+                    const double cp = sC[li + j];
+#pragma unroll
+                    for (int v = 0; v < V; ++v) xd[v] = fma(-cp, q1d[PEEK ? j : 0][v], xd[v]);
+                }
+#pragma unroll
+                for (int v = 0; v < V; ++v) xd[v] = (double)(float)xd[v];
+            }
 #pragma unroll
             for (int j = 0; j < RC; ++j) {
                 const double td = (double)sT[li + j];
@@ -1180,23 +1249,23 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
 }
 
 // V = 0: tiles of any vector width (few stacked columns); V = 1, 2, 4: one width only.
-template <int V, int RC, int U>
+template <int V, int RC, int U, bool PEEK = false>
 __global__ void __launch_bounds__(kThreads)
 col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
            const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
            float *const *__restrict__ xs, const float *__restrict__ phat,
-           double *__restrict__ qw) {
+           double *__restrict__ qw, const float *__restrict__ phat1, const float *__restrict__ q1) {
     extern __shared__ double smem[];  // [blk_rows][RC] Phat floats, then reused for the reduction
     float *sT = reinterpret_cast<float *>(smem);
     const ColTile t = tiles[tile_index(ntiles, reverse)];
     const PairDesc pd = pairs[t.pair];
     const float *X = xs[pd.worker] + pd.x_off;
     if constexpr (V != 0) {
-        col_body<V, RC, U>(t, pd, cols, X, phat, qw, sT);
+        col_body<V, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     } else {
-        if (pd.V == 4) col_body<4, RC, U>(t, pd, cols, X, phat, qw, sT);
-        else if (pd.V == 2) col_body<2, RC, U>(t, pd, cols, X, phat, qw, sT);
-        else col_body<1, RC, U>(t, pd, cols, X, phat, qw, sT);
+        if (pd.V == 4) col_body<4, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        else if (pd.V == 2) col_body<2, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        else col_body<1, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     }
 }
 
@@ -1556,16 +1625,17 @@ orth_gram_apply_kernel(const OrthTile *__restrict__ tiles, const EdgeLayerDesc *
 
 // Per (edge, layer): Q' = (sum of worker a's row-block partials) - (worker b's), rounded to
 // float into the state buffer; the column of a dropped Phat keeps its old state.
-// (Algorithm 2: v_ij <- p_j - p_i, unnormalised.)
+// (Algorithm 2: v_ij <- p_j - p_i, unnormalised.)  `hist` (may be null) receives the state as it was.
 __global__ void __launch_bounds__(kThreads)
 comb_kernel(const CombTile *__restrict__ tiles, const EdgeLayerDesc *__restrict__ els,
             const double *__restrict__ qw, const int32_t *__restrict__ flags,
-            float *__restrict__ qstate) {
+            float *__restrict__ qstate, float *__restrict__ hist) {
     const CombTile t = tiles[blockIdx.x];
     const EdgeLayerDesc d = els[t.el];
     const int64_t idx = (int64_t)t.first + threadIdx.x;  // k * q + c
     if (idx >= (int64_t)d.r * d.q) return;
     const int k = (int)(idx / d.q);
+    if (hist) hist[d.q_off + idx] = qstate[d.q_off + idx];
     if (flags[d.flag_off + k]) return;
     // four interleaved running sums keep several loads in flight; the order is fixed
     double sa[4] = {0.0, 0.0, 0.0, 0.0}, sb[4] = {0.0, 0.0, 0.0, 0.0};
