@@ -155,7 +155,7 @@ size_t lazy_col_lds(const ColClass &cc) {
     return (size_t)(cc.max_rows + 2) * cc.RC * (sizeof(float) + sizeof(double)) + 16;
 }
 bool runs_lazily(const Plan &P) {
-    if (P.light || P.steps != 1 || P.max_groups > 1) return false;
+    if (!P.stream || P.light || P.steps != 1 || P.max_groups > 1) return false;
     // the second Phat buffer lies in the column-by-column Gram-Schmidt's scratch
     if (P.ws_ph - P.ws_pd < P.pstate_floats * sizeof(float)) return false;
     for (const RowClass &rc : P.row_classes)
@@ -220,8 +220,16 @@ struct Launcher {
         if (hipGetLastError() != hipSuccess) status = PG_ERR_DEVICE;
     }
 
+    // NT: large parameter sets, see Plan::stream.  The narrow sweeps read through the caches even
+    // there (their next pass starts on what they left), the wide ones do not: X would push the
+    // operand vectors, which every tile reads again, out of the L2 caches.
     template <int RC, bool UPD, bool SWP, bool GRAD = false>
     void row_launch(const RowClass &rc) {
+        if (c->plan.stream) row_launch_nt<RC, UPD, SWP, GRAD, true>(rc);
+        else row_launch_nt<RC, UPD, SWP, GRAD, false>(rc);
+    }
+    template <int RC, bool UPD, bool SWP, bool GRAD, bool NT>
+    void row_launch_nt(const RowClass &rc) {
         const int n = (int)rc.tiles.size();
         const RowTile *tiles = c->d_row_tiles + rc.dev_first;
         if constexpr (RC < kWideCols) {
@@ -232,10 +240,10 @@ struct Launcher {
                 row_kernel<RC, kRowsPerGroupLight, kPrefetchSteps, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, nullptr, nullptr);
             else
-                row_kernel<RC, kRowsPerGroup, kPrefetchSteps, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
+                row_kernel<RC, kRowsPerGroup, kPrefetchSteps, UPD, SWP, GRAD, NT && UPD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, nullptr, nullptr);
         } else if (rc.mfma) {
-#define PG_MROW(VV) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD> \
+#define PG_MROW(VV) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD, NT> \
                 <<<dim3((unsigned)n), dim3(kThreads), kMrowLdsBytes, st>>>( \
                 tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta)
             if (rc.V == 4) PG_MROW(4);
@@ -246,7 +254,7 @@ struct Launcher {
             // register budget: RC accumulators and RC update coefficients per row
             constexpr int M = ((UPD && SWP) || GRAD || (RC > 8 && UPD)) ? 2 : 4;
             size_t lds = (size_t)RC * rc.max_seg * sizeof(float);
-#define PG_WIDE(VV) row_wide_kernel<VV, RC, M, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
+#define PG_WIDE(VV) row_wide_kernel<VV, RC, M, UPD, SWP, GRAD, NT><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
                 tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta)
             if (rc.V == 4) PG_WIDE(4);
             else if (rc.V == 2) PG_WIDE(2);
@@ -307,7 +315,7 @@ struct Launcher {
             if (rc.tiles.empty()) continue;
             const int n = (int)rc.tiles.size();
             begin(SWP ? K_UPDATE_SWEEP_P : K_UPDATE, rc.elems * 4.0 * (PEND == kPeek ? 1.0 : 2.0));
-#define PG_ROWP(RC, M) row_kernel<RC, M, kPrefetchSteps, true, SWP, false, PEND><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
+#define PG_ROWP(RC, M) row_kernel<RC, M, kPrefetchSteps, true, SWP, false, true, PEND><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
                 c->d_row_tiles + rc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, phat1, q1)
             if (rc.RC == 1) PG_ROWP(1, kRowsPerGroup);
             else if (rc.RC == 2) PG_ROWP(2, kRowsPerGroup);
@@ -354,7 +362,8 @@ struct Launcher {
             else
                 PG_COL(0);
         } else if (c->plan.mfma_cols) {
-#define PG_MCOL(VV, STAGE, LDS) mcol_kernel<VV, kMfmaColPrefetch, STAGE><<<dim3((unsigned)n), dim3(kThreads), LDS, st>>>( \
+#define PG_MCOL(VV, STAGE, LDS) do { if (c->plan.stream) PG_MCOL_NT(VV, STAGE, LDS, true); else PG_MCOL_NT(VV, STAGE, LDS, false); } while (0)
+#define PG_MCOL_NT(VV, STAGE, LDS, NT) mcol_kernel<VV, kMfmaColPrefetch, STAGE, NT><<<dim3((unsigned)n), dim3(kThreads), LDS, st>>>( \
             c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, \
             c->d_xs, left(), qw())
             // The row block's Phat slice in LDS, where it fits beside a second work-group's.  Measured:
@@ -371,6 +380,7 @@ struct Launcher {
                 else PG_MCOL(1, false, 0);
             }
 #undef PG_MCOL
+#undef PG_MCOL_NT
         } else {
             if (cc.V == 4) PG_COL(4);
             else if (cc.V == 2) PG_COL(2);
@@ -626,6 +636,7 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     if (const char *e = getenv("PG_MFMA_COLS")) tune.mfma_cols = atoi(e) != 0;
     if (const char *e = getenv("PG_MCOL_STAGE")) c->mcol_stage = atoi(e) != 0;
     if (const char *e = getenv("PG_LAZY")) c->lazy = atoi(e) != 0;
+    if (const char *e = getenv("PG_STREAM")) tune.stream = atoi(e) != 0;
     if (const char *e = getenv("PG_LIGHT")) tune.light = atoi(e) != 0;
     if (const char *e = getenv("PG_VEC_KERNELS")) tune.vec_kernels = std::min(2, std::max(0, atoi(e)));
     if (const char *e = getenv("PG_MFMA_ROW_COLS")) tune.mfma_row_cols = atoi(e) <= 8 ? 8 : 16;

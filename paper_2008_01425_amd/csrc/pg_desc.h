@@ -13,6 +13,12 @@ constexpr int kMaxCols = 16;   // largest R = deg(i) * r_l one pass supports
 constexpr int kThreads = 256;  // work-group size of the column-owner and combine kernels (4 wavefronts)
 constexpr int kRowThreads = 64;  // narrow row-owner kernels: one wavefront per tile
 constexpr int64_t kLightBytes = 64ll << 20;  // parameter bytes (all workers) up to which the narrow row kernels block 4 rows, not 8
+// Parameter bytes (all workers) above which passes stream them past the caches.  Measured with one
+// matrix cut to size, streamed / plain: up to 4 stacked columns 1.04 (round) and 0.97 (run) at 208 MB,
+// 1.01 and 0.93 at 302 MB, 0.97 and 0.88 at 377 MB; 8 columns 1.03 at 472 MB, 0.98 at 604 MB; 16
+// columns 1.00 at 377 MB, 0.97 at 604 MB.
+constexpr int64_t kStreamBytes = 320ll << 20;
+constexpr int64_t kStreamBytesWide = 512ll << 20;  // 8-16 stacked columns
 constexpr int kVecClassPairs = 1024;  // (worker, vector layer) pairs from which vector layers get kernels of their own
 constexpr int kWideCols = 8;     // from this many compiled columns on, row tiles stage Q in LDS
 constexpr int kWideLdsBytes = 48 * 1024;  // LDS budget of a wide row tile's Q slice

@@ -38,6 +38,20 @@ template <int V>
 __device__ __forceinline__ void stg(float *p, typename VecT<V>::T v) {
     *(PG_GLOBAL typename VecT<V>::T *)p = v;
 }
+// The same with the non-temporal hint when NT.  A pass that rewrites parameters too large for the
+// 256 MB memory-side cache leaves that cache full of dirty lines, and the pass after it pays for
+// their write-back; streamed past the caches the same pass is faster (plain in-place x *= c over
+// 1 GiB: 5.4 -> 6.3 TB/s; over 256 MB, where the cache holds everything: 8.5 -> 6.7).
+template <int V, bool NT>
+__device__ __forceinline__ typename VecT<V>::T ldgx(const float *p) {
+    if constexpr (NT) return __builtin_nontemporal_load((const PG_GLOBAL typename VecT<V>::T *)p);
+    return ldg<V>(p);
+}
+template <int V, bool NT>
+__device__ __forceinline__ void stgx(float *p, typename VecT<V>::T v) {
+    if constexpr (NT) __builtin_nontemporal_store(v, (PG_GLOBAL typename VecT<V>::T *)p);
+    else stg<V>(p, v);
+}
 __device__ __forceinline__ float ldg1(const float *p) { return *(const PG_GLOBAL float *)p; }
 
 // Which tile this work-group takes: the tile list in order, or backwards, so that a pass can start
@@ -122,7 +136,7 @@ __device__ __forceinline__ void group_sum_all(double (&v)[N], int width) {
 // ---------------------------------------------------------------------------------------
 enum Pending { kApply = 0, kPeek = 1, kApplyTwo = 2 };
 
-template <int V, int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND>
+template <int V, int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND, bool NT>
 __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                                          const ColDesc *__restrict__ cols, float *X,
                                          const float *__restrict__ qstate,
@@ -194,10 +208,10 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                 if (TWO) qv[TWO ? RC + j : 0] = ldg<V>(qcol1[TWO ? j : 0] + c);
             }
 #pragma unroll
-            for (int m = 0; m < M; ++m) xv[m] = ldg<V>(xrow[m] + c);
+            for (int m = 0; m < M; ++m) xv[m] = ldgx<V, NT>(xrow[m] + c);
             if (GRAD) {
 #pragma unroll
-                for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldg<V>(grow[m] + c);
+                for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldgx<V, NT>(grow[m] + c);
             }
         };
         auto process = [&](int c, vec(&xv)[M], vec(&qv)[NQ], vec(&gv)[GRAD ? M : 1]) {
@@ -225,7 +239,7 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                         xv[m][v] = (float)xd[v];
                         xd[v] = (double)xv[m][v];  // the sweep uses the stored (rounded) value
                     }
-                    if (PEND != kPeek && ok[m]) stg<V>(xrow[m] + c, xv[m]);
+                    if (PEND != kPeek && ok[m]) stgx<V, NT>(xrow[m] + c, xv[m]);
                 }
                 if (SWEEP) {
 #pragma unroll
@@ -363,7 +377,7 @@ __device__ __forceinline__ void vec_row_body(const RowTile &t, const PairDesc &p
 // One wavefront per tile; `reverse` walks the tile list backwards so that a pass can start on
 // the data the previous pass touched last (still resident in the memory-side cache).
 //   GRAD  : (with UPDATE) also subtract eta * G[row, c]: the update step of Algorithm 1 in one pass.
-template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND = kApply>
+template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT = false, int PEND = kApply>
 __global__ void __launch_bounds__(kRowThreads)
 row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
            const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
@@ -376,9 +390,9 @@ row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
     if (pd.q == 1) vec_row_body<RC, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
 }
 
 // The row passes over vector layers alone (one wavefront per tile): the same arithmetic as the
@@ -404,7 +418,7 @@ vec_row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
 // RC columns without the Q slice being re-fetched per row.  Lane groups own M rows each as in
 // the narrow kernel; only X is prefetched a step ahead, in registers.
 // ---------------------------------------------------------------------------------------
-template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD>
+template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD, bool NT>
 __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &pd,
                                               const ColDesc *__restrict__ cols, float *X,
                                               const float *__restrict__ qstate,
@@ -481,10 +495,10 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
 
         auto load = [&](int c, vec(&xv)[M], vec(&gv)[GRAD ? M : 1]) {
 #pragma unroll
-            for (int m = 0; m < M; ++m) xv[m] = ldg<V>(xrow[m] + c);
+            for (int m = 0; m < M; ++m) xv[m] = ldgx<V, NT>(xrow[m] + c);
             if (GRAD) {
 #pragma unroll
-                for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldg<V>(grow[m] + c);
+                for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldgx<V, NT>(grow[m] + c);
             }
         };
         auto process = [&](int c, vec(&xv)[M], vec(&gv)[GRAD ? M : 1]) {
@@ -515,7 +529,7 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
                         xv[m][v] = (float)xd[m][v];
                         xd[m][v] = (double)xv[m][v];  // the sweep uses the stored (rounded) value
                     }
-                    if (ok[m]) stg<V>(xrow[m] + c, xv[m]);
+                    if (ok[m]) stgx<V, NT>(xrow[m] + c, xv[m]);
                 }
             }
             if (SWEEP) {
@@ -571,7 +585,7 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
 
 // One instantiation per vector width V: with 8-16 stacked columns a kernel that carried all
 // three widths would be allocated the registers of its widest body and lose occupancy.
-template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD>
+template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD, bool NT>
 __global__ void __launch_bounds__(kThreads)
 row_wide_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
                 const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
@@ -584,7 +598,7 @@ row_wide_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     const PairDesc pd = pairs[t.pair];
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
-    row_wide_body<V, RC, M, UPDATE, SWEEP, GRAD>(t, pd, cols, X, qstate, phat, pw, sQ, Gp, eta);
+    row_wide_body<V, RC, M, UPDATE, SWEEP, GRAD, NT>(t, pd, cols, X, qstate, phat, pw, sQ, Gp, eta);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -621,25 +635,29 @@ __device__ __forceinline__ void ld4(const float *p, float (&x)[4]) {
 // byte offset of the step's first column in the row (always inside the row).  FULL: all 64
 // columns exist.  Otherwise `nvalid` columns are left in the row: units at or past that re-read
 // the first column (the caller discards or zeroes them) and are not stored.
-template <int V>
+template <int V, bool NT>
 __device__ __forceinline__ typename VecT<V>::T ldg_at(const float *base, uint32_t byte_off) {
-    return *(const PG_GLOBAL typename VecT<V>::T *)((const PG_GLOBAL char *)base + byte_off);
+    auto p = (const PG_GLOBAL typename VecT<V>::T *)((const PG_GLOBAL char *)base + byte_off);
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    return *p;
 }
-template <int V>
+template <int V, bool NT>
 __device__ __forceinline__ void stg_at(float *base, uint32_t byte_off, typename VecT<V>::T v) {
-    *(PG_GLOBAL typename VecT<V>::T *)((PG_GLOBAL char *)base + byte_off) = v;
+    auto p = (PG_GLOBAL typename VecT<V>::T *)((PG_GLOBAL char *)base + byte_off);
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
-template <int V, bool FULL>
+template <int V, bool FULL, bool NT = false>
 __device__ __forceinline__ void ldrow(const float *base, uint32_t off, int lo, int nvalid, float (&x)[4]) {
 #pragma unroll
     for (int u = 0; u < 4 / V; ++u) {
         const int c = 16 * V * u + V * lo;
-        const typename VecT<V>::T t = ldg_at<V>(base, off + 4u * (uint32_t)((FULL || c < nvalid) ? c : 0));
+        const typename VecT<V>::T t = ldg_at<V, NT>(base, off + 4u * (uint32_t)((FULL || c < nvalid) ? c : 0));
 #pragma unroll
         for (int e = 0; e < V; ++e) x[V * u + e] = t[e];
     }
 }
-template <int V, bool FULL>
+template <int V, bool FULL, bool NT>
 __device__ __forceinline__ void strow(float *base, uint32_t off, int lo, int nvalid, const float (&x)[4]) {
 #pragma unroll
     for (int u = 0; u < 4 / V; ++u) {
@@ -647,7 +665,7 @@ __device__ __forceinline__ void strow(float *base, uint32_t off, int lo, int nva
         typename VecT<V>::T t;
 #pragma unroll
         for (int e = 0; e < V; ++e) t[e] = x[V * u + e];
-        if (FULL || c < nvalid) stg_at<V>(base, off + 4u * (uint32_t)c, t);
+        if (FULL || c < nvalid) stg_at<V, NT>(base, off + 4u * (uint32_t)c, t);
     }
 }
 // The same lane-to-column map into an LDS row of 64 floats.
@@ -703,7 +721,7 @@ struct BoolTag {
 };
 // Two work-groups per CU: left alone the compiler takes every register it can (one work-group).
 // (measured: the sweep alone is 11 % faster at three wavefronts per SIMD, one register spilled).
-template <int V, int RCM, int MB, int D, bool UPDATE, bool SWEEP, bool GRAD>
+template <int V, int RCM, int MB, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((UPDATE || GRAD) ? 2 : 3)))
 mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const PairDesc *__restrict__ pairs,
             const ColDesc *__restrict__ cols, float *const *__restrict__ xs,
@@ -778,8 +796,8 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
         for (int b = 0; b < MB; ++b) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                ldrow<V, FULL>(X, roff[b][v] + cso, lo, nvalid, f.x[b][v]);
-                if (GRAD) ldrow<V, FULL>(Gp, roff[b][v] + cso, lo, nvalid, f.g[GRAD ? b : 0][v]);
+                ldrow<V, FULL, NT>(X, roff[b][v] + cso, lo, nvalid, f.x[b][v]);
+                if (GRAD) ldrow<V, FULL, NT>(Gp, roff[b][v] + cso, lo, nvalid, f.g[GRAD ? b : 0][v]);
             }
         }
         if (UPDATE) {
@@ -837,7 +855,7 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     if (FULL || row0w + 16 * b + 4 * v + hi < row_end)
-                        strow<V, FULL>(X, roff[b][v] + cso, lo, nvalid, f.x[b][v]);
+                        strow<V, FULL, NT>(X, roff[b][v] + cso, lo, nvalid, f.x[b][v]);
                 }
             }
             if (SWEEP) {
@@ -959,7 +977,7 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
 // ([j][row], rows past the block's end and columns j >= R as zeros) and the four wavefronts take
 // their B operands from there; otherwise every wavefront fetches them from global memory step by step.
 __host__ __device__ constexpr int mcol_stage_stride(int blk_rows) { return ((blk_rows + 31) & ~31) + 4; }
-template <int V, int D, bool STAGE>
+template <int V, int D, bool STAGE, bool NT>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 mcol_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
             const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
@@ -1016,7 +1034,7 @@ mcol_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
                 const int cw = 16 * V * w + V * lo;
                 // a lane past the row's end re-reads the row's last unit (a line the valid lanes
                 // fetch anyway): that sum is not stored
-                const typename VecT<V>::T xv = ldg<V>(xr + (cw < ncols ? cw : ncols - V));
+                const typename VecT<V>::T xv = ldgx<V, NT>(xr + (cw < ncols ? cw : ncols - V));
 #pragma unroll
                 for (int e = 0; e < V; ++e) f.x[u][V * w + e] = xv[e];
             }

@@ -124,6 +124,12 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         const double total_bytes = 4.0 * n_workers * P.elems_per_worker;
         const double slots = 4096.0;  // 256 CUs x 4 SIMDs x a few wavefronts
         P.light = tune.light < 0 ? total_bytes <= (double)kLightBytes : tune.light != 0;
+        bool wide = false;  // some worker has 8 or more stacked columns in a pass
+        for (const LayerInfo &L : P.layers) {
+            const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
+            wide = wide || compiled_cols(std::max(1, per_pass * L.r)) >= kWideCols;
+        }
+        P.stream = tune.stream < 0 ? total_bytes > (double)(wide ? kStreamBytesWide : kStreamBytes) : tune.stream != 0;
         tn.row_tile_bytes = (int)std::max((P.light ? 4.0 : 8.0) * 1024, std::min((double)tune.row_tile_bytes, total_bytes / slots));
         tn.col_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.col_tile_bytes, 4.0 * total_bytes / slots));
         tn.wide_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.wide_tile_bytes, 4.0 * total_bytes / slots));

@@ -51,6 +51,7 @@ struct Tuning {
     bool mfma_rows = true;            // P-sweep and update ...
     int mfma_row_cols = kMfmaRowCols; // ... of layers with at least this many stacked columns (8 or 16)
     int light = -1;                   // blocking for small parameter sets: -1 by size, 0 never, 1 always
+    int stream = -1;                  // non-temporal passes: -1 by size, 0 never, 1 always
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
                                       // 0 never, 1 where there are many of them, 2 always
 };
@@ -90,6 +91,9 @@ struct Plan {
     // dependent loads, so the narrow row kernels block fewer rows per lane group (half the
     // registers, twice the wavefronts per SIMD) over tiles half as large.
     bool light = false;
+    // The parameters of all workers do not fit the memory-side cache: passes that write them, and
+    // all passes over 8-16 stacked columns, stream them past the caches (non-temporal).
+    bool stream = false;
     int max_layer_rank = 1;                  // largest r_l
     int max_rows = 1;                        // largest p_l
 };

@@ -57,7 +57,9 @@ def kernel_kind(name: str):
     """Kernel name -> the kind pg_profile_collect reports it under (None: not a pass over X)."""
     m = re.match(r"pg::(row_kernel|row_wide_kernel|mrow_kernel|vec_row_kernel)<(.*)>", name)
     if m:
-        upd, swp, grad = [t.strip() == "true" for t in m.group(2).split(",")[-3:]]
+        # the first three truth values of the template arguments
+        upd, swp, grad = [t for t in (a.strip() for a in m.group(2).split(",")) if t in ("true", "false")][:3]
+        upd, swp, grad = upd == "true", swp == "true", grad == "true"
         if grad:
             return "update_sgd"
         return "update_sweep_p" if upd and swp else ("update" if upd else "sweep_p")

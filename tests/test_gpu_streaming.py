@@ -1,6 +1,6 @@
-"""Runs that write the parameters every second round perform the operations of the plain passes on
-every element, so they are held to the plain passes bit for bit (and those to the CPU oracle
-elsewhere)."""
+"""Passes of large parameter sets: streamed past the caches, and runs that write the parameters
+every second round.  Both perform the operations of the plain passes on every element, so each is
+held to the plain passes bit for bit (and those to the CPU oracle elsewhere)."""
 import numpy as np
 import pytest
 
@@ -21,9 +21,9 @@ def _workload(name, n, edges, rank, steps, sigma=0.05):
     return W.Workload(name, n, edges, w, SHAPES, rank, steps, sigma, 10, 77)
 
 
-def _buffers(wl, X, Q, lazy):
+def _buffers(wl, X, Q, stream, lazy):
     from paper_2008_01425_amd.device import GossipBuffers
-    with env_setting("PG_LAZY", lazy), env_setting("PG_LIGHT", 0):
+    with env_setting("PG_STREAM", stream), env_setting("PG_LAZY", lazy), env_setting("PG_LIGHT", 0):
         gb = GossipBuffers.from_workload(wl, fill=False)
     gb.fill_from_arrays(X, Q)
     return gb
@@ -56,7 +56,7 @@ def test_a_run_that_writes_every_second_round_equals_the_plain_run(graph, rounds
     X, Q = wl.all_params(), wl.all_q()
     for l in (1, 6):                                   # two neighbours agree: their columns are dropped
         X[1][l] = X[0][l].copy()
-    plain, lazy = _buffers(wl, X, Q, 0), _buffers(wl, X, Q, 1)
+    plain, lazy = _buffers(wl, X, Q, 0, 0), _buffers(wl, X, Q, 1, 1)
     for _ in range(2):                                 # the second call starts on what the first left
         plain.run(rounds)
         lazy.run(rounds)
@@ -66,3 +66,26 @@ def test_a_run_that_writes_every_second_round_equals_the_plain_run(graph, rounds
     _same(plain, lazy, wl, wl.name + " and one round")
     plain.close()
     lazy.close()
+
+
+@pytest.mark.parametrize("rank", [1, 2, 3, 4])
+def test_streamed_passes_equal_the_cached_ones(rank):
+    """1 to 16 stacked columns: every row and column kernel, each call."""
+    import torch
+    n, edges = 6, [(0, 1), (0, 2), (3, 0), (0, 4), (2, 1), (4, 5)]   # degrees 4, 2, 2, 1, 2, 1
+    wl = _workload(f"stream r{rank}", n, edges, rank, 2)
+    X, Q = wl.all_params(), wl.all_q()
+    a, b = _buffers(wl, X, Q, 0, 0), _buffers(wl, X, Q, 1, 1)
+    for gb in (a, b):
+        gb.alloc_grads()
+        gb.alloc_pstate()
+        for i, g in enumerate(gb.g):
+            g.normal_(generator=torch.Generator(device=g.device).manual_seed(i))
+    for what, call in (("round", lambda gb: gb.round()), ("run", lambda gb: gb.run(3)),
+                       ("sgd", lambda gb: gb.round_sgd(0.1)), ("odd iteration", lambda gb: gb.iterate(0, 1, 0.1)),
+                       ("even iteration", lambda gb: gb.iterate(1, 1))):
+        call(a)
+        call(b)
+        _same(a, b, wl, f"{wl.name} {what}")
+    a.close()
+    b.close()
