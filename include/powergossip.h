@@ -140,7 +140,8 @@ size_t pg_message_floats(const pg_ctx *ctx);
  * Algorithmic bytes of parameter traffic of one round: 4 * n * N * passes, N = sum p_l q_l,
  * passes = 2*power_steps + 2 for pg_round (each product reads every X once, the update reads
  * and writes it), 2*power_steps + 1 per round inside pg_run (the update also feeds the next
- * round's first product).
+ * round's first product).  A run of a large set with power_steps = 1 and at most four stacked
+ * columns moves less: it writes the parameters every second round (5 passes for two rounds).
  */
 double pg_round_bytes(const pg_ctx *ctx, int fused);
 
@@ -226,7 +227,8 @@ int pg_iterate(pg_ctx *ctx, float *const *worker_params, float *q_state, float *
  * `rounds` consecutive gossip rounds with nothing touching the parameters in between
  * (the pure consensus iteration, Eq. (4)).  Same result as calling pg_round `rounds` times;
  * the update of round t and the first product of round t+1 share one pass over the
- * parameters.  rounds >= 0.  Once a call has seen the same worker_params pointers (the first
+ * parameters, and large parameter sets with power_steps = 1 are written every second round only
+ * (the last one always).  rounds >= 0.  Once a call has seen the same worker_params pointers (the first
  * call with a new set copies the pointer table to the device and waits for the stream), a call
  * with profiling off only launches kernels: it may be recorded into a HIP graph on a capturing
  * stream and replayed.
