@@ -19,6 +19,11 @@ constexpr int64_t kLightBytes = 64ll << 20;  // parameter bytes (all workers) up
 // columns 1.00 at 377 MB, 0.97 at 604 MB.
 constexpr int64_t kStreamBytes = 320ll << 20;
 constexpr int64_t kStreamBytesWide = 512ll << 20;  // 8-16 stacked columns
+// Narrow kernels: rows of at least this many floats are moved four at a time whatever q is (see
+// row_body).  Shorter ones are a single vector or two; four at a time only if q % 4 == 0.  Measured on one
+// matrix of 531 MB, ring of 16, rank 1, one round: 4607 columns 597 -> 433 us, 577 columns 710 -> 540 us
+// (one and two floats at a time before; 4606 columns 476 -> 433 us).
+constexpr int kAnyAlignCols = 16;
 constexpr int kVecClassPairs = 1024;  // (worker, vector layer) pairs from which vector layers get kernels of their own
 constexpr int kWideCols = 8;     // from this many compiled columns on, row tiles stage Q in LDS
 constexpr int kWideLdsBytes = 48 * 1024;  // LDS budget of a wide row tile's Q slice
@@ -50,7 +55,8 @@ struct PairDesc {
     int32_t lg;        // column-owner kernel: lanes side by side over columns (power of two <= 64)
     int32_t nblk;      // column-owner kernel: row blocks
     int32_t blk_rows;  // rows per block
-    int32_t V;         // floats per vector load on this layer: 4, 2 or 1 (largest that divides q)
+    int32_t V;         // floats per vector load on this layer: 4, 2 or 1 (largest that divides q; 4 also where
+                       // the wide row kernels run on padded rows and from kAnyAlignCols on in the narrow kernels)
     int32_t wc;        // matrix-core row tiles: wavefronts side by side over the column steps (1, 2 or 4)
     int32_t ld;        // floats from one row of the layer to the next in a worker buffer (>= q)
 };

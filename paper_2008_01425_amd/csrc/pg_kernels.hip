@@ -38,19 +38,38 @@ template <int V>
 __device__ __forceinline__ void stg(float *p, typename VecT<V>::T v) {
     *(PG_GLOBAL typename VecT<V>::T *)p = v;
 }
+// Four consecutive floats in one 16-byte load at any 4-byte aligned address (global memory
+// takes under-aligned vector accesses; rows of a matrix with q % 4 != 0 start at such addresses).
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void ld4(const float *p, float (&x)[4]) {
+    const float4_any t = *(const PG_GLOBAL float4_any *)p;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = t[v];
+}
 // The same with the non-temporal hint when NT.  A pass that rewrites parameters too large for the
 // 256 MB memory-side cache leaves that cache full of dirty lines, and the pass after it pays for
 // their write-back; streamed past the caches the same pass is faster (plain in-place x *= c over
 // 1 GiB: 5.4 -> 6.3 TB/s; over 256 MB, where the cache holds everything: 8.5 -> 6.7).
-template <int V, bool NT>
+// ANY: V floats at any 4-byte aligned address (V = 4).
+template <int V, bool NT, bool ANY = false>
 __device__ __forceinline__ typename VecT<V>::T ldgx(const float *p) {
+    if constexpr (ANY) {
+        const PG_GLOBAL float4_any *pa = (const PG_GLOBAL float4_any *)p;
+        if constexpr (NT) return __builtin_nontemporal_load(pa);
+        return *pa;
+    }
     if constexpr (NT) return __builtin_nontemporal_load((const PG_GLOBAL typename VecT<V>::T *)p);
     return ldg<V>(p);
 }
-template <int V, bool NT>
+template <int V, bool NT, bool ANY = false>
 __device__ __forceinline__ void stgx(float *p, typename VecT<V>::T v) {
-    if constexpr (NT) __builtin_nontemporal_store(v, (PG_GLOBAL typename VecT<V>::T *)p);
-    else stg<V>(p, v);
+    if constexpr (ANY) {
+        if constexpr (NT) __builtin_nontemporal_store((float4_any)v, (PG_GLOBAL float4_any *)p);
+        else *(PG_GLOBAL float4_any *)p = v;
+    } else {
+        if constexpr (NT) __builtin_nontemporal_store(v, (PG_GLOBAL typename VecT<V>::T *)p);
+        else stg<V>(p, v);
+    }
 }
 __device__ __forceinline__ float ldg1(const float *p) { return *(const PG_GLOBAL float *)p; }
 
@@ -133,10 +152,13 @@ __device__ __forceinline__ void group_sum_all(double (&v)[N], int width) {
 //           kApply -- the latest update, stored; kPeek -- the latest update, in registers only;
 //           kApplyTwo -- the update before (phat1, q1), rounded, then the latest one, stored.
 //           Every element goes through the same operations and roundings as with kApply alone.
+//   ANY   : rows (and right-hand sides) start at any 4-byte aligned address and q % 4 != 0.  Units of
+//           four floats all the same; a row's last unit, partly past its end, is moved back to the
+//           row's last four floats, the ones its neighbour owns are zeroed on loading and not stored.
 // ---------------------------------------------------------------------------------------
 enum Pending { kApply = 0, kPeek = 1, kApplyTwo = 2 };
 
-template <int V, int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND, bool NT>
+template <int V, int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, int PEND, bool NT, bool ANY>
 __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                                          const ColDesc *__restrict__ cols, float *X,
                                          const float *__restrict__ qstate,
@@ -202,19 +224,32 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
 
         constexpr int NQ = TWO ? 2 * RC : RC;
         auto load = [&](int c, vec(&xv)[M], vec(&qv)[NQ], vec(&gv)[GRAD ? M : 1]) {
+            if (ANY) c = min(c, q - V);
 #pragma unroll
             for (int j = 0; j < RC; ++j) {
-                qv[j] = ldg<V>(qcol[j] + c);
-                if (TWO) qv[TWO ? RC + j : 0] = ldg<V>(qcol1[TWO ? j : 0] + c);
+                qv[j] = ldgx<V, false, ANY>(qcol[j] + c);
+                if (TWO) qv[TWO ? RC + j : 0] = ldgx<V, false, ANY>(qcol1[TWO ? j : 0] + c);
             }
 #pragma unroll
-            for (int m = 0; m < M; ++m) xv[m] = ldgx<V, NT>(xrow[m] + c);
+            for (int m = 0; m < M; ++m) xv[m] = ldgx<V, NT, ANY>(xrow[m] + c);
             if (GRAD) {
 #pragma unroll
-                for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldgx<V, NT>(grow[m] + c);
+                for (int m = 0; m < M; ++m) gv[GRAD ? m : 0] = ldgx<V, NT, ANY>(grow[m] + c);
             }
         };
         auto process = [&](int c, vec(&xv)[M], vec(&qv)[NQ], vec(&gv)[GRAD ? M : 1]) {
+            const bool whole = !ANY || c + V <= q;
+            const int back = ANY && !whole ? c + V - q : 0;  // floats of the unit that the neighbour owns
+            if (!whole) {
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (v < back) {
+#pragma unroll
+                        for (int j = 0; j < NQ; ++j) qv[j][v] = 0.0f;
+#pragma unroll
+                        for (int m = 0; m < M; ++m) xv[m][v] = 0.0f;
+                    }
+            }
             double qd[NQ][V];
 #pragma unroll
             for (int j = 0; j < NQ; ++j)
@@ -239,7 +274,12 @@ __device__ __forceinline__ void row_body(const RowTile &t, const PairDesc &pd,
                         xv[m][v] = (float)xd[v];
                         xd[v] = (double)xv[m][v];  // the sweep uses the stored (rounded) value
                     }
-                    if (PEND != kPeek && ok[m]) stgx<V, NT>(xrow[m] + c, xv[m]);
+                    if (PEND != kPeek && ok[m] && whole) stgx<V, NT, ANY>(xrow[m] + c, xv[m]);
+                    if (PEND != kPeek && ok[m] && !whole) {
+#pragma unroll
+                        for (int v = 0; v < V; ++v)
+                            if (v >= back) stgx<1, NT>(xrow[m] + c - back + v, typename VecT<1>::T(xv[m][v]));
+                    }
                 }
                 if (SWEEP) {
 #pragma unroll
@@ -390,9 +430,9 @@ row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
     if (pd.q == 1) vec_row_body<RC, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 4 && (pd.q & 3) == 0) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, true>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
 }
 
 // The row passes over vector layers alone (one wavefront per tile): the same arithmetic as the
@@ -445,8 +485,19 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
     for (int j = 0; j < RC; ++j) {
         if (j < R) {
             const float *src = qstate + cols[pd.col0 + j].q_off + c_begin;
-            for (int cc = tid * V; cc < seg_cols; cc += kThreads * V)
-                *reinterpret_cast<vec *>(sQ + j * sstride + cc) = ldg<V>(src + cc);
+            if constexpr (V < 4) {
+                for (int cc = tid * V; cc < seg_cols; cc += kThreads * V)
+                    *reinterpret_cast<vec *>(sQ + j * sstride + cc) = ldg<V>(src + cc);
+            } else {  // the vector starts at any 4-byte aligned address; a unit past its end reads as zeros
+                const int whole = seg_cols & ~3;
+                for (int cc = tid * 4; cc < whole; cc += kThreads * 4) {
+                    float x4[4];
+                    ld4(src + cc, x4);
+                    *reinterpret_cast<vec *>(sQ + j * sstride + cc) = vec{x4[0], x4[1], x4[2], x4[3]};
+                }
+                if (tid < 4 && whole < seg_cols)
+                    sQ[j * sstride + whole + tid] = whole + tid < seg_cols ? ldg1(src + whole + tid) : 0.0f;
+            }
         } else {
             vec z;
 #pragma unroll
@@ -503,6 +554,13 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
         };
         auto process = [&](int c, vec(&xv)[M], vec(&gv)[GRAD ? M : 1]) {
             const float *sq = sQ + (c - c_begin);
+            const bool whole = V < 4 || c + V <= c_end;  // otherwise the row's last unit, partly padding
+            if (!whole) {
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) xv[m][v] = c + v < c_end ? xv[m][v] : 0.0f;
+            }
             double xd[M][V];
 #pragma unroll
             for (int m = 0; m < M; ++m)
@@ -529,7 +587,12 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
                         xv[m][v] = (float)xd[m][v];
                         xd[m][v] = (double)xv[m][v];  // the sweep uses the stored (rounded) value
                     }
-                    if (ok[m]) stgx<V, NT>(xrow[m] + c, xv[m]);
+                    if (ok[m] && whole) stgx<V, NT>(xrow[m] + c, xv[m]);
+                    if (ok[m] && !whole) {
+#pragma unroll
+                        for (int v = 0; v < V; ++v)
+                            if (c + v < c_end) stg<1>(xrow[m] + c + v, typename VecT<1>::T(xv[m][v]));
+                    }
                 }
             }
             if (SWEEP) {
@@ -617,17 +680,6 @@ __device__ __forceinline__ mfma_acc mfma16(double a, double b, mfma_acc c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Four consecutive floats of a row as 4 / V vector loads.  `nvalid` (a multiple of V) floats
-// from p on are inside the row; units past them re-read the last valid unit and come back as
-// zeros.  nvalid >= 4 is the plain case.
-// Four consecutive floats in one 16-byte load at any 4-byte aligned address (global memory
-// takes under-aligned vector accesses; rows of a matrix with q % 4 != 0 start at such addresses).
-typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ void ld4(const float *p, float (&x)[4]) {
-    const float4_any t = *(const PG_GLOBAL float4_any *)p;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] = t[v];
-}
 // The 64 columns of one row step as the 16 lanes lo see them: 4 / V loads of V floats in which
 // the lanes sit side by side; a lane's float t is column 16 V (t / V) + V lo + t % V of the step.
 // Addresses are a wavefront-uniform base plus a 32-bit byte offset per lane (a layer is smaller
@@ -665,7 +717,29 @@ __device__ __forceinline__ void strow(float *base, uint32_t off, int lo, int nva
         typename VecT<V>::T t;
 #pragma unroll
         for (int e = 0; e < V; ++e) t[e] = x[V * u + e];
-        if (FULL || c < nvalid) stg_at<V, NT>(base, off + 4u * (uint32_t)c, t);
+        if (FULL || c + V <= nvalid) {
+            stg_at<V, NT>(base, off + 4u * (uint32_t)c, t);
+        } else {  // the row's last unit, partly padding
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (c + e < nvalid) stg_at<1, NT>(base, off + 4u * (uint32_t)(c + e), typename VecT<1>::T(t[e]));
+        }
+    }
+}
+// The same columns of a right-hand-side vector: those start at any 4-byte aligned address and have
+// no padding behind them.
+template <int V, bool FULL>
+__device__ __forceinline__ void ldrhs(const float *base, uint32_t off, int lo, int nvalid, float (&x)[4]) {
+    if constexpr (V < 4) {
+        ldrow<V, FULL>(base, off, lo, nvalid, x);
+    } else if constexpr (FULL) {
+        ld4((const float *)((const char *)base + off + 16u * (uint32_t)lo), x);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int c = 4 * lo + e;
+            x[e] = ldg_at<1, false>(base, off + 4u * (uint32_t)(c < nvalid ? c : 0))[0];
+        }
     }
 }
 // The same lane-to-column map into an LDS row of 64 floats.
@@ -802,11 +876,11 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
         }
         if (UPDATE) {
 #pragma unroll
-            for (int m = 0; m < RCM; ++m) ldrow<V, FULL>(qup[m], cso, lo, nvalid, f.qu[UPDATE ? m : 0]);
+            for (int m = 0; m < RCM; ++m) ldrhs<V, FULL>(qup[m], cso, lo, nvalid, f.qu[UPDATE ? m : 0]);
         }
         if (SWEEP && !UPDATE) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ldrow<V, FULL>(qsp[i], cso, lo, nvalid, f.qs[(SWEEP && !UPDATE) ? i : 0]);
+            for (int i = 0; i < 4; ++i) ldrhs<V, FULL>(qsp[i], cso, lo, nvalid, f.qs[(SWEEP && !UPDATE) ? i : 0]);
         }
     };
     auto process = [&](auto full, int s, Buf &f) {
@@ -834,7 +908,7 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
         // columns past the row's end: the sweep must see zeros there
         bool cok[4];
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) cok[tt] = FULL || 16 * V * (tt / V) + V * lo < nvalid;
+        for (int tt = 0; tt < 4; ++tt) cok[tt] = FULL || 16 * V * (tt / V) + V * lo + tt % V < nvalid;
 #pragma unroll
         for (int b = 0; b < MB; ++b) {
             if (UPDATE) {
@@ -993,7 +1067,8 @@ mcol_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
     const int c0 = t.c0 + 64 * __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool mine = c0 < q;  // a wavefront past the matrix's last column only helps staging
     if (!STAGE && !mine) return;
-    const int ncols = mine ? min(64, q - c0) : V;  // this wavefront's columns inside the matrix
+    const int ncols = mine ? min(64, q - c0) : V;  // this wavefront's columns inside the matrix (the last unit of
+                                                   // V may reach into a padded row's padding: sums not stored)
     const int rb = t.blk * pd.blk_rows;
     const int re = min(pd.p, rb + pd.blk_rows);
     const int nsteps = (re - rb + 15) >> 4;
@@ -1034,7 +1109,7 @@ mcol_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
                 const int cw = 16 * V * w + V * lo;
                 // a lane past the row's end re-reads the row's last unit (a line the valid lanes
                 // fetch anyway): that sum is not stored
-                const typename VecT<V>::T xv = ldgx<V, NT>(xr + (cw < ncols ? cw : ncols - V));
+                const typename VecT<V>::T xv = ldgx<V, NT>(xr + (cw < ncols ? cw : (ncols - 1) / V * V));
 #pragma unroll
                 for (int e = 0; e < V; ++e) f.x[u][V * w + e] = xv[e];
             }
@@ -1125,10 +1200,12 @@ sgd_only_kernel(const int32_t *__restrict__ pair_ids, const PairDesc *__restrict
 // arithmetic of the current U rows.
 //   Qw[blk][j][c] = sum_{row in blk} X[row, c] * Phat_j[row]   (Algorithm 2, even iteration:
 //   the product with X^T, for every incident edge in one read of X_i)
+//   ANY: rows at any 4-byte aligned address, q % 4 != 0; the lane of a row's last columns is moved
+//   back to the last four and leaves the ones its neighbour owns unstored.
 //   PEEK: X is one update (phat1, q1) behind; the update is applied to the loaded values,
 //   rounded as the row kernels round it, and not stored.
 // ---------------------------------------------------------------------------------------
-template <int V, int RC, int U, bool PEEK>
+template <int V, int RC, int U, bool PEEK, bool ANY>
 __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
                                          const ColDesc *__restrict__ cols, const float *X,
                                          const float *__restrict__ phat, double *__restrict__ qw,
@@ -1144,7 +1221,8 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
     const int q = pd.q, R = pd.R;
     int c = t.c0 + cg * V;
     const bool cok = c < q;
-    if (!cok) c = q - V;
+    const int c_own = c;
+    if (!cok || ANY) c = min(c, q - V);
     const int rb = t.blk * pd.blk_rows;
     const int re = min(pd.p, rb + pd.blk_rows);
     const int nrows = re - rb;
@@ -1169,7 +1247,7 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
             const double cf = (j < R) ? (double)cd.coef : 0.0;
             for (int rr = threadIdx.x; rr <= nrows; rr += kThreads)
                 sC[rr * RC + j] = cf * (double)ldg1(phat1 + cd.ph_off + rb + min(rr, nrows - 1));
-            const vec qv = ldg<V>(q1 + cd.q_off + c);
+            const vec qv = ldgx<V, false, ANY>(q1 + cd.q_off + c);
 #pragma unroll
             for (int v = 0; v < V; ++v) q1d[PEEK ? j : 0][v] = (double)qv[v];
         }
@@ -1186,7 +1264,7 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int rr = min(row + u * RG, re - 1);
-            xv[u] = ldg<V>(xcol + (int64_t)rr * pd.ld);
+            xv[u] = ldgx<V, false, ANY>(xcol + (int64_t)rr * pd.ld);
         }
     };
     auto process = [&](int row, vec(&xv)[U]) {
@@ -1258,7 +1336,7 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
                     double s = acc[j][v];
 #pragma unroll
                     for (int w = 0; w < kThreads / 64 - 1; ++w) s += red[w][lane][v];
-                    dst[v] = s;
+                    if (!ANY || c + v >= c_own) dst[v] = s;
                 }
             }
             __syncthreads();
@@ -1279,11 +1357,11 @@ col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
     const PairDesc pd = pairs[t.pair];
     const float *X = xs[pd.worker] + pd.x_off;
     if constexpr (V != 0) {
-        col_body<V, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        col_body<V, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     } else {
-        if (pd.V == 4) col_body<4, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
-        else if (pd.V == 2) col_body<2, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
-        else col_body<1, RC, U, PEEK>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        if (pd.V == 4 && (pd.q & 3) == 0) col_body<4, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        else if (pd.V == 4) col_body<4, RC, U, PEEK, true>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        else col_body<1, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     }
 }
 

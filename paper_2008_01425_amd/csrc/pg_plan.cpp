@@ -78,6 +78,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.max_layer_rank = std::max(P.max_layer_rank, L.r);
         P.max_rows = std::max(P.max_rows, p);
         L.V = (q % 4 == 0) ? 4 : (q % 2 == 0 ? 2 : 1);
+        L.Vn = (q >= kAnyAlignCols || q % 4 == 0) ? 4 : 1;
         // Row stride.  With 8 or more stacked columns a tile's wavefronts work side by side on
         // 64-column (256-byte) pieces of the same rows; when rows start at arbitrary addresses every
         // piece ends inside a 128-byte line that the neighbouring wavefront touches at another time,
@@ -145,23 +146,32 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         int lg, nblk, blk_rows;                  // column-owner
     };
     std::vector<Geo> geo(n_layers);
+    // Wide kernels in units of four floats on padded rows.  Every vector width is a launch of its own,
+    // so in a small set whose other layers need another width anyway the split costs more than the
+    // wider accesses save (11 workers, 115 MB, eight layers of odd lengths: 447 -> 475 us per SGD
+    // round); in large ones, or where all rows are padded, it pays (LSTM SGD round 2.87 -> 2.74 ms).
+    bool all_padded = true;
+    for (const LayerInfo &L : P.layers) all_padded = all_padded && L.ld % 4 == 0;
+    const bool wide_units = tune.mfma_cols && (P.stream || all_padded);
     constexpr int kColUnroll = 8;
     for (int l = 0; l < n_layers; ++l) {
         const LayerInfo &L = P.layers[l];
         Geo &g = geo[l];
-        int nv = L.q / L.V;  // vector loads per row
         // The row blocking depends on the stacked column count; size for the best-connected worker.
         // (a worker with more than kMaxCols stacked columns takes several passes of whole edges)
         const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
         int rc_max = compiled_cols(std::max(1, per_pass * L.r));
         g.wide = rc_max >= kWideCols;
+        const int Vg = g.wide ? L.V : L.Vn;
+        const int nv = (L.q + Vg - 1) / Vg;  // vector loads per row
         // Row passes on the matrix cores pay from 16 stacked columns on (measured: at 8 the vector
         // kernels' P-sweep is the faster one) and address a layer with 32-bit byte offsets.
         g.mrow = tune.mfma_rows && rc_max >= tune.mfma_row_cols && (int64_t)L.p * L.ld < ((int64_t)1 << 30);
         // Lanes per row: a whole wavefront for few stacked columns; 16 for many, where the
         // per-row lane reduction (RC values per row) would otherwise rival the products.
         g.lpr = std::min((g.wide && !g.mrow) ? 16 : 64, pow2_ceil(nv));
-        int chunk = g.lpr * L.V;  // floats one lane group covers per step
+        const int wide_V = g.wide && wide_units && L.ld % 4 == 0 ? 4 : Vg;  // width of the wide kernels' accesses to X
+        int chunk = g.lpr * wide_V;  // floats one lane group covers per step
         int nchunks = (L.q + chunk - 1) / chunk;
         int seg_chunks;
         if (!g.wide) {
@@ -208,7 +218,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         if (col_heavy && (double)nv / ((double)((nv + 63) / 64) * 64) > 0.6) best = std::min(64, pow2_ceil(nv));
         g.lg = best;
         int row_groups = 4 * (64 / g.lg);
-        int64_t row_bytes = (int64_t)g.lg * L.V * 4;
+        int64_t row_bytes = (int64_t)g.lg * (tune.fine_blocks ? Vg : L.V) * 4;
         int64_t want = std::max<int64_t>(1, tn.col_tile_bytes / row_bytes);
         int64_t unit = (int64_t)row_groups * kColUnroll;
         if (g.wide && tune.mfma_cols) {
@@ -367,6 +377,23 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     P.ws_uq = o;
     o = (size_t)round_up(o + (size_t)qo * 4, 256);
     P.ws_bytes = std::max<size_t>(o, 256);
+    // Four-float accesses to rows of odd length mean shorter row blocks at the same tile size, and more
+    // partial sums of the Q-sweep.  A problem that would outgrow the static workspace by that keeps
+    // the longer blocks.
+    if (tune.fine_blocks && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
+        bool any = false;
+        for (const LayerInfo &L : P.layers) any = any || L.Vn > L.V;
+        if (any) {
+            Tuning other = tune;
+            other.fine_blocks = false;
+            Plan Q;
+            const int rc = build_plan(Q, n_workers, n_edges, edges, edge_w, n_layers, rows, cols, rank, power_steps, other);
+            if (rc == PG_OK && Q.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES) {
+                P = std::move(Q);
+                return PG_OK;
+            }
+        }
+    }
 
     // ---- tiles, grouped by kernel instantiation, in address order ----
     P.row_classes.clear();
@@ -416,8 +443,14 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             }
             int RC = compiled_cols(pd.R);
             const bool mrow = g.mrow && RC >= kWideCols;
+            // Layers with padded rows are read and written four floats at a time by the wide kernels
+            // whatever q is; a row's last unit may reach into the padding (zeroed, never stored).
+            const bool wide4 = RC >= kWideCols && wide_units && L.ld % 4 == 0;
+            const int Vr = wide4 ? 4 : (RC < kWideCols ? L.Vn : L.V);
+            const int Vc = wide4 ? 4 : L.V;
+            P.pairs[pair].V = Vr;
             const bool vec = split_vec && L.q == 1 && RC < kWideCols;
-            RowClass &rc = P.row_classes[row_class(RC, L.V, mrow, gi, vec)];
+            RowClass &rc = P.row_classes[row_class(RC, Vr, mrow, gi, vec)];
             int rows_iter = g.rows_iter_base * rows_unroll(RC, P.light);
             int tile_rows;
             if (RC < kWideCols) {
@@ -445,8 +478,8 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             rc.elems += (double)L.p * L.q;
             P.pass_elems += (double)L.p * L.q;
 
-            ColClass &cc = P.col_classes[col_class(RC, L.V, vec)];
-            int cw = (RC >= kWideCols && tune.mfma_cols) ? kMfmaTileCols : g.lg * L.V;
+            ColClass &cc = P.col_classes[col_class(RC, Vc, vec)];
+            int cw = (RC >= kWideCols && tune.mfma_cols) ? kMfmaTileCols : g.lg * Vr;
             for (int b = 0; b < g.nblk; ++b)
                 for (int c0 = 0; c0 < L.q; c0 += cw) cc.tiles.push_back({pair, c0, b, 0});
             cc.elems += (double)L.p * L.q;

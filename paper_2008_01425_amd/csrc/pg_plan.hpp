@@ -12,6 +12,7 @@ namespace pg {
 struct LayerInfo {
     int p, q, r;        // r = min(rank, p, q)
     int V;              // floats per vector load: 4, 2 or 1 (largest that divides q)
+    int Vn;             // the same for the narrow kernels, which also take rows at any 4-byte aligned address
     int ld;             // row stride in a worker buffer, floats: q, or q rounded up to a whole number of
                         // 128-byte lines where several wavefronts share the rows of a tile
     int64_t x_off;      // float offset inside a worker buffer
@@ -51,6 +52,7 @@ struct Tuning {
     bool mfma_rows = true;            // P-sweep and update ...
     int mfma_row_cols = kMfmaRowCols; // ... of layers with at least this many stacked columns (8 or 16)
     int light = -1;                   // blocking for small parameter sets: -1 by size, 0 never, 1 always
+    bool fine_blocks = true;          // row blocks of layers with q % 4 != 0 sized for four-float accesses
     int stream = -1;                  // non-temporal passes: -1 by size, 0 never, 1 always
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
                                       // 0 never, 1 where there are many of them, 2 always

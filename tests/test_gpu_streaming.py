@@ -89,3 +89,88 @@ def test_streamed_passes_equal_the_cached_ones(rank):
         _same(a, b, wl, f"{wl.name} {what}")
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("stream", [0, 1])
+@pytest.mark.parametrize("rank", [2, 4])
+def test_padding_of_rows_is_neither_used_nor_written(rank, stream):
+    """Rows of 65, 66, 67 and more columns in a graph whose workers stack 2 to 16 columns: the wide kernels
+    read such rows in units of four floats, the last of which reaches into the padding.  NaNs there
+    stay where they are and change no result."""
+    import torch
+    from paper_2008_01425_amd.device import GossipBuffers
+    edges = [(0, 1), (0, 2), (3, 0), (0, 4), (2, 1), (4, 5)]
+    wl = _workload(f"padding r{rank}", 6, edges, rank, 1)
+    shapes = [(40, 65), (33, 66), (70, 67), (129, 130), (17, 259), (9, 3277), (16, 1023), (300, 72)]
+    wl = W.Workload(wl.name, 6, wl.edges, wl.edge_w, shapes, rank, 1, 0.05, 10, 78)
+    X, Q = wl.all_params(), wl.all_q()
+    bufs = []
+    for pad in (0.0, float("nan")):
+        with env_setting("PG_STREAM", stream), env_setting("PG_LIGHT", 0):
+            gb = GossipBuffers.from_workload(wl, fill=False)
+        gb.alloc_grads()
+        gb.alloc_pstate()
+        for i in range(gb.n):
+            gb.x[i].fill_(pad)
+            gb.g[i].fill_(pad)
+        gb.fill_from_arrays(X, Q)
+        for i in range(gb.n):
+            for l, s in enumerate(shapes):
+                gb.set_grad_layer(i, l, X[i][l][::-1] * 0.1)
+        bufs.append(gb)
+    a, b = bufs
+    holes = [torch.isnan(x) for x in b.x]
+    assert all(int(h.sum()) > 0 for h in holes)
+    for what, call in (("round", lambda gb: gb.round()), ("run", lambda gb: gb.run(3)),
+                       ("sgd", lambda gb: gb.round_sgd(0.1)), ("odd iteration", lambda gb: gb.iterate(0, 1, 0.1)),
+                       ("even iteration", lambda gb: gb.iterate(1, 1, 0.1))):
+        for gb in bufs:
+            call(gb)
+        for i in range(a.n):
+            assert bool((torch.isnan(b.x[i]) == holes[i]).all()), (what, i)
+            assert bool((torch.nan_to_num(b.x[i]) == a.x[i]).all()), (what, i)
+            assert bool((a.x[i][holes[i]] == 0).all()), (what, i)
+        assert bool((a.q == b.q).all()) and bool((a.pstate == b.pstate).all()), what
+    for gb in bufs:
+        gb.close()
+
+
+@pytest.mark.parametrize("rank", [1, 2])
+@pytest.mark.parametrize("light", [0, 1])
+def test_rows_of_any_length_and_alignment(rank, light):
+    """Rows of 16 and more floats at any 4-byte aligned address (every remainder modulo 4; a last unit
+    that overlaps its neighbour's, alone in a row or behind many) against the oracle: a round, a round
+    with gradient, an odd and an even iteration.  The one-round bar of the other parity tests."""
+    from oracle import pg_oracle as O
+    from parity_util import TOL_1, compare_state, oracle_problem
+    from paper_2008_01425_amd.device import GossipBuffers
+    n, edges = GRAPHS["ring"]
+    shapes = [(9, 17), (40, 18), (33, 19), (21, 16), (70, 255), (130, 257), (20, 1022), (65, 1023), (6, 4099)]
+    wl = _workload("any", n, edges, rank, 1)
+    wl = W.Workload(f"any alignment r{rank}", n, wl.edges, wl.edge_w, shapes, rank, 1, 0.05, 10, 79)
+    layers = list(range(len(shapes)))
+    prob, eta = oracle_problem(wl), 0.05
+    rng = np.random.default_rng(5)
+    G = [[rng.standard_normal(s).astype(np.float32) for s in shapes] for _ in range(n)]
+    for what in ("round", "sgd", "iterations"):
+        X, Q = wl.all_params(), wl.all_q()
+        with env_setting("PG_LIGHT", light):
+            gb = GossipBuffers.from_workload(wl, fill=False)
+        gb.fill_from_arrays(X, Q)
+        gb.alloc_grads()
+        gb.alloc_pstate()
+        for i in range(n):
+            for l in layers:
+                gb.set_grad_layer(i, l, G[i][l])
+        if what == "round":
+            gb.round()
+            O.gossip_round(prob, X, Q)
+        elif what == "sgd":
+            gb.round_sgd(eta)
+            O.gossip_round(prob, X, Q, G=G, eta=float(np.float32(eta)))
+        else:
+            P = [[np.zeros((wl.layer_rank(l), shapes[l][0]), np.float32) for l in layers] for _ in range(wl.n_edges)]
+            gb.iterate(0, 2, eta)
+            O.alg2_round(prob, X, Q, P, 0, 2, G=G, eta=float(np.float32(eta)))
+        print(f"   {what}: worst rel err", compare_state(gb, X, Q, layers, TOL_1, what=f"{wl.name} {what}"), flush=True)
+        gb.close()
