@@ -20,7 +20,7 @@ constexpr int64_t kLightBytes = 64ll << 20;  // parameter bytes (all workers) up
 constexpr int64_t kStreamBytes = 320ll << 20;
 constexpr int64_t kStreamBytesWide = 512ll << 20;  // 8-16 stacked columns
 // Narrow kernels: rows of at least this many floats are moved four at a time whatever q is (see
-// row_body).  Shorter ones are a single vector or two; four at a time only if q % 4 == 0.  Measured on one
+// row_body).  Shorter ones are a few vectors at most and go by the widest one that divides q.  Measured on one
 // matrix of 531 MB, ring of 16, rank 1, one round: 4607 columns 597 -> 433 us, 577 columns 710 -> 540 us
 // (one and two floats at a time before; 4606 columns 476 -> 433 us).
 constexpr int kAnyAlignCols = 16;

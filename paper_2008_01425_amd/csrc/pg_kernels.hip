@@ -432,6 +432,7 @@ row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     if (pd.q == 1) vec_row_body<RC, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else if (pd.V == 4 && (pd.q & 3) == 0) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, true>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
 }
 
@@ -1361,6 +1362,7 @@ col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
     } else {
         if (pd.V == 4 && (pd.q & 3) == 0) col_body<4, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
         else if (pd.V == 4) col_body<4, RC, U, PEEK, true>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        else if (pd.V == 2) col_body<2, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
         else col_body<1, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     }
 }

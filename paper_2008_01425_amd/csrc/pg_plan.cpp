@@ -78,7 +78,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.max_layer_rank = std::max(P.max_layer_rank, L.r);
         P.max_rows = std::max(P.max_rows, p);
         L.V = (q % 4 == 0) ? 4 : (q % 2 == 0 ? 2 : 1);
-        L.Vn = (q >= kAnyAlignCols || q % 4 == 0) ? 4 : 1;
+        L.Vn = q >= kAnyAlignCols ? 4 : L.V;
         // Row stride.  With 8 or more stacked columns a tile's wavefronts work side by side on
         // 64-column (256-byte) pieces of the same rows; when rows start at arbitrary addresses every
         // piece ends inside a 128-byte line that the neighbouring wavefront touches at another time,

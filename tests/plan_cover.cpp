@@ -57,6 +57,9 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
             REQUIRE(t.pair >= 0 && t.pair < (int)P.pairs.size(), "row tile pair %d", t.pair);
             const PairDesc &pd = P.pairs[t.pair];
             REQUIRE(compiled_cols(pd.R) == c.RC, "pair %d with R=%d in class RC=%d", t.pair, pd.R, c.RC);
+            // accesses as wide as the row length allows, or four floats wide
+            REQUIRE(pd.V == 4 || pd.q % 4 != 0, "rows of %d floats in units of %d", pd.q, pd.V);
+            REQUIRE(pd.V >= 2 || pd.q % 2 != 0, "rows of %d floats in units of %d", pd.q, pd.V);
             REQUIRE(t.nrows >= 1 && t.row0 >= 0 && t.row0 + t.nrows <= pd.p, "row tile rows %d+%d of %d", t.row0, t.nrows, pd.p);
             REQUIRE(t.seg >= 0 && t.seg < pd.nseg && (int64_t)t.seg * pd.seg_len < pd.q, "segment %d", t.seg);
             if (c.RC >= kWideCols) REQUIRE(c.V == pd.V, "class V=%d, layer V=%d", c.V, pd.V);

@@ -135,19 +135,15 @@ def test_padding_of_rows_is_neither_used_nor_written(rank, stream):
         gb.close()
 
 
-@pytest.mark.parametrize("rank", [1, 2])
-@pytest.mark.parametrize("light", [0, 1])
-def test_rows_of_any_length_and_alignment(rank, light):
-    """Rows of 16 and more floats at any 4-byte aligned address (every remainder modulo 4; a last unit
-    that overlaps its neighbour's, alone in a row or behind many) against the oracle: a round, a round
-    with gradient, an odd and an even iteration.  The one-round bar of the other parity tests."""
+def _against_the_oracle(name, shapes, rank, seed, light, steps=1, graph="ring"):
+    """A round, a round with gradient, an odd and an even iteration on `shapes`; the one-round bar of the
+    other parity tests."""
     from oracle import pg_oracle as O
     from parity_util import TOL_1, compare_state, oracle_problem
     from paper_2008_01425_amd.device import GossipBuffers
-    n, edges = GRAPHS["ring"]
-    shapes = [(9, 17), (40, 18), (33, 19), (21, 16), (70, 255), (130, 257), (20, 1022), (65, 1023), (6, 4099)]
-    wl = _workload("any", n, edges, rank, 1)
-    wl = W.Workload(f"any alignment r{rank}", n, wl.edges, wl.edge_w, shapes, rank, 1, 0.05, 10, 79)
+    n, edges = GRAPHS[graph]
+    wl = _workload(name, n, edges, rank, steps)
+    wl = W.Workload(f"{name} r{rank}", n, wl.edges, wl.edge_w, shapes, rank, steps, 0.05, 10, seed)
     layers = list(range(len(shapes)))
     prob, eta = oracle_problem(wl), 0.05
     rng = np.random.default_rng(5)
@@ -174,3 +170,22 @@ def test_rows_of_any_length_and_alignment(rank, light):
             O.alg2_round(prob, X, Q, P, 0, 2, G=G, eta=float(np.float32(eta)))
         print(f"   {what}: worst rel err", compare_state(gb, X, Q, layers, TOL_1, what=f"{wl.name} {what}"), flush=True)
         gb.close()
+
+
+@pytest.mark.parametrize("rank", [1, 2])
+@pytest.mark.parametrize("light", [0, 1])
+def test_rows_of_any_length_and_alignment(rank, light):
+    """Rows of 16 and more floats at any 4-byte aligned address (every remainder modulo 4; a last unit
+    that overlaps its neighbour's, alone in a row or behind many) against the oracle: a round, a round
+    with gradient, an odd and an even iteration.  The one-round bar of the other parity tests."""
+    shapes = [(9, 17), (40, 18), (33, 19), (21, 16), (70, 255), (130, 257), (20, 1022), (65, 1023), (6, 4099)]
+    _against_the_oracle("any alignment", shapes, rank, 79, light)
+
+
+@pytest.mark.parametrize("rank", [1, 2])
+@pytest.mark.parametrize("light", [0, 1])
+def test_rows_shorter_than_sixteen_floats(rank, light):
+    """Two floats at a time where q is even, one at a time where it is odd: q = 2 to 15, several row blocks
+    and fewer rows than a lane group takes."""
+    shapes = [(50, 2), (7, 6), (1030, 10), (33, 14), (260, 5), (9, 15), (3000, 6), (40, 3), (2, 14), (70, 12)]
+    _against_the_oracle("short rows", shapes, rank, 80, light)
