@@ -78,7 +78,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.max_layer_rank = std::max(P.max_layer_rank, L.r);
         P.max_rows = std::max(P.max_rows, p);
         L.V = (q % 4 == 0) ? 4 : (q % 2 == 0 ? 2 : 1);
-        L.Vn = q >= kAnyAlignCols ? 4 : L.V;
+        L.Vn = tune.odd_units && q >= kAnyAlignCols ? 4 : L.V;
         // Row stride.  With 8 or more stacked columns a tile's wavefronts work side by side on
         // 64-column (256-byte) pieces of the same rows; when rows start at arbitrary addresses every
         // piece ends inside a 128-byte line that the neighbouring wavefront touches at another time,
@@ -152,7 +152,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     // round); in large ones, or where all rows are padded, it pays (LSTM SGD round 2.87 -> 2.74 ms).
     bool all_padded = true;
     for (const LayerInfo &L : P.layers) all_padded = all_padded && L.ld % 4 == 0;
-    const bool wide_units = tune.mfma_cols && (P.stream || all_padded);
+    const bool wide_units = tune.odd_units && tune.mfma_cols && (P.stream || all_padded);
     constexpr int kColUnroll = 8;
     for (int l = 0; l < n_layers; ++l) {
         const LayerInfo &L = P.layers[l];
@@ -218,7 +218,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         if (col_heavy && (double)nv / ((double)((nv + 63) / 64) * 64) > 0.6) best = std::min(64, pow2_ceil(nv));
         g.lg = best;
         int row_groups = 4 * (64 / g.lg);
-        int64_t row_bytes = (int64_t)g.lg * (tune.fine_blocks ? Vg : L.V) * 4;
+        int64_t row_bytes = (int64_t)g.lg * (tune.long_blocks ? L.V : Vg) * 4;
         int64_t want = std::max<int64_t>(1, tn.col_tile_bytes / row_bytes);
         int64_t unit = (int64_t)row_groups * kColUnroll;
         if (g.wide && tune.mfma_cols) {
@@ -377,17 +377,18 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     P.ws_uq = o;
     o = (size_t)round_up(o + (size_t)qo * 4, 256);
     P.ws_bytes = std::max<size_t>(o, 256);
-    // Four-float accesses to rows of odd length mean shorter row blocks at the same tile size, and more
-    // partial sums of the Q-sweep.  A problem that would outgrow the static workspace by that keeps
-    // the longer blocks.
-    if (tune.fine_blocks && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
-        bool any = false;
-        for (const LayerInfo &L : P.layers) any = any || L.Vn > L.V;
-        if (any) {
-            Tuning other = tune;
-            other.fine_blocks = false;
+    // Units of four floats on rows of odd length change the segments and row blocks and with them the
+    // number of partial sums, mostly upwards.  A problem that does not fit the static workspace that
+    // way is planned with the widths that divide its rows, or with longer row blocks, if it fits then
+    // (54126 x 1162 on a ring of 8 at rank 2: 56.0 MB, 30.1 MB with the dividing widths; 23961 x 626 on
+    // a ring of 20 at rank 2: 36.7 MB with those, 31.9 MB with longer blocks).
+    if (tune.odd_units && !tune.long_blocks && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
+        Tuning other[2] = {tune, tune};
+        other[0].odd_units = false;
+        other[1].long_blocks = true;
+        for (const Tuning &tn2 : other) {
             Plan Q;
-            const int rc = build_plan(Q, n_workers, n_edges, edges, edge_w, n_layers, rows, cols, rank, power_steps, other);
+            const int rc = build_plan(Q, n_workers, n_edges, edges, edge_w, n_layers, rows, cols, rank, power_steps, tn2);
             if (rc == PG_OK && Q.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES) {
                 P = std::move(Q);
                 return PG_OK;

@@ -52,7 +52,8 @@ struct Tuning {
     bool mfma_rows = true;            // P-sweep and update ...
     int mfma_row_cols = kMfmaRowCols; // ... of layers with at least this many stacked columns (8 or 16)
     int light = -1;                   // blocking for small parameter sets: -1 by size, 0 never, 1 always
-    bool fine_blocks = true;          // row blocks of layers with q % 4 != 0 sized for four-float accesses
+    bool odd_units = true;            // units of four floats also on rows whose length is not a multiple of four ...
+    bool long_blocks = false;         // ... with the row blocks of the Q-sweep as long as one float per lane asks for
     int stream = -1;                  // non-temporal passes: -1 by size, 0 never, 1 always
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
                                       // 0 never, 1 where there are many of them, 2 always

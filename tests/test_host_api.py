@@ -228,6 +228,24 @@ def test_plan_with_mixed_degrees_in_one_layer():
     B.pg_destroy(ctx)
 
 
+@pytest.mark.parametrize("graph,rank,shapes", [
+    ("ring 8", 2, [(54126, 1162)]),
+    ("ring 16", 1, [(54126, 1310)]),
+    ("ring 16", 2, [(1518, 1438), (2411, 3939), (4117, 5466)]),
+    ("ring 14", 2, [(686, 5394), (1345, 78), (30054, 713)]),
+    ("ring 15", 2, [(487, 1772), (22676, 450), (5063, 10), (3994, 1699)]),
+    ("ring 20", 2, [(23961, 626)]),
+    ("ring 10", 1, [(59867, 443), (50006, 164)]),
+])
+def test_odd_rows_just_below_the_static_workspace_stay_accepted(graph, rank, shapes):
+    """Rows of odd length have two possible geometries (accesses of four floats, or of the width that
+    divides the row); where one of them fits the static workspace, pg_round_static takes the problem."""
+    n = int(graph.split()[1])
+    ctx = _init(n, W.ring_edges(n), 1 / 3, shapes, rank, 1)
+    assert B.pg_workspace_bytes(ctx) <= B.PG_STATIC_WORKSPACE_BYTES
+    B.pg_destroy(ctx)
+
+
 def test_planner_tiles_cover_every_matrix_exactly_once(tmp_path):
     """tests/plan_cover.cpp links the host planner alone (no HIP) and checks, for the benchmark
     shapes, odd shapes and mixed degrees, in each kernel-family setting: row tiles x segments and
