@@ -238,10 +238,10 @@ struct Launcher {
                     tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
             else if (c->plan.light)
                 row_kernel<RC, kRowsPerGroupLight, kPrefetchSteps, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
-                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, nullptr, nullptr);
+                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
             else
                 row_kernel<RC, kRowsPerGroup, kPrefetchSteps, UPD, SWP, GRAD, NT && UPD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
-                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, nullptr, nullptr);
+                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
         } else if (rc.mfma) {
 #define PG_MROW(VV) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD, NT> \
                 <<<dim3((unsigned)n), dim3(kThreads), kMrowLdsBytes, st>>>( \
@@ -315,8 +315,8 @@ struct Launcher {
             if (rc.tiles.empty()) continue;
             const int n = (int)rc.tiles.size();
             begin(SWP ? K_UPDATE_SWEEP_P : K_UPDATE, rc.elems * 4.0 * (PEND == kPeek ? 1.0 : 2.0));
-#define PG_ROWP(RC, M) row_kernel<RC, M, kPrefetchSteps, true, SWP, false, true, PEND><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
-                c->d_row_tiles + rc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta, phat1, q1)
+#define PG_ROWP(RC, M) row_pending_kernel<RC, M, kPrefetchSteps, SWP, PEND><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
+                c->d_row_tiles + rc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), phat1, q1)
             if (rc.RC == 1) PG_ROWP(1, kRowsPerGroup);
             else if (rc.RC == 2) PG_ROWP(2, kRowsPerGroup);
             else PG_ROWP(4, kRowsPerGroupLight);
@@ -350,14 +350,13 @@ struct Launcher {
                               (size_t)(kThreads / 64 - 1) * 64 * 4 * sizeof(double));
 #define PG_COL(VV) col_kernel<VV, RC, U><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
             c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, \
-            c->d_xs, left(), qw(), nullptr, nullptr)
+            c->d_xs, left(), qw())
         if constexpr (RC < kWideCols) {
             if (cc.vec)
                 vec_col_kernel<RC><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw());
             else if (RC <= kLazyCols && phat1)
-                col_kernel<0, RC <= kLazyCols ? RC : 1, U, true><<<dim3((unsigned)n), dim3(kThreads),
-                                                                 std::max(lds, lazy_col_lds(cc)), st>>>(
+                col_peek_kernel<RC <= kLazyCols ? RC : 1, U><<<dim3((unsigned)n), dim3(kThreads), std::max(lds, lazy_col_lds(cc)), st>>>(
                     c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw(), phat1, q1);
             else
                 PG_COL(0);
@@ -479,8 +478,9 @@ struct Launcher {
     void combine_q(float *hist = nullptr) {
         if (status || c->plan.comb_tiles.empty()) return;
         begin(K_COMBINE_Q, 0.0);
-        comb_kernel<<<dim3((unsigned)c->plan.comb_tiles.size()), dim3(kThreads), 0, st>>>(
-            c->d_comb, c->d_els, qw(), flags(), qstate, hist);
+        const dim3 grid((unsigned)c->plan.comb_tiles.size());
+        if (hist) comb_keep_kernel<<<grid, dim3(kThreads), 0, st>>>(c->d_comb, c->d_els, qw(), flags(), qstate, hist);
+        else comb_kernel<<<grid, dim3(kThreads), 0, st>>>(c->d_comb, c->d_els, qw(), flags(), qstate);
         check();
         end();
     }

@@ -414,17 +414,14 @@ __device__ __forceinline__ void vec_row_body(const RowTile &t, const PairDesc &p
     }
 }
 
-// One wavefront per tile; `reverse` walks the tile list backwards so that a pass can start on
-// the data the previous pass touched last (still resident in the memory-side cache).
-//   GRAD  : (with UPDATE) also subtract eta * G[row, c]: the update step of Algorithm 1 in one pass.
-template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT = false, int PEND = kApply>
-__global__ void __launch_bounds__(kRowThreads)
-row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
-           const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
-           float *const *__restrict__ xs, const float *__restrict__ qstate,
-           const float *__restrict__ phat, double *__restrict__ pw,
-           const float *const *__restrict__ gs, double eta,
-           const float *__restrict__ phat1, const float *__restrict__ q1) {
+// One tile of the narrow row kernels: the body that fits the layer.
+template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT, int PEND>
+__device__ __forceinline__ void row_tile(const RowTile *__restrict__ tiles, int ntiles, int reverse,
+                                         const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+                                         float *const *__restrict__ xs, const float *__restrict__ qstate,
+                                         const float *__restrict__ phat, double *__restrict__ pw,
+                                         const float *const *__restrict__ gs, double eta,
+                                         const float *__restrict__ phat1, const float *__restrict__ q1) {
     const RowTile t = tiles[tile_index(ntiles, reverse)];
     const PairDesc pd = pairs[t.pair];
     float *X = xs[pd.worker] + pd.x_off;
@@ -434,6 +431,31 @@ row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, true>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+}
+// One wavefront per tile; `reverse` walks the tile list backwards so that a pass can start on
+// the data the previous pass touched last (still resident in the memory-side cache).
+//   GRAD  : (with UPDATE) also subtract eta * G[row, c]: the update step of Algorithm 1 in one pass.
+template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT = false>
+__global__ void __launch_bounds__(kRowThreads)
+row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
+           const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+           float *const *__restrict__ xs, const float *__restrict__ qstate,
+           const float *__restrict__ phat, double *__restrict__ pw,
+           const float *const *__restrict__ gs, double eta) {
+    row_tile<RC, M, D, UPDATE, SWEEP, GRAD, NT, kApply>(tiles, ntiles, reverse, pairs, cols, xs, qstate, phat, pw, gs, eta, nullptr, nullptr);
+}
+// The passes of a run that writes every second round.  Kernels of their own for the two arguments
+// more: the host's share of a launch grows with every pointer argument, and small sets are bound by it
+// (100 x 100, ring of 8, ten rounds, 41 launches: 141 us; with two more pointers on the row and column
+// kernels and one on the combine 156 us, the kernels themselves taking the same time).
+template <int RC, int M, int D, bool SWEEP, int PEND>
+__global__ void __launch_bounds__(kRowThreads)
+row_pending_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
+                   const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+                   float *const *__restrict__ xs, const float *__restrict__ qstate,
+                   const float *__restrict__ phat, double *__restrict__ pw,
+                   const float *__restrict__ phat1, const float *__restrict__ q1) {
+    row_tile<RC, M, D, true, SWEEP, false, true, PEND>(tiles, ntiles, reverse, pairs, cols, xs, qstate, phat, pw, nullptr, 0.0, phat1, q1);
 }
 
 // The row passes over vector layers alone (one wavefront per tile): the same arithmetic as the
@@ -1345,15 +1367,14 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
     }
 }
 
-// V = 0: tiles of any vector width (few stacked columns); V = 1, 2, 4: one width only.
-template <int V, int RC, int U, bool PEEK = false>
-__global__ void __launch_bounds__(kThreads)
-col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
-           const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
-           float *const *__restrict__ xs, const float *__restrict__ phat,
-           double *__restrict__ qw, const float *__restrict__ phat1, const float *__restrict__ q1) {
-    extern __shared__ double smem[];  // [blk_rows][RC] Phat floats, then reused for the reduction
-    float *sT = reinterpret_cast<float *>(smem);
+// One tile of the column kernels.  V = 0: tiles of any vector width (few stacked columns); V = 1, 2,
+// 4: one width only.
+template <int V, int RC, int U, bool PEEK>
+__device__ __forceinline__ void col_tile(const ColTile *__restrict__ tiles, int ntiles, int reverse,
+                                         const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+                                         float *const *__restrict__ xs, const float *__restrict__ phat,
+                                         double *__restrict__ qw, float *sT,
+                                         const float *__restrict__ phat1, const float *__restrict__ q1) {
     const ColTile t = tiles[tile_index(ntiles, reverse)];
     const PairDesc pd = pairs[t.pair];
     const float *X = xs[pd.worker] + pd.x_off;
@@ -1365,6 +1386,25 @@ col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
         else if (pd.V == 2) col_body<2, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
         else col_body<1, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     }
+}
+template <int V, int RC, int U>
+__global__ void __launch_bounds__(kThreads)
+col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
+           const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+           float *const *__restrict__ xs, const float *__restrict__ phat,
+           double *__restrict__ qw) {
+    extern __shared__ double smem[];  // [blk_rows][RC] Phat floats, then reused for the reduction
+    col_tile<V, RC, U, false>(tiles, ntiles, reverse, pairs, cols, xs, phat, qw, reinterpret_cast<float *>(smem), nullptr, nullptr);
+}
+// X one update behind (see run_lazy in the launch code); a kernel of its own as row_pending_kernel is
+template <int RC, int U>
+__global__ void __launch_bounds__(kThreads)
+col_peek_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
+                const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+                float *const *__restrict__ xs, const float *__restrict__ phat,
+                double *__restrict__ qw, const float *__restrict__ phat1, const float *__restrict__ q1) {
+    extern __shared__ double smem[];
+    col_tile<0, RC, U, true>(tiles, ntiles, reverse, pairs, cols, xs, phat, qw, reinterpret_cast<float *>(smem), phat1, q1);
 }
 
 // The Q-sweep of vector layers alone: X_i^T Phat_j is a dot product per stacked column.  One
@@ -1723,11 +1763,11 @@ orth_gram_apply_kernel(const OrthTile *__restrict__ tiles, const EdgeLayerDesc *
 
 // Per (edge, layer): Q' = (sum of worker a's row-block partials) - (worker b's), rounded to
 // float into the state buffer; the column of a dropped Phat keeps its old state.
-// (Algorithm 2: v_ij <- p_j - p_i, unnormalised.)  `hist` (may be null) receives the state as it was.
-__global__ void __launch_bounds__(kThreads)
-comb_kernel(const CombTile *__restrict__ tiles, const EdgeLayerDesc *__restrict__ els,
-            const double *__restrict__ qw, const int32_t *__restrict__ flags,
-            float *__restrict__ qstate, float *__restrict__ hist) {
+// (Algorithm 2: v_ij <- p_j - p_i, unnormalised.)  `hist`, where there is one, receives the
+// state as it was.
+__device__ __forceinline__ void comb_tile(const CombTile *__restrict__ tiles, const EdgeLayerDesc *__restrict__ els,
+                                          const double *__restrict__ qw, const int32_t *__restrict__ flags,
+                                          float *__restrict__ qstate, float *__restrict__ hist) {
     const CombTile t = tiles[blockIdx.x];
     const EdgeLayerDesc d = els[t.el];
     const int64_t idx = (int64_t)t.first + threadIdx.x;  // k * q + c
@@ -1750,6 +1790,17 @@ comb_kernel(const CombTile *__restrict__ tiles, const EdgeLayerDesc *__restrict_
         sb[0] += qw[d.qwb_off + b * d.qwb_blk + idx];
     }
     qstate[d.q_off + idx] = (float)(((sa[0] + sa[1]) + (sa[2] + sa[3])) - ((sb[0] + sb[1]) + (sb[2] + sb[3])));
+}
+__global__ void __launch_bounds__(kThreads)
+comb_kernel(const CombTile *__restrict__ tiles, const EdgeLayerDesc *__restrict__ els,
+            const double *__restrict__ qw, const int32_t *__restrict__ flags, float *__restrict__ qstate) {
+    comb_tile(tiles, els, qw, flags, qstate, nullptr);
+}
+__global__ void __launch_bounds__(kThreads)
+comb_keep_kernel(const CombTile *__restrict__ tiles, const EdgeLayerDesc *__restrict__ els,
+                 const double *__restrict__ qw, const int32_t *__restrict__ flags,
+                 float *__restrict__ qstate, float *__restrict__ hist) {
+    comb_tile(tiles, els, qw, flags, qstate, hist);
 }
 
 }  // namespace pg

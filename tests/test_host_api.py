@@ -309,9 +309,28 @@ def test_profile_summaries_classify_every_pass_kernel():
     assert kernel_kind("pg::col_kernel<0, 2, 8>") == "sweep_q"
     assert kernel_kind("pg::mcol_kernel<4, 2>") == "sweep_q"
     assert kernel_kind("pg::vec_col_kernel<4>") == "sweep_q"
+    assert kernel_kind("pg::col_peek_kernel<2, 8>") == "sweep_q"
+    assert kernel_kind("pg::row_pending_kernel<2, 8, 1, true, 2>") == "update_sweep_p"
+    assert kernel_kind("pg::row_pending_kernel<2, 8, 1, false, 2>") == "update"
     assert kernel_kind("pg::comb_kernel") is None
     assert kernel_kind("pg::orth_gram_kernel<256, 2>") is None
     for wl in ("vgg16_r1", "vgg16_r2", "lstm", "resnet50"):
         path = os.path.join(ROOT, "profiles", f"{wl}_traffic_counters.txt")
         kinds = {line.split()[1] for line in open(path) if line.startswith("traffic ")}
         assert kinds == {"sweep_p", "sweep_q", "update", "update_sweep_p"}, (wl, kinds)
+
+
+def test_kernels_of_small_sets_take_only_the_arguments_they_use():
+    """Every pointer argument adds to the host's share of a launch, and calls on small sets are bound by it:
+    the vectors of a pending update are arguments of the kernels that apply one."""
+    import code_objects
+    kernels = code_objects.kernels(B.LIB_PATH)
+    found = {"row": 0, "col": 0, "comb": 0}
+    for name, kernel in kernels.items():
+        for stem, most in (("row_kernel<", 11), ("row_pending_kernel<", 11), ("vec_row_kernel<", 11), ("row_wide_kernel<", 11),
+                           ("mrow_kernel<", 11), ("col_kernel<", 8), ("vec_col_kernel<", 8), ("mcol_kernel<", 8),
+                           ("comb_kernel", 5)):
+            if name.startswith("pg::" + stem):
+                assert code_objects.arguments(kernel) <= most, (name, code_objects.arguments(kernel))
+                found[next(k for k in found if k in stem)] += 1
+    assert found["row"] >= 12 and found["col"] >= 3 and found["comb"] == 1
