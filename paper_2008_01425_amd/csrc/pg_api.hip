@@ -57,7 +57,6 @@ struct pg_ctx {
     float **d_gs = nullptr;
     std::vector<const float *> gs_cached;
     bool mcol_stage = true;  // matrix-core Q-sweep: Phat of a tile's row block staged in LDS
-    bool lazy = true;  // runs write the parameters every second round where that pays
     bool profiling = false;
     // Passes alternate direction through the parameters: each starts where the one before it
     // (also the last one of an earlier call) ended, on data still in the memory-side cache.
@@ -144,26 +143,6 @@ constexpr int kPrefetchSteps = 1;
 // LSTM-shaped torus: deeper rings only cost registers).
 constexpr int kMfmaRowPrefetch = 1;
 constexpr int kMfmaColPrefetch = 2;
-
-// Whether a run writes the parameters every second round only (see run_lazy).
-// Measured on VGG-16 shapes, ring of 16, ten rounds a call: rank 1 (2 stacked columns) 5.55 -> 4.50 ms;
-// rank 2 (4 columns) gains 7 % with 4 rows per lane group and loses 12 % with 8, whose coefficients
-// for two updates no longer fit the registers.
-constexpr int kLazyCols = 4;
-constexpr size_t kLazyColLds = 64 * 1024;
-size_t lazy_col_lds(const ColClass &cc) {
-    return (size_t)(cc.max_rows + 2) * cc.RC * (sizeof(float) + sizeof(double)) + 16;
-}
-bool runs_lazily(const Plan &P) {
-    if (!P.stream || P.light || P.steps != 1 || P.max_groups > 1) return false;
-    // the second Phat buffer lies in the column-by-column Gram-Schmidt's scratch
-    if (P.ws_ph - P.ws_pd < P.pstate_floats * sizeof(float)) return false;
-    for (const RowClass &rc : P.row_classes)
-        if (rc.RC > kLazyCols || rc.vec) return false;
-    for (const ColClass &cc : P.col_classes)
-        if (cc.RC > kLazyCols || cc.vec || lazy_col_lds(cc) > kLazyColLds) return false;
-    return true;
-}
 
 struct Launcher {
     pg_ctx *c;
@@ -305,7 +284,9 @@ struct Launcher {
         }
         turn();
     }
-    // Row pass of a run that writes every second round (narrow classes only): PEND as in row_body.
+    // Row pass of a run that writes every second round (narrow classes only): PEND as in row_body.  All
+    // of them stream, the peeking one too although it only reads (VGG-16 shapes, ring of 16, ten rounds:
+    // 4.30 ms, read through the caches 4.33).
     template <int PEND, bool SWP>
     void rows_pending() {
         if (status) return;
@@ -356,7 +337,7 @@ struct Launcher {
                 vec_col_kernel<RC><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw());
             else if (RC <= kLazyCols && phat1)
-                col_peek_kernel<RC <= kLazyCols ? RC : 1, U><<<dim3((unsigned)n), dim3(kThreads), std::max(lds, lazy_col_lds(cc)), st>>>(
+                col_peek_kernel<RC <= kLazyCols ? RC : 1, U><<<dim3((unsigned)n), dim3(kThreads), std::max(lds, lazy_col_lds(cc.max_rows, RC)), st>>>(
                     c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw(), phat1, q1);
             else
                 PG_COL(0);
@@ -584,7 +565,7 @@ int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *wor
     // Measured: with the passes that write (update + sweep) walking forwards and the Q-sweeps
     // backwards a run of fused rounds is 4 % faster than its mirror image, so a run starts forwards.
     if (fuse) c->reverse = 0;
-    if (c->lazy && fuse && rounds > 1 && runs_lazily(c->plan)) {
+    if (c->plan.lazy && fuse && rounds > 1) {
         run_lazy(L, rounds);
         return L.status;
     }
@@ -635,7 +616,7 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     if (const char *e = getenv("PG_MFMA_ROWS")) tune.mfma_rows = atoi(e) != 0;
     if (const char *e = getenv("PG_MFMA_COLS")) tune.mfma_cols = atoi(e) != 0;
     if (const char *e = getenv("PG_MCOL_STAGE")) c->mcol_stage = atoi(e) != 0;
-    if (const char *e = getenv("PG_LAZY")) c->lazy = atoi(e) != 0;
+    if (const char *e = getenv("PG_LAZY")) tune.lazy = atoi(e) != 0;
     if (const char *e = getenv("PG_STREAM")) tune.stream = atoi(e) != 0;
     if (const char *e = getenv("PG_LIGHT")) tune.light = atoi(e) != 0;
     if (const char *e = getenv("PG_VEC_KERNELS")) tune.vec_kernels = std::min(2, std::max(0, atoi(e)));

@@ -13,12 +13,22 @@ constexpr int kMaxCols = 16;   // largest R = deg(i) * r_l one pass supports
 constexpr int kThreads = 256;  // work-group size of the column-owner and combine kernels (4 wavefronts)
 constexpr int kRowThreads = 64;  // narrow row-owner kernels: one wavefront per tile
 constexpr int64_t kLightBytes = 64ll << 20;  // parameter bytes (all workers) up to which the narrow row kernels block 4 rows, not 8
-// Parameter bytes (all workers) above which passes stream them past the caches.  Measured with one
-// matrix cut to size, streamed / plain: up to 4 stacked columns 1.04 (round) and 0.97 (run) at 208 MB,
-// 1.01 and 0.93 at 302 MB, 0.97 and 0.88 at 377 MB; 8 columns 1.03 at 472 MB, 0.98 at 604 MB; 16
-// columns 1.00 at 377 MB, 0.97 at 604 MB.
+// Parameter bytes (all workers) above which passes stream them past the caches, where the rows suit
+// it (see streams()).  Measured with one matrix of 4608 columns cut to size, streamed / plain: up to 4
+// stacked columns 1.04 (round) and 0.97 (run) at 208 MB, 1.01 and 0.93 at 302 MB, 0.97 and 0.88 at
+// 377 MB; 8 columns 1.03 at 472 MB, 0.98 at 604 MB; 16 columns 1.00 at 377 MB, 0.97 at 604 MB.
 constexpr int64_t kStreamBytes = 320ll << 20;
 constexpr int64_t kStreamBytesWide = 512ll << 20;  // 8-16 stacked columns
+// Share of the elements that has to lie in layers that gain from streamed passes (from runs that write every
+// second round).  The hint goes with the launch, not the layer: it gains 3-5 % on rows that suit it and
+// costs 5-20 % on the others, so about three quarters break even.
+constexpr double kStreamShare = 0.75;
+// Runs that write every second round: at most this many stacked columns, and this much LDS for a
+// peeking column kernel's work-group (Phat and the pending coefficients of a row block).
+// Measured on VGG-16 shapes, ring of 16, ten rounds a call: rank 1 (2 stacked columns) 5.55 -> 4.50 ms; at 4
+// columns 4 rows per lane group gain 7 % and 8 rows, which spill, lose 12 %.
+constexpr int kLazyCols = 4;
+constexpr int kLazyColLds = 64 * 1024;
 // Narrow kernels: rows of at least this many floats are moved four at a time whatever q is (see
 // row_body).  Shorter ones are a few vectors at most and go by the widest one that divides q.  Measured on one
 // matrix of 531 MB, ring of 16, rank 1, one round: 4607 columns 597 -> 433 us, 577 columns 710 -> 540 us

@@ -27,6 +27,28 @@ int rows_unroll(int RC, bool light) {
     return 4;
 }
 
+// Whether streamed passes over this layer gain, given the stacked columns a pass compiles.  A cache
+// line that two load instructions share, or that a row fills in part, is fetched (and written) twice
+// when it is not kept.  Measured on single matrices of 350-1200 MB, streamed / plain time of a round, an SGD
+// round and a run of two to four rounds:
+//   1-4 columns  q % 32 == 0: 0.97-1.00, 0.94-0.97; q = 48, 80, 144: 1.00-1.03, 0.98-1.01;
+//                q = 100: 1.04, 1.01; 577: 1.17, 1.11; 4607: 1.04, 1.04; 50: 1.25, 1.15; 12: 1.24, 1.19
+//   8 columns    q % 16 == 0: 0.94-1.02; padded rows: q = 72 1.11-1.14, 1.04-1.08; 130: 1.06-1.11, 0.97-1.05;
+//                300: 0.96-1.05, 0.92-1.00; 650 and more: 0.94-1.00; unpadded q = 33 to 63: 1.25-1.67
+//   16 columns   padded rows: 0.92-1.00; unpadded q = 24, 40, 48: 0.96-1.00; q = 33, 50, 63: 1.01-1.18
+bool streams(const LayerInfo &L, int rc) {
+    if (rc < kWideCols) return L.q % 32 == 0;
+    if (rc < kMaxCols) return L.q % 16 == 0 || L.q >= 256;
+    return L.ld % 8 == 0;
+}
+// Whether runs that write every second round gain on this layer.  Measured as above, time of a run over the plain
+// run's: up to 2 columns q = 6 to 24: 1.03-1.19, 32 and more: 0.81-0.98; 4 columns q % 32 == 0: 0.97-1.02,
+// q = 12 to 300: 0.98-1.04, 577: 0.94-0.96, 4607: 0.88.
+bool gains_behind(const LayerInfo &L, int rc) {
+    if (rc <= 2) return L.q >= 32;
+    return L.q % 32 == 0 || L.q >= 512;
+}
+
 int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune) {
@@ -126,11 +148,19 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         const double slots = 4096.0;  // 256 CUs x 4 SIMDs x a few wavefronts
         P.light = tune.light < 0 ? total_bytes <= (double)kLightBytes : tune.light != 0;
         bool wide = false;  // some worker has 8 or more stacked columns in a pass
+        double streamed = 0.0, behind = 0.0, elems = 0.0;
         for (const LayerInfo &L : P.layers) {
             const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
-            wide = wide || compiled_cols(std::max(1, per_pass * L.r)) >= kWideCols;
+            const int rc = compiled_cols(std::max(1, per_pass * L.r));
+            const double n_el = (double)L.p * L.q;
+            wide = wide || rc >= kWideCols;
+            elems += n_el;
+            if (streams(L, rc)) streamed += n_el;
+            if (gains_behind(L, rc)) behind += n_el;
         }
-        P.stream = tune.stream < 0 ? total_bytes > (double)(wide ? kStreamBytesWide : kStreamBytes) : tune.stream != 0;
+        P.large = tune.stream < 0 ? total_bytes > (double)(wide ? kStreamBytesWide : kStreamBytes) : tune.stream != 0;
+        P.stream = tune.stream < 0 ? P.large && streamed >= kStreamShare * elems : tune.stream != 0;
+        P.lazy = tune.lazy < 0 ? P.large && behind >= kStreamShare * elems : tune.lazy != 0;
         tn.row_tile_bytes = (int)std::max((P.light ? 4.0 : 8.0) * 1024, std::min((double)tune.row_tile_bytes, total_bytes / slots));
         tn.col_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.col_tile_bytes, 4.0 * total_bytes / slots));
         tn.wide_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.wide_tile_bytes, 4.0 * total_bytes / slots));
@@ -152,7 +182,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     // round); in large ones, or where all rows are padded, it pays (LSTM SGD round 2.87 -> 2.74 ms).
     bool all_padded = true;
     for (const LayerInfo &L : P.layers) all_padded = all_padded && L.ld % 4 == 0;
-    const bool wide_units = tune.odd_units && tune.mfma_cols && (P.stream || all_padded);
+    const bool wide_units = tune.odd_units && tune.mfma_cols && (P.large || all_padded);
     constexpr int kColUnroll = 8;
     for (int l = 0; l < n_layers; ++l) {
         const LayerInfo &L = P.layers[l];
@@ -487,6 +517,12 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             cc.max_rows = std::max(cc.max_rows, g.blk_rows);
         }
     }
+    // Runs that write every second round: narrow kernels only, one power step, one column group, and the
+    // second Phat buffer lies in the column-by-column Gram-Schmidt's scratch.
+    P.lazy = P.lazy && !P.light && P.steps == 1 && P.max_groups == 1 && P.ws_ph - P.ws_pd >= P.pstate_floats * sizeof(float);
+    for (const RowClass &rc : P.row_classes) P.lazy = P.lazy && rc.RC <= kLazyCols && !rc.vec;
+    for (const ColClass &cc : P.col_classes)
+        P.lazy = P.lazy && cc.RC <= kLazyCols && !cc.vec && lazy_col_lds(cc.max_rows, cc.RC) <= (size_t)kLazyColLds;
     return PG_OK;
 }
 

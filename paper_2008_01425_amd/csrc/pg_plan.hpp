@@ -54,7 +54,8 @@ struct Tuning {
     int light = -1;                   // blocking for small parameter sets: -1 by size, 0 never, 1 always
     bool odd_units = true;            // units of four floats also on rows whose length is not a multiple of four ...
     bool long_blocks = false;         // ... with the row blocks of the Q-sweep as long as one float per lane asks for
-    int stream = -1;                  // non-temporal passes: -1 by size, 0 never, 1 always
+    int stream = -1;                  // non-temporal passes: -1 by size and row length, 0 never, 1 always
+    int lazy = -1;                    // runs that write every second round: the same, where the kernels can
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
                                       // 0 never, 1 where there are many of them, 2 always
 };
@@ -94,9 +95,13 @@ struct Plan {
     // dependent loads, so the narrow row kernels block fewer rows per lane group (half the
     // registers, twice the wavefronts per SIMD) over tiles half as large.
     bool light = false;
-    // The parameters of all workers do not fit the memory-side cache: passes that write them, and
-    // all passes over 8-16 stacked columns, stream them past the caches (non-temporal).
+    // The parameters of all workers do not fit the memory-side cache.
+    bool large = false;
+    // Passes that write them, and all passes over 8-16 stacked columns, stream them past the caches
+    // (non-temporal): large sets whose rows mostly consist of whole cache lines.
     bool stream = false;
+    // Runs write them every second round only.
+    bool lazy = false;
     int max_layer_rank = 1;                  // largest r_l
     int max_rows = 1;                        // largest p_l
 };
@@ -108,6 +113,11 @@ int rows_unroll(int RC, bool light = false);
 int compiled_cols(int R);
 
 // Returns PG_OK or a negative status; on success `plan` is complete.
+// LDS of a peeking column kernel's work-group: the row block's Phat (floats) and pending coefficients (doubles).
+inline size_t lazy_col_lds(int max_rows, int RC) {
+    return (size_t)(max_rows + 2) * RC * (sizeof(float) + sizeof(double)) + 16;
+}
+
 int build_plan(Plan &plan, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune);

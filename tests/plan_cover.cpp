@@ -153,6 +153,22 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
     return 0;
 }
 
+// Which sets have their passes streamed, and which runs write every second round (`one` layer shape besides
+// an optional second).
+static int check_paths(const char *name, int n, const std::vector<int32_t> &e, const std::vector<int32_t> &rows,
+                       const std::vector<int32_t> &cols, int rank, int steps, bool stream, bool lazy) {
+    Plan P;
+    std::vector<float> w(e.size() / 2, 0.2f);
+    int rc = build_plan(P, n, (int)w.size(), e.data(), w.data(), (int)rows.size(), rows.data(), cols.data(), rank, steps, Tuning());
+    REQUIRE(rc == PG_OK, "build_plan returned %d", rc);
+    REQUIRE(P.stream == stream, "streamed: %d", P.stream);
+    REQUIRE(P.lazy == lazy, "writes every second round: %d", P.lazy);
+    for (const ColClass &c : P.col_classes)
+        if (P.lazy) REQUIRE(lazy_col_lds(c.max_rows, c.RC) <= 64 * 1024 && c.RC <= 4 && !c.vec, "peeking column kernel of %d rows", c.max_rows);
+    printf("as expected: %s\n", name);
+    return 0;
+}
+
 int main() {
     int bad = 0;
     std::vector<Tuning> tunings(4);
@@ -240,6 +256,32 @@ int main() {
         bad |= check(label, n, e, w, r, c, rnd(1, 16), rnd(1, 3), tunings[trial % tunings.size()]);
         ++nrandom;
     }
+    std::vector<int32_t> r16, t4, t3;
+    ring(16, r16);
+    torus(4, 4, t4);
+    torus(3, 3, t3);
+    const std::vector<int32_t> vr = {64, 64, 128, 128, 256, 256, 256, 512, 512, 512, 512, 512, 512, 10, 512},
+                               vc = {27, 576, 576, 1152, 1152, 2304, 2304, 2304, 4608, 4608, 4608, 4608, 4608, 512, 1};
+    bad |= check_paths("vgg16 rank 1", 16, r16, vr, vc, 1, 1, true, true);
+    bad |= check_paths("vgg16 rank 2", 16, r16, vr, vc, 2, 1, true, true);
+    bad |= check_paths("vgg16, two power steps", 16, r16, vr, vc, 1, 2, true, false);
+    bad |= check_paths("lstm torus rank 4", 16, t4, {33278, 2600, 2600, 2600, 2600}, {650, 650, 650, 650, 650}, 4, 1, true, false);
+    bad |= check_paths("small", 16, r16, {512}, {4608}, 1, 1, false, false);
+    // rows that are not whole cache lines are not streamed, however large the set
+    bad |= check_paths("table of 12 columns", 16, r16, {600000}, {12}, 1, 1, false, false);
+    bad |= check_paths("577 columns", 16, r16, {13000}, {577}, 1, 1, false, true);
+    bad |= check_paths("577 columns rank 2", 16, r16, {13000}, {577}, 2, 1, false, true);
+    bad |= check_paths("100 columns rank 2", 16, r16, {80000}, {100}, 2, 1, false, false);
+    bad |= check_paths("63 columns, 8 stacked", 9, t3, {400000}, {63}, 2, 1, false, false);
+    bad |= check_paths("100 columns, 8 stacked", 9, t3, {300000}, {100}, 2, 1, false, false);
+    bad |= check_paths("100 columns, 16 stacked", 9, t3, {300000}, {100}, 4, 1, true, false);
+    bad |= check_paths("50 columns, 16 stacked", 9, t3, {600000}, {50}, 4, 1, false, false);
+    // three quarters of the elements decide
+    bad |= check_paths("lines beside few odd rows", 16, r16, {4096, 1000}, {4608, 577}, 1, 1, true, true);
+    bad |= check_paths("lines beside many odd rows", 16, r16, {2048, 13000}, {4608, 577}, 1, 1, false, true);
+    // one long vector or tall narrow layer keeps the whole run writing every round (its row block of the
+    // column kernel does not fit beside the pending coefficients)
+    bad |= check_paths("a bias of 2800", 16, r16, {4096, 2800}, {4608, 1}, 1, 1, true, false);
     if (!bad) printf("ok %d random problems\n", nrandom);
     return bad;
 }
