@@ -207,6 +207,15 @@ struct Launcher {
         if (c->plan.stream) row_launch_nt<RC, UPD, SWP, GRAD, true>(rc);
         else row_launch_nt<RC, UPD, SWP, GRAD, false>(rc);
     }
+    template <int RC, int M, bool UPD, bool SWP, bool GRAD, bool NT>
+    void narrow_launch(const RowTile *tiles, int n) {
+        if (c->plan.odd_rows)
+            row_kernel<RC, M, kPrefetchSteps, UPD, SWP, GRAD, NT, true><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
+                tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
+        else
+            row_kernel<RC, M, kPrefetchSteps, UPD, SWP, GRAD, NT, false><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
+                tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
+    }
     template <int RC, bool UPD, bool SWP, bool GRAD, bool NT>
     void row_launch_nt(const RowClass &rc) {
         const int n = (int)rc.tiles.size();
@@ -216,11 +225,9 @@ struct Launcher {
                 vec_row_kernel<RC, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
             else if (c->plan.light)
-                row_kernel<RC, kRowsPerGroupLight, kPrefetchSteps, UPD, SWP, GRAD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
-                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
+                narrow_launch<RC, kRowsPerGroupLight, UPD, SWP, GRAD, false>(tiles, n);
             else
-                row_kernel<RC, kRowsPerGroup, kPrefetchSteps, UPD, SWP, GRAD, NT && UPD><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
-                    tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta);
+                narrow_launch<RC, kRowsPerGroup, UPD, SWP, GRAD, NT && UPD>(tiles, n);
         } else if (rc.mfma) {
 #define PG_MROW(VV) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD, NT> \
                 <<<dim3((unsigned)n), dim3(kThreads), kMrowLdsBytes, st>>>( \
@@ -296,12 +303,14 @@ struct Launcher {
             if (rc.tiles.empty()) continue;
             const int n = (int)rc.tiles.size();
             begin(SWP ? K_UPDATE_SWEEP_P : K_UPDATE, rc.elems * 4.0 * (PEND == kPeek ? 1.0 : 2.0));
-#define PG_ROWP(RC, M) row_pending_kernel<RC, M, kPrefetchSteps, SWP, PEND><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
+#define PG_ROWP_(RC, M, ANY) row_pending_kernel<RC, M, kPrefetchSteps, SWP, PEND, ANY><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
                 c->d_row_tiles + rc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), phat1, q1)
+#define PG_ROWP(RC, M) do { if (c->plan.odd_rows) PG_ROWP_(RC, M, true); else PG_ROWP_(RC, M, false); } while (0)
             if (rc.RC == 1) PG_ROWP(1, kRowsPerGroup);
             else if (rc.RC == 2) PG_ROWP(2, kRowsPerGroup);
             else PG_ROWP(4, kRowsPerGroupLight);
 #undef PG_ROWP
+#undef PG_ROWP_
             check();
             end();
         }
@@ -329,18 +338,24 @@ struct Launcher {
         // LDS: the staged Phat slice plus one zero row, later reused for the cross-wavefront sums
         size_t lds = std::max((size_t)(cc.max_rows + 1) * RC * sizeof(float),
                               (size_t)(kThreads / 64 - 1) * 64 * 4 * sizeof(double));
-#define PG_COL(VV) col_kernel<VV, RC, U><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
+#define PG_COL(VV, ANY) col_kernel<VV, RC, U, ANY><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
             c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, \
             c->d_xs, left(), qw())
         if constexpr (RC < kWideCols) {
             if (cc.vec)
                 vec_col_kernel<RC><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>(
                     c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw());
-            else if (RC <= kLazyCols && phat1)
-                col_peek_kernel<RC <= kLazyCols ? RC : 1, U><<<dim3((unsigned)n), dim3(kThreads), std::max(lds, lazy_col_lds(cc.max_rows, RC)), st>>>(
-                    c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw(), phat1, q1);
+            else if (RC <= kLazyCols && phat1) {
+#define PG_PEEK(ANY) col_peek_kernel<RC <= kLazyCols ? RC : 1, U, ANY><<<dim3((unsigned)n), dim3(kThreads), \
+                std::max(lds, lazy_col_lds(cc.max_rows, RC)), st>>>( \
+                c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, left(), qw(), phat1, q1)
+                if (c->plan.odd_rows) PG_PEEK(true);
+                else PG_PEEK(false);
+#undef PG_PEEK
+            } else if (c->plan.odd_rows)
+                PG_COL(0, true);
             else
-                PG_COL(0);
+                PG_COL(0, false);
         } else if (c->plan.mfma_cols) {
 #define PG_MCOL(VV, STAGE, LDS) do { if (c->plan.stream) PG_MCOL_NT(VV, STAGE, LDS, true); else PG_MCOL_NT(VV, STAGE, LDS, false); } while (0)
 #define PG_MCOL_NT(VV, STAGE, LDS, NT) mcol_kernel<VV, kMfmaColPrefetch, STAGE, NT><<<dim3((unsigned)n), dim3(kThreads), LDS, st>>>( \
@@ -362,9 +377,9 @@ struct Launcher {
 #undef PG_MCOL
 #undef PG_MCOL_NT
         } else {
-            if (cc.V == 4) PG_COL(4);
-            else if (cc.V == 2) PG_COL(2);
-            else PG_COL(1);
+            if (cc.V == 4) PG_COL(4, false);
+            else if (cc.V == 2) PG_COL(2, false);
+            else PG_COL(1, false);
         }
 #undef PG_COL
     }
@@ -618,6 +633,8 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     if (const char *e = getenv("PG_MCOL_STAGE")) c->mcol_stage = atoi(e) != 0;
     if (const char *e = getenv("PG_LAZY")) tune.lazy = atoi(e) != 0;
     if (const char *e = getenv("PG_STREAM")) tune.stream = atoi(e) != 0;
+    if (const char *e = getenv("PG_ODD_ROWS")) tune.odd_rows = atoi(e) != 0;
+    if (const char *e = getenv("PG_WIDE_UNITS")) tune.wide_units = atoi(e) != 0;
     if (const char *e = getenv("PG_LIGHT")) tune.light = atoi(e) != 0;
     if (const char *e = getenv("PG_VEC_KERNELS")) tune.vec_kernels = std::min(2, std::max(0, atoi(e)));
     if (const char *e = getenv("PG_MFMA_ROW_COLS")) tune.mfma_row_cols = atoi(e) <= 8 ? 8 : 16;

@@ -34,6 +34,11 @@ constexpr int kLazyColLds = 64 * 1024;
 // matrix of 531 MB, ring of 16, rank 1, one round: 4607 columns 597 -> 433 us, 577 columns 710 -> 540 us
 // (one and two floats at a time before; 4606 columns 476 -> 433 us).
 constexpr int kAnyAlignCols = 16;
+// Share of the elements in such rows from which the kernels that carry a body for them are launched.
+// Measured, those kernels / the ones without on matrices of 576 (4608, 32, 152) columns beside some of
+// 577 (4607, 27, 153), 8 to 300 MB, ring of 8, round, SGD round and run at ranks 1 and 2: no such rows
+// 0.98-1.03; share 0.003: 0.94-1.04; 0.01: 0.80-1.05; 0.05: 0.75-1.04; all rows: 0.49-1.08.
+constexpr double kOddShare = 0.01;
 constexpr int kVecClassPairs = 1024;  // (worker, vector layer) pairs from which vector layers get kernels of their own
 constexpr int kWideCols = 8;     // from this many compiled columns on, row tiles stage Q in LDS
 constexpr int kWideLdsBytes = 48 * 1024;  // LDS budget of a wide row tile's Q slice

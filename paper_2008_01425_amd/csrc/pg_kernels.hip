@@ -414,8 +414,11 @@ __device__ __forceinline__ void vec_row_body(const RowTile &t, const PairDesc &p
     }
 }
 
-// One tile of the narrow row kernels: the body that fits the layer.
-template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT, int PEND>
+// One tile of the narrow row kernels: the body that fits the layer.  ANY: sets planned with units of
+// four floats on rows of odd length (Plan::odd_rows).  Instantiations of their own, because that body needs
+// the most registers and every other set would run at its occupancy (2 columns, sweep of small sets: 127 against 136
+// VGPRs, 4 against 3 wavefronts per SIMD; resnet20, ring of 8: SGD round 29.8 against 30.7 us, ten rounds 241 against 248).
+template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT, int PEND, bool ANY>
 __device__ __forceinline__ void row_tile(const RowTile *__restrict__ tiles, int ntiles, int reverse,
                                          const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
                                          float *const *__restrict__ xs, const float *__restrict__ qstate,
@@ -427,35 +430,35 @@ __device__ __forceinline__ void row_tile(const RowTile *__restrict__ tiles, int 
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
     if (pd.q == 1) vec_row_body<RC, UPDATE, SWEEP, GRAD, PEND>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else if (pd.V == 4 && (pd.q & 3) == 0) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
-    else if (pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, true>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (pd.V == 4 && (!ANY || (pd.q & 3) == 0)) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
+    else if (ANY && pd.V == 4) row_body<4, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, true>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else if (pd.V == 2) row_body<2, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
     else row_body<1, RC, M, D, UPDATE, SWEEP, GRAD, PEND, NT, false>(t, pd, cols, X, qstate, phat, pw, Gp, eta, phat1, q1);
 }
 // One wavefront per tile; `reverse` walks the tile list backwards so that a pass can start on
 // the data the previous pass touched last (still resident in the memory-side cache).
 //   GRAD  : (with UPDATE) also subtract eta * G[row, c]: the update step of Algorithm 1 in one pass.
-template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT = false>
+template <int RC, int M, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT, bool ANY>
 __global__ void __launch_bounds__(kRowThreads)
 row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
            const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
            float *const *__restrict__ xs, const float *__restrict__ qstate,
            const float *__restrict__ phat, double *__restrict__ pw,
            const float *const *__restrict__ gs, double eta) {
-    row_tile<RC, M, D, UPDATE, SWEEP, GRAD, NT, kApply>(tiles, ntiles, reverse, pairs, cols, xs, qstate, phat, pw, gs, eta, nullptr, nullptr);
+    row_tile<RC, M, D, UPDATE, SWEEP, GRAD, NT, kApply, ANY>(tiles, ntiles, reverse, pairs, cols, xs, qstate, phat, pw, gs, eta, nullptr, nullptr);
 }
 // The passes of a run that writes every second round.  Kernels of their own for the two arguments
 // more: the host's share of a launch grows with every pointer argument, and small sets are bound by it
 // (100 x 100, ring of 8, ten rounds, 41 launches: 141 us; with two more pointers on the row and column
 // kernels and one on the combine 156 us, the kernels themselves taking the same time).
-template <int RC, int M, int D, bool SWEEP, int PEND>
+template <int RC, int M, int D, bool SWEEP, int PEND, bool ANY>
 __global__ void __launch_bounds__(kRowThreads)
 row_pending_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
                    const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
                    float *const *__restrict__ xs, const float *__restrict__ qstate,
                    const float *__restrict__ phat, double *__restrict__ pw,
                    const float *__restrict__ phat1, const float *__restrict__ q1) {
-    row_tile<RC, M, D, true, SWEEP, false, true, PEND>(tiles, ntiles, reverse, pairs, cols, xs, qstate, phat, pw, nullptr, 0.0, phat1, q1);
+    row_tile<RC, M, D, true, SWEEP, false, true, PEND, ANY>(tiles, ntiles, reverse, pairs, cols, xs, qstate, phat, pw, nullptr, 0.0, phat1, q1);
 }
 
 // The row passes over vector layers alone (one wavefront per tile): the same arithmetic as the
@@ -1368,8 +1371,8 @@ __device__ __forceinline__ void col_body(const ColTile &t, const PairDesc &pd,
 }
 
 // One tile of the column kernels.  V = 0: tiles of any vector width (few stacked columns); V = 1, 2,
-// 4: one width only.
-template <int V, int RC, int U, bool PEEK>
+// 4: one width only.  ANY as in row_tile.
+template <int V, int RC, int U, bool PEEK, bool ANY>
 __device__ __forceinline__ void col_tile(const ColTile *__restrict__ tiles, int ntiles, int reverse,
                                          const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
                                          float *const *__restrict__ xs, const float *__restrict__ phat,
@@ -1381,30 +1384,30 @@ __device__ __forceinline__ void col_tile(const ColTile *__restrict__ tiles, int 
     if constexpr (V != 0) {
         col_body<V, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     } else {
-        if (pd.V == 4 && (pd.q & 3) == 0) col_body<4, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
-        else if (pd.V == 4) col_body<4, RC, U, PEEK, true>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        if (pd.V == 4 && (!ANY || (pd.q & 3) == 0)) col_body<4, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
+        else if (ANY && pd.V == 4) col_body<4, RC, U, PEEK, true>(t, pd, cols, X, phat, qw, sT, phat1, q1);
         else if (pd.V == 2) col_body<2, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
         else col_body<1, RC, U, PEEK, false>(t, pd, cols, X, phat, qw, sT, phat1, q1);
     }
 }
-template <int V, int RC, int U>
+template <int V, int RC, int U, bool ANY>
 __global__ void __launch_bounds__(kThreads)
 col_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
            const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
            float *const *__restrict__ xs, const float *__restrict__ phat,
            double *__restrict__ qw) {
     extern __shared__ double smem[];  // [blk_rows][RC] Phat floats, then reused for the reduction
-    col_tile<V, RC, U, false>(tiles, ntiles, reverse, pairs, cols, xs, phat, qw, reinterpret_cast<float *>(smem), nullptr, nullptr);
+    col_tile<V, RC, U, false, ANY>(tiles, ntiles, reverse, pairs, cols, xs, phat, qw, reinterpret_cast<float *>(smem), nullptr, nullptr);
 }
 // X one update behind (see run_lazy in the launch code); a kernel of its own as row_pending_kernel is
-template <int RC, int U>
+template <int RC, int U, bool ANY>
 __global__ void __launch_bounds__(kThreads)
 col_peek_kernel(const ColTile *__restrict__ tiles, int ntiles, int reverse,
                 const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
                 float *const *__restrict__ xs, const float *__restrict__ phat,
                 double *__restrict__ qw, const float *__restrict__ phat1, const float *__restrict__ q1) {
     extern __shared__ double smem[];
-    col_tile<0, RC, U, true>(tiles, ntiles, reverse, pairs, cols, xs, phat, qw, reinterpret_cast<float *>(smem), phat1, q1);
+    col_tile<0, RC, U, true, ANY>(tiles, ntiles, reverse, pairs, cols, xs, phat, qw, reinterpret_cast<float *>(smem), phat1, q1);
 }
 
 // The Q-sweep of vector layers alone: X_i^T Phat_j is a dot product per stacked column.  One

@@ -89,6 +89,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     P.layers.resize(n_layers);
     int64_t off = 0;
     P.elems_per_worker = 0;
+    double odd_elems = 0.0;  // in rows that units of four floats would speed up
     P.message_floats = 0;
     for (int l = 0; l < n_layers; ++l) {
         int p = rows[l], q = cols[l];
@@ -100,7 +101,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.max_layer_rank = std::max(P.max_layer_rank, L.r);
         P.max_rows = std::max(P.max_rows, p);
         L.V = (q % 4 == 0) ? 4 : (q % 2 == 0 ? 2 : 1);
-        L.Vn = tune.odd_units && q >= kAnyAlignCols ? 4 : L.V;
+        if (L.V < 4 && q >= kAnyAlignCols) odd_elems += (double)p * q;
         // Row stride.  With 8 or more stacked columns a tile's wavefronts work side by side on
         // 64-column (256-byte) pieces of the same rows; when rows start at arbitrary addresses every
         // piece ends inside a 128-byte line that the neighbouring wavefront touches at another time,
@@ -115,6 +116,8 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.message_floats += (size_t)L.r * ((size_t)p + q);
     }
     P.param_floats = (size_t)off;
+    P.odd_rows = tune.odd_rows < 0 ? odd_elems >= kOddShare * P.elems_per_worker : tune.odd_rows != 0;
+    for (LayerInfo &L : P.layers) L.Vn = P.odd_rows && L.q >= kAnyAlignCols ? 4 : L.V;
     for (int l = 0; l < n_layers; ++l)
         if (P.layers[l].r > kMaxCols) return PG_ERR_ARG;  // one edge's columns must fit one pass
 
@@ -182,7 +185,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     // round); in large ones, or where all rows are padded, it pays (LSTM SGD round 2.87 -> 2.74 ms).
     bool all_padded = true;
     for (const LayerInfo &L : P.layers) all_padded = all_padded && L.ld % 4 == 0;
-    const bool wide_units = tune.odd_units && tune.mfma_cols && (P.large || all_padded);
+    const bool wide_units = tune.mfma_cols && (tune.wide_units < 0 ? P.large || all_padded : tune.wide_units != 0);
     constexpr int kColUnroll = 8;
     for (int l = 0; l < n_layers; ++l) {
         const LayerInfo &L = P.layers[l];
@@ -412,10 +415,12 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     // way is planned with the widths that divide its rows, or with longer row blocks, if it fits then
     // (54126 x 1162 on a ring of 8 at rank 2: 56.0 MB, 30.1 MB with the dividing widths; 23961 x 626 on
     // a ring of 20 at rank 2: 36.7 MB with those, 31.9 MB with longer blocks).
-    if (tune.odd_units && !tune.long_blocks && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
-        Tuning other[2] = {tune, tune};
-        other[0].odd_units = false;
-        other[1].long_blocks = true;
+    if (tune.odd_rows < 0 && tune.wide_units < 0 && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
+        Tuning other[3] = {tune, tune, tune};
+        other[0].odd_rows = other[0].wide_units = 0;
+        other[1].odd_rows = 1;
+        other[2].odd_rows = 1;
+        other[2].long_blocks = true;
         for (const Tuning &tn2 : other) {
             Plan Q;
             const int rc = build_plan(Q, n_workers, n_edges, edges, edge_w, n_layers, rows, cols, rank, power_steps, tn2);

@@ -52,8 +52,10 @@ struct Tuning {
     bool mfma_rows = true;            // P-sweep and update ...
     int mfma_row_cols = kMfmaRowCols; // ... of layers with at least this many stacked columns (8 or 16)
     int light = -1;                   // blocking for small parameter sets: -1 by size, 0 never, 1 always
-    bool odd_units = true;            // units of four floats also on rows whose length is not a multiple of four ...
-    bool long_blocks = false;         // ... with the row blocks of the Q-sweep as long as one float per lane asks for
+    // units of four floats on rows whose length is not a multiple of four: -1 by rule, 0 never, 1 always
+    int odd_rows = -1;                // narrow kernels, at any 4-byte aligned address
+    int wide_units = -1;              // wide kernels, on padded rows
+    bool long_blocks = false;         // (with odd_rows) row blocks of the Q-sweep as long as one float per lane asks for
     int stream = -1;                  // non-temporal passes: -1 by size and row length, 0 never, 1 always
     int lazy = -1;                    // runs that write every second round: the same, where the kernels can
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
@@ -95,6 +97,9 @@ struct Plan {
     // dependent loads, so the narrow row kernels block fewer rows per lane group (half the
     // registers, twice the wavefronts per SIMD) over tiles half as large.
     bool light = false;
+    // Enough of the parameters lie in rows of odd length that the narrow kernels move those four floats at a
+    // time as well (LayerInfo::Vn; instantiations of their own).
+    bool odd_rows = false;
     // The parameters of all workers do not fit the memory-side cache.
     bool large = false;
     // Passes that write them, and all passes over 8-16 stacked columns, stream them past the caches

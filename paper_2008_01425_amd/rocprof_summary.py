@@ -63,7 +63,7 @@ def kernel_kind(name: str):
         if grad:
             return "update_sgd"
         return "update_sweep_p" if upd and swp else ("update" if upd else "sweep_p")
-    m = re.match(r"pg::row_pending_kernel<\d+, \d+, \d+, (true|false), \d>", name)
+    m = re.match(r"pg::row_pending_kernel<\d+, \d+, \d+, (true|false), \d, (true|false)>", name)
     if m:
         return "update_sweep_p" if m.group(1) == "true" else "update"
     if re.match(r"pg::(col_kernel|mcol_kernel|vec_col_kernel|col_peek_kernel)<", name):

@@ -60,6 +60,10 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
             // accesses as wide as the row length allows, or four floats wide
             REQUIRE(pd.V == 4 || pd.q % 4 != 0, "rows of %d floats in units of %d", pd.q, pd.V);
             REQUIRE(pd.V >= 2 || pd.q % 2 != 0, "rows of %d floats in units of %d", pd.q, pd.V);
+            // wider ones: in narrow kernels where the set is planned for it, from 16 columns on (the last unit is
+            // moved back to the row's end); in wide kernels on rows padded to whole units
+            if (pd.q % pd.V != 0 && c.RC < kWideCols) REQUIRE(P.odd_rows && pd.V == 4 && pd.q >= 16 && pd.seg_len % 4 == 0, "narrow rows of %d floats in units of %d", pd.q, pd.V);
+            if (pd.q % pd.V != 0 && c.RC >= kWideCols) REQUIRE(pd.V == 4 && pd.ld % 4 == 0, "wide rows of %d floats (stride %d) in units of %d", pd.q, pd.ld, pd.V);
             REQUIRE(t.nrows >= 1 && t.row0 >= 0 && t.row0 + t.nrows <= pd.p, "row tile rows %d+%d of %d", t.row0, t.nrows, pd.p);
             REQUIRE(t.seg >= 0 && t.seg < pd.nseg && (int64_t)t.seg * pd.seg_len < pd.q, "segment %d", t.seg);
             if (c.RC >= kWideCols) REQUIRE(c.V == pd.V, "class V=%d, layer V=%d", c.V, pd.V);
@@ -282,6 +286,21 @@ int main() {
     // one long vector or tall narrow layer keeps the whole run writing every round (its row block of the
     // column kernel does not fit beside the pending coefficients)
     bad |= check_paths("a bias of 2800", 16, r16, {4096, 2800}, {4608, 1}, 1, 1, true, false);
+    // kernels with the body for rows of odd length: from one element in a hundred on
+    auto odd = [&](const char *name, const std::vector<int32_t> &rows, const std::vector<int32_t> &cols, bool want) {
+        Plan P;
+        std::vector<float> w(16, 0.2f);
+        int rc = build_plan(P, 16, 16, r16.data(), w.data(), (int)rows.size(), rows.data(), cols.data(), 1, 1, Tuning());
+        REQUIRE(rc == PG_OK, "build_plan returned %d", rc);
+        REQUIRE(P.odd_rows == want, "planned for rows of odd length: %d", P.odd_rows);
+        printf("as expected: %s\n", name);
+        return 0;
+    };
+    bad |= odd("vgg16 layers", vr, vc, false);
+    bad |= odd("whole units only", {100, 40, 3000, 64}, {100, 16, 4, 576}, false);
+    bad |= odd("short odd rows", {100, 4000, 900}, {100, 3, 14}, false);
+    bad |= odd("one layer of 27 columns", {100, 64}, {100, 27}, true);
+    bad |= odd("a sliver of 27 columns", {1000, 16}, {1000, 27}, false);
     if (!bad) printf("ok %d random problems\n", nrandom);
     return bad;
 }

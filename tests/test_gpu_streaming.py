@@ -21,9 +21,12 @@ def _workload(name, n, edges, rank, steps, sigma=0.05):
     return W.Workload(name, n, edges, w, SHAPES, rank, steps, sigma, 10, 77)
 
 
-def _buffers(wl, X, Q, stream, lazy):
+def _buffers(wl, X, Q, stream, lazy, odd):
+    """`odd`: whether the kernels that move rows of odd length four floats at a time are used.  The wide
+    kernels' units are held fixed, so that `stream` changes nothing but the cache hint."""
     from paper_2008_01425_amd.device import GossipBuffers
-    with env_setting("PG_STREAM", stream), env_setting("PG_LAZY", lazy), env_setting("PG_LIGHT", 0):
+    with env_setting("PG_STREAM", stream), env_setting("PG_LAZY", lazy), env_setting("PG_LIGHT", 0), \
+            env_setting("PG_ODD_ROWS", odd), env_setting("PG_WIDE_UNITS", odd):
         gb = GossipBuffers.from_workload(wl, fill=False)
     gb.fill_from_arrays(X, Q)
     return gb
@@ -50,13 +53,14 @@ GRAPHS = {"ring": (4, [(0, 1), (1, 2), (2, 3), (3, 0)]),          # two (four) s
 @pytest.mark.parametrize("graph", GRAPHS)
 @pytest.mark.parametrize("rounds", [2, 3, 4, 7])
 @pytest.mark.parametrize("rank", [1, 2])
-def test_a_run_that_writes_every_second_round_equals_the_plain_run(graph, rounds, rank):
+@pytest.mark.parametrize("odd", [0, 1])
+def test_a_run_that_writes_every_second_round_equals_the_plain_run(graph, rounds, rank, odd):
     n, edges = GRAPHS[graph]
     wl = _workload(f"lazy {graph} {rounds} r{rank}", n, edges, rank, 1)
     X, Q = wl.all_params(), wl.all_q()
     for l in (1, 6):                                   # two neighbours agree: their columns are dropped
         X[1][l] = X[0][l].copy()
-    plain, lazy = _buffers(wl, X, Q, 0, 0), _buffers(wl, X, Q, 1, 1)
+    plain, lazy = _buffers(wl, X, Q, 0, 0, odd), _buffers(wl, X, Q, 1, 1, odd)
     for _ in range(2):                                 # the second call starts on what the first left
         plain.run(rounds)
         lazy.run(rounds)
@@ -69,13 +73,14 @@ def test_a_run_that_writes_every_second_round_equals_the_plain_run(graph, rounds
 
 
 @pytest.mark.parametrize("rank", [1, 2, 3, 4])
-def test_streamed_passes_equal_the_cached_ones(rank):
+@pytest.mark.parametrize("odd", [0, 1])
+def test_streamed_passes_equal_the_cached_ones(rank, odd):
     """1 to 16 stacked columns: every row and column kernel, each call."""
     import torch
     n, edges = 6, [(0, 1), (0, 2), (3, 0), (0, 4), (2, 1), (4, 5)]   # degrees 4, 2, 2, 1, 2, 1
     wl = _workload(f"stream r{rank}", n, edges, rank, 2)
     X, Q = wl.all_params(), wl.all_q()
-    a, b = _buffers(wl, X, Q, 0, 0), _buffers(wl, X, Q, 1, 1)
+    a, b = _buffers(wl, X, Q, 0, 0, odd), _buffers(wl, X, Q, 1, 1, odd)
     for gb in (a, b):
         gb.alloc_grads()
         gb.alloc_pstate()
@@ -135,7 +140,7 @@ def test_padding_of_rows_is_neither_used_nor_written(rank, stream):
         gb.close()
 
 
-def _against_the_oracle(name, shapes, rank, seed, light, steps=1, graph="ring"):
+def _against_the_oracle(name, shapes, rank, seed, light, odd, steps=1, graph="ring"):
     """A round, a round with gradient, an odd and an even iteration on `shapes`; the one-round bar of the
     other parity tests."""
     from oracle import pg_oracle as O
@@ -150,7 +155,7 @@ def _against_the_oracle(name, shapes, rank, seed, light, steps=1, graph="ring"):
     G = [[rng.standard_normal(s).astype(np.float32) for s in shapes] for _ in range(n)]
     for what in ("round", "sgd", "iterations"):
         X, Q = wl.all_params(), wl.all_q()
-        with env_setting("PG_LIGHT", light):
+        with env_setting("PG_LIGHT", light), env_setting("PG_ODD_ROWS", odd):
             gb = GossipBuffers.from_workload(wl, fill=False)
         gb.fill_from_arrays(X, Q)
         gb.alloc_grads()
@@ -174,18 +179,20 @@ def _against_the_oracle(name, shapes, rank, seed, light, steps=1, graph="ring"):
 
 @pytest.mark.parametrize("rank", [1, 2])
 @pytest.mark.parametrize("light", [0, 1])
-def test_rows_of_any_length_and_alignment(rank, light):
+@pytest.mark.parametrize("odd", [0, 1])
+def test_rows_of_any_length_and_alignment(rank, light, odd):
     """Rows of 16 and more floats at any 4-byte aligned address (every remainder modulo 4; a last unit
-    that overlaps its neighbour's, alone in a row or behind many) against the oracle: a round, a round
-    with gradient, an odd and an even iteration.  The one-round bar of the other parity tests."""
+    that overlaps its neighbour's, alone in a row or behind many), in units of four and in the widths that
+    divide the row, against the oracle: a round, a round with gradient, an odd and an even iteration."""
     shapes = [(9, 17), (40, 18), (33, 19), (21, 16), (70, 255), (130, 257), (20, 1022), (65, 1023), (6, 4099)]
-    _against_the_oracle("any alignment", shapes, rank, 79, light)
+    _against_the_oracle("any alignment", shapes, rank, 79, light, odd)
 
 
 @pytest.mark.parametrize("rank", [1, 2])
 @pytest.mark.parametrize("light", [0, 1])
-def test_rows_shorter_than_sixteen_floats(rank, light):
+@pytest.mark.parametrize("odd", [0, 1])
+def test_rows_shorter_than_sixteen_floats(rank, light, odd):
     """Two floats at a time where q is even, one at a time where it is odd: q = 2 to 15, several row blocks
     and fewer rows than a lane group takes."""
     shapes = [(50, 2), (7, 6), (1030, 10), (33, 14), (260, 5), (9, 15), (3000, 6), (40, 3), (2, 14), (70, 12)]
-    _against_the_oracle("short rows", shapes, rank, 80, light)
+    _against_the_oracle("short rows", shapes, rank, 80, light, odd)

@@ -310,8 +310,8 @@ def test_profile_summaries_classify_every_pass_kernel():
     assert kernel_kind("pg::mcol_kernel<4, 2>") == "sweep_q"
     assert kernel_kind("pg::vec_col_kernel<4>") == "sweep_q"
     assert kernel_kind("pg::col_peek_kernel<2, 8>") == "sweep_q"
-    assert kernel_kind("pg::row_pending_kernel<2, 8, 1, true, 2>") == "update_sweep_p"
-    assert kernel_kind("pg::row_pending_kernel<2, 8, 1, false, 2>") == "update"
+    assert kernel_kind("pg::row_pending_kernel<2, 8, 1, true, 2, false>") == "update_sweep_p"
+    assert kernel_kind("pg::row_pending_kernel<2, 8, 1, false, 2, true>") == "update"
     assert kernel_kind("pg::comb_kernel") is None
     assert kernel_kind("pg::orth_gram_kernel<256, 2>") is None
     for wl in ("vgg16_r1", "vgg16_r2", "lstm", "resnet50"):
@@ -334,3 +334,18 @@ def test_kernels_of_small_sets_take_only_the_arguments_they_use():
                 assert code_objects.arguments(kernel) <= most, (name, code_objects.arguments(kernel))
                 found[next(k for k in found if k in stem)] += 1
     assert found["row"] >= 12 and found["col"] >= 3 and found["comb"] == 1
+
+
+def test_kernels_of_even_rows_keep_their_registers():
+    """The body for rows at any alignment needs the most registers; it lives in instantiations of its own (last
+    template argument true), so that the others keep their wavefronts per SIMD: 512 registers of a lane, in eights."""
+    import code_objects
+    kernels = code_objects.kernels(B.LIB_PATH)
+    # row_kernel<columns, rows per lane group, steps ahead, update, sweep, gradient, streamed, any alignment>
+    for args, waves in (("1, 4, 1, false, true, false", 4), ("2, 4, 1, false, true, false", 4), ("1, 8, 1, false, true, false", 3),
+                        ("2, 8, 1, false, true, false", 2), ("2, 4, 1, true, false, false", 4), ("2, 4, 1, true, false, true", 3),
+                        ("1, 4, 1, true, true, false", 3), ("2, 4, 1, true, true, false", 2)):
+        kernel = kernels[f"pg::row_kernel<{args}, false, false>"]
+        used = (kernel[".vgpr_count"] + kernel.get(".agpr_count", 0) + 7) // 8 * 8
+        assert 512 // used >= waves, (args, used)
+        assert kernel[".vgpr_spill_count"] == 0, args
