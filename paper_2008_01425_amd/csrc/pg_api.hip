@@ -201,7 +201,8 @@ struct Launcher {
 
     // NT: large parameter sets, see Plan::stream.  The narrow sweeps read through the caches even
     // there (their next pass starts on what they left), the wide ones do not: X would push the
-    // operand vectors, which every tile reads again, out of the L2 caches.
+    // operand vectors, which every tile reads again, out of the L2 caches.  Wide classes of one or two floats per
+    // access are short unpadded rows, which do not suit it.
     template <int RC, bool UPD, bool SWP, bool GRAD = false>
     void row_launch(const RowClass &rc) {
         if (c->plan.stream) row_launch_nt<RC, UPD, SWP, GRAD, true>(rc);
@@ -229,22 +230,26 @@ struct Launcher {
             else
                 narrow_launch<RC, kRowsPerGroup, UPD, SWP, GRAD, NT && UPD>(tiles, n);
         } else if (rc.mfma) {
-#define PG_MROW(VV) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD, NT> \
+#define PG_MROW(VV, STREAMED, PAD) mrow_kernel<VV, RC / 4, kMfmaRowBlocks, kMfmaRowPrefetch, UPD, SWP, GRAD, STREAMED, PAD> \
                 <<<dim3((unsigned)n), dim3(kThreads), kMrowLdsBytes, st>>>( \
                 tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta)
-            if (rc.V == 4) PG_MROW(4);
-            else if (rc.V == 2) PG_MROW(2);
-            else PG_MROW(1);
+            if (rc.V == 4 && rc.pad) PG_MROW(4, NT, true);
+            else if (rc.V == 4) PG_MROW(4, NT, false);
+            else if (rc.V == 2) PG_MROW(2, false, false);
+            else PG_MROW(1, false, false);
 #undef PG_MROW
         } else {
             // register budget: RC accumulators and RC update coefficients per row
             constexpr int M = ((UPD && SWP) || GRAD || (RC > 8 && UPD)) ? 2 : 4;
+            // 16 columns on the vector ALUs: only layers beyond the matrix-core kernels' addresses
+            constexpr bool kStreamed = NT && RC < kMaxCols;
             size_t lds = (size_t)RC * rc.max_seg * sizeof(float);
-#define PG_WIDE(VV) row_wide_kernel<VV, RC, M, UPD, SWP, GRAD, NT><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
+#define PG_WIDE(VV, STREAMED, PAD) row_wide_kernel<VV, RC, M, UPD, SWP, GRAD, STREAMED, PAD><<<dim3((unsigned)n), dim3(kThreads), lds, st>>>( \
                 tiles, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), c->d_gs, eta)
-            if (rc.V == 4) PG_WIDE(4);
-            else if (rc.V == 2) PG_WIDE(2);
-            else PG_WIDE(1);
+            if (rc.V == 4 && rc.pad) PG_WIDE(4, kStreamed, true);
+            else if (rc.V == 4) PG_WIDE(4, kStreamed, false);
+            else if (rc.V == 2) PG_WIDE(2, false, false);
+            else PG_WIDE(1, false, false);
 #undef PG_WIDE
         }
     }
@@ -357,7 +362,7 @@ struct Launcher {
             else
                 PG_COL(0, false);
         } else if (c->plan.mfma_cols) {
-#define PG_MCOL(VV, STAGE, LDS) do { if (c->plan.stream) PG_MCOL_NT(VV, STAGE, LDS, true); else PG_MCOL_NT(VV, STAGE, LDS, false); } while (0)
+#define PG_MCOL(VV, STAGE, LDS) do { if (VV == 4 && c->plan.stream) PG_MCOL_NT(VV, STAGE, LDS, VV == 4); else PG_MCOL_NT(VV, STAGE, LDS, false); } while (0)
 #define PG_MCOL_NT(VV, STAGE, LDS, NT) mcol_kernel<VV, kMfmaColPrefetch, STAGE, NT><<<dim3((unsigned)n), dim3(kThreads), LDS, st>>>( \
             c->d_col_tiles + cc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, \
             c->d_xs, left(), qw())

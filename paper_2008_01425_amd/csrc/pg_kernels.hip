@@ -484,7 +484,7 @@ vec_row_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
 // RC columns without the Q slice being re-fetched per row.  Lane groups own M rows each as in
 // the narrow kernel; only X is prefetched a step ahead, in registers.
 // ---------------------------------------------------------------------------------------
-template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD, bool NT>
+template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD, bool NT, bool PAD>
 __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &pd,
                                               const ColDesc *__restrict__ cols, float *X,
                                               const float *__restrict__ qstate,
@@ -511,7 +511,7 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
     for (int j = 0; j < RC; ++j) {
         if (j < R) {
             const float *src = qstate + cols[pd.col0 + j].q_off + c_begin;
-            if constexpr (V < 4) {
+            if constexpr (!PAD) {
                 for (int cc = tid * V; cc < seg_cols; cc += kThreads * V)
                     *reinterpret_cast<vec *>(sQ + j * sstride + cc) = ldg<V>(src + cc);
             } else {  // the vector starts at any 4-byte aligned address; a unit past its end reads as zeros
@@ -580,7 +580,7 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
         };
         auto process = [&](int c, vec(&xv)[M], vec(&gv)[GRAD ? M : 1]) {
             const float *sq = sQ + (c - c_begin);
-            const bool whole = V < 4 || c + V <= c_end;  // otherwise the row's last unit, partly padding
+            const bool whole = !PAD || c + V <= c_end;  // otherwise the row's last unit, partly padding
             if (!whole) {
 #pragma unroll
                 for (int m = 0; m < M; ++m)
@@ -674,7 +674,9 @@ __device__ __forceinline__ void row_wide_body(const RowTile &t, const PairDesc &
 
 // One instantiation per vector width V: with 8-16 stacked columns a kernel that carried all
 // three widths would be allocated the registers of its widest body and lose occupancy.
-template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD, bool NT>
+// PAD (V = 4): units of four floats on padded rows whose length is not a multiple of four.  The masked last unit
+// is in the way where there is none: launches over whole units only do without.
+template <int V, int RC, int M, bool UPDATE, bool SWEEP, bool GRAD, bool NT, bool PAD>
 __global__ void __launch_bounds__(kThreads)
 row_wide_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
                 const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
@@ -687,7 +689,7 @@ row_wide_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse,
     const PairDesc pd = pairs[t.pair];
     float *X = xs[pd.worker] + pd.x_off;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
-    row_wide_body<V, RC, M, UPDATE, SWEEP, GRAD, NT>(t, pd, cols, X, qstate, phat, pw, sQ, Gp, eta);
+    row_wide_body<V, RC, M, UPDATE, SWEEP, GRAD, NT, PAD>(t, pd, cols, X, qstate, phat, pw, sQ, Gp, eta);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -735,7 +737,7 @@ __device__ __forceinline__ void ldrow(const float *base, uint32_t off, int lo, i
         for (int e = 0; e < V; ++e) x[V * u + e] = t[e];
     }
 }
-template <int V, bool FULL, bool NT>
+template <int V, bool FULL, bool NT, bool PAD>
 __device__ __forceinline__ void strow(float *base, uint32_t off, int lo, int nvalid, const float (&x)[4]) {
 #pragma unroll
     for (int u = 0; u < 4 / V; ++u) {
@@ -743,7 +745,9 @@ __device__ __forceinline__ void strow(float *base, uint32_t off, int lo, int nva
         typename VecT<V>::T t;
 #pragma unroll
         for (int e = 0; e < V; ++e) t[e] = x[V * u + e];
-        if (FULL || c + V <= nvalid) {
+        if (!PAD) {
+            if (FULL || c < nvalid) stg_at<V, NT>(base, off + 4u * (uint32_t)c, t);
+        } else if (FULL || c + V <= nvalid) {
             stg_at<V, NT>(base, off + 4u * (uint32_t)c, t);
         } else {  // the row's last unit, partly padding
 #pragma unroll
@@ -752,11 +756,11 @@ __device__ __forceinline__ void strow(float *base, uint32_t off, int lo, int nva
         }
     }
 }
-// The same columns of a right-hand-side vector: those start at any 4-byte aligned address and have
-// no padding behind them.
-template <int V, bool FULL>
+// The same columns of a right-hand-side vector.  Where rows are padded (PAD) it starts at any 4-byte aligned
+// address and has no padding behind it.
+template <int V, bool FULL, bool PAD>
 __device__ __forceinline__ void ldrhs(const float *base, uint32_t off, int lo, int nvalid, float (&x)[4]) {
-    if constexpr (V < 4) {
+    if constexpr (!PAD) {
         ldrow<V, FULL>(base, off, lo, nvalid, x);
     } else if constexpr (FULL) {
         ld4((const float *)((const char *)base + off + 16u * (uint32_t)lo), x);
@@ -821,7 +825,7 @@ struct BoolTag {
 };
 // Two work-groups per CU: left alone the compiler takes every register it can (one work-group).
 // (measured: the sweep alone is 11 % faster at three wavefronts per SIMD, one register spilled).
-template <int V, int RCM, int MB, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT>
+template <int V, int RCM, int MB, int D, bool UPDATE, bool SWEEP, bool GRAD, bool NT, bool PAD>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((UPDATE || GRAD) ? 2 : 3)))
 mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const PairDesc *__restrict__ pairs,
             const ColDesc *__restrict__ cols, float *const *__restrict__ xs,
@@ -902,11 +906,11 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
         }
         if (UPDATE) {
 #pragma unroll
-            for (int m = 0; m < RCM; ++m) ldrhs<V, FULL>(qup[m], cso, lo, nvalid, f.qu[UPDATE ? m : 0]);
+            for (int m = 0; m < RCM; ++m) ldrhs<V, FULL, PAD>(qup[m], cso, lo, nvalid, f.qu[UPDATE ? m : 0]);
         }
         if (SWEEP && !UPDATE) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ldrhs<V, FULL>(qsp[i], cso, lo, nvalid, f.qs[(SWEEP && !UPDATE) ? i : 0]);
+            for (int i = 0; i < 4; ++i) ldrhs<V, FULL, PAD>(qsp[i], cso, lo, nvalid, f.qs[(SWEEP && !UPDATE) ? i : 0]);
         }
     };
     auto process = [&](auto full, int s, Buf &f) {
@@ -934,7 +938,7 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
         // columns past the row's end: the sweep must see zeros there
         bool cok[4];
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) cok[tt] = FULL || 16 * V * (tt / V) + V * lo + tt % V < nvalid;
+        for (int tt = 0; tt < 4; ++tt) cok[tt] = FULL || 16 * V * (tt / V) + V * lo + (PAD ? tt % V : 0) < nvalid;
 #pragma unroll
         for (int b = 0; b < MB; ++b) {
             if (UPDATE) {
@@ -955,7 +959,7 @@ mrow_kernel(const RowTile *__restrict__ tiles, int ntiles, int reverse, const Pa
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     if (FULL || row0w + 16 * b + 4 * v + hi < row_end)
-                        strow<V, FULL, NT>(X, roff[b][v] + cso, lo, nvalid, f.x[b][v]);
+                        strow<V, FULL, NT, PAD>(X, roff[b][v] + cso, lo, nvalid, f.x[b][v]);
                 }
             }
             if (SWEEP) {

@@ -446,7 +446,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             if (P.row_classes[k].RC == RC && P.row_classes[k].V == V && P.row_classes[k].mfma == mfma &&
                 P.row_classes[k].group == group && P.row_classes[k].vec == vec)
                 return k;
-        P.row_classes.push_back({RC, V, mfma, {}, 0, 0, 0, group, vec});
+        P.row_classes.push_back({RC, V, mfma, {}, 0, 0, 0, group, false, vec});
         return P.row_classes.size() - 1;
     };
     auto col_class = [&](int RC, int V, bool vec) -> size_t {
@@ -487,6 +487,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             P.pairs[pair].V = Vr;
             const bool vec = split_vec && L.q == 1 && RC < kWideCols;
             RowClass &rc = P.row_classes[row_class(RC, Vr, mrow, gi, vec)];
+            rc.pad = rc.pad || (RC >= kWideCols && L.q % Vr != 0);
             int rows_iter = g.rows_iter_base * rows_unroll(RC, P.light);
             int tile_rows;
             if (RC < kWideCols) {

@@ -30,6 +30,7 @@ struct RowClass {
     int max_seg = 0;        // RC >= kWideCols: longest column segment (sizes the Q slice in LDS)
     int group = 0;          // which of a worker's column groups these tiles belong to (0 unless a worker
                             // has more than kMaxCols stacked columns)
+    bool pad = false;       // RC >= kWideCols: some rows end inside a unit of V floats (padded rows)
     bool vec = false;       // vector layers (q = 1) only, run by the light-weight vector kernel
 };
 struct ColClass {

@@ -63,7 +63,7 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
             // wider ones: in narrow kernels where the set is planned for it, from 16 columns on (the last unit is
             // moved back to the row's end); in wide kernels on rows padded to whole units
             if (pd.q % pd.V != 0 && c.RC < kWideCols) REQUIRE(P.odd_rows && pd.V == 4 && pd.q >= 16 && pd.seg_len % 4 == 0, "narrow rows of %d floats in units of %d", pd.q, pd.V);
-            if (pd.q % pd.V != 0 && c.RC >= kWideCols) REQUIRE(pd.V == 4 && pd.ld % 4 == 0, "wide rows of %d floats (stride %d) in units of %d", pd.q, pd.ld, pd.V);
+            if (pd.q % pd.V != 0 && c.RC >= kWideCols) REQUIRE(c.pad && pd.V == 4 && pd.ld % 4 == 0, "wide rows of %d floats (stride %d) in units of %d", pd.q, pd.ld, pd.V);
             REQUIRE(t.nrows >= 1 && t.row0 >= 0 && t.row0 + t.nrows <= pd.p, "row tile rows %d+%d of %d", t.row0, t.nrows, pd.p);
             REQUIRE(t.seg >= 0 && t.seg < pd.nseg && (int64_t)t.seg * pd.seg_len < pd.q, "segment %d", t.seg);
             if (c.RC >= kWideCols) REQUIRE(c.V == pd.V, "class V=%d, layer V=%d", c.V, pd.V);

@@ -349,3 +349,17 @@ def test_kernels_of_even_rows_keep_their_registers():
         used = (kernel[".vgpr_count"] + kernel.get(".agpr_count", 0) + 7) // 8 * 8
         assert 512 // used >= waves, (args, used)
         assert kernel[".vgpr_spill_count"] == 0, args
+
+
+def test_wide_kernels_of_whole_units_keep_their_registers():
+    """The masked last unit of padded rows (last template argument true) is in instantiations of its own."""
+    import code_objects
+    kernels = code_objects.kernels(B.LIB_PATH)
+    # row_wide_kernel<floats per access, columns, rows per lane group, update, sweep, gradient, streamed, padded>
+    for name, waves in (("row_wide_kernel<4, 8, 2, true, true, false, false, false>", 3), ("row_wide_kernel<4, 8, 4, false, true, false, false, false>", 3),
+                        ("row_wide_kernel<4, 8, 2, true, false, true, false, false>", 2),
+                        ("mrow_kernel<4, 4, 2, 1, false, true, false, false, false>", 3), ("mrow_kernel<4, 4, 2, 1, true, true, false, false, false>", 2)):
+        kernel = kernels["pg::" + name]
+        used = (kernel[".vgpr_count"] + kernel.get(".agpr_count", 0) + 7) // 8 * 8
+        assert 512 // used >= waves, (name, used)
+        assert kernel[".vgpr_spill_count"] == 0, name
