@@ -29,11 +29,12 @@ constexpr double kStreamShare = 0.75;
 // columns 4 rows per lane group gain 7 % and 8 rows, which spill, lose 12 %.
 constexpr int kLazyCols = 4;
 constexpr int kLazyColLds = 64 * 1024;
-// Narrow kernels: rows of at least this many floats are moved four at a time whatever q is (see
-// row_body).  Shorter ones are a few vectors at most and go by the widest one that divides q.  Measured on one
-// matrix of 531 MB, ring of 16, rank 1, one round: 4607 columns 597 -> 433 us, 577 columns 710 -> 540 us
-// (one and two floats at a time before; 4606 columns 476 -> 433 us).
+// Narrow kernels: rows of at least this many floats may be moved four at a time whatever q is (see
+// row_body, and gains_units_of_four() in the planner for which are).  Shorter ones are a few vectors
+// at most and go by the widest one that divides q.
 constexpr int kAnyAlignCols = 16;
+constexpr int64_t kOddLongBytes = 40ll << 20;    // parameter bytes (all workers) from which long rows of odd length are ...
+constexpr int64_t kOddLongBytes4 = 128ll << 20;  // ... at 4 stacked columns, unless the set is light or a row fits one step
 // Share of the elements in such rows from which the kernels that carry a body for them are launched.
 // Measured, those kernels / the ones without on matrices of 576 (4608, 32, 152) columns beside some of
 // 577 (4607, 27, 153), 8 to 300 MB, ring of 8, round, SGD round and run at ranks 1 and 2: no such rows

@@ -49,6 +49,27 @@ bool gains_behind(const LayerInfo &L, int rc) {
     return L.q % 32 == 0 || L.q >= 512;
 }
 
+// Whether the narrow kernels gain from units of four floats on this layer's rows (a multiple of four, or not: see
+// row_body).  They make a quarter of the accesses, but their tiles are four times as wide: a small set has too few
+// of them, and the Q-sweep's row blocks get shorter and its partial sums more.  Measured on single
+// matrices, time in the dividing width / in units of four, SGD round and run, rings and a tree, ranks 1 and 2:
+//   odd q up to 128 (18 to 113): 1.0-1.4 at 1 to 30 MB, 1.1-2.4 above;  175 to 4607: 0.88-1.09 at 1 and 8 MB, 0.71-1.07
+//   at 30 MB, 0.98-1.12 at 40 MB, 0.97-1.19 at 55 MB; at 2 columns 0.99-1.13 at 80 MB, 1.07-1.27 at 150 MB; at 4 columns
+//   0.90-1.03 at 80 MB (eight rows per lane group from 64 MB on; 235 columns, one step of a wavefront, 1.20 at 77 MB),
+//   0.93-1.13 at 150 MB; 1.02-1.48 at 450 MB
+//   even q above 128: 0.86-1.04 at 40 and 62 MB, 0.86-1.10 at 150 MB; 300 to 800 MB: 202 to 4606 columns 1.00-1.24
+//   at 2 stacked columns, 130 columns 0.94; at 4 stacked columns 510 to 4606 columns 0.93-1.09, 130 to 310 0.86-1.06
+// Workers with few columns in a layer that others take in wide kernels keep the tiles of those; there the units gain
+// once they fill the lanes side by side over a row (16, with 16 columns 64): trees at rank 2, 201 to 3042 columns,
+// 1.18-1.36, 155 columns 0.95, an even 178 columns 0.94; at ranks 3 and 4, 43 to 78 columns, 0.90-0.95.
+bool gains_units_of_four(const LayerInfo &L, int rc, double total_bytes, const Plan &P) {
+    if (L.q % 4 == 0 || L.q < kAnyAlignCols) return false;
+    const bool odd = L.q % 2 != 0;
+    if (rc >= kWideCols) return (odd || P.large) && L.q >= (rc < kMaxCols ? 192 : 256);
+    if (L.q <= 128) return true;
+    if (!odd) return P.large && L.q >= (rc <= 2 ? 192 : 512);
+    return total_bytes >= (double)(rc <= 2 || P.light || L.q <= 256 ? kOddLongBytes : kOddLongBytes4);
+}
 int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune) {
@@ -89,7 +110,6 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     P.layers.resize(n_layers);
     int64_t off = 0;
     P.elems_per_worker = 0;
-    double odd_elems = 0.0;  // in rows that units of four floats would speed up
     P.message_floats = 0;
     for (int l = 0; l < n_layers; ++l) {
         int p = rows[l], q = cols[l];
@@ -101,7 +121,6 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.max_layer_rank = std::max(P.max_layer_rank, L.r);
         P.max_rows = std::max(P.max_rows, p);
         L.V = (q % 4 == 0) ? 4 : (q % 2 == 0 ? 2 : 1);
-        if (L.V < 4 && q >= kAnyAlignCols) odd_elems += (double)p * q;
         // Row stride.  With 8 or more stacked columns a tile's wavefronts work side by side on
         // 64-column (256-byte) pieces of the same rows; when rows start at arbitrary addresses every
         // piece ends inside a 128-byte line that the neighbouring wavefront touches at another time,
@@ -116,8 +135,6 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.message_floats += (size_t)L.r * ((size_t)p + q);
     }
     P.param_floats = (size_t)off;
-    P.odd_rows = tune.odd_rows < 0 ? odd_elems >= kOddShare * P.elems_per_worker : tune.odd_rows != 0;
-    for (LayerInfo &L : P.layers) L.Vn = P.odd_rows && L.q >= kAnyAlignCols ? 4 : L.V;
     for (int l = 0; l < n_layers; ++l)
         if (P.layers[l].r > kMaxCols) return PG_ERR_ARG;  // one edge's columns must fit one pass
 
@@ -164,6 +181,18 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.large = tune.stream < 0 ? total_bytes > (double)(wide ? kStreamBytesWide : kStreamBytes) : tune.stream != 0;
         P.stream = tune.stream < 0 ? P.large && streamed >= kStreamShare * elems : tune.stream != 0;
         P.lazy = tune.lazy < 0 ? P.large && behind >= kStreamShare * elems : tune.lazy != 0;
+        double odd = 0.0;  // elements in rows that units of four floats speed up
+        for (LayerInfo &L : P.layers) {
+            const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
+            const int rc = compiled_cols(std::max(1, per_pass * L.r));
+            const bool gains = tune.odd_rows < 0 ? gains_units_of_four(L, rc, total_bytes, P)
+                                                 : tune.odd_rows != 0 && L.q >= kAnyAlignCols;
+            L.Vn = gains ? 4 : L.V;
+            if (L.Vn > L.V) odd += (double)L.p * L.q;
+        }
+        P.odd_rows = tune.odd_rows < 0 ? odd >= kOddShare * elems && odd > 0.0 : tune.odd_rows != 0;
+        if (!P.odd_rows)
+            for (LayerInfo &L : P.layers) L.Vn = L.V;
         tn.row_tile_bytes = (int)std::max((P.light ? 4.0 : 8.0) * 1024, std::min((double)tune.row_tile_bytes, total_bytes / slots));
         tn.col_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.col_tile_bytes, 4.0 * total_bytes / slots));
         tn.wide_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.wide_tile_bytes, 4.0 * total_bytes / slots));

@@ -300,6 +300,12 @@ int main() {
     bad |= odd("whole units only", {100, 40, 3000, 64}, {100, 16, 4, 576}, false);
     bad |= odd("short odd rows", {100, 4000, 900}, {100, 3, 14}, false);
     bad |= odd("one layer of 27 columns", {100, 64}, {100, 27}, true);
+    bad |= odd("577 columns, 15 MB", {400}, {577}, false);
+    bad |= odd("577 columns, 59 MB", {1600}, {577}, true);
+    bad |= odd("109 columns, 1 MB", {160}, {109}, true);
+    bad |= odd("1150 columns, 150 MB", {2000}, {1150}, false);
+    bad |= odd("1150 columns, 500 MB", {7000}, {1150}, true);
+    bad |= odd("130 columns, 500 MB", {60000}, {130}, false);
     bad |= odd("a sliver of 27 columns", {1000, 16}, {1000, 27}, false);
     if (!bad) printf("ok %d random problems\n", nrandom);
     return bad;
