@@ -70,6 +70,14 @@ bool gains_units_of_four(const LayerInfo &L, int rc, double total_bytes, const P
     if (!odd) return P.large && L.q >= (rc <= 2 ? 192 : 512);
     return total_bytes >= (double)(rc <= 2 || P.light || L.q <= 256 ? kOddLongBytes : kOddLongBytes4);
 }
+// The wide kernels, on padded rows.  Measured over 600 drawn sets, time in the dividing width / in units of four:
+// odd q 0.94-2.1 (49 of 53 above 1).  Even q in light sets: 8 columns 70 to 342 columns 0.88-0.98, 510 to 5222 columns
+// 1.04-1.22; 16 columns 174 to 2434 columns 0.94-1.04; in larger sets 1.03-1.11 (2906 to 4942 columns, 73 to 602 MB; 650
+// columns, 850 MB: SGD round 2.87 -> 2.74 ms).
+bool gains_wide_units(const LayerInfo &L, int rc, const Plan &P) {
+    return L.q % 2 != 0 || !P.light || (rc < kMaxCols && L.q >= 512);
+}
+
 int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune) {
@@ -205,16 +213,24 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         int wc;                                  // matrix-core row tiles: wavefronts across the column steps
         bool wide;                               // row-owner: many stacked columns, Q slice in LDS
         bool mrow;                               // row-owner: matrix-core tiles
+        bool units;                              // wide kernels: units of four floats
         int lg, nblk, blk_rows;                  // column-owner
     };
     std::vector<Geo> geo(n_layers);
     // Wide kernels in units of four floats on padded rows.  Every vector width is a launch of its own,
     // so in a small set whose other layers need another width anyway the split costs more than the
     // wider accesses save (11 workers, 115 MB, eight layers of odd lengths: 447 -> 475 us per SGD
-    // round); in large ones, or where all rows are padded, it pays (LSTM SGD round 2.87 -> 2.74 ms).
-    bool all_padded = true;
-    for (const LayerInfo &L : P.layers) all_padded = all_padded && L.ld % 4 == 0;
-    const bool wide_units = tune.mfma_cols && (tune.wide_units < 0 ? P.large || all_padded : tune.wide_units != 0);
+    // round); in large ones, or where all rows are padded, it pays.  For the same reason a layer that gains nothing
+    // by itself goes along with others that are moved in units of four anyway (143 x 32, 378 x 182, 72 x 345 and 83 x 36
+    // on a 3x3 torus at rank 3, one round: 60 us with a launch of its own for the even rows, 39 us without).
+    bool all_padded = true, some_units = false;
+    for (const LayerInfo &L : P.layers) {
+        const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
+        const int rc = compiled_cols(std::max(1, per_pass * L.r));
+        all_padded = all_padded && L.ld % 4 == 0;
+        if (rc >= kWideCols && L.ld % 4 == 0) some_units = some_units || L.q % 4 == 0 || gains_wide_units(L, rc, P);
+    }
+    const bool wide_units = tune.mfma_cols && (tune.wide_units < 0 ? some_units && (P.large || all_padded) : tune.wide_units != 0);
     constexpr int kColUnroll = 8;
     for (int l = 0; l < n_layers; ++l) {
         const LayerInfo &L = P.layers[l];
@@ -232,7 +248,8 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         // Lanes per row: a whole wavefront for few stacked columns; 16 for many, where the
         // per-row lane reduction (RC values per row) would otherwise rival the products.
         g.lpr = std::min((g.wide && !g.mrow) ? 16 : 64, pow2_ceil(nv));
-        const int wide_V = g.wide && wide_units && L.ld % 4 == 0 ? 4 : Vg;  // width of the wide kernels' accesses to X
+        g.units = g.wide && wide_units && L.ld % 4 == 0;
+        const int wide_V = g.units ? 4 : Vg;  // width of the wide kernels' accesses to X
         int chunk = g.lpr * wide_V;  // floats one lane group covers per step
         int nchunks = (L.q + chunk - 1) / chunk;
         int seg_chunks;
@@ -510,7 +527,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             const bool mrow = g.mrow && RC >= kWideCols;
             // Layers with padded rows are read and written four floats at a time by the wide kernels
             // whatever q is; a row's last unit may reach into the padding (zeroed, never stored).
-            const bool wide4 = RC >= kWideCols && wide_units && L.ld % 4 == 0;
+            const bool wide4 = RC >= kWideCols && g.units;
             const int Vr = wide4 ? 4 : (RC < kWideCols ? L.Vn : L.V);
             const int Vc = wide4 ? 4 : L.V;
             P.pairs[pair].V = Vr;

@@ -307,6 +307,24 @@ int main() {
     bad |= odd("1150 columns, 500 MB", {7000}, {1150}, true);
     bad |= odd("130 columns, 500 MB", {60000}, {130}, false);
     bad |= odd("a sliver of 27 columns", {1000, 16}, {1000, 27}, false);
+    // wide kernels: which floats per access the padded layers get
+    auto widths = [&](const char *name, const std::vector<int32_t> &edges, int n, const std::vector<int32_t> &rows,
+                      const std::vector<int32_t> &cols, int rank, int want) {
+        Plan P;
+        std::vector<float> w(edges.size() / 2, 0.2f);
+        int rc = build_plan(P, n, (int)w.size(), edges.data(), w.data(), (int)rows.size(), rows.data(), cols.data(), rank, 1, Tuning());
+        REQUIRE(rc == PG_OK, "build_plan returned %d", rc);
+        for (const RowClass &c : P.row_classes)
+            if (c.RC >= kWideCols) REQUIRE(c.V == want, "%d floats per access", c.V);
+        printf("as expected: %s\n", name);
+        return 0;
+    };
+    bad |= widths("odd rows, 16 columns", t3, 9, {126}, {927}, 4, 4);
+    bad |= widths("even rows, 16 columns, small", t3, 9, {241}, {1642}, 4, 2);
+    bad |= widths("even rows, 16 columns, 130 MB", t3, 9, {2400}, {1506}, 4, 4);
+    bad |= widths("short even rows, 8 columns", t3, 9, {260}, {70}, 2, 2);
+    bad |= widths("long even rows, 8 columns", t3, 9, {57}, {5222}, 2, 4);
+    bad |= widths("even rows beside whole units", t3, 9, {143, 378, 72, 83}, {32, 182, 345, 36}, 3, 4);
     if (!bad) printf("ok %d random problems\n", nrandom);
     return bad;
 }
