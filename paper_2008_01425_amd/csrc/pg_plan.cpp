@@ -458,15 +458,16 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     P.ws_bytes = std::max<size_t>(o, 256);
     // Units of four floats on rows of odd length change the segments and row blocks and with them the
     // number of partial sums, mostly upwards.  A problem that does not fit the static workspace that
-    // way is planned with the widths that divide its rows, or with longer row blocks, if it fits then
+    // way is planned with longer row blocks if it fits then, next with the widths that divide its rows
     // (54126 x 1162 on a ring of 8 at rank 2: 56.0 MB, 30.1 MB with the dividing widths; 23961 x 626 on
-    // a ring of 20 at rank 2: 36.7 MB with those, 31.9 MB with longer blocks).
-    if (tune.odd_rows < 0 && tune.wide_units < 0 && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
-        Tuning other[3] = {tune, tune, tune};
-        other[0].odd_rows = other[0].wide_units = 0;
-        other[1].odd_rows = 1;
+    // a ring of 20 at rank 2: 36.7 MB with those, 31.9 MB with units of four and longer blocks).
+    if (tune.odd_rows < 0 && tune.wide_units < 0 && !tune.long_blocks && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
+        Tuning other[4] = {tune, tune, tune, tune};
+        other[0].long_blocks = true;
+        other[1].odd_rows = other[1].wide_units = 0;
         other[2].odd_rows = 1;
-        other[2].long_blocks = true;
+        other[3].odd_rows = 1;
+        other[3].long_blocks = true;
         for (const Tuning &tn2 : other) {
             Plan Q;
             const int rc = build_plan(Q, n_workers, n_edges, edges, edge_w, n_layers, rows, cols, rank, power_steps, tn2);

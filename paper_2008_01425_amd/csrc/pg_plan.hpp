@@ -56,7 +56,7 @@ struct Tuning {
     // units of four floats on rows whose length is not a multiple of four: -1 by rule, 0 never, 1 always
     int odd_rows = -1;                // narrow kernels, at any 4-byte aligned address
     int wide_units = -1;              // wide kernels, on padded rows
-    bool long_blocks = false;         // (with odd_rows) row blocks of the Q-sweep as long as one float per lane asks for
+    bool long_blocks = false;         // with those: row blocks of the Q-sweep as long as the dividing width asks for
     int stream = -1;                  // non-temporal passes: -1 by size and row length, 0 never, 1 always
     int lazy = -1;                    // runs that write every second round: the same, where the kernels can
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):

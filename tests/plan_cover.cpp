@@ -307,6 +307,23 @@ int main() {
     bad |= odd("1150 columns, 500 MB", {7000}, {1150}, true);
     bad |= odd("130 columns, 500 MB", {60000}, {130}, false);
     bad |= odd("a sliver of 27 columns", {1000, 16}, {1000, 27}, false);
+    // a set that units of four floats take beyond the static workspace keeps them where longer row blocks bring it back
+    {
+        const char *name = "longer blocks before narrower accesses";
+        std::vector<int32_t> t54;
+        torus(5, 4, t54);
+        const std::vector<int32_t> r = {106, 265, 1234, 755, 70, 2198, 4076, 365, 999, 105, 60, 3563, 75, 42},
+                                   c = {115, 63, 1, 3, 45, 148, 1211, 883, 47, 1197, 1701, 7, 108, 2628};
+        Plan P, Q;
+        std::vector<float> w(t54.size() / 2, 0.2f);
+        Tuning narrow;
+        narrow.odd_rows = 1;
+        build_plan(Q, 20, (int)w.size(), t54.data(), w.data(), (int)r.size(), r.data(), c.data(), 1, 1, narrow);
+        REQUIRE(Q.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES, "%zu bytes", Q.ws_bytes);
+        build_plan(P, 20, (int)w.size(), t54.data(), w.data(), (int)r.size(), r.data(), c.data(), 1, 1, Tuning());
+        REQUIRE(P.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES && P.odd_rows, "%zu bytes, units of four %d", P.ws_bytes, P.odd_rows);
+        printf("as expected: %s\n", name);
+    }
     // wide kernels: which floats per access the padded layers get
     auto widths = [&](const char *name, const std::vector<int32_t> &edges, int n, const std::vector<int32_t> &rows,
                       const std::vector<int32_t> &cols, int rank, int want) {
