@@ -59,13 +59,14 @@ bool gains_behind(const LayerInfo &L, int rc) {
 //   0.93-1.13 at 150 MB; 1.02-1.48 at 450 MB
 //   even q above 128: 0.86-1.04 at 40 and 62 MB, 0.86-1.10 at 150 MB; 300 to 800 MB: 202 to 4606 columns 1.00-1.24
 //   at 2 stacked columns, 130 columns 0.94; at 4 stacked columns 510 to 4606 columns 0.93-1.09, 130 to 310 0.86-1.06
-// Workers with few columns in a layer that others take in wide kernels keep the tiles of those; there the units gain
-// once they fill the lanes side by side over a row (16, with 16 columns 64): trees at rank 2, 201 to 3042 columns,
-// 1.18-1.36, 155 columns 0.95, an even 178 columns 0.94; at ranks 3 and 4, 43 to 78 columns, 0.90-0.95.
+// Workers with few columns in a layer that others take in wide kernels keep the tiles of those (trees at ranks 2 to 4, 3
+// to 120 MB, SGD round and run): 8 columns, odd q 37 to 117: 0.95-1.10, 135 and 155: 0.90-1.01, 175 to 513: 0.97-1.32, even
+// 62 to 254: 0.89-1.03, 510: 1.00-1.09; 16 columns, odd q 37 to 513: 0.71-1.02, 801 to 8191: 0.97-1.07, even: 0.83-1.00.
 bool gains_units_of_four(const LayerInfo &L, int rc, double total_bytes, const Plan &P) {
     if (L.q % 4 == 0 || L.q < kAnyAlignCols) return false;
     const bool odd = L.q % 2 != 0;
-    if (rc >= kWideCols) return (odd || P.large) && L.q >= (rc < kMaxCols ? 192 : 256);
+    if (rc >= kMaxCols) return odd && L.q >= 768;
+    if (rc >= kWideCols) return odd ? L.q <= 128 || L.q >= 168 : L.q >= 400;
     if (L.q <= 128) return true;
     if (!odd) return P.large && L.q >= (rc <= 2 ? 192 : 512);
     return total_bytes >= (double)(rc <= 2 || P.light || L.q <= 256 ? kOddLongBytes : kOddLongBytes4);
@@ -171,8 +172,8 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     // ---- tile sizes: the byte targets suit workloads that fill the chip many times over; small
     // parameter sets are cut finer so that every SIMD still gets a tile ----
     Tuning tn = tune;
+    const double total_bytes = 4.0 * n_workers * P.elems_per_worker;
     {
-        const double total_bytes = 4.0 * n_workers * P.elems_per_worker;
         const double slots = 4096.0;  // 256 CUs x 4 SIMDs x a few wavefronts
         P.light = tune.light < 0 ? total_bytes <= (double)kLightBytes : tune.light != 0;
         bool wide = false;  // some worker has 8 or more stacked columns in a pass
@@ -189,23 +190,39 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         P.large = tune.stream < 0 ? total_bytes > (double)(wide ? kStreamBytesWide : kStreamBytes) : tune.stream != 0;
         P.stream = tune.stream < 0 ? P.large && streamed >= kStreamShare * elems : tune.stream != 0;
         P.lazy = tune.lazy < 0 ? P.large && behind >= kStreamShare * elems : tune.lazy != 0;
-        double odd = 0.0;  // elements in rows that units of four floats speed up
-        for (LayerInfo &L : P.layers) {
-            const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
-            const int rc = compiled_cols(std::max(1, per_pass * L.r));
-            const bool gains = tune.odd_rows < 0 ? gains_units_of_four(L, rc, total_bytes, P)
-                                                 : tune.odd_rows != 0 && L.q >= kAnyAlignCols;
-            L.Vn = gains ? 4 : L.V;
-            if (L.Vn > L.V) odd += (double)L.p * L.q;
-        }
-        P.odd_rows = tune.odd_rows < 0 ? odd >= kOddShare * elems && odd > 0.0 : tune.odd_rows != 0;
-        if (!P.odd_rows)
-            for (LayerInfo &L : P.layers) L.Vn = L.V;
         tn.row_tile_bytes = (int)std::max((P.light ? 4.0 : 8.0) * 1024, std::min((double)tune.row_tile_bytes, total_bytes / slots));
         tn.col_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.col_tile_bytes, 4.0 * total_bytes / slots));
         tn.wide_tile_bytes = (int)std::max(32.0 * 1024, std::min((double)tune.wide_tile_bytes, 4.0 * total_bytes / slots));
         tn.mcol_tile_bytes = (int)std::max(64.0 * 1024, std::min((double)tune.mcol_tile_bytes, 8.0 * total_bytes / slots));
     }
+
+    // ---- workspace sections, given the doubles of the P- and Q-partials ----
+    int64_t orth_chunks = 0;  // tall layers: row chunks for the two-kernel orthonormalisation (36 Gram sums per chunk)
+    {
+        bool tall = false;
+        for (const LayerInfo &L : P.layers) tall = tall || L.p > kOrthTallRows;
+        if (tall)
+            for (const LayerInfo &L : P.layers) orth_chunks += (int64_t)n_edges * ((L.p + kOrthChunkRows - 1) / kOrthChunkRows);
+    }
+    auto sections = [&](int64_t pwo, int64_t qwo) {
+        size_t o = 0;
+        P.ws_pw = o;
+        o = (size_t)round_up(o + (size_t)pwo * 8, 256);
+        P.ws_qw = o;
+        o = (size_t)round_up(o + (size_t)qwo * 8, 256);
+        P.ws_pd = o;
+        o = (size_t)round_up(o + (size_t)pdo * 8, 256);
+        P.ws_ph = o;
+        o = (size_t)round_up(o + (size_t)pho * 4, 256);
+        P.ws_flag = o;
+        o = (size_t)round_up(o + (size_t)flo * 4, 256);
+        P.ws_gpart = o;
+        o = (size_t)round_up(o + (size_t)orth_chunks * 36 * 8, 256);
+        // unit vectors in R^q of Algorithm 2's odd iterations (state layout)
+        P.ws_uq = o;
+        o = (size_t)round_up(o + (size_t)qo * 4, 256);
+        P.ws_bytes = std::max<size_t>(o, 256);
+    };
 
     // ---- per-layer launch geometry ----
     struct Geo {
@@ -217,103 +234,144 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         int lg, nblk, blk_rows;                  // column-owner
     };
     std::vector<Geo> geo(n_layers);
-    // Wide kernels in units of four floats on padded rows.  Every vector width is a launch of its own,
-    // so in a small set whose other layers need another width anyway the split costs more than the
-    // wider accesses save (11 workers, 115 MB, eight layers of odd lengths: 447 -> 475 us per SGD
-    // round); in large ones, or where all rows are padded, it pays.  For the same reason a layer that gains nothing
-    // by itself goes along with others that are moved in units of four anyway (143 x 32, 378 x 182, 72 x 345 and 83 x 36
-    // on a 3x3 torus at rank 3, one round: 60 us with a launch of its own for the even rows, 39 us without).
-    bool all_padded = true, some_units = false;
-    for (const LayerInfo &L : P.layers) {
-        const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
-        const int rc = compiled_cols(std::max(1, per_pass * L.r));
-        all_padded = all_padded && L.ld % 4 == 0;
-        if (rc >= kWideCols && L.ld % 4 == 0) some_units = some_units || L.q % 4 == 0 || gains_wide_units(L, rc, P);
-    }
-    const bool wide_units = tune.mfma_cols && (tune.wide_units < 0 ? some_units && (P.large || all_padded) : tune.wide_units != 0);
-    constexpr int kColUnroll = 8;
-    for (int l = 0; l < n_layers; ++l) {
-        const LayerInfo &L = P.layers[l];
-        Geo &g = geo[l];
-        // The row blocking depends on the stacked column count; size for the best-connected worker.
-        // (a worker with more than kMaxCols stacked columns takes several passes of whole edges)
-        const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
-        int rc_max = compiled_cols(std::max(1, per_pass * L.r));
-        g.wide = rc_max >= kWideCols;
-        const int Vg = g.wide ? L.V : L.Vn;
-        const int nv = (L.q + Vg - 1) / Vg;  // vector loads per row
-        // Row passes on the matrix cores pay from 16 stacked columns on (measured: at 8 the vector
-        // kernels' P-sweep is the faster one) and address a layer with 32-bit byte offsets.
-        g.mrow = tune.mfma_rows && rc_max >= tune.mfma_row_cols && (int64_t)L.p * L.ld < ((int64_t)1 << 30);
-        // Lanes per row: a whole wavefront for few stacked columns; 16 for many, where the
-        // per-row lane reduction (RC values per row) would otherwise rival the products.
-        g.lpr = std::min((g.wide && !g.mrow) ? 16 : 64, pow2_ceil(nv));
-        g.units = g.wide && wide_units && L.ld % 4 == 0;
-        const int wide_V = g.units ? 4 : Vg;  // width of the wide kernels' accesses to X
-        int chunk = g.lpr * wide_V;  // floats one lane group covers per step
-        int nchunks = (L.q + chunk - 1) / chunk;
-        int seg_chunks;
-        if (!g.wide) {
-            // one wavefront per tile: column segments keep a tile near the byte target when a
-            // single row is long
-            int rows_iter = (64 / g.lpr) * rows_unroll(rc_max, P.light);
-            int64_t chunk_bytes = (int64_t)rows_iter * chunk * 4;
-            seg_chunks = (int)std::max<int64_t>(1, tn.row_tile_bytes / chunk_bytes);
-            g.rows_iter_base = 64 / g.lpr;
-        } else if (g.mrow) {
-            // matrix cores: steps of 64 columns; a row is cut only when it is very long
-            chunk = 64;
-            nchunks = (L.q + chunk - 1) / chunk;
-            seg_chunks = kMfmaSegCols / chunk;
-            g.rows_iter_base = 64 / g.lpr;  // for this layer's workers with few stacked columns
-        } else {
-            // four wavefronts per tile share the Q slice in LDS: RC * seg_len floats must fit
-            seg_chunks = std::max(1, kWideLdsBytes / (rc_max * 4) / chunk);
-            g.rows_iter_base = (kThreads / 64) * (64 / g.lpr);
+    // The geometry under the settings `t` for rows of odd length; sets the workspace sections.
+    auto lay_out = [&](const Tuning &t) {
+        double odd = 0.0;  // elements in rows that units of four floats speed up
+        for (LayerInfo &L : P.layers) {
+            const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
+            const int rc = compiled_cols(std::max(1, per_pass * L.r));
+            const bool gains = t.odd_rows < 0 ? gains_units_of_four(L, rc, total_bytes, P)
+                                              : t.odd_rows != 0 && L.q >= kAnyAlignCols;
+            L.Vn = gains ? 4 : L.V;
+            if (L.Vn > L.V) odd += (double)L.p * L.q;
         }
-        g.nseg = (nchunks + seg_chunks - 1) / seg_chunks;
-        seg_chunks = (nchunks + g.nseg - 1) / g.nseg;
-        g.nseg = (nchunks + seg_chunks - 1) / seg_chunks;
-        g.seg_len = seg_chunks * chunk;
-        g.wc = 1;
-        if (g.mrow) g.wc = seg_chunks >= 4 ? 4 : (seg_chunks >= 2 ? 2 : 1);
-
-        // Column-owner kernel: lanes side by side over columns; pick the lane-group width that
-        // wastes the fewest lanes on the ragged end of a row (ties go to the wider group).
-        int best = 64;
-        double best_util = -1;
-        for (int lg : {64, 32, 16}) {
-            int lgc = std::min(lg, pow2_ceil(nv));
-            int groups = (nv + lgc - 1) / lgc;
-            double util = (double)nv / ((double)groups * lgc);
-            if (util > best_util + 0.05) {
-                best_util = util;
-                best = lgc;
+        P.odd_rows = t.odd_rows < 0 ? odd >= kOddShare * P.elems_per_worker && odd > 0.0 : t.odd_rows != 0;
+        if (!P.odd_rows)
+            for (LayerInfo &L : P.layers) L.Vn = L.V;
+        // Wide kernels in units of four floats on padded rows.  Every vector width is a launch of its own,
+        // so in a small set whose other layers need another width anyway the split costs more than the
+        // wider accesses save (11 workers, 115 MB, eight layers of odd lengths: 447 -> 475 us per SGD
+        // round); in large ones, or where all rows are padded, it pays.  For the same reason a layer that gains nothing
+        // by itself goes along with others that are moved in units of four anyway (143 x 32, 378 x 182, 72 x 345 and 83 x 36
+        // on a 3x3 torus at rank 3, one round: 60 us with a launch of its own for the even rows, 39 us without).
+        bool all_padded = true, some_units = false;
+        for (const LayerInfo &L : P.layers) {
+            const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
+            const int rc = compiled_cols(std::max(1, per_pass * L.r));
+            all_padded = all_padded && L.ld % 4 == 0;
+            if (rc >= kWideCols && L.ld % 4 == 0) some_units = some_units || L.q % 4 == 0 || gains_wide_units(L, rc, P);
+        }
+        const bool wide_units = tune.mfma_cols && (t.wide_units < 0 ? some_units && (P.large || all_padded) : t.wide_units != 0);
+        constexpr int kColUnroll = 8;
+        for (int l = 0; l < n_layers; ++l) {
+            const LayerInfo &L = P.layers[l];
+            Geo &g = geo[l];
+            // The row blocking depends on the stacked column count; size for the best-connected worker.
+            // (a worker with more than kMaxCols stacked columns takes several passes of whole edges)
+            const int per_pass = std::min<int>((int)max_deg, std::max(1, kMaxCols / L.r));
+            int rc_max = compiled_cols(std::max(1, per_pass * L.r));
+            g.wide = rc_max >= kWideCols;
+            const int Vg = g.wide ? L.V : L.Vn;
+            const int nv = (L.q + Vg - 1) / Vg;  // vector loads per row
+            // Row passes on the matrix cores pay from 16 stacked columns on (measured: at 8 the vector
+            // kernels' P-sweep is the faster one) and address a layer with 32-bit byte offsets.
+            g.mrow = tune.mfma_rows && rc_max >= tune.mfma_row_cols && (int64_t)L.p * L.ld < ((int64_t)1 << 30);
+            // Lanes per row: a whole wavefront for few stacked columns; 16 for many, where the
+            // per-row lane reduction (RC values per row) would otherwise rival the products.
+            g.lpr = std::min((g.wide && !g.mrow) ? 16 : 64, pow2_ceil(nv));
+            g.units = g.wide && wide_units && L.ld % 4 == 0;
+            const int wide_V = g.units ? 4 : Vg;  // width of the wide kernels' accesses to X
+            int chunk = g.lpr * wide_V;  // floats one lane group covers per step
+            int nchunks = (L.q + chunk - 1) / chunk;
+            int seg_chunks;
+            if (!g.wide) {
+                // one wavefront per tile: column segments keep a tile near the byte target when a
+                // single row is long
+                int rows_iter = (64 / g.lpr) * rows_unroll(rc_max, P.light);
+                int64_t chunk_bytes = (int64_t)rows_iter * chunk * 4;
+                seg_chunks = (int)std::max<int64_t>(1, tn.row_tile_bytes / chunk_bytes);
+                g.rows_iter_base = 64 / g.lpr;
+            } else if (g.mrow) {
+                // matrix cores: steps of 64 columns; a row is cut only when it is very long
+                chunk = 64;
+                nchunks = (L.q + chunk - 1) / chunk;
+                seg_chunks = kMfmaSegCols / chunk;
+                g.rows_iter_base = 64 / g.lpr;  // for this layer's workers with few stacked columns
+            } else {
+                // four wavefronts per tile share the Q slice in LDS: RC * seg_len floats must fit
+                seg_chunks = std::max(1, kWideLdsBytes / (rc_max * 4) / chunk);
+                g.rows_iter_base = (kThreads / 64) * (64 / g.lpr);
             }
+            g.nseg = (nchunks + seg_chunks - 1) / seg_chunks;
+            seg_chunks = (nchunks + g.nseg - 1) / g.nseg;
+            g.nseg = (nchunks + seg_chunks - 1) / seg_chunks;
+            g.seg_len = seg_chunks * chunk;
+            g.wc = 1;
+            if (g.mrow) g.wc = seg_chunks >= 4 ? 4 : (seg_chunks >= 2 ? 2 : 1);
+
+            // Column-owner kernel: lanes side by side over columns; pick the lane-group width that
+            // wastes the fewest lanes on the ragged end of a row (ties go to the wider group).
+            int best = 64;
+            double best_util = -1;
+            for (int lg : {64, 32, 16}) {
+                int lgc = std::min(lg, pow2_ceil(nv));
+                int groups = (nv + lgc - 1) / lgc;
+                double util = (double)nv / ((double)groups * lgc);
+                if (util > best_util + 0.05) {
+                    best_util = util;
+                    best = lgc;
+                }
+            }
+            // With many stacked columns the kernel is bound by arithmetic and LDS reads of Phat, and
+            // one row per wavefront (all 64 lanes side by side) with shorter row blocks measures best.
+            const bool col_heavy = rc_max >= 16;
+            if (col_heavy && (double)nv / ((double)((nv + 63) / 64) * 64) > 0.6) best = std::min(64, pow2_ceil(nv));
+            g.lg = best;
+            int row_groups = 4 * (64 / g.lg);
+            int64_t row_bytes = (int64_t)g.lg * (t.long_blocks ? L.V : Vg) * 4;
+            int64_t want = std::max<int64_t>(1, tn.col_tile_bytes / row_bytes);
+            int64_t unit = (int64_t)row_groups * kColUnroll;
+            if (g.wide && tune.mfma_cols) {
+                // four wavefronts per tile of kMfmaTileCols columns
+                want = std::max<int64_t>(16, tn.mcol_tile_bytes / (kMfmaTileCols * 4));
+                unit = 16;
+            }
+            int64_t br = round_up(want, unit);
+            if (!(g.wide && tune.mfma_cols)) {
+                // the vector column kernel stages the block's Phat slice in LDS: (rows + 1) x columns floats
+                const int64_t cap = kColLdsBytes / (4 * rc_max) - 1;
+                if (br > cap) br = cap >= unit ? cap / unit * unit : cap;
+            }
+            if (br >= L.p) br = L.p;
+            g.blk_rows = (int)br;
+            g.nblk = (L.p + g.blk_rows - 1) / g.blk_rows;
         }
-        // With many stacked columns the kernel is bound by arithmetic and LDS reads of Phat, and
-        // one row per wavefront (all 64 lanes side by side) with shorter row blocks measures best.
-        const bool col_heavy = rc_max >= 16;
-        if (col_heavy && (double)nv / ((double)((nv + 63) / 64) * 64) > 0.6) best = std::min(64, pow2_ceil(nv));
-        g.lg = best;
-        int row_groups = 4 * (64 / g.lg);
-        int64_t row_bytes = (int64_t)g.lg * (tune.long_blocks ? L.V : Vg) * 4;
-        int64_t want = std::max<int64_t>(1, tn.col_tile_bytes / row_bytes);
-        int64_t unit = (int64_t)row_groups * kColUnroll;
-        if (g.wide && tune.mfma_cols) {
-            // four wavefronts per tile of kMfmaTileCols columns
-            want = std::max<int64_t>(16, tn.mcol_tile_bytes / (kMfmaTileCols * 4));
-            unit = 16;
+        // every edge brings r columns to the partials of both its ends
+        int64_t pw = 0, qw = 0;
+        for (int l = 0; l < n_layers; ++l) {
+            const int64_t c2 = 2 * (int64_t)n_edges * P.layers[l].r;
+            pw += geo[l].nseg * c2 * P.layers[l].p;
+            qw += geo[l].nblk * c2 * P.layers[l].q;
         }
-        int64_t br = round_up(want, unit);
-        if (!(g.wide && tune.mfma_cols)) {
-            // the vector column kernel stages the block's Phat slice in LDS: (rows + 1) x columns floats
-            const int64_t cap = kColLdsBytes / (4 * rc_max) - 1;
-            if (br > cap) br = cap >= unit ? cap / unit * unit : cap;
+        sections(pw, qw);
+    };
+    lay_out(tune);
+    // Units of four floats on rows of odd length change the segments and row blocks and with them the
+    // number of partial sums, mostly upwards.  A problem that does not fit the static workspace that
+    // way is planned with longer row blocks if it fits then, next with the widths that divide its rows
+    // (54126 x 1162 on a ring of 8 at rank 2: 56.0 MB, 30.1 MB with the dividing widths; 23961 x 626 on
+    // a ring of 20 at rank 2: 36.7 MB with those, 31.9 MB with units of four and longer blocks).
+    if (tune.odd_rows < 0 && tune.wide_units < 0 && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
+        Tuning other[5] = {tune, tune, tune, tune, tune};
+        other[0].long_blocks = true;
+        other[1].odd_rows = other[1].wide_units = 0;
+        other[2].odd_rows = 1;
+        other[3].odd_rows = 1;
+        other[3].long_blocks = true;
+        for (const Tuning &t : other) {  // the last one, where none fits: as at first
+            lay_out(t);
+            if (P.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES) break;
         }
-        if (br >= L.p) br = L.p;
-        g.blk_rows = (int)br;
-        g.nblk = (L.p + g.blk_rows - 1) / g.blk_rows;
     }
 
     // ---- (worker, layer) pairs with their stacked columns ----
@@ -425,56 +483,15 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         }
     }
 
-    // ---- workspace sections ----
-    size_t o = 0;
-    P.ws_pw = o;
-    o = (size_t)round_up(o + (size_t)pwo * 8, 256);
-    P.ws_qw = o;
-    o = (size_t)round_up(o + (size_t)qwo * 8, 256);
-    P.ws_pd = o;
-    o = (size_t)round_up(o + (size_t)pdo * 8, 256);
-    P.ws_ph = o;
-    o = (size_t)round_up(o + (size_t)pho * 4, 256);
-    P.ws_flag = o;
-    o = (size_t)round_up(o + (size_t)flo * 4, 256);
-    // tall layers: row chunks for the two-kernel orthonormalisation (36 Gram sums per chunk)
+    sections(pwo, qwo);
     P.orth_tiles.clear();
-    bool tall = false;
-    for (int l = 0; l < n_layers; ++l) tall = tall || P.layers[l].p > kOrthTallRows;
-    if (tall) {
+    if (orth_chunks > 0) {
         for (size_t el = 0; el < P.els.size(); ++el) {
             const int p = P.els[el].p;
             const int nch = (p + kOrthChunkRows - 1) / kOrthChunkRows;
             for (int ch = 0; ch < nch; ++ch)
                 P.orth_tiles.push_back({(int32_t)el, ch * kOrthChunkRows,
                                         std::min(kOrthChunkRows, p - ch * kOrthChunkRows), ch, nch, 0});
-        }
-    }
-    P.ws_gpart = o;
-    o = (size_t)round_up(o + P.orth_tiles.size() * 36 * 8, 256);
-    // unit vectors in R^q of Algorithm 2's odd iterations (state layout)
-    P.ws_uq = o;
-    o = (size_t)round_up(o + (size_t)qo * 4, 256);
-    P.ws_bytes = std::max<size_t>(o, 256);
-    // Units of four floats on rows of odd length change the segments and row blocks and with them the
-    // number of partial sums, mostly upwards.  A problem that does not fit the static workspace that
-    // way is planned with longer row blocks if it fits then, next with the widths that divide its rows
-    // (54126 x 1162 on a ring of 8 at rank 2: 56.0 MB, 30.1 MB with the dividing widths; 23961 x 626 on
-    // a ring of 20 at rank 2: 36.7 MB with those, 31.9 MB with units of four and longer blocks).
-    if (tune.odd_rows < 0 && tune.wide_units < 0 && !tune.long_blocks && P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) {
-        Tuning other[4] = {tune, tune, tune, tune};
-        other[0].long_blocks = true;
-        other[1].odd_rows = other[1].wide_units = 0;
-        other[2].odd_rows = 1;
-        other[3].odd_rows = 1;
-        other[3].long_blocks = true;
-        for (const Tuning &tn2 : other) {
-            Plan Q;
-            const int rc = build_plan(Q, n_workers, n_edges, edges, edge_w, n_layers, rows, cols, rank, power_steps, tn2);
-            if (rc == PG_OK && Q.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES) {
-                P = std::move(Q);
-                return PG_OK;
-            }
         }
     }
 

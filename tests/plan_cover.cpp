@@ -150,6 +150,7 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
     // a row class holds tiles of one column group only (groups of one matrix never share a launch)
     for (const RowClass &c : P.row_classes)
         for (const RowTile &t : c.tiles) REQUIRE(P.pair_group[t.pair] == c.group, "tile of group %d in class of group %d", P.pair_group[t.pair], c.group);
+    REQUIRE(P.orth_tiles.empty() || P.ws_uq >= P.ws_gpart + P.orth_tiles.size() * 36 * 8, "Gram sums do not fit their section");
     REQUIRE(P.ws_qw >= P.ws_pw + (size_t)pw_need * 8, "P partial sums do not fit their section");
     REQUIRE(P.ws_pd >= P.ws_qw + (size_t)qw_need * 8, "Q partial sums do not fit their section");
     REQUIRE(P.ws_bytes >= P.ws_uq, "workspace size");
@@ -312,8 +313,8 @@ int main() {
         const char *name = "longer blocks before narrower accesses";
         std::vector<int32_t> t54;
         torus(5, 4, t54);
-        const std::vector<int32_t> r = {106, 265, 1234, 755, 70, 2198, 4076, 365, 999, 105, 60, 3563, 75, 42},
-                                   c = {115, 63, 1, 3, 45, 148, 1211, 883, 47, 1197, 1701, 7, 108, 2628};
+        const std::vector<int32_t> r = {106, 265, 1234, 755, 34, 70, 2198, 4076, 365, 999, 105, 446, 60, 3563, 3749, 2415, 75, 42, 198, 151},
+                                   c = {115, 63, 1, 3, 1, 45, 148, 1211, 883, 47, 1197, 3, 1701, 7, 7, 1, 108, 2628, 1, 1};
         Plan P, Q;
         std::vector<float> w(t54.size() / 2, 0.2f);
         Tuning narrow;
