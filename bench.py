@@ -128,7 +128,7 @@ def measure_other(name: str, rounds: int):
     k_fused = kernel_table(B, gb, lambda: gb.run(kp))
     k_unfused = kernel_table(B, gb, lambda: [gb.round() for _ in range(kp)])
     nparam = wl.n_workers * wl.params_per_worker
-    bf, bu = B.pg_round_bytes(gb.ctx, True), B.pg_round_bytes(gb.ctx, False)
+    bf, bu = B.pg_run_bytes(gb.ctx, rounds) / rounds, B.pg_round_bytes(gb.ctx, False)
     traffic, src = traffic_from_profiles(name)
     slim = lambda tab: {k: {"avg_ms": v["avg_ms"], "GBps": v["GBps"], "frac_of_peak": v["frac_of_peak"],
                             "launches": v["launches"]} for k, v in tab.items()}
@@ -272,7 +272,8 @@ def main():
         "sweep_q_in_pg_round": sq_u and {"GBps": sq_u["GBps"], "frac": sq_u["frac_of_peak"], "avg_ms": sq_u["avg_ms"],
                                          "runs_after": "the P-sweep (a read-only pass)"},
         "sweep_q_in_pg_run": sq_f and {"GBps": sq_f["GBps"], "frac": sq_f["frac_of_peak"], "avg_ms": sq_f["avg_ms"],
-                                       "runs_after": "the fused update + P-sweep (a pass that wrote every parameter)"},
+                                       "runs_after": "the fused update + P-sweep (a pass that wrote every parameter; "
+                                                     "the rounds in between peek, see peek_sweep_q)"},
         "sweep_p_in_pg_round_after_evicting_read": k_evicted.get("sweep_p") and {
             "GBps": k_evicted["sweep_p"]["GBps"], "frac": k_evicted["sweep_p"]["frac_of_peak"],
             "avg_ms": k_evicted["sweep_p"]["avg_ms"],
@@ -285,7 +286,7 @@ def main():
     sweeps["target_met_where"] = {k: v["frac"] >= TARGET_FRAC for k, v in sweeps.items() if isinstance(v, dict)}
 
     nparam = wl.n_workers * wl.params_per_worker
-    bytes_fused = B.pg_round_bytes(gb.ctx, True)
+    bytes_fused = B.pg_run_bytes(gb.ctx, K) / K
     bytes_unfused = B.pg_round_bytes(gb.ctx, False)
     result = {
         "metric": "gossip rounds/sec + achieved HBM GB/s (% of peak), fp32, 1 MI355X",

@@ -139,11 +139,18 @@ size_t pg_message_floats(const pg_ctx *ctx);
 /*
  * Algorithmic bytes of parameter traffic of one round: 4 * n * N * passes, N = sum p_l q_l,
  * passes = 2*power_steps + 2 for pg_round (each product reads every X once, the update reads
- * and writes it), 2*power_steps + 1 per round inside pg_run (the update also feeds the next
- * round's first product).  A run of a large set with power_steps = 1 and at most four stacked
- * columns moves less: it writes the parameters every second round (5 passes for two rounds).
+ * and writes it), 2*power_steps + 1 for a round in the middle of a pg_run that writes the parameters
+ * every round (the update also feeds the next round's first product).  What a given pg_run moves in
+ * all, first and last round and runs that write every second round included, is pg_run_bytes.
  */
 double pg_round_bytes(const pg_ctx *ctx, int fused);
+
+/*
+ * Algorithmic bytes of parameter traffic of pg_run(ctx, ..., rounds), all rounds together, workers without
+ * neighbours left out (no pass reads them).  Runs that write the parameters every second round (see
+ * pg_run) make 5 passes over them for two rounds instead of 6.
+ */
+double pg_run_bytes(const pg_ctx *ctx, int rounds);
 
 /* Upload the descriptor tables to the current device now (otherwise the first round does it).
    Allocates device memory and synchronises. */
@@ -227,8 +234,12 @@ int pg_iterate(pg_ctx *ctx, float *const *worker_params, float *q_state, float *
  * `rounds` consecutive gossip rounds with nothing touching the parameters in between
  * (the pure consensus iteration, Eq. (4)).  Same result as calling pg_round `rounds` times;
  * the update of round t and the first product of round t+1 share one pass over the
- * parameters, and large parameter sets with power_steps = 1 are written every second round only
- * (the last one always).  rounds >= 0.  Once a call has seen the same worker_params pointers (the first
+ * parameters.  A large parameter set (more than 320 MB over all workers) is written every second round
+ * only, the last one always, if power_steps = 1, no worker stacks more than four columns (degree x rank),
+ * most of the parameters lie in layers with q >= 32 (at four columns q % 32 == 0 or q >= 512), there are
+ * fewer than 1024 (worker, layer with q = 1) pairs, and no layer is so tall and narrow that the Q-sweep
+ * takes a block of more than 2728 of its rows at once (1363 at three and four columns; a layer with q = 1 is
+ * one block).  rounds >= 0.  Once a call has seen the same worker_params pointers (the first
  * call with a new set copies the pointer table to the device and waits for the stream), a call
  * with profiling off only launches kernels: it may be recorded into a HIP graph on a capturing
  * stream and replayed.
@@ -243,7 +254,8 @@ int pg_run(pg_ctx *ctx, float *const *worker_params, float *q_state, void *works
  */
 typedef struct pg_kernel_time {
     char name[32];   /* "sweep_p", "orth_p", "sweep_q", "combine_q", "update", "update_sweep_p", "update_sgd",
-                        "orth_v", "combine_p" */
+                        "orth_v", "combine_p"; in runs that write the parameters every second round also
+                        "peek_sweep_p", "peek_sweep_q": sweeps that apply an update without storing it */
     int launches;    /* kernel launches of this kind */
     double ms;       /* summed duration */
     double bytes;    /* summed algorithmic bytes of parameter traffic (4 B per element read or written) */

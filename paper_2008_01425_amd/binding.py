@@ -18,7 +18,7 @@ PG_STATIC_WORKSPACE_BYTES = 32 << 20
 EXPORTS = [
     "pg_strerror", "pg_init", "pg_destroy", "pg_param_floats", "pg_layer_offset", "pg_layer_stride", "pg_layer_rank",
     "pg_qstate_floats", "pg_q_offset", "pg_workspace_bytes", "pg_ws_phat_offset",
-    "pg_ws_flag_offset", "pg_message_floats", "pg_round_bytes", "pg_upload", "pg_round", "pg_round_static", "pg_round_sgd",
+    "pg_ws_flag_offset", "pg_message_floats", "pg_round_bytes", "pg_run_bytes", "pg_upload", "pg_round", "pg_round_static", "pg_round_sgd",
     "pg_run", "pg_iterate", "pg_pstate_floats", "pg_p_offset",
     "pg_profile_enable", "pg_profile_collect",
 ]
@@ -70,6 +70,8 @@ def _load():
     lib.pg_layer_rank.argtypes = [vp, ci]
     lib.pg_round_bytes.restype = ctypes.c_double
     lib.pg_round_bytes.argtypes = [vp, ci]
+    lib.pg_run_bytes.restype = ctypes.c_double
+    lib.pg_run_bytes.argtypes = [vp, ci]
     lib.pg_upload.restype = ci
     lib.pg_upload.argtypes = [vp]
     lib.pg_round.restype = ci
@@ -142,6 +144,7 @@ def pg_ws_phat_offset(ctx, edge, layer): return lib.pg_ws_phat_offset(ctx, edge,
 def pg_ws_flag_offset(ctx, edge, layer): return lib.pg_ws_flag_offset(ctx, edge, layer)
 def pg_message_floats(ctx): return lib.pg_message_floats(ctx)
 def pg_round_bytes(ctx, fused: bool): return lib.pg_round_bytes(ctx, 1 if fused else 0)
+def pg_run_bytes(ctx, rounds: int): return lib.pg_run_bytes(ctx, rounds)
 
 
 def pg_upload(ctx) -> None:

@@ -28,9 +28,10 @@ constexpr int kMaxDevices = 64;
 void *g_scratch_ptr[kMaxDevices];  // per device: address of `scratch` there (null = not asked yet)
 
 enum Kind { K_SWEEP_P = 0, K_ORTH_P, K_SWEEP_Q, K_COMBINE_Q, K_UPDATE, K_UPDATE_SWEEP_P, K_UPDATE_SGD,
-            K_ORTH_V, K_COMBINE_P, K_COUNT };
+            K_ORTH_V, K_COMBINE_P, K_PEEK_SWEEP_P, K_PEEK_SWEEP_Q, K_COUNT };
 const char *const kKindName[K_COUNT] = {"sweep_p", "orth_p", "sweep_q", "combine_q", "update",
-                                        "update_sweep_p", "update_sgd", "orth_v", "combine_p"};
+                                        "update_sweep_p", "update_sgd", "orth_v", "combine_p",
+                                        "peek_sweep_p", "peek_sweep_q"};
 
 struct ProfRec {
     int kind;
@@ -307,7 +308,7 @@ struct Launcher {
             const RowClass &rc = classes[c->reverse ? classes.size() - 1 - k : k];
             if (rc.tiles.empty()) continue;
             const int n = (int)rc.tiles.size();
-            begin(SWP ? K_UPDATE_SWEEP_P : K_UPDATE, rc.elems * 4.0 * (PEND == kPeek ? 1.0 : 2.0));
+            begin(PEND == kPeek ? K_PEEK_SWEEP_P : (SWP ? K_UPDATE_SWEEP_P : K_UPDATE), rc.elems * 4.0 * (PEND == kPeek ? 1.0 : 2.0));
 #define PG_ROWP_(RC, M, ANY) row_pending_kernel<RC, M, kPrefetchSteps, SWP, PEND, ANY><<<dim3((unsigned)n), dim3(kRowThreads), 0, st>>>( \
                 c->d_row_tiles + rc.dev_first, n, c->reverse, c->d_pairs, c->d_cols, c->d_xs, right(), left(), pw(), phat1, q1)
 #define PG_ROWP(RC, M) do { if (c->plan.odd_rows) PG_ROWP_(RC, M, true); else PG_ROWP_(RC, M, false); } while (0)
@@ -394,7 +395,7 @@ struct Launcher {
         for (size_t k = 0; k < classes.size(); ++k) {
             const ColClass &cc = classes[c->reverse ? classes.size() - 1 - k : k];
             if (cc.tiles.empty()) continue;
-            begin(K_SWEEP_Q, cc.elems * 4.0);
+            begin(phat1 ? K_PEEK_SWEEP_Q : K_SWEEP_Q, cc.elems * 4.0);
             switch (cc.RC) {
                 case 1: col_launch<1>(cc); break;
                 case 2: col_launch<2>(cc); break;
@@ -721,6 +722,16 @@ double pg_round_bytes(const pg_ctx *c, int fused) {
         return 4.0 * c->plan.pass_elems * (2 * c->plan.steps + 2);
     int passes = 2 * c->plan.steps + (fused ? 1 : 2);
     return 4.0 * c->plan.n * c->plan.elems_per_worker * passes;
+}
+
+double pg_run_bytes(const pg_ctx *c, int rounds) {
+    if (!c || rounds < 0) return -1.0;
+    if (rounds == 0 || c->plan.n_edges == 0) return 0.0;
+    const double T = rounds;
+    if (c->plan.max_groups > 1) return T * pg_round_bytes(c, 0);
+    double passes = 2.0 * c->plan.steps * T + T + 1.0;  // both sweeps; every update also writes, the last one reads once more
+    if (c->plan.lazy && rounds > 1) passes = 2.0 * T + (rounds - 1) / 2 + 2.0;  // run_lazy: odd rounds from the third write
+    return 4.0 * c->plan.pass_elems * passes;
 }
 
 int pg_upload(pg_ctx *c) {

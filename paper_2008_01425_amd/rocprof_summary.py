@@ -63,10 +63,15 @@ def kernel_kind(name: str):
         if grad:
             return "update_sgd"
         return "update_sweep_p" if upd and swp else ("update" if upd else "sweep_p")
-    m = re.match(r"pg::row_pending_kernel<\d+, \d+, \d+, (true|false), \d, (true|false)>", name)
+    # <columns, rows per lane group, steps ahead, sweep, pending updates (1: peek, 2: apply two), any alignment>
+    m = re.match(r"pg::row_pending_kernel<\d+, \d+, \d+, (true|false), (\d), (true|false)>", name)
     if m:
+        if m.group(2) == "1":
+            return "peek_sweep_p"
         return "update_sweep_p" if m.group(1) == "true" else "update"
-    if re.match(r"pg::(col_kernel|mcol_kernel|vec_col_kernel|col_peek_kernel)<", name):
+    if re.match(r"pg::col_peek_kernel<", name):
+        return "peek_sweep_q"
+    if re.match(r"pg::(col_kernel|mcol_kernel|vec_col_kernel)<", name):
         return "sweep_q"
     return None
 

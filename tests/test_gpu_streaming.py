@@ -12,13 +12,14 @@ pytestmark = pytest.mark.gpu
 # every vector width, rows shorter and longer than a wavefront's step, several column segments, row
 # counts around the eight rows of a lane group and the staged row blocks, vectors, single entries
 SHAPES = [(64, 576), (33, 130), (17, 259), (5, 4609), (1030, 36), (9, 3), (700, 1), (1, 77), (1, 1), (7, 8), (8, 2306)]
+TALL = SHAPES + [(4500, 33)]   # more than 4096 rows: Phat by the chunked kernels
 
 
-def _workload(name, n, edges, rank, steps, sigma=0.05):
+def _workload(name, n, edges, rank, steps, sigma=0.05, shapes=SHAPES):
     edges = np.asarray(edges, np.int32).reshape(-1, 2)
     deg = np.bincount(edges.reshape(-1), minlength=n)
     w = np.array([1.0 / (1 + max(deg[a], deg[b])) for a, b in edges], np.float32)
-    return W.Workload(name, n, edges, w, SHAPES, rank, steps, sigma, 10, 77)
+    return W.Workload(name, n, edges, w, shapes, rank, steps, sigma, 10, 77)
 
 
 def _buffers(wl, X, Q, stream, lazy, odd):
@@ -48,6 +49,20 @@ def _same(a, b, wl, what):
 GRAPHS = {"ring": (4, [(0, 1), (1, 2), (2, 3), (3, 0)]),          # two (four) stacked columns everywhere
           "path": (4, [(1, 0), (1, 2), (3, 2)]),                  # one and two (two and four)
           "pair and a lone worker": (3, [(0, 1)])}
+STARS = {"three columns": (5, [(0, 1), (2, 0), (0, 3)]),          # a kernel compiled for four; worker 4 alone
+         "four columns": (5, [(0, 1), (2, 0), (0, 3), (4, 0)])}
+
+
+def _run_profiled(gb, rounds):
+    """gb.run(rounds), and what it launched: {kind: launches}.  The bytes booked are the run's."""
+    from paper_2008_01425_amd import binding as B
+    B.pg_profile_enable(gb.ctx, True)
+    gb.run(rounds)
+    rows = B.pg_profile_collect(gb.ctx)
+    B.pg_profile_enable(gb.ctx, False)
+    moved = B.pg_run_bytes(gb.ctx, rounds)
+    assert abs(sum(r["bytes"] for r in rows) - moved) <= 1e-9 * moved
+    return {r["name"]: r["launches"] for r in rows}
 
 
 @pytest.mark.parametrize("graph", GRAPHS)
@@ -55,15 +70,28 @@ GRAPHS = {"ring": (4, [(0, 1), (1, 2), (2, 3), (3, 0)]),          # two (four) s
 @pytest.mark.parametrize("rank", [1, 2])
 @pytest.mark.parametrize("odd", [0, 1])
 def test_a_run_that_writes_every_second_round_equals_the_plain_run(graph, rounds, rank, odd):
-    n, edges = GRAPHS[graph]
-    wl = _workload(f"lazy {graph} {rounds} r{rank}", n, edges, rank, 1)
+    _run_both(f"lazy {graph} {rounds} r{rank}", *GRAPHS[graph], rounds, rank, odd)
+
+
+@pytest.mark.parametrize("graph", STARS)
+@pytest.mark.parametrize("rounds", [2, 5])
+@pytest.mark.parametrize("odd", [0, 1])
+def test_a_run_that_writes_every_second_round_with_three_and_four_neighbours(graph, rounds, odd):
+    _run_both(f"lazy star {graph} {rounds}", *STARS[graph], rounds, 1, odd)
+
+
+def _run_both(name, n, edges, rounds, rank, odd):
+    wl = _workload(name, n, edges, rank, 1, shapes=TALL)
     X, Q = wl.all_params(), wl.all_q()
     for l in (1, 6):                                   # two neighbours agree: their columns are dropped
         X[1][l] = X[0][l].copy()
     plain, lazy = _buffers(wl, X, Q, 0, 0, odd), _buffers(wl, X, Q, 1, 1, odd)
     for _ in range(2):                                 # the second call starts on what the first left
-        plain.run(rounds)
-        lazy.run(rounds)
+        did, did_lazily = _run_profiled(plain, rounds), _run_profiled(lazy, rounds)
+        # no silent comparison of the plain run with itself
+        assert "peek_sweep_p" not in did and did["update_sweep_p"] > 0
+        assert did_lazily["peek_sweep_p"] > 0 and did_lazily["peek_sweep_q"] > 0
+        assert ("update_sweep_p" in did_lazily) == (rounds > 2)
         _same(plain, lazy, wl, wl.name)
     plain.round()
     lazy.round()
