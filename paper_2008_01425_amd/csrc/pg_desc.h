@@ -71,8 +71,8 @@ struct PairDesc {
     int32_t lg;        // column-owner kernel: lanes side by side over columns (power of two <= 64)
     int32_t nblk;      // column-owner kernel: row blocks
     int32_t blk_rows;  // rows per block
-    int32_t V;         // floats per vector load on this layer: 4, 2 or 1 (largest that divides q; 4 also where
-                       // the wide row kernels run on padded rows and from kAnyAlignCols on in the narrow kernels)
+    int32_t V;         // floats per access to X: 4, 2 or 1.  The largest that divides q, or 4 where the planner
+                       // chose units of four: any rows from kAnyAlignCols on in the narrow kernels, padded rows in the wide ones
     int32_t wc;        // matrix-core row tiles: wavefronts side by side over the column steps (1, 2 or 4)
     int32_t ld;        // floats from one row of the layer to the next in a worker buffer (>= q)
 };
