@@ -10,7 +10,9 @@ average per-dispatch value of every collected counter.  --traffic: from one FETC
 WRITE_SIZE run of `bench.py --counters MiB`, the bytes per launch of every kernel kind that
 crossed the L2 -> fabric boundary, each counter scaled by what it reads for the plain device
 copies of known size at the end of that run; the `traffic <kind> <read> <written> <total>`
-lines are what bench.py reads back from profiles/.
+lines are what bench.py reads back from profiles/.  Give such a run an odd number of --steps: runs that
+write the parameters every second round end an even number with another kernel of the kind "update",
+and kernels of one kind are added up as the parts of one pass.
 """
 from __future__ import annotations
 
