@@ -178,8 +178,9 @@ int pg_round(pg_ctx *ctx, float *const *worker_params, float *q_state, void *wor
  * hipMalloc, hipFree or other allocating call: no table upload (the context must have been
  * through pg_upload, else PG_ERR_ARG), no timing events (pg_profile_enable is ignored).  A new
  * set of worker_params pointers is still copied to the device table (a synchronous copy).
- * A problem with pg_workspace_bytes > PG_STATIC_WORKSPACE_BYTES is refused with
- * PG_ERR_TOO_LARGE and nothing is launched.  All contexts and calls on one GPU share the one
+ * A problem whose single rounds need more than PG_STATIC_WORKSPACE_BYTES is refused with
+ * PG_ERR_TOO_LARGE and nothing is launched (pg_workspace_bytes is that need, but for sets of small layers, where it
+ * also holds a second copy of the parameters for pg_run).  All contexts and calls on one GPU share the one
  * array: calls that overlap on a GPU (different streams or threads) race; calls ordered on one
  * stream, or separated by a synchronisation, do not.  Phat and the flags of the round are not
  * reachable through pg_ws_*_offset for this call.  Other arguments and errors as pg_round.
@@ -234,7 +235,7 @@ int pg_iterate(pg_ctx *ctx, float *const *worker_params, float *q_state, float *
  * `rounds` consecutive gossip rounds with nothing touching the parameters in between
  * (the pure consensus iteration, Eq. (4)).  Same result as calling pg_round `rounds` times;
  * the update of round t and the first product of round t+1 share one pass over the
- * parameters.  A large parameter set (more than 320 MB over all workers) is written every second round
+ * parameters (sets of small layers: one launch a round).  A large parameter set (more than 320 MB over all workers) is written every second round
  * only, the last one always, if power_steps = 1, no worker stacks more than four columns (degree x rank),
  * most of the parameters lie in layers with q >= 32 (at four columns q % 32 == 0 or q >= 512), there are
  * fewer than 1024 (worker, layer with q = 1) pairs, and no layer is so tall and narrow that the Q-sweep
@@ -255,7 +256,8 @@ int pg_run(pg_ctx *ctx, float *const *worker_params, float *q_state, void *works
 typedef struct pg_kernel_time {
     char name[32];   /* "sweep_p", "orth_p", "sweep_q", "combine_q", "update", "update_sweep_p", "update_sgd",
                         "orth_v", "combine_p"; in runs that write the parameters every second round also
-                        "peek_sweep_p", "peek_sweep_q": sweeps that apply an update without storing it */
+                        "peek_sweep_p", "peek_sweep_q": sweeps that apply an update without storing it;
+                        sets of small layers: "edge", all a round does between two updates */
     int launches;    /* kernel launches of this kind */
     double ms;       /* summed duration */
     double bytes;    /* summed algorithmic bytes of parameter traffic (4 B per element read or written) */

@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpowergossip.so")
-SOURCES = ["pg_api.hip", "pg_plan.cpp"]
-DEPS = SOURCES + ["pg_kernels.hip", "pg_desc.h", "pg_plan.hpp", os.path.join("..", "..", "include", "powergossip.h")]
+SOURCES = ["pg_api.hip", "pg_edge.hip", "pg_plan.cpp"]
+DEPS = SOURCES + ["pg_kernels.hip", "pg_device.h", "pg_launch.h", "pg_desc.h", "pg_plan.hpp",
+                  os.path.join("..", "..", "include", "powergossip.h")]
 
 
 def up_to_date() -> bool:
@@ -23,14 +25,20 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if not force and up_to_date():
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           # packed fp32 instructions are kept out of the generated code
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wall", "-Wno-unused-result",
-           "-x", "hip"] + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+             # packed fp32 instructions are kept out of the generated code
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-Wall", "-Wno-unused-result"]
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        cmds = [[hipcc] + flags + ["-x", "hip", "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
+        if verbose:
+            print("\n".join(" ".join(c) for c in cmds), flush=True)
+        procs = [subprocess.Popen(c) for c in cmds]
+        failed = [c for c, p in zip(cmds, procs) if p.wait() != 0]
+        if failed:
+            raise subprocess.CalledProcessError(1, failed[0])
+        subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-o", LIB] + objs, check=True)
     return LIB
 
 

@@ -10,6 +10,7 @@
 
 #include "../../include/powergossip.h"
 #include "pg_kernels.hip"
+#include "pg_launch.h"
 #include "pg_plan.hpp"
 
 using namespace pg;
@@ -28,10 +29,10 @@ constexpr int kMaxDevices = 64;
 void *g_scratch_ptr[kMaxDevices];  // per device: address of `scratch` there (null = not asked yet)
 
 enum Kind { K_SWEEP_P = 0, K_ORTH_P, K_SWEEP_Q, K_COMBINE_Q, K_UPDATE, K_UPDATE_SWEEP_P, K_UPDATE_SGD,
-            K_ORTH_V, K_COMBINE_P, K_PEEK_SWEEP_P, K_PEEK_SWEEP_Q, K_COUNT };
+            K_ORTH_V, K_COMBINE_P, K_PEEK_SWEEP_P, K_PEEK_SWEEP_Q, K_EDGE, K_COUNT };
 const char *const kKindName[K_COUNT] = {"sweep_p", "orth_p", "sweep_q", "combine_q", "update",
                                         "update_sweep_p", "update_sgd", "orth_v", "combine_p",
-                                        "peek_sweep_p", "peek_sweep_q"};
+                                        "peek_sweep_p", "peek_sweep_q", "edge"};
 
 struct ProfRec {
     int kind;
@@ -53,6 +54,8 @@ struct pg_ctx {
     CombTile *d_comb = nullptr;
     OrthTile *d_orth = nullptr;
     int32_t *d_iso = nullptr;
+    EdgeTile *d_edge = nullptr;
+    ApplyTile *d_apply = nullptr;
     float **d_xs = nullptr;
     std::vector<float *> xs_cached;
     float **d_gs = nullptr;
@@ -125,6 +128,10 @@ int do_upload(pg_ctx *c) {
     if ((rc = upload_vec(&c->d_comb, P.comb_tiles))) return rc;
     if ((rc = upload_vec(&c->d_orth, P.orth_tiles))) return rc;
     if ((rc = upload_vec(&c->d_iso, P.isolated_pairs))) return rc;
+    if (P.edge) {
+        if ((rc = upload_vec(&c->d_edge, P.edge_tiles))) return rc;
+        if ((rc = upload_vec(&c->d_apply, P.apply_tiles))) return rc;
+    }
     PG_HIP(hipMalloc((void **)&c->d_xs, sizeof(float *) * (size_t)P.n));
     PG_HIP(hipMalloc((void **)&c->d_gs, sizeof(float *) * (size_t)P.n));
     void *unused = nullptr;
@@ -170,6 +177,7 @@ struct Launcher {
     double *pdb() const { return (double *)(ws + c->plan.ws_pd); }
     float *ph() const { return (float *)(ws + c->plan.ws_ph); }
     float *ph2() const { return (float *)(ws + c->plan.ws_pd); }  // runs only (r <= 8 there: scratch unused)
+    float *y() const { return (float *)(ws + c->plan.ws_y); }
     float *ph_out = nullptr;  // where orth_p leaves Phat, when not in ph()
     float *phw() const { return ph_out ? ph_out : ph(); }
     int32_t *flags() const { return (int32_t *)(ws + c->plan.ws_flag); }
@@ -477,6 +485,41 @@ struct Launcher {
         check();
         end();
     }
+    // Sets of small layers: what lies between two updates, one work-group per (edge, layer).
+    EdgeLaunch edge_launch(bool pending = false) const {
+        const Plan &P = c->plan;
+        return {P.edge_threads, P.max_layer_rank, pending ? P.edge_run_lds : P.edge_lds, (unsigned)P.edge_tiles.size(), st, c->d_edge, c->d_xs, flags()};
+    }
+    void edge_round(const float *qin, float *qout, float *phat) {
+        if (status) return;
+        begin(K_EDGE, 4.0 * c->plan.edge_elems);
+        launch_edge_round(edge_launch(), qin, qout, phat, c->plan.steps);
+        check();
+        end();
+    }
+    void edge_pending(bool from_y, const float *qin, float *qout, const float *before, float *phat) {
+        if (status) return;
+        begin(K_EDGE, 4.0 * (c->plan.edge_elems + c->plan.pass_elems));
+        launch_edge_pending(edge_launch(true), c->d_cols, y(), (int64_t)c->plan.param_floats, from_y, qin, qout, before, phat, c->plan.steps);
+        check();
+        end();
+    }
+    void edge_iterate(float *pstate, int iterations, bool odd) {
+        if (status) return;
+        begin(K_EDGE, 4.0 * c->plan.edge_elems);
+        launch_edge_iterate(edge_launch(), qstate, pstate, uq(), ph(), iterations, odd);
+        check();
+        end();
+    }
+    void apply(bool grad, const float *from = nullptr) {
+        if (status) return;
+        const Plan &P = c->plan;
+        begin(grad ? K_UPDATE_SGD : K_UPDATE, P.pass_elems * 4.0 * (grad ? 3.0 : 2.0));
+        launch_apply(P.apply_cols, (unsigned)P.apply_tiles.size(), st, c->d_apply, c->d_pairs, c->d_cols, c->d_xs, from,
+                     (int64_t)P.param_floats, right(), left(), grad ? (const float *const *)c->d_gs : nullptr, eta);
+        check();
+        end();
+    }
     void combine_q(float *hist = nullptr) {
         if (status || c->plan.comb_tiles.empty()) return;
         begin(K_COMBINE_Q, 0.0);
@@ -571,6 +614,20 @@ void run_lazy(Launcher &L, int rounds) {
     L.ph_out = nullptr;
 }
 
+// All rounds of a run on a set of small layers, one launch per round: from the second round on the edge
+// kernels apply the round before to the matrices as they load them and store the result to the other of two buffers, the
+// workers' own and one in the workspace (other work-groups still read the first).  Phat and the state alternate as well;
+// the last round leaves them in their places.
+void run_edge(Launcher &L, int rounds) {
+    float *const ph[2] = {L.ph(), (float *)(L.ws + L.c->plan.ws_ph2)}, *const q[2] = {L.qstate, L.uq()};
+    for (int t = 1; t <= rounds; ++t) {
+        const int now = (rounds - t) & 1, before = now ^ 1;
+        if (t == 1) L.edge_round(L.qstate, q[now], ph[now]);
+        else L.edge_pending((t & 1) != 0, q[before], q[now], ph[before], ph[now]);
+    }
+    L.apply(false, (rounds & 1) ? nullptr : L.y());
+}
+
 int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *workspace,
                void *hip_stream, int rounds, bool fuse, bool may_allocate = true) {
     hipStream_t st = (hipStream_t)hip_stream;
@@ -580,6 +637,17 @@ int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *wor
     Launcher L{c, st, q_state, (char *)workspace};
     L.quiet = !may_allocate;
     const int s = c->plan.steps;
+    if (c->plan.edge) {
+        if (fuse && c->plan.edge_run) {
+            run_edge(L, rounds);
+        } else {
+            for (int t = 0; t < rounds; ++t) {
+                L.edge_round(q_state, q_state, L.ph());
+                L.apply(false);
+            }
+        }
+        return L.status;
+    }
     // Several column groups per worker: the update takes one pass per group, so no single pass
     // sees the finished parameters together with all of a worker's columns; rounds run unfused.
     if (c->plan.max_groups > 1) fuse = false;
@@ -643,6 +711,12 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     if (const char *e = getenv("PG_WIDE_UNITS")) tune.wide_units = atoi(e) != 0;
     if (const char *e = getenv("PG_LIGHT")) tune.light = atoi(e) != 0;
     if (const char *e = getenv("PG_VEC_KERNELS")) tune.vec_kernels = std::min(2, std::max(0, atoi(e)));
+    // a setting of the streaming kernels keeps a small set on them
+    for (const char *name : {"PG_MFMA_ROWS", "PG_MFMA_COLS", "PG_LAZY", "PG_STREAM", "PG_ODD_ROWS", "PG_WIDE_UNITS", "PG_LIGHT",
+                             "PG_VEC_KERNELS", "PG_MFMA_ROW_COLS", "PG_ROW_TILE_BYTES", "PG_COL_TILE_BYTES"})
+        if (getenv(name)) tune.edge = 0;
+    if (const char *e = getenv("PG_EDGE")) tune.edge = atoi(e) != 0;
+    if (const char *e = getenv("PG_EDGE_THREADS")) tune.edge_threads = atoi(e);
     if (const char *e = getenv("PG_MFMA_ROW_COLS")) tune.mfma_row_cols = atoi(e) <= 8 ? 8 : 16;
     int rc;
     try {
@@ -678,6 +752,8 @@ int pg_destroy(pg_ctx *c) {
         (void)hipFree(c->d_xs);
         (void)hipFree(c->d_gs);
         (void)hipFree(c->d_iso);
+        (void)hipFree(c->d_edge);
+        (void)hipFree(c->d_apply);
     }
     delete c;
     return PG_OK;
@@ -746,7 +822,7 @@ int pg_round(pg_ctx *c, float *const *worker_params, float *q_state, void *works
 int pg_round_static(pg_ctx *c, float *const *worker_params, float *q_state, void *hip_stream) {
     if (!c) return PG_ERR_ARG;
     if (!c->uploaded) return PG_ERR_ARG;  // uploading allocates: pg_upload comes first
-    if (c->plan.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) return PG_ERR_TOO_LARGE;
+    if (c->plan.ws_static_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES) return PG_ERR_TOO_LARGE;
     void *ws = nullptr;
     int rc = static_scratch(&ws);
     if (rc) return rc;
@@ -765,7 +841,10 @@ int pg_round_sgd(pg_ctx *c, float *const *worker_params, const float *const *wor
     Launcher L{c, st, q_state, (char *)workspace};
     L.eta = (double)eta;
     const int s = c->plan.steps;
-    if (c->plan.n_edges > 0) {
+    if (c->plan.edge) {
+        L.edge_round(q_state, q_state, L.ph());
+        L.apply(true);
+    } else if (c->plan.n_edges > 0) {
         for (int step = 0; step < s; ++step) {
             L.rows(false, true);
             L.orth_p();
@@ -790,7 +869,14 @@ int pg_iterate(pg_ctx *c, float *const *worker_params, float *q_state, float *p_
     if (worker_grads && (rc = prepare_grads(c, worker_grads, st))) return rc;
     Launcher L{c, st, q_state, (char *)workspace};
     L.eta = (double)eta;
-    if (c->plan.n_edges > 0) {
+    if (c->plan.edge) {
+        L.edge_iterate(p_state, iterations, ((k_done + 1) & 1) != 0);
+        if ((k_done + iterations) & 1) {
+            L.rhs = L.uq();
+            L.lhs = p_state;
+        }
+        L.apply(worker_grads != nullptr);
+    } else if (c->plan.n_edges > 0) {
         for (int it = 1; it <= iterations; ++it) {
             if ((k_done + it) & 1) {
                 // odd: vhat = v / |v| in R^q, p = X_a vhat - X_b vhat, v <- p (in R^p)

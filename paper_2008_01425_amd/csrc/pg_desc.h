@@ -7,6 +7,12 @@
 #pragma once
 #include <stdint.h>
 
+#ifdef __HIPCC__
+#define PG_BOTH __host__ __device__
+#else
+#define PG_BOTH
+#endif
+
 namespace pg {
 
 constexpr int kMaxCols = 16;   // largest R = deg(i) * r_l one pass supports
@@ -109,6 +115,62 @@ struct OrthTile {
 constexpr int kOrthTallRows = 4096;   // layers taller than this are orthonormalised chunk by chunk
 constexpr int kCombPRows = 2048;      // rows per work-group of the p-side combine of single iterations
 constexpr int kOrthChunkRows = 1024;  // rows per chunk (one work-group of 256 threads)
+
+// Edge kernels (sets of small layers): one work-group holds the difference of the two workers' matrices of
+// one (edge, layer) in registers, kEdgeUnits units of four floats of one row per thread.
+constexpr int kEdgeThreads[] = {256, 512};  // work-group sizes; a set takes the smallest that its layers fit
+constexpr int kEdgeUnits = 9;
+constexpr int kEdgeMaxRank = 4;
+// Elements of a layer up to which they are taken.  Time of the streaming kernels over theirs, 60 drawn sets: largest layer 1400 to
+// 7200 elements 1.3-3.5, 8300 to 12700 1.2-2.0, above 14000 0.8-1.1 (a work-group is then longer at it than the launches it saves);
+// 100 x 100, ring of 8, ten rounds 138 -> 115 us, three layers of 64 x 32 and less, ring of 4, one round 20.0 -> 10.2 us.
+constexpr int kEdgeSize = 12800;
+constexpr int kEdgeLdsBytes = 152 * 1024;
+constexpr int kEdgeSumBytes = 72 * 1024;    // of that, column sums of the wavefronts
+constexpr int kApplyUnits = 4;  // units of four floats per thread of the update kernel that goes with them
+struct EdgeTile {
+    int32_t p, q, r, ld;
+    int32_t wa, wb;          // the edge's workers
+    int32_t tc_shift;        // log2 of the threads side by side over the units of a row
+    int32_t own;             // bit 0 (1): this work-group stores worker a's (b's) matrix when it applies a pending update
+    int32_t col_a, Ra, col_b, Rb;  // the two workers' stacked columns of this layer
+    int64_t x_off, q_off, ph_off, flag_off;
+};
+// Units of a thread whose column sums an edge kernel exchanges at once.
+PG_BOTH inline int edge_units_at_once(int tc_shift, int nt) {
+    const int groups = tc_shift <= 6 ? nt / 64 : nt >> tc_shift;  // wavefronts with the same columns
+    const int fit = kEdgeSumBytes / (groups * 32 << tc_shift);
+    return fit < 1 ? 1 : fit;
+}
+// LDS sections of an edge kernel's work-group, byte offsets: sums of the wavefronts; P [r][ps] in double (ps = p in whole
+// units of four); the right vectors [r][vs], zeros behind q; the threads' entries of the unit vectors; single iterations:
+// unit vectors in R^q and the vectors in R^p.  At first the operands of a pending update (R vectors of each side in all).
+struct EdgeLds {
+    int red, p, v, ph, u, pst, bytes;
+};
+PG_BOTH inline EdgeLds edge_lds(int p, int q, int r, int tc_shift, int nt, int R) {
+    const int vs = (q + 3) & ~3, ps = (p + 3) & ~3;
+    const int groups = tc_shift <= 6 ? nt / 64 : nt >> tc_shift;
+    int units = edge_units_at_once(tc_shift, nt), all = ((vs >> 2) + (1 << tc_shift) - 1) >> tc_shift;
+    if (units > all) units = all;
+    EdgeLds o;
+    o.red = 0;
+    int red = units * groups * 32 << tc_shift;
+    const int part = tc_shift > 6 ? r * (1 << (tc_shift - 6)) * ps * 8 : 0;  // row sums of the wavefronts of a row
+    if (red < part) red = part;
+    if (red < R * (vs + ps) * 4) red = R * (vs + ps) * 4;
+    o.p = red;
+    o.v = o.p + r * ps * 8;
+    o.ph = o.v + r * vs * 4;
+    o.u = o.ph + r * nt * 4;
+    o.pst = o.u + r * vs * 4;
+    o.bytes = o.pst + r * ps * 4;
+    return o;
+}
+// Update tile: units [first, first + kThreads * kApplyUnits) of one pair, counted row by row.
+struct ApplyTile {
+    int32_t pair, first;
+};
 
 // combine_q tile: 256 consecutive elements of the r*q block of one (edge, layer).
 struct CombTile {

@@ -1,0 +1,26 @@
+// Host functions that launch the kernels of the other translation units.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "pg_desc.h"
+
+namespace pg {
+
+// What every launch of an edge kernel takes.
+struct EdgeLaunch {
+    int threads, rank, lds;   // work-group size (one of kEdgeThreads), largest layer rank, LDS bytes
+    unsigned tiles;
+    hipStream_t stream;
+    const EdgeTile *d_tiles;
+    float *const *d_xs;
+    int32_t *d_flags;
+};
+void launch_edge_round(const EdgeLaunch &l, const float *qin, float *qout, float *phat, int steps);
+void launch_edge_pending(const EdgeLaunch &l, const ColDesc *cols, float *y, int64_t stride, bool from_y, const float *qin, float *qout,
+                         const float *before, float *phat, int steps);
+void launch_edge_iterate(const EdgeLaunch &l, float *q, float *pstate, float *uq, float *phat, int iterations, bool odd);
+// y: where the matrices are read (null: in place); gs: gradients (null: none)
+void launch_apply(int cols_compiled, unsigned ntiles, hipStream_t stream, const ApplyTile *tiles, const PairDesc *pairs, const ColDesc *cols,
+                  float *const *xs, const float *y, int64_t stride, const float *right, const float *left, const float *const *gs, double eta);
+
+}  // namespace pg

@@ -79,6 +79,16 @@ bool gains_wide_units(const LayerInfo &L, int rc, const Plan &P) {
     return L.q % 2 != 0 || !P.light || (rc < kMaxCols && L.q >= 512);
 }
 
+// Whether a layer fits the edge kernels with `nt` threads, and then the threads side by side over a row's units
+// (log2): as many as the rows leave, no more than a row has units.
+static bool edge_split(const LayerInfo &L, int nt, int &tc_shift) {
+    if (L.r > kEdgeMaxRank || L.p > nt) return false;
+    const int nv = (L.q + 3) / 4;
+    tc_shift = 0;
+    while ((int64_t)L.p << (tc_shift + 1) <= nt && (1 << tc_shift) < nv) ++tc_shift;
+    return (nv + (1 << tc_shift) - 1) >> tc_shift <= kEdgeUnits && edge_lds(L.p, L.q, L.r, tc_shift, nt, 0).bytes <= kEdgeLdsBytes;
+}
+
 int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune) {
@@ -587,6 +597,57 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             cc.max_rows = std::max(cc.max_rows, g.blk_rows);
         }
     }
+    // ---- sets of small layers: edge kernels ----
+    P.ws_static_bytes = P.ws_bytes;
+    P.edge_tiles.clear();
+    P.apply_tiles.clear();
+    P.edge_elems = 0;
+    P.edge = tune.edge != 0 && n_edges > 0 && P.max_groups == 1;
+    for (const LayerInfo &L : P.layers) P.edge = P.edge && (tune.edge > 0 || (int64_t)L.p * L.q <= kEdgeSize);
+    std::vector<int> shift(n_layers);
+    bool fits = false;
+    for (int nt : kEdgeThreads) {
+        P.edge_threads = nt;
+        fits = nt >= tune.edge_threads;
+        for (int l = 0; l < n_layers && fits; ++l) fits = edge_split(P.layers[l], nt, shift[l]);
+        if (fits) break;
+    }
+    P.edge = P.edge && fits;
+    if (P.edge) {
+        std::vector<int> order(n_layers);
+        for (int l = 0; l < n_layers; ++l) order[l] = l;
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+            return (int64_t)P.layers[a].p * P.layers[a].q > (int64_t)P.layers[b].p * P.layers[b].q;
+        });
+        for (int l : order) {
+            const LayerInfo &L = P.layers[l];
+            P.edge_lds = std::max(P.edge_lds, edge_lds(L.p, L.q, L.r, shift[l], P.edge_threads, 0).bytes);
+            P.edge_run_lds = std::max(P.edge_run_lds, edge_lds(L.p, L.q, L.r, shift[l], P.edge_threads, 2 * (int)max_deg * L.r).bytes);
+            for (int e = 0; e < n_edges; ++e) {
+                const int a = P.edges[2 * e], b = P.edges[2 * e + 1];
+                const size_t id = (size_t)e * n_layers + l;
+                const PairDesc &pa = P.pairs[P.pair_first[(size_t)l * n_workers + a]], &pb = P.pairs[P.pair_first[(size_t)l * n_workers + b]];
+                const int own = (P.incident[a][0] == e ? 1 : 0) | (P.incident[b][0] == e ? 2 : 0);
+                P.edge_tiles.push_back({L.p, L.q, L.r, L.ld, a, b, shift[l], own, pa.col0, pa.R, pb.col0, pb.R,
+                                        L.x_off, P.q_off[id], P.ph_off[id], P.flag_off[id]});
+                P.edge_elems += 2.0 * L.p * L.q;
+            }
+            for (int i = 0; i < n_workers; ++i) {
+                const int pair = P.pair_first[(size_t)l * n_workers + i];
+                if (P.pairs[pair].R == 0) continue;
+                P.apply_cols = std::max(P.apply_cols, compiled_cols(P.pairs[pair].R));
+                const int units = L.p * ((L.q + 3) / 4);
+                for (int u = 0; u < units; u += kThreads * kApplyUnits) P.apply_tiles.push_back({pair, u});
+            }
+        }
+        P.edge_run = P.edge_run_lds <= kEdgeLdsBytes;
+        if (P.edge_run) {
+            P.ws_y = P.ws_bytes;
+            P.ws_ph2 = (size_t)round_up(P.ws_y + (size_t)n_workers * P.param_floats * 4, 256);
+            P.ws_bytes = (size_t)round_up(P.ws_ph2 + P.pstate_floats * 4, 256);
+        }
+    }
+
     // Runs that write every second round: narrow kernels only, one power step, one column group, and the
     // second Phat buffer lies in the column-by-column Gram-Schmidt's scratch.
     P.lazy = P.lazy && !P.light && P.steps == 1 && P.max_groups == 1 && P.ws_ph - P.ws_pd >= P.pstate_floats * sizeof(float);

@@ -59,6 +59,8 @@ struct Tuning {
     bool long_blocks = false;         // with those: row blocks of the Q-sweep as long as the dividing width asks for
     int stream = -1;                  // non-temporal passes: -1 by size and row length, 0 never, 1 always
     int lazy = -1;                    // runs that write every second round: the same, where the kernels can
+    int edge = -1;                    // edge kernels (small layers): -1 by rule, 0 never, 1 where they can
+    int edge_threads = 0;             // ... in work-groups of at least this many threads
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
                                       // 0 never, 1 where there are many of them, 2 always
 };
@@ -108,6 +110,19 @@ struct Plan {
     bool stream = false;
     // Runs write them every second round only.
     bool lazy = false;
+    // Every layer is small enough for the edge kernels, and the set for them to gain: one work-group per
+    // (edge, layer) takes the place of the two sweeps, the orthonormalisation and the combine.
+    bool edge = false;
+    int edge_threads = 0;                    // threads of their work-groups
+    int edge_lds = 0;                        // the most LDS one of them needs
+    bool edge_run = false;                   // runs apply a round's update in the next round's edge kernel ...
+    int edge_run_lds = 0;                    // ... if its operands fit as well
+    double edge_elems = 0;                   // elements they read
+    std::vector<EdgeTile> edge_tiles;        // largest layers first
+    std::vector<ApplyTile> apply_tiles;
+    int apply_cols = 1;                      // compiled stacked columns of the update kernel
+    size_t ws_y = 0, ws_ph2 = 0;             // runs: the second buffer of every worker's matrices, and of Phat
+    size_t ws_static_bytes = 0;              // workspace of a single round
     int max_layer_rank = 1;                  // largest r_l
     int max_rows = 1;                        // largest p_l
 };
