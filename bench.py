@@ -109,6 +109,11 @@ def kernel_table(B, gb, fn):
     return out
 
 
+def moved(table, rounds):
+    """Bytes of parameters per round that the launches in a kernel table were booked with."""
+    return sum(v["algorithmic_bytes_per_launch"] * v["launches"] for v in table.values()) / rounds
+
+
 def measure_other(name: str, rounds: int):
     """A named configuration beside the headline: ms per round through pg_run and pg_round
     (HIP events), per-kernel GB/s in both pipelines, bytes per parameter per round."""
@@ -128,7 +133,7 @@ def measure_other(name: str, rounds: int):
     k_fused = kernel_table(B, gb, lambda: gb.run(kp))
     k_unfused = kernel_table(B, gb, lambda: [gb.round() for _ in range(kp)])
     nparam = wl.n_workers * wl.params_per_worker
-    bf, bu = B.pg_run_bytes(gb.ctx, rounds) / rounds, B.pg_round_bytes(gb.ctx, False)
+    bf, bu = moved(k_fused, kp), moved(k_unfused, kp)
     traffic, src = traffic_from_profiles(name)
     slim = lambda tab: {k: {"avg_ms": v["avg_ms"], "GBps": v["GBps"], "frac_of_peak": v["frac_of_peak"],
                             "launches": v["launches"]} for k, v in tab.items()}
@@ -287,7 +292,7 @@ def main():
 
     nparam = wl.n_workers * wl.params_per_worker
     bytes_fused = B.pg_run_bytes(gb.ctx, K) / K
-    bytes_unfused = B.pg_round_bytes(gb.ctx, False)
+    bytes_unfused = moved(k_unfused, Kp)   # (edge sweeps read the parameters once for both products)
     result = {
         "metric": "gossip rounds/sec + achieved HBM GB/s (% of peak), fp32, 1 MI355X",
         "value": K / dt,

@@ -140,7 +140,9 @@ size_t pg_message_floats(const pg_ctx *ctx);
  * Algorithmic bytes of parameter traffic of one round: 4 * n * N * passes, N = sum p_l q_l,
  * passes = 2*power_steps + 2 for pg_round (each product reads every X once, the update reads
  * and writes it), 2*power_steps + 1 for a round in the middle of a pg_run that writes the parameters
- * every round (the update also feeds the next round's first product).  What a given pg_run moves in
+ * every round (the update also feeds the next round's first product).  These are the passes of the streaming kernels;
+ * rounds that take edge sweeps (both products in one read) or edge kernels move less, which the bytes of
+ * pg_profile_collect show.  What a given pg_run moves in
  * all, first and last round and runs that write every second round included, is pg_run_bytes.
  */
 double pg_round_bytes(const pg_ctx *ctx, int fused);
@@ -257,7 +259,8 @@ typedef struct pg_kernel_time {
     char name[32];   /* "sweep_p", "orth_p", "sweep_q", "combine_q", "update", "update_sweep_p", "update_sgd",
                         "orth_v", "combine_p"; in runs that write the parameters every second round also
                         "peek_sweep_p", "peek_sweep_q": sweeps that apply an update without storing it;
-                        sets of small layers: "edge", all a round does between two updates */
+                        sets of small layers: "edge", all a round does between two updates;
+                        edge sweeps: "edge_sweep", both products in one read, and "finish", the orthonormalisation of their results */
     int launches;    /* kernel launches of this kind */
     double ms;       /* summed duration */
     double bytes;    /* summed algorithmic bytes of parameter traffic (4 B per element read or written) */

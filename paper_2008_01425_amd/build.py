@@ -9,7 +9,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpowergossip.so")
-SOURCES = ["pg_api.hip", "pg_edge.hip", "pg_plan.cpp"]
+SOURCES = ["pg_api.hip", "pg_edge.hip", "pg_sweep.hip", "pg_plan.cpp"]
 DEPS = SOURCES + ["pg_kernels.hip", "pg_device.h", "pg_launch.h", "pg_desc.h", "pg_plan.hpp",
                   os.path.join("..", "..", "include", "powergossip.h")]
 

@@ -29,10 +29,10 @@ constexpr int kMaxDevices = 64;
 void *g_scratch_ptr[kMaxDevices];  // per device: address of `scratch` there (null = not asked yet)
 
 enum Kind { K_SWEEP_P = 0, K_ORTH_P, K_SWEEP_Q, K_COMBINE_Q, K_UPDATE, K_UPDATE_SWEEP_P, K_UPDATE_SGD,
-            K_ORTH_V, K_COMBINE_P, K_PEEK_SWEEP_P, K_PEEK_SWEEP_Q, K_EDGE, K_COUNT };
+            K_ORTH_V, K_COMBINE_P, K_PEEK_SWEEP_P, K_PEEK_SWEEP_Q, K_EDGE, K_EDGE_SWEEP, K_FINISH, K_COUNT };
 const char *const kKindName[K_COUNT] = {"sweep_p", "orth_p", "sweep_q", "combine_q", "update",
                                         "update_sweep_p", "update_sgd", "orth_v", "combine_p",
-                                        "peek_sweep_p", "peek_sweep_q", "edge"};
+                                        "peek_sweep_p", "peek_sweep_q", "edge", "edge_sweep", "finish"};
 
 struct ProfRec {
     int kind;
@@ -56,6 +56,9 @@ struct pg_ctx {
     int32_t *d_iso = nullptr;
     EdgeTile *d_edge = nullptr;
     ApplyTile *d_apply = nullptr;
+    SweepDesc *d_sweep_descs = nullptr;
+    SweepTile *d_sweep = nullptr;
+    FinishTile *d_finish = nullptr;
     float **d_xs = nullptr;
     std::vector<float *> xs_cached;
     float **d_gs = nullptr;
@@ -131,6 +134,11 @@ int do_upload(pg_ctx *c) {
     if (P.edge) {
         if ((rc = upload_vec(&c->d_edge, P.edge_tiles))) return rc;
         if ((rc = upload_vec(&c->d_apply, P.apply_tiles))) return rc;
+    }
+    if (P.sweep) {
+        if ((rc = upload_vec(&c->d_sweep_descs, P.sweep_descs))) return rc;
+        if ((rc = upload_vec(&c->d_sweep, P.sweep_tiles))) return rc;
+        if ((rc = upload_vec(&c->d_finish, P.finish_tiles))) return rc;
     }
     PG_HIP(hipMalloc((void **)&c->d_xs, sizeof(float *) * (size_t)P.n));
     PG_HIP(hipMalloc((void **)&c->d_gs, sizeof(float *) * (size_t)P.n));
@@ -520,6 +528,23 @@ struct Launcher {
         check();
         end();
     }
+    // Edge sweep: a whole power step, P to Q'.
+    void edge_sweep() {
+        if (status) return;
+        const Plan &P = c->plan;
+        const SweepLaunch l{P.sweep_threads, P.max_layer_rank, P.sweep_lds, (int)(P.sweep_tiles.size() / 8), c->reverse, st,
+                            c->d_sweep, c->d_sweep_descs, c->d_xs, qstate, pw(), ph(), flags()};
+        begin(K_EDGE_SWEEP, 4.0 * P.sweep_elems);  // workers' matrices, once: what edges share comes from the L2 caches
+        launch_sweep(l);
+        check();
+        end();
+        if (status) return;
+        begin(K_FINISH, 0.0);
+        launch_sweep_finish(l, c->d_finish, (unsigned)P.finish_tiles.size());
+        check();
+        end();
+        turn();
+    }
     void combine_q(float *hist = nullptr) {
         if (status || c->plan.comb_tiles.empty()) return;
         begin(K_COMBINE_Q, 0.0);
@@ -648,13 +673,21 @@ int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *wor
         }
         return L.status;
     }
+    const bool lazy = c->plan.lazy && fuse && rounds > 1;
+    if (c->plan.sweep && !lazy) {
+        for (int t = 0; t < rounds; ++t) {
+            for (int step = 0; step < s; ++step) L.edge_sweep();
+            L.rows(true, false);
+        }
+        return L.status;
+    }
     // Several column groups per worker: the update takes one pass per group, so no single pass
     // sees the finished parameters together with all of a worker's columns; rounds run unfused.
     if (c->plan.max_groups > 1) fuse = false;
     // Measured: with the passes that write (update + sweep) walking forwards and the Q-sweeps
     // backwards a run of fused rounds is 4 % faster than its mirror image, so a run starts forwards.
     if (fuse) c->reverse = 0;
-    if (c->plan.lazy && fuse && rounds > 1) {
+    if (lazy) {
         run_lazy(L, rounds);
         return L.status;
     }
@@ -714,7 +747,11 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     // a setting of the streaming kernels keeps a small set on them
     for (const char *name : {"PG_MFMA_ROWS", "PG_MFMA_COLS", "PG_LAZY", "PG_STREAM", "PG_ODD_ROWS", "PG_WIDE_UNITS", "PG_LIGHT",
                              "PG_VEC_KERNELS", "PG_MFMA_ROW_COLS", "PG_ROW_TILE_BYTES", "PG_COL_TILE_BYTES"})
-        if (getenv(name)) tune.edge = 0;
+        if (getenv(name)) tune.edge = tune.sweep = 0;
+    if (const char *e = getenv("PG_SWEEP")) tune.sweep = atoi(e) != 0;
+    if (const char *e = getenv("PG_SWEEP_TILE_BYTES")) tune.sweep_tile_bytes = std::max(1024, atoi(e));
+    if (const char *e = getenv("PG_SWEEP_THREADS")) tune.sweep_threads = atoi(e);
+    if (const char *e = getenv("PG_SWEEP_UNITS")) tune.sweep_units = atoi(e);
     if (const char *e = getenv("PG_EDGE")) tune.edge = atoi(e) != 0;
     if (const char *e = getenv("PG_EDGE_THREADS")) tune.edge_threads = atoi(e);
     if (const char *e = getenv("PG_MFMA_ROW_COLS")) tune.mfma_row_cols = atoi(e) <= 8 ? 8 : 16;
@@ -754,6 +791,9 @@ int pg_destroy(pg_ctx *c) {
         (void)hipFree(c->d_iso);
         (void)hipFree(c->d_edge);
         (void)hipFree(c->d_apply);
+        (void)hipFree(c->d_sweep_descs);
+        (void)hipFree(c->d_sweep);
+        (void)hipFree(c->d_finish);
     }
     delete c;
     return PG_OK;
@@ -844,6 +884,9 @@ int pg_round_sgd(pg_ctx *c, float *const *worker_params, const float *const *wor
     if (c->plan.edge) {
         L.edge_round(q_state, q_state, L.ph());
         L.apply(true);
+    } else if (c->plan.sweep) {
+        for (int step = 0; step < s; ++step) L.edge_sweep();
+        L.rows(true, false, /*grad=*/true);
     } else if (c->plan.n_edges > 0) {
         for (int step = 0; step < s; ++step) {
             L.rows(false, true);

@@ -172,6 +172,36 @@ struct ApplyTile {
     int32_t pair, first;
 };
 
+// Edge sweeps: one (edge, layer).
+constexpr int kSweepMaxRank = 4;
+constexpr int kSweepGram = 10;         // Gram sums per row block (rank 4)
+constexpr int kSweepVectorRows = 512;  // vectors up to this length are one wavefront's
+constexpr int kSweepExactSize = 10000; // elements up to which a layer is walked twice
+constexpr int kSweepExactRows = 2048;  // rows x rank of such a layer (its P lies in LDS)
+constexpr int64_t kSweepMixedBytes = 160ll << 20;  // parameter bytes (all workers) up to which mixed degrees alone decide
+constexpr int kSweepLongRows = 8;      // most rows of a tile whose rows are too long for the registers
+constexpr int kSweepLdsBytes = 152 * 1024;
+constexpr double kSweepSpreadBytes = 8.0 * (1 << 20);  // sets up to which a row block's edges are spread over the dies
+struct SweepDesc {
+    int32_t p, q, r, ld;
+    int32_t wa, wb;          // the edge's workers
+    int32_t tc_shift;        // log2 of the threads side by side over the units (four floats) of a row
+    int32_t units;           // units per thread, compiled: 1, 2, 3 or 5; 0: rows too long for the registers
+    int32_t nblk, flag_off;
+    int32_t exact, pad;      // one block, walked twice: the column sums are formed with Phat rounded to float
+    int64_t x_off, q_off, ph_off;
+    int64_t pe_off, qe_off, g_off; // double offsets of P [k][row], the blocks' D^T P [blk][k][c] and their Gram sums
+};
+// Rows [row0, row0 + nrows) of one (edge, layer), block blk; blk < 0: nrows vectors, (edge, layer)s el and the next.
+struct SweepTile {
+    int32_t el, row0, nrows, blk;
+};
+// Entries [first, first + count) of the p rows of P followed by the q entries of Q' of one (edge, layer).
+constexpr int kFinishEntries = 1024;
+struct FinishTile {
+    int32_t el, first, count;
+};
+
 // combine_q tile: 256 consecutive elements of the r*q block of one (edge, layer).
 struct CombTile {
     int32_t el, first;

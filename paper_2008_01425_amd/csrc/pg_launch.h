@@ -23,4 +23,19 @@ void launch_edge_iterate(const EdgeLaunch &l, float *q, float *pstate, float *uq
 void launch_apply(int cols_compiled, unsigned ntiles, hipStream_t stream, const ApplyTile *tiles, const PairDesc *pairs, const ColDesc *cols,
                   float *const *xs, const float *y, int64_t stride, const float *right, const float *left, const float *const *gs, double eta);
 
+// Edge sweeps.
+struct SweepLaunch {
+    int threads, rank, lds, nslots, reverse;
+    hipStream_t stream;
+    const SweepTile *tiles;
+    const SweepDesc *descs;
+    float *const *xs;
+    float *qstate;
+    double *part;
+    float *phat;
+    int32_t *flags;
+};
+void launch_sweep(const SweepLaunch &l);
+void launch_sweep_finish(const SweepLaunch &l, const FinishTile *tiles, unsigned ntiles);
+
 }  // namespace pg

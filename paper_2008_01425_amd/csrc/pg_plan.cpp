@@ -89,6 +89,54 @@ static bool edge_split(const LayerInfo &L, int nt, int &tc_shift) {
     return (nv + (1 << tc_shift) - 1) >> tc_shift <= kEdgeUnits && edge_lds(L.p, L.q, L.r, tc_shift, nt, 0).bytes <= kEdgeLdsBytes;
 }
 
+// Whether a set gains from edge sweeps.  They read the parameters once per power step where the streaming kernels read them twice, and
+// three launches make a round where those need five, and on a graph of mixed degrees five kinds of row and column kernels one after the other.
+// Against that stand their work per edge instead of per worker and, at higher ranks, column sums that leave few wavefronts per SIMD.
+// Time of the streaming kernels over that of the sweeps, 400 drawn sets of 0.1 to 950 MB, single rounds and SGD rounds:
+//   rank 1                            1.1-1.5, a few sets of three workers or few row blocks 0.75-1.0; VGG-16 on a ring of 16 1.10
+//   rank 2, q up to 900               1.1-1.6;  q above 900: 0.6-1.0 (VGG-16 0.90)
+//   rank 3 and 4, q up to 512         1.1-1.6;  q above 512: 0.3-1.1 (4 x 4 torus, 650 columns, 2.8 GB: 0.78)
+//   mixed degrees (trees, hubs)       rank 1 and 2 1.2-2.3, ranks 3 and 4 1.1-1.8; above 160 MB with long rows at rank 2 and more 0.66-1.1
+static bool gains_sweeps(const Plan &P, size_t max_deg, double total_bytes) {
+    size_t min_deg = max_deg;
+    for (const auto &inc : P.incident)
+        if (!inc.empty()) min_deg = std::min(min_deg, inc.size());
+    double heavy = 0.0;
+    for (const LayerInfo &L : P.layers)
+        if ((L.r >= 3 && L.q > 512) || (L.r == 2 && L.q > 900)) heavy += (double)L.p * L.q;
+    const bool mixed = min_deg < max_deg && total_bytes <= (double)kSweepMixedBytes;
+    return mixed || heavy <= 0.25 * P.elems_per_worker;
+}
+// Threads side by side over a row's units (log2) and units per thread of the edge sweeps: the split that covers the row with the
+// fewest idle units, of those the one with the most units per thread.  At rank 3 and 4 the sums of five units per
+// thread do not fit the registers.
+static bool sweep_split(const LayerInfo &L, int nt, int rank, int max_units, SweepDesc &d) {
+    const int nv = (L.q + 3) / 4;
+    int best = 0;
+    d.exact = (int64_t)L.p * L.q <= kSweepExactSize && (int64_t)L.p * L.r <= (L.q < 4 ? kSweepExactSize : kSweepExactRows);
+    for (int units : {1, 2, 3, 5}) {
+        if (units > 3 && (rank > 1 || max_units < 5)) break;
+        if (d.exact && units != 1 && units != 3) continue;
+        int sh = 0;
+        while ((units << sh) < nv) ++sh;
+        if ((1 << sh) > nt) continue;
+        if (best == 0 || units << sh <= best) {
+            best = units << sh;
+            d.tc_shift = sh;
+            d.units = units;
+        }
+    }
+    if (best == 0) d.tc_shift = d.units = d.exact = 0;
+    return best > 0;
+}
+// Rows a work-group takes per step (see sweep_tile).
+static int sweep_step_rows(const LayerInfo &L, int nt, int rank, const SweepDesc &d) {
+    if (L.q < 4) return nt;
+    if (d.units == 0) return 1;
+    const int m = d.exact ? (d.units == 1 ? 2 : 1) : d.units == 1 ? 4 : d.units == 5 || (d.units == 3 && rank > 2) ? 1 : 2;
+    return (nt >> d.tc_shift) * m;
+}
+
 int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune) {
@@ -645,6 +693,145 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             P.ws_y = P.ws_bytes;
             P.ws_ph2 = (size_t)round_up(P.ws_y + (size_t)n_workers * P.param_floats * 4, 256);
             P.ws_bytes = (size_t)round_up(P.ws_ph2 + P.pstate_floats * 4, 256);
+        }
+    }
+
+    // ---- edge sweeps ----
+    P.sweep = !P.edge && tune.sweep != 0 && n_edges > 0 && P.max_layer_rank <= kSweepMaxRank &&
+              (tune.sweep > 0 || gains_sweeps(P, max_deg, total_bytes));
+    std::vector<SweepDesc> geometry(n_layers);
+    if (P.sweep) {
+        // work-groups of 256, or of 512 where more than a quarter of the elements lie in rows that need those; the rows that do
+        // not fit either are walked twice
+        for (int nt : {512, 256}) {
+            double too_long = 0.0;
+            for (int l = 0; l < n_layers; ++l) {
+                if (!sweep_split(P.layers[l], nt, P.max_layer_rank, tune.sweep_units, geometry[l])) too_long += (double)P.layers[l].p * P.layers[l].q;
+                P.sweep = P.sweep && (int64_t)P.layers[l].p * P.layers[l].ld < ((int64_t)1 << 30);
+            }
+            if (nt == 256 && (tune.sweep_threads > nt || too_long > 0.25 * P.elems_per_worker)) break;
+            P.sweep_threads = nt;
+        }
+        for (int l = 0; l < n_layers; ++l) sweep_split(P.layers[l], P.sweep_threads, P.max_layer_rank, tune.sweep_units, geometry[l]);
+    }
+    if (P.sweep) {
+        // Row blocks: two work-groups per CU take the whole set where it is small enough, at most 1.5 MB each.  The blocks' column sums
+        // cost r / rows of the traffic and the time to add them up, so a block has 16 r rows, unless that leaves the chip idle.
+        // Few enough blocks that the workspace stays within the static one if it was.
+        const int nt = P.sweep_threads;
+        const double all = 8.0 * n_edges * P.elems_per_worker;
+        const size_t room = P.ws_pd - P.ws_pw, others = P.ws_bytes - room;
+        std::vector<int> blk_rows(n_layers), nblk(n_layers);
+        int64_t pe = 0, qe = 0, gr = 0;
+        int least = 16, max_cols = 1;
+        for (const LayerInfo &L : P.layers) max_cols = std::max(max_cols, L.q);
+        for (; least > 4; least /= 2) {
+            int64_t tiles = 0;
+            for (const LayerInfo &L : P.layers) tiles += (int64_t)n_edges * ((L.p + least * L.r - 1) / (least * L.r));
+            if (tiles >= 256) break;
+        }
+        for (double target = std::max(16.0 * 1024, std::min((double)tune.sweep_tile_bytes, all / 512));; target *= 1.25) {
+            pe = qe = gr = 0;
+            for (int l = 0; l < n_layers; ++l) {
+                const LayerInfo &L = P.layers[l];
+                const int step = sweep_step_rows(L, nt, P.max_layer_rank, geometry[l]);
+                int64_t rows_l = std::max<int64_t>((int64_t)(target / (8.0 * L.q)), least * L.r);
+                rows_l = std::max(rows_l, std::min<int64_t>(16 * L.r, (L.p + 15) / 16));
+                if (L.q >= 4 && geometry[l].units == 0) rows_l = std::min<int64_t>(kSweepLongRows, std::max<int64_t>(1, (int64_t)(target / (8.0 * L.q))));
+                if ((L.q == 1 && L.p <= kSweepVectorRows) || geometry[l].exact) rows_l = L.p;
+                rows_l = std::min<int64_t>(round_up(rows_l, step), L.p);
+                nblk[l] = (int)((L.p + rows_l - 1) / rows_l);
+                blk_rows[l] = nblk[l] == 1 ? L.p : (int)std::min<int64_t>(round_up((L.p + nblk[l] - 1) / nblk[l], step), L.p);
+                nblk[l] = (L.p + blk_rows[l] - 1) / blk_rows[l];
+                pe += (int64_t)n_edges * L.r * L.p;
+                qe += (int64_t)n_edges * nblk[l] * L.r * L.q;
+                gr += (int64_t)n_edges * nblk[l] * kSweepGram;
+            }
+            const size_t need = (size_t)(pe + qe + gr) * 8;
+            if (P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES || others + std::max(need, room) + 512 <= (size_t)PG_STATIC_WORKSPACE_BYTES) break;
+            if (target > 8.0 * P.max_rows * (double)max_cols) {  // no longer blocks to be had
+                P.sweep = false;
+                break;
+            }
+        }
+        if (P.sweep) {
+            if ((size_t)(pe + qe + gr) * 8 > room) sections(pwo, std::max(qwo, pe + qe + gr - pwo));
+            P.ws_static_bytes = P.ws_bytes;
+            P.sweep_descs.clear();
+            P.sweep_tiles.clear();
+            P.finish_tiles.clear();
+            P.sweep_elems = P.elems_per_worker * (double)std::count_if(P.incident.begin(), P.incident.end(), [](const std::vector<int> &e) { return !e.empty(); });
+            std::vector<std::vector<SweepTile>> die(8);
+            std::vector<double> load(8, 0.0);
+            int next_die = 0;
+            int64_t at_p = 0, at_q = pe, at_g = pe + qe;
+            auto vector = [&](int l) { return P.layers[l].q == 1 && P.layers[l].p <= kSweepVectorRows; };
+            auto add = [&](int l, int e) {
+                const LayerInfo &L = P.layers[l];
+                const int a = P.edges[2 * e], b = P.edges[2 * e + 1];
+                const size_t id = (size_t)e * n_layers + l;
+                SweepDesc d = geometry[l];
+                d.p = L.p;
+                d.q = L.q;
+                d.r = L.r;
+                d.ld = L.ld;
+                d.wa = a;
+                d.wb = b;
+                d.nblk = nblk[l];
+                d.flag_off = (int32_t)P.flag_off[id];
+                d.pad = 0;
+                d.x_off = L.x_off;
+                d.q_off = P.q_off[id];
+                d.ph_off = P.ph_off[id];
+                d.pe_off = at_p;
+                d.qe_off = at_q;
+                d.g_off = at_g;
+                at_p += (int64_t)L.r * L.p;
+                at_q += (int64_t)nblk[l] * L.r * L.q;
+                at_g += (int64_t)nblk[l] * kSweepGram;
+                const int el = (int)P.sweep_descs.size();
+                P.sweep_descs.push_back(d);
+                for (int f = 0; f < L.p + L.q; f += kFinishEntries) P.finish_tiles.push_back({el, f, kFinishEntries});
+                // LDS: see sweep_body
+                const int vs = 4 * d.units << d.tc_shift;
+                const int sums = nt * d.units * 32;
+                const int plain = L.r * vs * 4 + 2 * (nt / 64) * 4 * kSweepMaxRank * 8 + (d.exact && L.q >= 4 ? L.r * L.p * 8 : 0);
+                if (!vector(l)) {
+                    P.sweep_lds = std::max(P.sweep_lds, std::max(plain, sums));
+                }
+                return el;
+            };
+            for (int l = 0; l < n_layers; ++l) {
+                if (vector(l)) continue;
+                const int first = (int)P.sweep_descs.size();
+                for (int e = 0; e < n_edges; ++e) add(l, e);
+                for (int b = 0; b < nblk[l]; ++b) {
+                    const int row0 = b * blk_rows[l], nrows = std::min(blk_rows[l], P.layers[l].p - row0);
+                    const double bytes = 8.0 * nrows * P.layers[l].q;
+                    int to = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+                    for (int e = 0; e < n_edges; ++e) {
+                        if (!P.large && all <= kSweepSpreadBytes) to = next_die++ & 7;
+                        die[to].push_back({first + e, row0, nrows, b});
+                        load[to] += bytes;
+                    }
+                }
+            }
+            const int first_vector = (int)P.sweep_descs.size();
+            for (int l = 0; l < n_layers; ++l)
+                if (vector(l))
+                    for (int e = 0; e < n_edges; ++e) add(l, e);
+            const int waves = nt / 64, nvec = (int)P.sweep_descs.size() - first_vector;
+            for (int v = 0; v < nvec; v += waves) {
+                size_t to = 0;
+                for (size_t k = 1; k < 8; ++k)
+                    if (die[k].size() < die[to].size()) to = k;
+                die[to].push_back({first_vector + v, 0, std::min(waves, nvec - v), -1});
+            }
+            size_t slots = 0;
+            for (auto &v : die) slots = std::max(slots, v.size());
+            for (size_t s = 0; s < slots; ++s)
+                for (int k = 0; k < 8; ++k) P.sweep_tiles.push_back(s < die[k].size() ? die[k][s] : SweepTile{0, 0, 0, 0});
+            if (P.sweep_lds > kSweepLdsBytes) P.sweep = false;
         }
     }
 

@@ -59,6 +59,9 @@ struct Tuning {
     bool long_blocks = false;         // with those: row blocks of the Q-sweep as long as the dividing width asks for
     int stream = -1;                  // non-temporal passes: -1 by size and row length, 0 never, 1 always
     int lazy = -1;                    // runs that write every second round: the same, where the kernels can
+    int sweep = -1;                   // edge sweeps: -1 by rule, 0 never, 1 where they can
+    int sweep_tile_bytes = 1536 * 1024; // target bytes (both workers' rows) of their tiles
+    int sweep_threads = 256, sweep_units = 5;
     int edge = -1;                    // edge kernels (small layers): -1 by rule, 0 never, 1 where they can
     int edge_threads = 0;             // ... in work-groups of at least this many threads
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
@@ -123,6 +126,13 @@ struct Plan {
     int apply_cols = 1;                      // compiled stacked columns of the update kernel
     size_t ws_y = 0, ws_ph2 = 0;             // runs: the second buffer of every worker's matrices, and of Phat
     size_t ws_static_bytes = 0;              // workspace of a single round
+    // Edge sweeps: both products of a power step in one pass over the parameters.
+    bool sweep = false;
+    int sweep_threads = 0, sweep_lds = 0;
+    double sweep_elems = 0;                  // elements of the workers that have edges
+    std::vector<SweepDesc> sweep_descs;
+    std::vector<SweepTile> sweep_tiles;      // slots of eight, one tile per die
+    std::vector<FinishTile> finish_tiles;
     int max_layer_rank = 1;                  // largest r_l
     int max_rows = 1;                        // largest p_l
 };

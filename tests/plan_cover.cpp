@@ -154,6 +154,50 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
     REQUIRE(P.ws_qw >= P.ws_pw + (size_t)pw_need * 8, "P partial sums do not fit their section");
     REQUIRE(P.ws_pd >= P.ws_qw + (size_t)qw_need * 8, "Q partial sums do not fit their section");
     REQUIRE(P.ws_bytes >= P.ws_uq, "workspace size");
+    // ---- edge sweeps: the blocks of every (edge, layer) tile [0, p), each once; vectors once; entries of the results once; sums fit ----
+    if (P.sweep) {
+        std::map<int, std::vector<std::pair<int, int>>> scover, fcover;
+        REQUIRE(P.sweep_tiles.size() % 8 == 0, "slots of eight");
+        for (const SweepTile &t : P.sweep_tiles) {
+            if (t.nrows == 0) continue;
+            if (t.blk < 0) {
+                REQUIRE(t.nrows <= P.sweep_threads / 64, "%d vectors in a tile", t.nrows);
+                for (int k = 0; k < t.nrows; ++k) {
+                    REQUIRE(t.el + k < (int)P.sweep_descs.size() && P.sweep_descs[t.el + k].q == 1 && P.sweep_descs[t.el + k].nblk == 1, "vector %d", t.el + k);
+                    scover[t.el + k].push_back({0, P.sweep_descs[t.el + k].p});
+                }
+                continue;
+            }
+            const SweepDesc &d = P.sweep_descs[t.el];
+            REQUIRE(t.blk < d.nblk && t.nrows > 0, "block %d of %d", t.blk, d.nblk);
+            if (d.exact) REQUIRE(d.nblk == 1 && (d.q < 4 || d.units == 1 || d.units == 3), "exact layer: %d blocks, %d units", d.nblk, d.units);
+            if (d.q >= 4 && d.units == 0) REQUIRE(t.nrows <= kSweepLongRows, "%d long rows", t.nrows);
+            if (d.q >= 4 && d.units > 0) REQUIRE((4 * d.units << d.tc_shift) >= d.q && (1 << d.tc_shift) <= P.sweep_threads, "%d floats over %d x %d units", d.q, d.units, 1 << d.tc_shift);
+            scover[t.el].push_back({t.row0, t.row0 + t.nrows});
+        }
+        for (const FinishTile &t : P.finish_tiles) fcover[t.el].push_back({t.first, std::min(t.first + t.count, P.sweep_descs[t.el].p + P.sweep_descs[t.el].q)});
+        REQUIRE(P.sweep_descs.size() == (size_t)L * P.n_edges, "%zu (edge, layer)s", P.sweep_descs.size());
+        const int64_t room = (int64_t)(P.ws_pd - P.ws_pw) / 8;
+        for (int el = 0; el < (int)P.sweep_descs.size(); ++el) {
+            const SweepDesc &d = P.sweep_descs[el];
+            REQUIRE(tiles_exactly(scover[el], d.p), "rows of (edge, layer) %d", el);
+            REQUIRE(tiles_exactly(fcover[el], d.p + d.q), "entries of (edge, layer) %d", el);
+            REQUIRE(d.pe_off + (int64_t)d.r * d.p <= room && d.qe_off + (int64_t)d.nblk * d.r * d.q <= room &&
+                    d.g_off + (int64_t)d.nblk * kSweepGram <= room, "sums of (edge, layer) %d", el);
+        }
+        REQUIRE(P.sweep_lds <= kSweepLdsBytes, "%d bytes of LDS", P.sweep_lds);
+    }
+    if (P.edge) {
+        REQUIRE(P.edge_tiles.size() == (size_t)L * P.n_edges && P.edge_lds <= kEdgeLdsBytes, "edge tiles");
+        for (const EdgeTile &t : P.edge_tiles)
+            REQUIRE(((int64_t)t.p << t.tc_shift) <= P.edge_threads && (4 * kEdgeUnits << t.tc_shift) >= t.q, "%d x %d over %d threads", t.p, t.q, P.edge_threads);
+        std::map<int, std::vector<std::pair<int, int>>> acover;
+        for (const ApplyTile &t : P.apply_tiles) {
+            const int units = P.pairs[t.pair].p * ((P.pairs[t.pair].q + 3) / 4);
+            acover[t.pair].push_back({t.first, std::min(units, t.first + kThreads * kApplyUnits)});
+        }
+        for (auto &a : acover) REQUIRE(tiles_exactly(a.second, P.pairs[a.first].p * ((P.pairs[a.first].q + 3) / 4)), "units of pair %d", a.first);
+    }
     if (name[0] != 'r' || name[1] != 'a') printf("ok %s\n", name);  // the random problems stay quiet
     return 0;
 }
@@ -177,6 +221,10 @@ static int check_paths(const char *name, int n, const std::vector<int32_t> &e, c
 int main() {
     int bad = 0;
     std::vector<Tuning> tunings(4);
+    tunings[0].sweep = 1;
+    tunings[1].edge = 1;
+    tunings[3].edge = 0;
+    tunings[3].sweep = 1;
     tunings[1].mfma_rows = false;
     tunings[1].vec_kernels = 0;
     tunings[2].mfma_rows = false;

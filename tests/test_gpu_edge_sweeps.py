@@ -1,0 +1,85 @@
+"""Edge sweeps -- both products of a power step in one pass, edge by edge -- against the oracle: every split of
+rows over threads, one and many row blocks, short rows, vectors of every length class, dropped columns."""
+import numpy as np
+import pytest
+
+from oracle import pg_oracle as O
+from paper_2008_01425_amd import workloads as W
+from parity_util import TOL_1, TOL_10, compare_state, env_setting, oracle_problem, oracle_rounds
+
+pytestmark = pytest.mark.gpu
+
+# one thread to a whole work-group per row, one to five units per thread, every remainder of q modulo 4, fewer rows than a step
+# takes and several row blocks, rows of one to three floats, vectors for one wavefront and for many
+SHAPES = [(300, 576), (33, 130), (517, 259), (50, 4609), (40, 3000), (1030, 36), (9, 3), (4100, 2), (700, 1), (5000, 1), (1, 77),
+          (1, 1), (7, 8), (130, 1024), (20, 2306), (4, 4), (64, 17), (3, 640), (21, 12001)]
+WIDE = [(140, 7001), (30, 650), (90, 1), (9, 5121), (600, 5), (11, 25002)]     # rows that take work-groups of 512
+GRAPHS = {"ring": (5, [(0, 1), (1, 2), (2, 3), (3, 4), (4, 0)]),
+          "path and a lone worker": (4, [(1, 0), (1, 2)]),
+          "hub": (6, [(0, 1), (2, 0), (0, 3), (4, 0), (3, 5)])}
+
+
+def _workload(graph, shapes, rank, steps, seed=41):
+    n, edges = GRAPHS[graph]
+    edges = np.asarray(edges, np.int32)
+    deg = np.bincount(edges.reshape(-1), minlength=n)
+    w = np.array([1.0 / (1 + max(deg[a], deg[b])) for a, b in edges], np.float32)
+    return W.Workload(f"sweep {graph} {len(shapes)} r{rank}", n, edges, w, shapes, rank, steps, 0.05, 10, seed)
+
+
+def _buffers(wl, X, Q):
+    from paper_2008_01425_amd.device import GossipBuffers
+    with env_setting("PG_EDGE", 0), env_setting("PG_SWEEP", 1):
+        gb = GossipBuffers.from_workload(wl, fill=False)
+    gb.fill_from_arrays(X, Q)
+    return gb
+
+
+def _kinds(gb, call):
+    from paper_2008_01425_amd import binding as B
+    B.pg_profile_enable(gb.ctx, True)
+    call()
+    kinds = {r["name"]: r["launches"] for r in B.pg_profile_collect(gb.ctx)}
+    B.pg_profile_enable(gb.ctx, False)
+    return kinds
+
+
+@pytest.mark.parametrize("graph", GRAPHS)
+@pytest.mark.parametrize("rank,steps", [(1, 1), (2, 2), (3, 1), (4, 1)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_rounds_runs_and_gradients_against_the_oracle(graph, rank, steps, wide):
+    shapes = WIDE if wide else SHAPES
+    wl = _workload(graph, shapes, rank, steps)
+    layers = list(range(len(wl.shapes)))
+    prob = oracle_problem(wl)
+    X, Q = wl.all_params(), wl.all_q()
+    for l in (0, 1, 2):                               # two neighbours agree: their columns are dropped
+        X[1][l] = X[0][l].copy()
+    print(f"case {wl.name}", flush=True)
+    a, b, c, d = (_buffers(wl, X, Q) for _ in range(4))
+    kinds = _kinds(a, a.round)
+    assert kinds["edge_sweep"] == steps and kinds["finish"] == steps and "sweep_p" not in kinds, kinds
+    kinds = _kinds(b, lambda: b.run(3))
+    assert kinds["edge_sweep"] == 3 * steps, kinds
+    c.run(4)
+    rng = np.random.default_rng(5)
+    G = [[rng.standard_normal(s).astype(np.float32) for s in wl.shapes] for _ in range(wl.n_workers)]
+    d.alloc_grads()
+    for i in range(wl.n_workers):
+        for l in layers:
+            d.set_grad_layer(i, l, G[i][l])
+    d.round_sgd(0.05)
+    Xg, Qg = [[x.copy() for x in w] for w in X], [[q.copy() for q in e] for e in Q]
+    O.gossip_round(prob, Xg, Qg, G=G, eta=float(np.float32(0.05)))
+    compare_state(d, Xg, Qg, layers, TOL_1, what="sgd " + wl.name)
+    info, snaps = oracle_rounds(wl, X, Q, 4, layers, snap_at=(1, 3))
+    compare_state(a, snaps[1].X, snaps[1].Q, layers, TOL_1, what="round", phat=snaps[1].phat, flags=snaps[1].degenerate)
+    # (Phat is compared after one round: the column sums of a large layer are formed before it is rounded, and after a few
+    # rounds on 30 rows what is left of the difference reacts to that by more than the ten-round bar)
+    compare_state(b, snaps[3].X, snaps[3].Q, layers, TOL_10, what="run of 3", flags=snaps[3].degenerate)
+    compare_state(c, X, Q, layers, TOL_10, what="run of 4", flags=info.degenerate)
+    for _ in range(3):                                # a run is its rounds, bit for bit
+        a.round()
+    assert all(bool((x == y).all()) for x, y in zip(a.x, c.x)) and bool((a.q == c.q).all())
+    for gb in (a, b, c, d):
+        gb.close()
