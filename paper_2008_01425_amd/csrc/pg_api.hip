@@ -59,6 +59,7 @@ struct pg_ctx {
     SweepDesc *d_sweep_descs = nullptr;
     SweepTile *d_sweep = nullptr;
     FinishTile *d_finish = nullptr;
+    MixedTile *d_mixed = nullptr;
     float **d_xs = nullptr;
     std::vector<float *> xs_cached;
     float **d_gs = nullptr;
@@ -139,6 +140,7 @@ int do_upload(pg_ctx *c) {
         if ((rc = upload_vec(&c->d_sweep_descs, P.sweep_descs))) return rc;
         if ((rc = upload_vec(&c->d_sweep, P.sweep_tiles))) return rc;
         if ((rc = upload_vec(&c->d_finish, P.finish_tiles))) return rc;
+        if ((rc = upload_vec(&c->d_mixed, P.mixed_tiles))) return rc;
     }
     PG_HIP(hipMalloc((void **)&c->d_xs, sizeof(float *) * (size_t)P.n));
     PG_HIP(hipMalloc((void **)&c->d_gs, sizeof(float *) * (size_t)P.n));
@@ -545,6 +547,21 @@ struct Launcher {
         end();
         turn();
     }
+    // The update behind edge sweeps.
+    void sweep_update(bool grad) {
+        const Plan &P = c->plan;
+        if (status) return;
+        if (P.mixed_tiles.empty()) {
+            rows(true, false, grad);
+            return;
+        }
+        begin(grad ? K_UPDATE_SGD : K_UPDATE, P.pass_elems * 4.0 * (grad ? 3.0 : 2.0));
+        launch_apply_mixed((unsigned)P.mixed_tiles.size(), st, c->d_mixed, c->d_pairs, c->d_cols, c->d_xs, right(), left(),
+                           grad ? (const float *const *)c->d_gs : nullptr, eta);
+        check();
+        end();
+        turn();
+    }
     void combine_q(float *hist = nullptr) {
         if (status || c->plan.comb_tiles.empty()) return;
         begin(K_COMBINE_Q, 0.0);
@@ -677,7 +694,7 @@ int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *wor
     if (c->plan.sweep && !lazy) {
         for (int t = 0; t < rounds; ++t) {
             for (int step = 0; step < s; ++step) L.edge_sweep();
-            L.rows(true, false);
+            L.sweep_update(false);
         }
         return L.status;
     }
@@ -750,6 +767,7 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
         if (getenv(name)) tune.edge = tune.sweep = 0;
     if (const char *e = getenv("PG_SWEEP")) tune.sweep = atoi(e) != 0;
     if (const char *e = getenv("PG_SWEEP_TILE_BYTES")) tune.sweep_tile_bytes = std::max(1024, atoi(e));
+    if (const char *e = getenv("PG_MIXED")) tune.mixed = atoi(e) != 0;
     if (const char *e = getenv("PG_SWEEP_THREADS")) tune.sweep_threads = atoi(e);
     if (const char *e = getenv("PG_SWEEP_UNITS")) tune.sweep_units = atoi(e);
     if (const char *e = getenv("PG_EDGE")) tune.edge = atoi(e) != 0;
@@ -794,6 +812,7 @@ int pg_destroy(pg_ctx *c) {
         (void)hipFree(c->d_sweep_descs);
         (void)hipFree(c->d_sweep);
         (void)hipFree(c->d_finish);
+        (void)hipFree(c->d_mixed);
     }
     delete c;
     return PG_OK;
@@ -886,7 +905,7 @@ int pg_round_sgd(pg_ctx *c, float *const *worker_params, const float *const *wor
         L.apply(true);
     } else if (c->plan.sweep) {
         for (int step = 0; step < s; ++step) L.edge_sweep();
-        L.rows(true, false, /*grad=*/true);
+        L.sweep_update(/*grad=*/true);
     } else if (c->plan.n_edges > 0) {
         for (int step = 0; step < s; ++step) {
             L.rows(false, true);

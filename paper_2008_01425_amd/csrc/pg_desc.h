@@ -172,6 +172,14 @@ struct ApplyTile {
     int32_t pair, first;
 };
 
+// Tile of the update kernel for workers with different numbers of columns: rows [row0, row0 + nrows) and units (four columns)
+// [unit0, unit0 + nunits) of one pair, 2^tc_shift threads side by side over the units, kMixedRows rows per thread at a time.
+constexpr int kMixedRows = 4;
+constexpr int kMixedTileBytes = 32 * 1024, kMixedTiles = 1024;  // most parameter bytes of a tile, tiles to aim at
+struct MixedTile {
+    int32_t pair, row0, nrows, unit0, nunits, tc_shift;
+};
+
 // Edge sweeps: one (edge, layer).
 constexpr int kSweepMaxRank = 4;
 constexpr int kSweepGram = 10;         // Gram sums per row block (rank 4)

@@ -518,6 +518,86 @@ apply_kernel(const ApplyTile *__restrict__ tiles, const PairDesc *__restrict__ p
     }
 }
 
+// The update of sets whose workers stack different numbers of columns, in one launch: the row kernels are compiled per column count and
+// access width and would follow each other, each too small to fill the chip (eight layers of odd lengths, tree of 11, rank 3: six launches).
+// Bound by the fetches of
+// the vectors from the caches: a thread takes the same unit of four rows, so a right vector's unit is fetched once for the four; the columns
+// go by in fours, as many as the worker has.  Same operations in the same order as everywhere else.
+template <bool GRAD>
+__global__ void __launch_bounds__(kThreads)
+apply_mixed_kernel(const MixedTile *__restrict__ tiles, const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
+                   float *const *__restrict__ xs, const float *__restrict__ right, const float *__restrict__ left,
+                   const float *const *__restrict__ gs, double eta) {
+    constexpr int M = kMixedRows;
+    const MixedTile t = tiles[blockIdx.x];
+    const PairDesc pd = pairs[t.pair];
+    float *X = xs[pd.worker] + pd.x_off;
+    const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
+    const int q = pd.q, R = pd.R, u1 = t.unit0 + t.nunits, end = t.row0 + t.nrows;
+    const int TC = 1 << t.tc_shift, tc = threadIdx.x & (TC - 1), g = (int)threadIdx.x >> t.tc_shift, G = kThreads >> t.tc_shift;
+    auto fetch = [&](const float *at, int n, float (&x)[4]) {
+        if (n == 4) {
+            ld4(at, x);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[v] = ldg1(at + min(v, n - 1));
+        }
+    };
+    for (int row = t.row0 + g * M; row < end; row += G * M)
+        for (int u = t.unit0 + tc; u < u1; u += TC) {
+            const int c = 4 * u, n = min(4, q - c);
+            float x[M][4], gr[GRAD ? M : 1][4];
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int64_t at = (int64_t)min(row + m, end - 1) * pd.ld + c;
+                fetch(X + at, n, x[m]);
+                if (GRAD) fetch(Gp + at, n, gr[GRAD ? m : 0]);
+            }
+            double xd[M][4];
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) xd[m][v] = (double)x[m][v];
+            for (int k0 = 0; k0 < R; k0 += 4) {
+                float qv[4][4], ph[4][M];
+                double coef[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const ColDesc cd = cols[pd.col0 + min(k0 + k, R - 1)];
+                    coef[k] = k0 + k < R ? (double)cd.coef : 0.0;
+                    fetch(right + cd.q_off + c, n, qv[k]);
+#pragma unroll
+                    for (int m = 0; m < M; ++m) ph[k][m] = ldg1(left + cd.ph_off + min(row + m, end - 1));
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int m = 0; m < M; ++m) {
+                        const double cp = coef[k] * (double)ph[k][m];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) xd[m][v] = fma(-cp, (double)qv[k][v], xd[m][v]);
+                    }
+            }
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                if (row + m >= end) continue;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (GRAD) xd[m][v] = fma(-eta, (double)gr[GRAD ? m : 0][v], xd[m][v]);
+                    x[m][v] = (float)xd[m][v];
+                }
+                float *at = X + (int64_t)(row + m) * pd.ld + c;
+                if (n == 4) {
+                    *(PG_GLOBAL float4_any *)at = float4_any{x[m][0], x[m][1], x[m][2], x[m][3]};
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 3; ++v)
+                        if (v < n) *(PG_GLOBAL float *)(at + v) = x[m][v];
+                }
+            }
+        }
+}
+
 // ---- launches ----
 template <int NT, int RMAX>
 struct EdgeTag {
@@ -562,6 +642,12 @@ void launch_apply(int cols_compiled, unsigned ntiles, hipStream_t stream, const 
     else if (cols_compiled <= 8) PG_APPLY(8);
     else PG_APPLY(16);
 #undef PG_APPLY
+}
+
+void launch_apply_mixed(unsigned ntiles, hipStream_t stream, const MixedTile *tiles, const PairDesc *pairs, const ColDesc *cols,
+                        float *const *xs, const float *right, const float *left, const float *const *gs, double eta) {
+    if (gs) apply_mixed_kernel<true><<<dim3(ntiles), dim3(kThreads), 0, stream>>>(tiles, pairs, cols, xs, right, left, gs, eta);
+    else apply_mixed_kernel<false><<<dim3(ntiles), dim3(kThreads), 0, stream>>>(tiles, pairs, cols, xs, right, left, gs, eta);
 }
 
 }  // namespace pg

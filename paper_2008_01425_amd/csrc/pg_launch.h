@@ -23,6 +23,9 @@ void launch_edge_iterate(const EdgeLaunch &l, float *q, float *pstate, float *uq
 void launch_apply(int cols_compiled, unsigned ntiles, hipStream_t stream, const ApplyTile *tiles, const PairDesc *pairs, const ColDesc *cols,
                   float *const *xs, const float *y, int64_t stride, const float *right, const float *left, const float *const *gs, double eta);
 
+void launch_apply_mixed(unsigned ntiles, hipStream_t stream, const MixedTile *tiles, const PairDesc *pairs, const ColDesc *cols,
+                        float *const *xs, const float *right, const float *left, const float *const *gs, double eta);
+
 // Edge sweeps.
 struct SweepLaunch {
     int threads, rank, lds, nslots, reverse;

@@ -835,6 +835,36 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         }
     }
 
+    // ---- update of sets with several kinds of row kernels, in one launch ----
+    // Row launches over time of this one, whole calls (random trees of 3 to 21 workers, a torus and a ring with several layers):
+    //   rank 2 to 4, two or more kinds, up to 25 MB   1.1-2.5 (361 x 45, tree of 9: 32.8 -> 23.1 us; 50 x 5760, tree of 21, run of 5: 500 -> 251)
+    //   rank 2, 64 MB 1.04;  ragged layers of 131 MB, rank 3: 322 -> 292
+    //   rank 1                                        0.91-1.12: the row kernels' few columns suit them better
+    //   one kind of row kernel                        0.78-0.91
+    // Tiles: with 32 KB for every set 103 x 194 on a tree of 10 took 37 us against 31; about a thousand tiles mend that.  Long rows are
+    // cut as well: whole rows of 70001 columns left five work-groups per worker with all the work (780 us against 324).
+    P.mixed_tiles.clear();
+    if (P.sweep && P.max_groups == 1 && tune.mixed != 0 &&
+        (tune.mixed > 0 || (rank >= 2 && P.row_classes.size() > 1 && total_bytes <= (double)kSweepMixedBytes))) {
+        const double bytes = std::min((double)kMixedTileBytes, total_bytes / kMixedTiles);
+        for (int l = 0; l < n_layers; ++l) {
+            const LayerInfo &L = P.layers[l];
+            const int units = (L.q + 3) / 4, parts = (units + kThreads - 1) / kThreads, width = (units + parts - 1) / parts;
+            int sh = 0;
+            while ((1 << sh) < width) ++sh;
+            const int step = (kThreads >> sh) * kMixedRows;
+            const int steps = (int)std::max(1.0, bytes / ((double)step * width * 16));
+            const int64_t rows_t = std::min<int64_t>((int64_t)step * steps, L.p);
+            for (int i = 0; i < n_workers; ++i) {
+                const int pair = P.pair_first[(size_t)l * n_workers + i];
+                if (P.pairs[pair].R == 0) continue;
+                for (int64_t r0 = 0; r0 < L.p; r0 += rows_t)
+                    for (int u0 = 0; u0 < units; u0 += width)
+                        P.mixed_tiles.push_back({pair, (int32_t)r0, (int32_t)std::min<int64_t>(rows_t, L.p - r0), u0, std::min(width, units - u0), sh});
+            }
+        }
+    }
+
     // Runs that write every second round: narrow kernels only, one power step, one column group, and the
     // second Phat buffer lies in the column-by-column Gram-Schmidt's scratch.
     P.lazy = P.lazy && !P.light && P.steps == 1 && P.max_groups == 1 && P.ws_ph - P.ws_pd >= P.pstate_floats * sizeof(float);

@@ -62,6 +62,7 @@ struct Tuning {
     int sweep = -1;                   // edge sweeps: -1 by rule, 0 never, 1 where they can
     int sweep_tile_bytes = 1536 * 1024; // target bytes (both workers' rows) of their tiles
     int sweep_threads = 256, sweep_units = 5;
+    int mixed = -1;                   // one launch for the update of sets with different column counts: -1 by rule, 0 never, 1 always
     int edge = -1;                    // edge kernels (small layers): -1 by rule, 0 never, 1 where they can
     int edge_threads = 0;             // ... in work-groups of at least this many threads
     int vec_kernels = 1;              // vector layers in launches of their own (light-weight kernels):
@@ -133,6 +134,7 @@ struct Plan {
     std::vector<SweepDesc> sweep_descs;
     std::vector<SweepTile> sweep_tiles;      // slots of eight, one tile per die
     std::vector<FinishTile> finish_tiles;
+    std::vector<MixedTile> mixed_tiles;      // the update of such sets in one launch, where it pays (empty: the row kernels)
     int max_layer_rank = 1;                  // largest r_l
     int max_rows = 1;                        // largest p_l
 };

@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <algorithm>
 #include <map>
+#include <set>
 #include <vector>
 
 #include "../include/powergossip.h"
@@ -154,6 +155,20 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
     REQUIRE(P.ws_qw >= P.ws_pw + (size_t)pw_need * 8, "P partial sums do not fit their section");
     REQUIRE(P.ws_pd >= P.ws_qw + (size_t)qw_need * 8, "Q partial sums do not fit their section");
     REQUIRE(P.ws_bytes >= P.ws_uq, "workspace size");
+    // ---- one-launch update: every element of every pair with columns once ----
+    if (!P.mixed_tiles.empty()) {
+        std::vector<int64_t> covered(P.pairs.size(), 0);
+        std::vector<std::set<std::pair<int, int>>> corners(P.pairs.size());
+        for (const MixedTile &t : P.mixed_tiles) {
+            const PairDesc &pd = P.pairs[t.pair];
+            REQUIRE(t.nrows > 0 && t.nunits > 0 && t.row0 >= 0 && t.unit0 >= 0 && t.row0 + t.nrows <= pd.p && t.unit0 + t.nunits <= (pd.q + 3) / 4, "update tile of pair %d", t.pair);
+            REQUIRE(t.tc_shift >= 0 && (1 << t.tc_shift) <= kThreads, "%d threads on a row", 1 << t.tc_shift);
+            REQUIRE(corners[t.pair].insert({t.row0, t.unit0}).second, "update tile of pair %d twice", t.pair);
+            covered[t.pair] += (int64_t)t.nrows * t.nunits;
+        }
+        for (size_t i = 0; i < P.pairs.size(); ++i)
+            REQUIRE(covered[i] == (P.pairs[i].R ? (int64_t)P.pairs[i].p * ((P.pairs[i].q + 3) / 4) : 0), "update of pair %zu", i);
+    }
     // ---- edge sweeps: the blocks of every (edge, layer) tile [0, p), each once; vectors once; entries of the results once; sums fit ----
     if (P.sweep) {
         std::map<int, std::vector<std::pair<int, int>>> scover, fcover;
@@ -222,6 +237,7 @@ int main() {
     int bad = 0;
     std::vector<Tuning> tunings(4);
     tunings[0].sweep = 1;
+    tunings[0].mixed = 1;
     tunings[1].edge = 1;
     tunings[3].edge = 0;
     tunings[3].sweep = 1;

@@ -83,3 +83,33 @@ def test_rounds_runs_and_gradients_against_the_oracle(graph, rank, steps, wide):
     assert all(bool((x == y).all()) for x, y in zip(a.x, c.x)) and bool((a.q == c.q).all())
     for gb in (a, b, c, d):
         gb.close()
+
+
+@pytest.mark.parametrize("graph", GRAPHS)
+@pytest.mark.parametrize("rank", [1, 2, 4])
+@pytest.mark.parametrize("wide", [False, True])
+def test_update_in_one_launch_is_the_row_kernels_update(graph, rank, wide):
+    """Same operations in the same order: bit for bit, with and without gradients, on every length of row and remainder of four."""
+    wl = _workload(graph, WIDE if wide else SHAPES, rank, 1, seed=43)
+    X, Q = wl.all_params(), wl.all_q()
+    rng = np.random.default_rng(6)
+    G = [[rng.standard_normal(s).astype(np.float32) for s in wl.shapes] for _ in range(wl.n_workers)]
+    print(f"case {wl.name}", flush=True)
+    got, launches = [], []
+    for mixed in (0, 1):
+        with env_setting("PG_MIXED", mixed):
+            gb = _buffers(wl, X, Q)
+        gb.alloc_grads()
+        for i in range(wl.n_workers):
+            for l in range(len(wl.shapes)):
+                gb.set_grad_layer(i, l, G[i][l])
+        kinds = _kinds(gb, gb.round)
+        launches.append(kinds["update"])
+        gb.round_sgd(0.05)
+        gb.run(2)
+        got.append(gb)
+    assert launches[1] == 1 <= launches[0], launches
+    a, b = got
+    assert all(bool((x == y).all()) for x, y in zip(a.x, b.x)) and bool((a.q == b.q).all())
+    a.close()
+    b.close()
