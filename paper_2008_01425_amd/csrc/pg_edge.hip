@@ -499,7 +499,12 @@ apply_kernel(const ApplyTile *__restrict__ tiles, const PairDesc *__restrict__ p
             }
         }
 #pragma unroll
-        for (int j = 0; j < RC; ++j) ph[j] = ldg1(lc[j] + row);
+        for (int j = 0; j < RC; ++j) {  // (a column past the worker's counts nothing, also where the one read in its place has overflowed)
+            const float l = ldg1(lc[j] + row);
+            ph[j] = j < R ? l : 0.0f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) qv[j][v] = j < R ? qv[j][v] : 0.0f;
+        }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             double xd = (double)x[v];
@@ -570,13 +575,17 @@ apply_mixed_kernel(const MixedTile *__restrict__ tiles, const PairDesc *__restri
                     for (int m = 0; m < M; ++m) ph[k][m] = ldg1(left + cd.ph_off + min(row + m, end - 1));
                 }
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+                for (int k = 0; k < 4; ++k) {
+                    const bool on = k0 + k < R;  // (as above)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) qv[k][v] = on ? qv[k][v] : 0.0f;
 #pragma unroll
                     for (int m = 0; m < M; ++m) {
-                        const double cp = coef[k] * (double)ph[k][m];
+                        const double cp = coef[k] * (double)(on ? ph[k][m] : 0.0f);
 #pragma unroll
                         for (int v = 0; v < 4; ++v) xd[m][v] = fma(-cp, (double)qv[k][v], xd[m][v]);
                     }
+                }
             }
 #pragma unroll
             for (int m = 0; m < M; ++m) {

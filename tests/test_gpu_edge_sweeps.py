@@ -113,3 +113,24 @@ def test_update_in_one_launch_is_the_row_kernels_update(graph, rank, wide):
     assert all(bool((x == y).all()) for x, y in zip(a.x, b.x)) and bool((a.q == b.q).all())
     a.close()
     b.close()
+
+
+def test_overflow_stays_where_it_is():
+    """Columns that overflow a float (differences of 3e37, sums over 400 rows; P itself fits) reach the entries that the row kernels' update gives them, on workers with fewer columns too."""
+    from paper_2008_01425_amd.device import GossipBuffers
+    wl = _workload("hub", [(400, 5), (900, 4)], 1, 1, seed=47)
+    X, Q = wl.all_params(), wl.all_q()
+    X = [[np.full_like(x, -1.5e37 if i in (1, 2, 3, 4) else 1.5e37) for x in w] for i, w in enumerate(X)]
+    got = []
+    for edge, sweep, mixed in ((0, 0, 0), (0, 1, 0), (0, 1, 1), (1, 0, 0)):
+        print(f"edge {edge} sweep {sweep} mixed {mixed}", flush=True)
+        with env_setting("PG_EDGE", edge), env_setting("PG_SWEEP", sweep), env_setting("PG_MIXED", mixed):
+            gb = GossipBuffers.from_workload(wl, fill=False)
+        gb.fill_from_arrays(X, Q)
+        gb.round()
+        got.append([x.cpu().numpy().copy() for x in gb.x])
+        gb.close()
+    assert any(np.isinf(x).any() for x in got[0])
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            assert (np.isnan(x) == np.isnan(y)).all() and (np.isinf(x) == np.isinf(y)).all()
