@@ -209,6 +209,30 @@ __device__ __forceinline__ void sweep_body(const SweepTile &t, const SweepDesc &
                         for (int v = 0; v < 4; ++v) p[m * RM + j] = fma(D[m][k][v], (double)w[v], p[m * RM + j]);
                 }
             }
+            // An infinite parameter in a float that is not this thread's own met a zero: without that float.  (A test per step; a mask on
+            // every float would be two instructions more for each.)
+            bool nan = false;
+#pragma unroll
+            for (int i = 0; i < M * RM; ++i) nan = nan || p[i] != p[i];
+            if (nan && 4 * (tc + (K - 1) * TC) > last) {
+                int at = 4 * tc;
+                asm volatile("" : "+v"(at));  // (empty: keeps the masks from being formed, and held, ahead of the loop)
+#pragma unroll
+                for (int j = 0; j < RM; ++j) {
+                    if (j >= r) continue;
+#pragma unroll
+                    for (int m = 0; m < M; ++m) p[m * RM + j] = 0.0;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const VecT<4>::T w = *reinterpret_cast<const VecT<4>::T *>(sV + j * vs + at + 4 * k * TC);
+                        const int back = at + 4 * k * TC - last;  // floats of the unit that are not its own (none: 0 or less)
+#pragma unroll
+                        for (int m = 0; m < M; ++m)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) p[m * RM + j] = fma(v < back ? 0.0 : D[m][k][v], (double)w[v], p[m * RM + j]);
+                    }
+                }
+            }
             if (TC < 64) {
                 group_sum_all<M * RM>(p, TC);
             } else {

@@ -134,3 +134,35 @@ def test_overflow_stays_where_it_is():
     for other in got[1:]:
         for x, y in zip(got[0], other):
             assert (np.isnan(x) == np.isnan(y)).all() and (np.isinf(x) == np.isinf(y)).all()
+
+
+@pytest.mark.parametrize("rank", [1, 2, 3])
+@pytest.mark.parametrize("place", ["last", "inside the last unit", "first"])
+def test_an_infinite_parameter_spreads_as_it_does_with_the_row_kernels(rank, place):
+    """A unit that is moved back to the row's end, and threads past it, load floats that are others' own: an infinity there must not
+    turn the products into NaN and drop the columns.  Rows of every remainder of four, with and without idle units, walked once and twice."""
+    from paper_2008_01425_amd.device import GossipBuffers
+    shapes = [(100, 130), (300, 577), (64, 4610), (70, 1151), (2100, 5), (33, 131), (40, 17), (9, 7), (21, 12001), (5000, 3), (90, 128), (60, 4608),
+              (700, 1), (20, 642)]
+    wl = _workload("hub", shapes, rank, 1, seed=53)
+    X, Q = wl.all_params(), wl.all_q()
+    for l, (p, q) in enumerate(shapes):
+        X[1][l][p // 2, {"last": q - 1, "inside the last unit": max(0, q - 3), "first": 0}[place]] = np.inf if l % 2 else -np.inf
+    got = []
+    for sweep in (0, 1):
+        print(f"rank {rank} {place} sweep {sweep}", flush=True)
+        with env_setting("PG_EDGE", 0), env_setting("PG_SWEEP", sweep):
+            gb = GossipBuffers.from_workload(wl, fill=False)
+        gb.fill_from_arrays(X, Q)
+        gb.round()
+        got.append(gb)
+    a, b = got
+    for l in range(len(shapes)):
+        for e in range(wl.n_edges):
+            assert np.array_equal(a.get_flags(e, l), b.get_flags(e, l)), (shapes[l], "flags", e)
+            assert np.array_equal(np.isfinite(a.get_q(e, l)), np.isfinite(b.get_q(e, l))), (shapes[l], "state", e)
+        for i in range(wl.n_workers):
+            x, y = a.get_layer(i, l), b.get_layer(i, l)
+            assert np.array_equal(np.isnan(x), np.isnan(y)) and np.array_equal(np.isinf(x), np.isinf(y)), (shapes[l], "worker", i)
+    a.close()
+    b.close()
