@@ -701,8 +701,8 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
               (tune.sweep > 0 || gains_sweeps(P, max_deg, total_bytes));
     std::vector<SweepDesc> geometry(n_layers);
     if (P.sweep) {
-        // work-groups of 256, or of 512 where more than a quarter of the elements lie in rows that need those; the rows that do
-        // not fit either are walked twice
+        // work-groups of 256, or of 512 where more than a quarter of the elements lie in rows that need those; of the rows
+        // that do not fit either the finishing kernel forms the column sums
         for (int nt : {512, 256}) {
             double too_long = 0.0;
             for (int l = 0; l < n_layers; ++l) {
@@ -717,10 +717,11 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     if (P.sweep) {
         // Row blocks: two work-groups per CU take the whole set where it is small enough, at most 1.5 MB each.  The blocks' column sums
         // cost r / rows of the traffic and the time to add them up, so a block has 16 r rows, unless that leaves the chip idle.
-        // Few enough blocks that the workspace stays within the static one if it was.
         const int nt = P.sweep_threads;
+        P.sweep_elems = P.elems_per_worker * (double)std::count_if(P.incident.begin(), P.incident.end(), [](const std::vector<int> &e) { return !e.empty(); });
         const double all = 8.0 * n_edges * P.elems_per_worker;
         const size_t room = P.ws_pd - P.ws_pw, others = P.ws_bytes - room;
+        auto long_rows = [&](int l) { return P.layers[l].q >= 4 && geometry[l].units == 0; };  // leave no column sums
         std::vector<int> blk_rows(n_layers), nblk(n_layers);
         int64_t pe = 0, qe = 0, gr = 0;
         int least = 16, max_cols = 1;
@@ -730,6 +731,10 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             for (const LayerInfo &L : P.layers) tiles += (int64_t)n_edges * ((L.p + least * L.r - 1) / (least * L.r));
             if (tiles >= 256) break;
         }
+        // Most bytes of sums: what the static workspace leaves; where a set is beyond that anyway, a quarter of the parameters.
+        const size_t fixed = (size_t)PG_STATIC_WORKSPACE_BYTES - 512;
+        const size_t most = P.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES ? (others < fixed ? fixed - others : 0)
+                                                                            : std::max(room, (size_t)(P.sweep_elems));
         for (double target = std::max(16.0 * 1024, std::min((double)tune.sweep_tile_bytes, all / 512));; target *= 1.25) {
             pe = qe = gr = 0;
             for (int l = 0; l < n_layers; ++l) {
@@ -737,18 +742,18 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
                 const int step = sweep_step_rows(L, nt, P.max_layer_rank, geometry[l]);
                 int64_t rows_l = std::max<int64_t>((int64_t)(target / (8.0 * L.q)), least * L.r);
                 rows_l = std::max(rows_l, std::min<int64_t>(16 * L.r, (L.p + 15) / 16));
-                if (L.q >= 4 && geometry[l].units == 0) rows_l = std::min<int64_t>(kSweepLongRows, std::max<int64_t>(1, (int64_t)(target / (8.0 * L.q))));
+                if (long_rows(l)) rows_l = std::min<int64_t>(kSweepLongRows, std::max<int64_t>(1, (int64_t)(target / (8.0 * L.q))));
                 if ((L.q == 1 && L.p <= kSweepVectorRows) || geometry[l].exact) rows_l = L.p;
                 rows_l = std::min<int64_t>(round_up(rows_l, step), L.p);
                 nblk[l] = (int)((L.p + rows_l - 1) / rows_l);
                 blk_rows[l] = nblk[l] == 1 ? L.p : (int)std::min<int64_t>(round_up((L.p + nblk[l] - 1) / nblk[l], step), L.p);
                 nblk[l] = (L.p + blk_rows[l] - 1) / blk_rows[l];
                 pe += (int64_t)n_edges * L.r * L.p;
-                qe += (int64_t)n_edges * nblk[l] * L.r * L.q;
+                if (!long_rows(l)) qe += (int64_t)n_edges * nblk[l] * L.r * L.q;
                 gr += (int64_t)n_edges * nblk[l] * kSweepGram;
             }
             const size_t need = (size_t)(pe + qe + gr) * 8;
-            if (P.ws_bytes > (size_t)PG_STATIC_WORKSPACE_BYTES || others + std::max(need, room) + 512 <= (size_t)PG_STATIC_WORKSPACE_BYTES) break;
+            if (need <= most) break;
             if (target > 8.0 * P.max_rows * (double)max_cols) {  // no longer blocks to be had
                 P.sweep = false;
                 break;
@@ -760,7 +765,6 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             P.sweep_descs.clear();
             P.sweep_tiles.clear();
             P.finish_tiles.clear();
-            P.sweep_elems = P.elems_per_worker * (double)std::count_if(P.incident.begin(), P.incident.end(), [](const std::vector<int> &e) { return !e.empty(); });
             std::vector<std::vector<SweepTile>> die(8);
             std::vector<double> load(8, 0.0);
             int next_die = 0;
@@ -787,11 +791,12 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
                 d.qe_off = at_q;
                 d.g_off = at_g;
                 at_p += (int64_t)L.r * L.p;
-                at_q += (int64_t)nblk[l] * L.r * L.q;
+                if (!long_rows(l)) at_q += (int64_t)nblk[l] * L.r * L.q;
                 at_g += (int64_t)nblk[l] * kSweepGram;
                 const int el = (int)P.sweep_descs.size();
                 P.sweep_descs.push_back(d);
-                for (int f = 0; f < L.p + L.q; f += kFinishEntries) P.finish_tiles.push_back({el, f, kFinishEntries});
+                const int entries = long_rows(l) ? kThreads : kFinishEntries;
+                for (int f = 0; f < L.p + L.q; f += entries) P.finish_tiles.push_back({el, f, entries});
                 // LDS: see sweep_body
                 const int vs = 4 * d.units << d.tc_shift;
                 const int sums = nt * d.units * 32;
@@ -831,7 +836,14 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             for (auto &v : die) slots = std::max(slots, v.size());
             for (size_t s = 0; s < slots; ++s)
                 for (int k = 0; k < 8; ++k) P.sweep_tiles.push_back(s < die[k].size() ? die[k][s] : SweepTile{0, 0, 0, 0});
-            if (P.sweep_lds > kSweepLdsBytes) P.sweep = false;
+            P.sweep = P.sweep_lds <= kSweepLdsBytes;
+        }
+        if (!P.sweep) {  // as if there were none
+            sections(pwo, qwo);
+            P.ws_static_bytes = P.ws_bytes;
+            P.sweep_descs.clear();
+            P.sweep_tiles.clear();
+            P.finish_tiles.clear();
         }
     }
 

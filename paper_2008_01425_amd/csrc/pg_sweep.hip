@@ -478,7 +478,9 @@ __device__ __forceinline__ void sweep_vector(const SweepDesc &d, const float *Xa
     }
 }
 
-// Rows too long for the registers of a work-group: a few rows, walked once for P and, from the caches, once for their share of D^T P.
+// Rows too long for the registers of a work-group: P of a few rows.  Their share of D^T P is left to sweep_finish_kernel, which reads
+// the rows again: as sums of a block it would be r doubles written and read per column and block, and a workspace that grows with the parameters
+// (one matrix of 4096 x 70001, ring of 8, 9.2 GB: 9.2 GB of it).
 template <int NT, int RM>
 __device__ __forceinline__ void sweep_long_body(const SweepTile &t, const SweepDesc &d, const float *Xa, const float *Xb,
                                                 const float *__restrict__ qin, double *__restrict__ part) {
@@ -531,28 +533,6 @@ __device__ __forceinline__ void sweep_long_body(const SweepTile &t, const SweepD
         }
     }
     __syncthreads();
-    double *dst = part + d.qe_off + (int64_t)t.blk * r * q;
-    for (int u = tid; u < nv; u += NT) {
-        double acc[RM][4];
-#pragma unroll
-        for (int j = 0; j < RM; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[j][v] = 0.0;
-        for (int m = 0; m < t.nrows; ++m) {
-            double D[4];
-            diff(t.row0 + m, u, D);
-#pragma unroll
-            for (int j = 0; j < RM; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[j][v] = fma(D[v], sP[m][j], acc[j][v]);
-        }
-        const int c = min(4 * u, last), back = 4 * u - c;
-#pragma unroll
-        for (int j = 0; j < RM; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (j < r && v >= back) dst[(int64_t)j * q + c + v] = acc[j][v];
-    }
     if (tid == 0) {
 #pragma unroll
         for (int j = 0; j < RM; ++j)
@@ -605,11 +585,12 @@ sweep_kernel(const SweepTile *__restrict__ tiles, int nslots, int reverse, const
 
 // What is left of a power step per (edge, layer): the factor R of the Gram matrix, Phat = P R^-1 and Q' = (D^T P) R^-1 by forward
 // substitution, rounded to float; the column of a dropped Phat is zero and its Q column keeps its old state.  A tile is a run of
-// the p rows of P followed by the q entries of Q', all r columns; the sums over the blocks run in a fixed order.
+// the p rows of P followed by the q entries of Q', all r columns; the sums over the blocks run in a fixed order.  Of layers whose rows are too
+// long for the sweep's registers it forms D^T P itself, entry by entry over the rows.
 template <int RM>
 __global__ void __launch_bounds__(kThreads)
-sweep_finish_kernel(const FinishTile *__restrict__ tiles, const SweepDesc *__restrict__ descs, const double *__restrict__ part,
-                    float *__restrict__ qstate, float *__restrict__ phat, int32_t *__restrict__ flags) {
+sweep_finish_kernel(const FinishTile *__restrict__ tiles, const SweepDesc *__restrict__ descs, float *const *__restrict__ xs,
+                    const double *__restrict__ part, float *__restrict__ qstate, float *__restrict__ phat, int32_t *__restrict__ flags) {
     constexpr int NG = RM * (RM + 1) / 2;
     __shared__ double sG[NG];
     __shared__ double sR[RM][RM];
@@ -624,6 +605,25 @@ sweep_finish_kernel(const FinishTile *__restrict__ tiles, const SweepDesc *__res
 #pragma unroll
             for (int k = 0; k < RM; ++k)
                 if (k < r) v[k] = part[d.pe_off + (int64_t)k * d.p + i];
+        } else if (i < d.p + d.q && d.units == 0 && d.q >= 4) {
+            const float *Xa = xs[d.wa] + d.x_off + (i - d.p), *Xb = xs[d.wb] + d.x_off + (i - d.p);
+            constexpr int U = 8;  // rows in flight
+            for (int m = 0; m < d.p; m += U) {
+                float a[U], b[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t at = (int64_t)min(m + u, d.p - 1) * d.ld;
+                    a[u] = ldg1(Xa + at);
+                    b[u] = ldg1(Xb + at);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (m + u >= d.p) continue;
+#pragma unroll
+                    for (int k = 0; k < RM; ++k)
+                        if (k < r) v[k] = fma((double)a[u] - (double)b[u], part[d.pe_off + (int64_t)k * d.p + m + u], v[k]);
+                }
+            }
         } else if (i < d.p + d.q) {
             const double *src = part + d.qe_off + (i - d.p);
             const int64_t blk = (int64_t)r * d.q;
@@ -711,7 +711,7 @@ void launch_sweep(const SweepLaunch &l) {
     }
 }
 void launch_sweep_finish(const SweepLaunch &l, const FinishTile *tiles, unsigned ntiles) {
-#define PG_FINISH(RM) sweep_finish_kernel<RM><<<dim3(ntiles), dim3(kThreads), 0, l.stream>>>(tiles, l.descs, l.part, l.qstate, l.phat, l.flags)
+#define PG_FINISH(RM) sweep_finish_kernel<RM><<<dim3(ntiles), dim3(kThreads), 0, l.stream>>>(tiles, l.descs, l.xs, l.part, l.qstate, l.phat, l.flags)
     if (l.rank <= 1) PG_FINISH(1);
     else if (l.rank <= 2) PG_FINISH(2);
     else PG_FINISH(4);

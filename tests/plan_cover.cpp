@@ -155,6 +155,16 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
     REQUIRE(P.ws_qw >= P.ws_pw + (size_t)pw_need * 8, "P partial sums do not fit their section");
     REQUIRE(P.ws_pd >= P.ws_qw + (size_t)qw_need * 8, "Q partial sums do not fit their section");
     REQUIRE(P.ws_bytes >= P.ws_uq, "workspace size");
+    // ---- sweeps do not take a problem beyond the static workspace, and beyond that add at most a quarter of the parameters ----
+    {
+        Plan S;
+        Tuning plain = tune;
+        plain.edge = plain.sweep = 0;
+        build_plan(S, n, (int)ew.size(), e.data(), ew.data(), L, rows.data(), cols.data(), rank, steps, plain);
+        const size_t limit = S.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES ? (size_t)PG_STATIC_WORKSPACE_BYTES : S.ws_bytes + (size_t)(n * S.elems_per_worker);
+        REQUIRE(P.ws_static_bytes <= limit, "workspace %zu, %zu without sweeps, parameters %.0f", P.ws_static_bytes, S.ws_bytes, 4.0 * n * S.elems_per_worker);
+        if (!P.sweep && !P.edge) REQUIRE(P.ws_bytes == S.ws_bytes && P.sweep_tiles.empty() && P.finish_tiles.empty(), "workspace %zu, %zu without sweeps", P.ws_bytes, S.ws_bytes);
+    }
     // ---- one-launch update: every element of every pair with columns once ----
     if (!P.mixed_tiles.empty()) {
         std::vector<int64_t> covered(P.pairs.size(), 0);
@@ -197,7 +207,8 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
             const SweepDesc &d = P.sweep_descs[el];
             REQUIRE(tiles_exactly(scover[el], d.p), "rows of (edge, layer) %d", el);
             REQUIRE(tiles_exactly(fcover[el], d.p + d.q), "entries of (edge, layer) %d", el);
-            REQUIRE(d.pe_off + (int64_t)d.r * d.p <= room && d.qe_off + (int64_t)d.nblk * d.r * d.q <= room &&
+            const int64_t left = d.q >= 4 && d.units == 0 ? 0 : (int64_t)d.nblk * d.r * d.q;  // long rows leave no column sums
+            REQUIRE(d.pe_off + (int64_t)d.r * d.p <= room && d.qe_off + left <= room &&
                     d.g_off + (int64_t)d.nblk * kSweepGram <= room, "sums of (edge, layer) %d", el);
         }
         REQUIRE(P.sweep_lds <= kSweepLdsBytes, "%d bytes of LDS", P.sweep_lds);
@@ -323,6 +334,34 @@ int main() {
         char label[64];
         snprintf(label, sizeof(label), "random %d", trial);
         bad |= check(label, n, e, w, r, c, rnd(1, 16), rnd(1, 3), tunings[trial % tunings.size()]);
+        ++nrandom;
+    }
+    // the same on graphs up to complete ones of 24 workers, with long rows among the layers
+    for (int trial = 0; trial < 60 && !bad; ++trial) {
+        const int n = rnd(2, 24), kind = trial % 3;
+        std::vector<int32_t> e;
+        if (kind == 0)
+            for (int a = 0; a < n; ++a)
+                for (int b = a + 1; b < n; ++b) { e.push_back(a); e.push_back(b); }
+        else if (kind == 1 && n > 2)
+            ring(n, e);
+        else
+            for (int a = 1; a < n; ++a) { e.push_back((a - 1) / 3); e.push_back(a); }
+        std::vector<float> w(e.size() / 2, 1.0f / n);
+        std::vector<int32_t> r, c;
+        const int nl = rnd(1, 3);
+        for (int l = 0; l < nl; ++l) {
+            r.push_back(rnd(0, 2) ? rnd(1, 400) : rnd(1, 4096));
+            c.push_back(rnd(0, 2) ? rnd(4000, 80000) : rnd(1, 8000));
+        }
+        char label[64];
+        snprintf(label, sizeof(label), "random long rows %d", trial);
+        Tuning forced;
+        forced.edge = 0;
+        forced.sweep = 1;
+        const int rank = rnd(1, 4), steps = rnd(1, 2);
+        bad |= check(label, n, e, w, r, c, rank, steps, Tuning());
+        bad |= check(label, n, e, w, r, c, rank, steps, forced);
         ++nrandom;
     }
     std::vector<int32_t> r16, t4, t3;
