@@ -137,6 +137,80 @@ static int sweep_step_rows(const LayerInfo &L, int nt, int rank, const SweepDesc
     return (nt >> d.tc_shift) * m;
 }
 
+// Time of a power step, us, with the edge sweeps and with the streaming kernels, and what a run of the latter saves per round by its fused pass.
+// Least squares (of the logarithm) over 2200 drawn sets of 0.04 MB to 4 GB -- rings, trees, tori, stars, hypercubes, complete graphs and circulants of degree
+// up to 23, rows of 1 to 80000 floats, up to 4000 layers, 2 to 40 workers -- each called both ways: 80 % of the estimates lie within 20 % for the sweeps,
+// within 30 % for the streaming kernels.
+struct StepTimes {
+    double sweep, stream, fused;
+};
+static StepTimes step_times(const Plan &P) {
+    const int k = P.max_layer_rank <= 1 ? 0 : P.max_layer_rank <= 2 ? 1 : 2, nt = P.sweep_threads;
+    StepTimes T;
+    // The sweep: the work-groups of a die side by side on its 32 CUs (two of 256 threads each, one of 512), then the longest alone.  Work in units of
+    // four floats that one thread takes.
+    std::vector<double> load(8, 0.0);
+    double longest = 0.0, sums = 0.0, long_rows = 0.0;
+    int blocks = 0;
+    for (size_t i = 0; i < P.sweep_tiles.size(); ++i) {
+        const SweepTile &t = P.sweep_tiles[i];
+        if (t.nrows <= 0) continue;
+        double work = 8.0;
+        if (t.blk >= 0) {
+            const SweepDesc &d = P.sweep_descs[t.el];
+            const LayerInfo L{d.p, d.q, d.r, 0, 0, d.ld, 0};
+            const int rows = sweep_step_rows(L, nt, P.max_layer_rank, d);
+            const double units = d.q < 4 ? 1.0 : d.units ? (double)rows / (nt >> d.tc_shift) * d.units : d.q / (4.0 * nt);
+            work += (t.nrows + rows - 1) / rows * units * (d.exact ? 2 : 1);
+        }
+        load[i & 7] += work;
+        longest = std::max(longest, work);
+    }
+    for (const SweepDesc &d : P.sweep_descs) {
+        blocks = std::max(blocks, d.nblk);
+        if (d.q >= 4 && d.units == 0) long_rows += 8e-6 * d.p * d.q;
+        else sums += 16e-6 * d.nblk * d.r * d.q;
+    }
+    const double all = *std::max_element(load.begin(), load.end()) / (nt == 256 ? 64 : 32), wide = nt == 256 ? 1.0 : 1.36;
+    const double per_unit[] = {0.24, 0.38, 0.64}, alone[] = {0.14, 0.25, 0.49}, per_block[] = {0.11, 0.12, 0.26}, per_slot[] = {1.4, 1.4, 4.0};
+    T.sweep = 7.0 + wide * (per_unit[k] * all + alone[k] * longest) + per_slot[k] * (double)P.sweep_tiles.size() / 512 +  // sweep
+              per_block[k] * blocks + 0.6 * sums + 0.2 * long_rows;                                                       // finish, MB
+    // The streaming kernels: launches of every class, the longest tile of each, the partial sums, both reads.
+    int widest = 1, segments = 1, rblocks = 1;
+    double tiles = 0.0;
+    for (const RowClass &rc : P.row_classes) {
+        double most = 0.0;
+        for (const RowTile &t : rc.tiles) {
+            const PairDesc &pd = P.pairs[t.pair];
+            const double w = pd.q == 1 ? t.nrows / 64.0 : (double)t.nrows * std::min(pd.seg_len, pd.q) / (64.0 * pd.V);
+            most = std::max(most, rc.RC >= kWideCols && pd.q > 1 ? w / 4 : w);
+        }
+        tiles += most;
+        widest = std::max(widest, rc.RC);
+    }
+    for (const EdgeLayerDesc &d : P.els) {
+        segments = std::max(segments, d.nseg);
+        rblocks = std::max(rblocks, d.nblk);
+    }
+    const double read = (widest < kWideCols ? 0.16 : widest == kWideCols ? 0.12 : 0.15) * 4e-6 * P.pass_elems;
+    const size_t launches = P.row_classes.size() + P.col_classes.size();
+    T.stream = 6.3 + 4.4 * launches + 0.17 * tiles + 0.14 * segments + 0.27 * rblocks + 2.4e-6 * P.part_bytes + 2.0 * read;
+    T.fused = 4.4 * P.row_classes.size() + 0.4 * read;
+    return T;
+}
+// What the streaming kernels' time has to be of the sweeps'.  Of 1364 drawn sets that the rule above takes, 230 were slower with the sweeps in some call by
+// more than 4 % (single rounds, SGD rounds, runs of two and five), 150 by more than 10 %; of the 997 that these lines leave, 38 and 13.  Sets of
+// few workers, whose streaming passes are short, and of many edges per worker are overrated by the estimate.
+constexpr double kSweepGain = 0.95, kSweepGainFew = 1.2;
+static bool sweeps_are_faster(const Plan &P) {
+    const StepTimes T = step_times(P);
+    int workers = 0;
+    for (const auto &inc : P.incident) workers += !inc.empty();
+    const double need = workers <= 4 || P.n_edges >= 4 * workers ? kSweepGainFew : kSweepGain;
+    // (runs that write every second round stay with the streaming kernels)
+    return P.steps * T.stream - (P.lazy ? 0.0 : T.fused) >= need * P.steps * T.sweep;
+}
+
 int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const float *edge_w,
                int n_layers, const int32_t *rows, const int32_t *cols, int rank, int power_steps,
                const Tuning &tune) {
@@ -645,8 +719,15 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             cc.max_rows = std::max(cc.max_rows, g.blk_rows);
         }
     }
+    // Runs that write every second round: narrow kernels only, one power step, one column group, and the
+    // second Phat buffer lies in the column-by-column Gram-Schmidt's scratch.
+    P.lazy = P.lazy && !P.light && P.steps == 1 && P.max_groups == 1 && P.ws_ph - P.ws_pd >= P.pstate_floats * sizeof(float);
+    for (const RowClass &rc : P.row_classes) P.lazy = P.lazy && rc.RC <= kLazyCols && !rc.vec;
+    for (const ColClass &cc : P.col_classes)
+        P.lazy = P.lazy && cc.RC <= kLazyCols && !cc.vec && lazy_col_lds(cc.max_rows, cc.RC) <= (size_t)kLazyColLds;
     // ---- sets of small layers: edge kernels ----
     P.ws_static_bytes = P.ws_bytes;
+    P.part_bytes = 8.0 * (double)(pwo + qwo);
     P.edge_tiles.clear();
     P.apply_tiles.clear();
     P.edge_elems = 0;
@@ -836,7 +917,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             for (auto &v : die) slots = std::max(slots, v.size());
             for (size_t s = 0; s < slots; ++s)
                 for (int k = 0; k < 8; ++k) P.sweep_tiles.push_back(s < die[k].size() ? die[k][s] : SweepTile{0, 0, 0, 0});
-            P.sweep = P.sweep_lds <= kSweepLdsBytes;
+            P.sweep = P.sweep_lds <= kSweepLdsBytes && (tune.sweep > 0 || sweeps_are_faster(P));
         }
         if (!P.sweep) {  // as if there were none
             sections(pwo, qwo);
@@ -876,13 +957,6 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             }
         }
     }
-
-    // Runs that write every second round: narrow kernels only, one power step, one column group, and the
-    // second Phat buffer lies in the column-by-column Gram-Schmidt's scratch.
-    P.lazy = P.lazy && !P.light && P.steps == 1 && P.max_groups == 1 && P.ws_ph - P.ws_pd >= P.pstate_floats * sizeof(float);
-    for (const RowClass &rc : P.row_classes) P.lazy = P.lazy && rc.RC <= kLazyCols && !rc.vec;
-    for (const ColClass &cc : P.col_classes)
-        P.lazy = P.lazy && cc.RC <= kLazyCols && !cc.vec && lazy_col_lds(cc.max_rows, cc.RC) <= (size_t)kLazyColLds;
     return PG_OK;
 }
 

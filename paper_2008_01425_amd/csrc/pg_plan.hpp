@@ -90,6 +90,7 @@ struct Plan {
     std::vector<int> pair_first, pair_count; // [l * n + i]: that worker's groups in `pairs`
     std::vector<int> pair_group, pair_layer; // per pair: its group index and layer
     int max_groups = 1;                      // most column groups any (worker, layer) has
+    double part_bytes = 0;                   // the streaming kernels' partial sums
     double pass_elems = 0;                   // elements one sweep reads: sum of p * q over all pairs with edges
     std::vector<ColDesc> cols;
     std::vector<EdgeLayerDesc> els;          // [l * n_edges + e]

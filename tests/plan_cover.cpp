@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <map>
 #include <set>
+#include <string>
 #include <vector>
 
 #include "../include/powergossip.h"
@@ -428,6 +429,47 @@ int main() {
         REQUIRE(P.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES && P.odd_rows, "%zu bytes, units of four %d", P.ws_bytes, P.odd_rows);
         printf("as expected: %s\n", name);
     }
+    // which kernels a round takes
+    auto path = [&](const char *name, const std::vector<int32_t> &edges, int n, const std::vector<int32_t> &rows, const std::vector<int32_t> &cols,
+                    int rank, int steps, const char *want) {
+        Plan P;
+        std::vector<float> w(edges.size() / 2, 1.0f / n);
+        int rc = build_plan(P, n, (int)w.size(), edges.data(), w.data(), (int)rows.size(), rows.data(), cols.data(), rank, steps, Tuning());
+        REQUIRE(rc == PG_OK, "build_plan returned %d", rc);
+        const std::string got = P.edge ? (P.edge_run ? "edge, runs too" : "edge") : P.sweep ? (P.mixed_tiles.empty() ? "sweep" : "sweep, one update") : "stream";
+        REQUIRE(got == want, "%s", got.c_str());
+        printf("as expected: %s\n", name);
+        return 0;
+    };
+    std::vector<int32_t> r8, r3, t11, c16, c24;
+    ring(8, r8);
+    ring(3, r3);
+    for (int v = 1; v < 11; ++v) { t11.push_back((v - 1) / 3); t11.push_back(v); }
+    for (int a = 0; a < 24; ++a)
+        for (int b = a + 1; b < 24; ++b) {
+            c24.push_back(a); c24.push_back(b);
+            if (b < 16) { c16.push_back(a); c16.push_back(b); }
+        }
+    std::vector<int32_t> nr, nc;  // three convolutions of a small image model's three widths, with their biases
+    for (int k = 0; k < 19; ++k) {
+        const int ch = k < 7 ? 16 : k < 13 ? 32 : 64;
+        nr.insert(nr.end(), {ch, ch, ch});
+        nc.insert(nc.end(), {k == 0 ? 27 : 9 * ch, 1, 1});
+    }
+    bad |= path("vgg16 layers, rank 1", r16, 16, vr, vc, 1, 1, "sweep");
+    bad |= path("vgg16 layers, rank 2", r16, 16, vr, vc, 2, 1, "stream");
+    bad |= path("small convolutions, ring of 8", r8, 8, nr, nc, 1, 1, "sweep");
+    bad |= path("ragged layers, tree of 11", t11, 11, {510, 77, 1301, 2047, 33, 129, 5, 40001}, {1023, 4099, 333, 255, 1, 2, 70001, 7}, 3, 1, "sweep, one update");
+    // rows beyond the registers; a dense graph with much to read per edge, and with little; three workers
+    bad |= path("4096 x 70001", r8, 8, {4096}, {70001}, 1, 1, "stream");
+    bad |= path("8192 x 20000", r8, 8, {8192}, {20000}, 1, 1, "stream");
+    bad |= path("a head of 25088 columns", r16, 16, {4096, 4096, 1000}, {25088, 4096, 4096}, 1, 1, "stream");
+    bad |= path("complete graph of 16, 512 x 4608", c16, 16, {512, 512, 512}, {4608, 4608, 4608}, 1, 1, "stream");
+    bad |= path("complete graph of 16, 768 x 50257", c16, 16, {768}, {50257}, 1, 1, "stream");
+    bad |= path("complete graph of 24, 136 x 23931", c24, 24, {136}, {23931}, 1, 2, "stream");
+    bad |= path("complete graph of 24, 55 x 2532", c24, 24, {55}, {2532}, 1, 1, "stream");
+    bad |= path("three workers, 100 MB", r3, 3, {3208}, {2644}, 1, 2, "stream");
+    bad |= path("three workers, two layers", r3, 3, {2210, 40}, {950, 700}, 1, 2, "stream");
     // wide kernels: which floats per access the padded layers get
     auto widths = [&](const char *name, const std::vector<int32_t> &edges, int n, const std::vector<int32_t> &rows,
                       const std::vector<int32_t> &cols, int rank, int want) {
