@@ -140,8 +140,8 @@ int do_upload(pg_ctx *c) {
         if ((rc = upload_vec(&c->d_sweep_descs, P.sweep_descs))) return rc;
         if ((rc = upload_vec(&c->d_sweep, P.sweep_tiles))) return rc;
         if ((rc = upload_vec(&c->d_finish, P.finish_tiles))) return rc;
-        if ((rc = upload_vec(&c->d_mixed, P.mixed_tiles))) return rc;
     }
+    if (!P.mixed_tiles.empty() && (rc = upload_vec(&c->d_mixed, P.mixed_tiles))) return rc;
     PG_HIP(hipMalloc((void **)&c->d_xs, sizeof(float *) * (size_t)P.n));
     PG_HIP(hipMalloc((void **)&c->d_gs, sizeof(float *) * (size_t)P.n));
     void *unused = nullptr;
@@ -524,9 +524,14 @@ struct Launcher {
     void apply(bool grad, const float *from = nullptr) {
         if (status) return;
         const Plan &P = c->plan;
+        const float *const *gs = grad ? (const float *const *)c->d_gs : nullptr;
         begin(grad ? K_UPDATE_SGD : K_UPDATE, P.pass_elems * 4.0 * (grad ? 3.0 : 2.0));
-        launch_apply(P.apply_cols, (unsigned)P.apply_tiles.size(), st, c->d_apply, c->d_pairs, c->d_cols, c->d_xs, from,
-                     (int64_t)P.param_floats, right(), left(), grad ? (const float *const *)c->d_gs : nullptr, eta);
+        if (!P.mixed_tiles.empty())
+            launch_apply_mixed((unsigned)P.mixed_tiles.size(), st, c->d_mixed, c->d_pairs, c->d_cols, c->d_xs, from,
+                               (int64_t)P.param_floats, right(), left(), gs, eta);
+        else
+            launch_apply(P.apply_cols, (unsigned)P.apply_tiles.size(), st, c->d_apply, c->d_pairs, c->d_cols, c->d_xs, from,
+                         (int64_t)P.param_floats, right(), left(), gs, eta);
         check();
         end();
     }
@@ -555,11 +560,7 @@ struct Launcher {
             rows(true, false, grad);
             return;
         }
-        begin(grad ? K_UPDATE_SGD : K_UPDATE, P.pass_elems * 4.0 * (grad ? 3.0 : 2.0));
-        launch_apply_mixed((unsigned)P.mixed_tiles.size(), st, c->d_mixed, c->d_pairs, c->d_cols, c->d_xs, right(), left(),
-                           grad ? (const float *const *)c->d_gs : nullptr, eta);
-        check();
-        end();
+        apply(grad);
         turn();
     }
     void combine_q(float *hist = nullptr) {

@@ -531,12 +531,13 @@ apply_kernel(const ApplyTile *__restrict__ tiles, const PairDesc *__restrict__ p
 template <bool GRAD>
 __global__ void __launch_bounds__(kThreads)
 apply_mixed_kernel(const MixedTile *__restrict__ tiles, const PairDesc *__restrict__ pairs, const ColDesc *__restrict__ cols,
-                   float *const *__restrict__ xs, const float *__restrict__ right, const float *__restrict__ left,
+                   float *const *__restrict__ xs, const float *y, int64_t stride, const float *__restrict__ right, const float *__restrict__ left,
                    const float *const *__restrict__ gs, double eta) {
     constexpr int M = kMixedRows;
     const MixedTile t = tiles[blockIdx.x];
     const PairDesc pd = pairs[t.pair];
     float *X = xs[pd.worker] + pd.x_off;
+    const float *S = y ? y + pd.worker * stride + pd.x_off : X;
     const float *Gp = GRAD ? gs[pd.worker] + pd.x_off : nullptr;
     const int q = pd.q, R = pd.R, u1 = t.unit0 + t.nunits, end = t.row0 + t.nrows;
     const int TC = 1 << t.tc_shift, tc = threadIdx.x & (TC - 1), g = (int)threadIdx.x >> t.tc_shift, G = kThreads >> t.tc_shift;
@@ -555,7 +556,7 @@ apply_mixed_kernel(const MixedTile *__restrict__ tiles, const PairDesc *__restri
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const int64_t at = (int64_t)min(row + m, end - 1) * pd.ld + c;
-                fetch(X + at, n, x[m]);
+                fetch(S + at, n, x[m]);
                 if (GRAD) fetch(Gp + at, n, gr[GRAD ? m : 0]);
             }
             double xd[M][4];
@@ -648,15 +649,14 @@ void launch_apply(int cols_compiled, unsigned ntiles, hipStream_t stream, const 
     if (cols_compiled <= 1) PG_APPLY(1);
     else if (cols_compiled <= 2) PG_APPLY(2);
     else if (cols_compiled <= 4) PG_APPLY(4);
-    else if (cols_compiled <= 8) PG_APPLY(8);
-    else PG_APPLY(16);
+    else PG_APPLY(8);  // (more: launch_apply_mixed)
 #undef PG_APPLY
 }
 
 void launch_apply_mixed(unsigned ntiles, hipStream_t stream, const MixedTile *tiles, const PairDesc *pairs, const ColDesc *cols,
-                        float *const *xs, const float *right, const float *left, const float *const *gs, double eta) {
-    if (gs) apply_mixed_kernel<true><<<dim3(ntiles), dim3(kThreads), 0, stream>>>(tiles, pairs, cols, xs, right, left, gs, eta);
-    else apply_mixed_kernel<false><<<dim3(ntiles), dim3(kThreads), 0, stream>>>(tiles, pairs, cols, xs, right, left, gs, eta);
+                        float *const *xs, const float *y, int64_t stride, const float *right, const float *left, const float *const *gs, double eta) {
+    if (gs) apply_mixed_kernel<true><<<dim3(ntiles), dim3(kThreads), 0, stream>>>(tiles, pairs, cols, xs, y, stride, right, left, gs, eta);
+    else apply_mixed_kernel<false><<<dim3(ntiles), dim3(kThreads), 0, stream>>>(tiles, pairs, cols, xs, y, stride, right, left, gs, eta);
 }
 
 }  // namespace pg

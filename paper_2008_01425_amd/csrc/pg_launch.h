@@ -24,7 +24,7 @@ void launch_apply(int cols_compiled, unsigned ntiles, hipStream_t stream, const 
                   float *const *xs, const float *y, int64_t stride, const float *right, const float *left, const float *const *gs, double eta);
 
 void launch_apply_mixed(unsigned ntiles, hipStream_t stream, const MixedTile *tiles, const PairDesc *pairs, const ColDesc *cols,
-                        float *const *xs, const float *right, const float *left, const float *const *gs, double eta);
+                        float *const *xs, const float *y, int64_t stride, const float *right, const float *left, const float *const *gs, double eta);
 
 // Edge sweeps.
 struct SweepLaunch {

@@ -937,8 +937,12 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     // Tiles: with 32 KB for every set 103 x 194 on a tree of 10 took 37 us against 31; about a thousand tiles mend that.  Long rows are
     // cut as well: whole rows of 70001 columns left five work-groups per worker with all the work (780 us against 324).
     P.mixed_tiles.clear();
-    if (P.sweep && P.max_groups == 1 && tune.mixed != 0 &&
-        (tune.mixed > 0 || (rank >= 2 && P.row_classes.size() > 1 && total_bytes <= (double)kSweepMixedBytes))) {
+    // Behind edge kernels: more than eight columns.  Calls with a kernel that holds all 16 columns of a unit over calls with this one, 72 sets: SGD round and
+    // single iteration 1.16, up to 1.5; round 0.87-1.12.
+    const bool one_update = P.edge ? P.apply_cols > kWideCols
+                                   : P.sweep && P.max_groups == 1 && tune.mixed != 0 &&
+                                         (tune.mixed > 0 || (rank >= 2 && P.row_classes.size() > 1 && total_bytes <= (double)kSweepMixedBytes));
+    if (one_update) {
         const double bytes = std::min((double)kMixedTileBytes, total_bytes / kMixedTiles);
         for (int l = 0; l < n_layers; ++l) {
             const LayerInfo &L = P.layers[l];

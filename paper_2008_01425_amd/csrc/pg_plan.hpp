@@ -135,7 +135,8 @@ struct Plan {
     std::vector<SweepDesc> sweep_descs;
     std::vector<SweepTile> sweep_tiles;      // slots of eight, one tile per die
     std::vector<FinishTile> finish_tiles;
-    std::vector<MixedTile> mixed_tiles;      // the update of such sets in one launch, where it pays (empty: the row kernels)
+    std::vector<MixedTile> mixed_tiles;      // the update of such sets in one launch, where it pays (empty: the row kernels), and the
+                                             // one behind edge kernels at more than eight columns (empty: apply_tiles)
     int max_layer_rank = 1;                  // largest r_l
     int max_rows = 1;                        // largest p_l
 };

@@ -436,7 +436,7 @@ int main() {
         std::vector<float> w(edges.size() / 2, 1.0f / n);
         int rc = build_plan(P, n, (int)w.size(), edges.data(), w.data(), (int)rows.size(), rows.data(), cols.data(), rank, steps, Tuning());
         REQUIRE(rc == PG_OK, "build_plan returned %d", rc);
-        const std::string got = P.edge ? (P.edge_run ? "edge, runs too" : "edge") : P.sweep ? (P.mixed_tiles.empty() ? "sweep" : "sweep, one update") : "stream";
+        const std::string got = P.edge ? (P.edge_run ? "edge, runs too" : P.mixed_tiles.empty() ? "edge" : "edge, one update") : P.sweep ? (P.mixed_tiles.empty() ? "sweep" : "sweep, one update") : "stream";
         REQUIRE(got == want, "%s", got.c_str());
         printf("as expected: %s\n", name);
         return 0;

@@ -122,3 +122,21 @@ def test_a_layer_that_does_not_fit_keeps_the_set_on_the_streaming_kernels():
         gb = _buffers(wl, wl.all_params(), wl.all_q(), 1)
         assert "edge" not in _kinds(gb, gb.round), shapes
         gb.close()
+
+
+@pytest.mark.parametrize("rounds", [2, 3])
+def test_runs_with_sixteen_columns_are_their_rounds(rounds):
+    """More than eight columns: the update in fours of columns, at a run's end from the second buffer (even) or in place."""
+    wl = _workload("hub, leaves and a lone worker", [(33, 40), (20, 64), (64, 1), (7, 9), (1, 77)], 4, 1, 33)
+    X, Q = wl.all_params(), wl.all_q()
+    layers = list(range(len(wl.shapes)))
+    print(f"case {wl.name} {rounds}", flush=True)
+    a, b = _buffers(wl, X, Q, 1), _buffers(wl, X, Q, 1)
+    assert _kinds(a, lambda: a.run(rounds)) == {"edge": rounds, "update": 1}
+    for _ in range(rounds):
+        b.round()
+    assert all(bool((x == y).all()) for x, y in zip(a.x, b.x)) and bool((a.q == b.q).all())
+    info = oracle_rounds(wl, X, Q, rounds, layers)
+    compare_state(a, X, Q, layers, TOL_10, what=f"run of {rounds}", flags=info.degenerate)
+    a.close()
+    b.close()
