@@ -125,6 +125,12 @@ constexpr int kEdgeMaxRank = 4;
 // 7200 elements 1.3-3.5, 8300 to 12700 1.2-2.0, above 14000 0.8-1.1 (a work-group is then longer at it than the launches it saves);
 // 100 x 100, ring of 8, ten rounds 138 -> 115 us, three layers of 64 x 32 and less, ring of 4, one round 20.0 -> 10.2 us.
 constexpr int kEdgeSize = 12800;
+// Runs: a round's update goes into the next round's edge kernel up to one pair per CU, and where that work, done once per edge, is less than the
+// launch it saves.  Run of five with it / without it, times of the streaming kernels over both (median): up to 64 pairs 2.05 / 1.57, 128 to 256
+// 2.06 / 1.87, 256 to 512 2.26 / 2.73, 2000 1.2 / 1.7.
+constexpr int kEdgeRunTiles = 256;
+constexpr int kEdgeRunCost = 150;                   // see edge_run_cost()
+constexpr int64_t kEdgeRunBytes = 32ll << 20;       // most of the second buffer that it takes
 constexpr int kEdgeLdsBytes = 152 * 1024;
 constexpr int kEdgeSumBytes = 72 * 1024;    // of that, column sums of the wavefronts
 constexpr int kApplyUnits = 4;  // units of four floats per thread of the update kernel that goes with them

@@ -89,6 +89,15 @@ static bool edge_split(const LayerInfo &L, int nt, int &tc_shift) {
     return (nv + (1 << tc_shift) - 1) >> tc_shift <= kEdgeUnits && edge_lds(L.p, L.q, L.r, tc_shift, nt, 0).bytes <= kEdgeLdsBytes;
 }
 
+// What applying a pending update of R columns, both ends together, adds to an edge kernel, in units of 1/30 us: vectors staged four at a time, a loop of
+// loads each, and a multiply-add per column and unit.  (Least squares over 388 sets, us: 0.39 per staging step, 0.034 per column and unit; the launch that it
+// saves 5.2.  Single rows of 4000 to 6000 floats and work-groups with 16 or more columns lost up to 1.7 times.)
+static int edge_run_cost(const LayerInfo &L, int nt, int tc_shift, int R) {
+    const int nv = (L.q + 3) / 4, units = (nv + (1 << tc_shift) - 1) >> tc_shift;
+    const int stage = (R + 3) / 4 * ((std::max(L.p, L.q) + nt - 1) / nt);
+    return 12 * stage + R * units;
+}
+
 // Whether a set gains from edge sweeps.  They read the parameters once per power step where the streaming kernels read them twice, and
 // three launches make a round where those need five, and on a graph of mixed degrees five kinds of row and column kernels one after the other.
 // Against that stand their work per edge instead of per worker and, at higher ranks, column sums that leave few wavefronts per SIMD.
@@ -770,6 +779,12 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
             }
         }
         P.edge_run = P.edge_run_lds <= kEdgeLdsBytes;
+        if (tune.edge <= 0) {
+            P.edge_run = P.edge_run && P.edge_tiles.size() <= (size_t)kEdgeRunTiles &&
+                         4 * (int64_t)n_workers * (int64_t)P.param_floats <= kEdgeRunBytes;
+            for (int l = 0; l < n_layers; ++l)
+                P.edge_run = P.edge_run && edge_run_cost(P.layers[l], P.edge_threads, shift[l], 2 * (int)max_deg * P.layers[l].r) <= kEdgeRunCost;
+        }
         if (P.edge_run) {
             P.ws_y = P.ws_bytes;
             P.ws_ph2 = (size_t)round_up(P.ws_y + (size_t)n_workers * P.param_floats * 4, 256);

@@ -164,6 +164,8 @@ static int check(const char *name, int n, const std::vector<int32_t> &e, const s
         build_plan(S, n, (int)ew.size(), e.data(), ew.data(), L, rows.data(), cols.data(), rank, steps, plain);
         const size_t limit = S.ws_bytes <= (size_t)PG_STATIC_WORKSPACE_BYTES ? (size_t)PG_STATIC_WORKSPACE_BYTES : S.ws_bytes + (size_t)(n * S.elems_per_worker);
         REQUIRE(P.ws_static_bytes <= limit, "workspace %zu, %zu without sweeps, parameters %.0f", P.ws_static_bytes, S.ws_bytes, 4.0 * n * S.elems_per_worker);
+        // the second buffer of runs on edge kernels, with one of the unit vectors
+        if (tune.edge <= 0) REQUIRE(P.ws_bytes - P.ws_static_bytes <= (size_t)kEdgeRunBytes + 512 + 4 * P.pstate_floats, "workspace %zu, single rounds %zu", P.ws_bytes, P.ws_static_bytes);
         if (!P.sweep && !P.edge) REQUIRE(P.ws_bytes == S.ws_bytes && P.sweep_tiles.empty() && P.finish_tiles.empty(), "workspace %zu, %zu without sweeps", P.ws_bytes, S.ws_bytes);
     }
     // ---- one-launch update: every element of every pair with columns once ----
@@ -458,6 +460,12 @@ int main() {
     }
     bad |= path("vgg16 layers, rank 1", r16, 16, vr, vc, 1, 1, "sweep");
     bad |= path("vgg16 layers, rank 2", r16, 16, vr, vc, 2, 1, "stream");
+    bad |= path("100 x 100, ring of 8", r8, 8, {100}, {100}, 1, 1, "edge, runs too");
+    bad |= path("small layers, ring of 8, rank 4", r8, 8, {40, 64, 64}, {60, 32, 1}, 4, 1, "edge, runs too");
+    // a pending update costs more than a launch: long rows, many columns, more work-groups than CUs
+    bad |= path("1 x 5936", r8, 8, {1}, {5936}, 1, 1, "edge");
+    bad |= path("122 x 56, 16 columns", t4, 16, {122}, {56}, 4, 1, "edge, one update");
+    bad |= path("forty layers of 60 x 64", r8, 8, std::vector<int32_t>(40, 60), std::vector<int32_t>(40, 64), 1, 1, "edge");
     bad |= path("small convolutions, ring of 8", r8, 8, nr, nc, 1, 1, "sweep");
     bad |= path("ragged layers, tree of 11", t11, 11, {510, 77, 1301, 2047, 33, 129, 5, 40001}, {1023, 4099, 333, 255, 1, 2, 70001, 7}, 3, 1, "sweep, one update");
     // rows beyond the registers; a dense graph with much to read per edge, and with little; three workers
