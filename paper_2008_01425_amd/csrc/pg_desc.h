@@ -125,6 +125,10 @@ constexpr int kEdgeMaxRank = 4;
 // 7200 elements 1.3-3.5, 8300 to 12700 1.2-2.0, above 14000 0.8-1.1 (a work-group is then longer at it than the launches it saves);
 // 100 x 100, ring of 8, ten rounds 138 -> 115 us, three layers of 64 x 32 and less, ring of 4, one round 20.0 -> 10.2 us.
 constexpr int kEdgeSize = 12800;
+// (Edge, layer) pairs, one work-group each, up to which they are taken: streaming kernels over theirs, 400 drawn sets of up to 4000 layers, round and
+// single iteration (worst twentieth / median): up to 2048 pairs 1.43 / 2.0 and 1.07 / 1.5, 3000 to 5000 1.16 / 1.29 and 0.87 / 0.95,
+// above 10000 0.66 / 0.92 and 0.62 / 0.78.
+constexpr int kEdgeTiles = 2048;
 // Runs: a round's update goes into the next round's edge kernel up to one pair per CU, and where that work, done once per edge, is less than the
 // launch it saves.  Run of five with it / without it, times of the streaming kernels over both (median): up to 64 pairs 2.05 / 1.57, 128 to 256
 // 2.06 / 1.87, 256 to 512 2.26 / 2.73, 2000 1.2 / 1.7.

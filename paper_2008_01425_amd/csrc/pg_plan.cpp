@@ -740,7 +740,7 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     P.edge_tiles.clear();
     P.apply_tiles.clear();
     P.edge_elems = 0;
-    P.edge = tune.edge != 0 && n_edges > 0 && P.max_groups == 1;
+    P.edge = tune.edge != 0 && n_edges > 0 && P.max_groups == 1 && (tune.edge > 0 || (int64_t)n_edges * n_layers <= kEdgeTiles);
     for (const LayerInfo &L : P.layers) P.edge = P.edge && (tune.edge > 0 || (int64_t)L.p * L.q <= kEdgeSize);
     std::vector<int> shift(n_layers);
     bool fits = false;

@@ -466,6 +466,7 @@ int main() {
     bad |= path("1 x 5936", r8, 8, {1}, {5936}, 1, 1, "edge");
     bad |= path("122 x 56, 16 columns", t4, 16, {122}, {56}, 4, 1, "edge, one update");
     bad |= path("forty layers of 60 x 64", r8, 8, std::vector<int32_t>(40, 60), std::vector<int32_t>(40, 64), 1, 1, "edge");
+    bad |= path("a thousand layers of 8 x 64", r8, 8, std::vector<int32_t>(1000, 8), std::vector<int32_t>(1000, 64), 1, 1, "stream");
     bad |= path("small convolutions, ring of 8", r8, 8, nr, nc, 1, 1, "sweep");
     bad |= path("ragged layers, tree of 11", t11, 11, {510, 77, 1301, 2047, 33, 129, 5, 40001}, {1023, 4099, 333, 255, 1, 2, 70001, 7}, 3, 1, "sweep, one update");
     // rows beyond the registers; a dense graph with much to read per edge, and with little; three workers
