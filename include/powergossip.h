@@ -235,7 +235,7 @@ int pg_iterate(pg_ctx *ctx, float *const *worker_params, float *q_state, float *
 
 /*
  * `rounds` consecutive gossip rounds with nothing touching the parameters in between
- * (the pure consensus iteration, Eq. (4)).  Same result as calling pg_round `rounds` times;
+ * (the pure consensus iteration, Eq. (4)).  Same result as calling pg_round `rounds` times, bit for bit;
  * the update of round t and the first product of round t+1 share one pass over the
  * parameters (sets of small layers: one launch a round).  A large parameter set (more than 320 MB over all workers) is written every second round
  * only, the last one always, if power_steps = 1, no worker stacks more than four columns (degree x rank),

@@ -692,7 +692,9 @@ int run_rounds(pg_ctx *c, float *const *worker_params, float *q_state, void *wor
         return L.status;
     }
     const bool lazy = c->plan.lazy && fuse && rounds > 1;
-    if (c->plan.sweep && !lazy) {
+    // Sets whose runs write every second round: single rounds by the streaming kernels as well, so that a run leaves what its
+    // rounds leave, bit for bit (sweeps form Q' of P, those of Phat rounded to float).  SGD rounds have no run to agree with.
+    if (c->plan.sweep && !c->plan.lazy) {
         for (int t = 0; t < rounds; ++t) {
             for (int step = 0; step < s; ++step) L.edge_sweep();
             L.sweep_update(false);

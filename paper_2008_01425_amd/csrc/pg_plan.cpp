@@ -216,7 +216,7 @@ static bool sweeps_are_faster(const Plan &P) {
     int workers = 0;
     for (const auto &inc : P.incident) workers += !inc.empty();
     const double need = workers <= 4 || P.n_edges >= 4 * workers ? kSweepGainFew : kSweepGain;
-    // (runs that write every second round stay with the streaming kernels)
+    // (where runs write every second round, they and single rounds stay with the streaming kernels: what is left are SGD rounds)
     return P.steps * T.stream - (P.lazy ? 0.0 : T.fused) >= need * P.steps * T.sweep;
 }
 

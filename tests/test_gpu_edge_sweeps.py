@@ -166,3 +166,33 @@ def test_an_infinite_parameter_spreads_as_it_does_with_the_row_kernels(rank, pla
             assert np.array_equal(np.isnan(x), np.isnan(y)) and np.array_equal(np.isinf(x), np.isinf(y)), (shapes[l], "worker", i)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("graph", ["ring", "path and a lone worker"])
+@pytest.mark.parametrize("rank", [1, 2])
+def test_runs_that_write_every_second_round_are_their_rounds(graph, rank):
+    """Sets that qualify for both: a run of any length, its rounds one by one and runs of one round leave the same, bit for
+    bit; the SGD round, which no run contains, takes the sweeps."""
+    from paper_2008_01425_amd.device import GossipBuffers
+    wl = _workload(graph, [(64, 576), (33, 130), (517, 259), (50, 4609), (1030, 36), (700, 1), (1, 77), (7, 8)], rank, 1, seed=59)
+    X, Q = wl.all_params(), wl.all_q()
+    got, kinds = [], []
+    calls = {"run": lambda gb: gb.run(3), "rounds": lambda gb: [gb.round() for _ in range(3)], "runs of two and one": lambda gb: (gb.run(2), gb.run(1))}
+    for what, call in calls.items():
+        print(f"case {wl.name} {what}", flush=True)
+        with env_setting("PG_EDGE", 0), env_setting("PG_LIGHT", 0), env_setting("PG_LAZY", 1), env_setting("PG_SWEEP", 1):
+            gb = GossipBuffers.from_workload(wl, fill=False)
+        gb.fill_from_arrays(X, Q)
+        kinds.append(_kinds(gb, lambda: call(gb)))
+        got.append(gb)
+    assert "peek_sweep_p" in kinds[0] and "peek_sweep_p" in kinds[2] and all("edge_sweep" not in k for k in kinds), kinds
+    for other in got[1:]:
+        assert all(bool((x == y).all()) for x, y in zip(got[0].x, other.x)) and bool((got[0].q == other.q).all())
+    info = oracle_rounds(wl, X, Q, 3, list(range(len(wl.shapes))))
+    compare_state(got[0], X, Q, list(range(len(wl.shapes))), TOL_10, what="run of 3", flags=info.degenerate)
+    got[0].alloc_grads()
+    for g in got[0].g:
+        g.zero_()
+    assert "edge_sweep" in _kinds(got[0], lambda: got[0].round_sgd(0.0))
+    for gb in got:
+        gb.close()
