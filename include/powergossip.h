@@ -141,8 +141,8 @@ size_t pg_message_floats(const pg_ctx *ctx);
  * passes = 2*power_steps + 2 for pg_round (each product reads every X once, the update reads
  * and writes it), 2*power_steps + 1 for a round in the middle of a pg_run that writes the parameters
  * every round (the update also feeds the next round's first product).  These are the passes of the streaming kernels;
- * rounds that take edge sweeps (both products in one read) or edge kernels move less, which the bytes of
- * pg_profile_collect show.  What a given pg_run moves in
+ * a pg_round that takes edge sweeps (both products in one read) or edge kernels moves less, which
+ * pg_run_bytes(ctx, 1) tells.  What a given pg_run moves in
  * all, first and last round and runs that write every second round included, is pg_run_bytes.
  */
 double pg_round_bytes(const pg_ctx *ctx, int fused);
@@ -150,7 +150,10 @@ double pg_round_bytes(const pg_ctx *ctx, int fused);
 /*
  * Algorithmic bytes of parameter traffic of pg_run(ctx, ..., rounds), all rounds together, workers without
  * neighbours left out (no pass reads them).  Runs that write the parameters every second round (see
- * pg_run) make 5 passes over them for two rounds instead of 6.
+ * pg_run) make 5 passes over them for two rounds instead of 6.  Edge sweeps make power_steps + 2 per round.  Edge
+ * kernels read each worker's matrices once per edge and round, whatever power_steps; their updates make two passes, all
+ * but a run's last one only one where the next round's kernel applies them.  The sum of the bytes that
+ * pg_profile_collect reports for the same run.
  */
 double pg_run_bytes(const pg_ctx *ctx, int rounds);
 

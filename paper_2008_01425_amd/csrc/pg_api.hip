@@ -864,12 +864,16 @@ double pg_round_bytes(const pg_ctx *c, int fused) {
 
 double pg_run_bytes(const pg_ctx *c, int rounds) {
     if (!c || rounds < 0) return -1.0;
-    if (rounds == 0 || c->plan.n_edges == 0) return 0.0;
+    const Plan &P = c->plan;
+    if (rounds == 0 || P.n_edges == 0) return 0.0;
     const double T = rounds;
-    if (c->plan.max_groups > 1) return T * pg_round_bytes(c, 0);
-    double passes = 2.0 * c->plan.steps * T + T + 1.0;  // both sweeps; every update also writes, the last one reads once more
-    if (c->plan.lazy && rounds > 1) passes = 2.0 * T + (rounds - 1) / 2 + 2.0;  // run_lazy: odd rounds from the third write
-    return 4.0 * c->plan.pass_elems * passes;
+    // edge kernels: each worker's matrix once per edge, and the updates (run_edge: all but the last one written from there)
+    if (P.edge) return 4.0 * (T * P.edge_elems + (P.edge_run ? T + 1.0 : 2.0 * T) * P.pass_elems);
+    if (P.sweep && !P.lazy) return 4.0 * T * (P.steps * P.sweep_elems + 2.0 * P.pass_elems);
+    if (P.max_groups > 1) return T * pg_round_bytes(c, 0);
+    double passes = 2.0 * P.steps * T + T + 1.0;  // both sweeps; every update also writes, the last one reads once more
+    if (P.lazy && rounds > 1) passes = 2.0 * T + (rounds - 1) / 2 + 2.0;  // run_lazy: odd rounds from the third write
+    return 4.0 * P.pass_elems * passes;
 }
 
 int pg_upload(pg_ctx *c) {

@@ -196,3 +196,28 @@ def test_runs_that_write_every_second_round_are_their_rounds(graph, rank):
     assert "edge_sweep" in _kinds(got[0], lambda: got[0].round_sgd(0.0))
     for gb in got:
         gb.close()
+
+
+@pytest.mark.parametrize("graph", GRAPHS)
+@pytest.mark.parametrize("settings", [dict(PG_EDGE=0, PG_SWEEP=0, PG_LIGHT=1), dict(PG_EDGE=0, PG_SWEEP=0, PG_LIGHT=0, PG_LAZY=1),
+                                      dict(PG_EDGE=0, PG_SWEEP=1, PG_MIXED=0), dict(PG_EDGE=0, PG_SWEEP=1, PG_MIXED=1),
+                                      dict(PG_EDGE=0, PG_SWEEP=1, PG_LIGHT=0, PG_LAZY=1), dict(PG_EDGE=1)], ids=str)
+def test_bytes_of_a_run_are_those_of_its_launches(graph, settings):
+    from contextlib import ExitStack
+    from paper_2008_01425_amd import binding as B
+    from paper_2008_01425_amd.device import GossipBuffers
+    for rank, steps in ((1, 1), (2, 2)):
+        wl = _workload(graph, [(64, 96), (33, 130), (100, 1), (7, 8)], rank, steps)
+        print(f"case {wl.name} {settings}", flush=True)
+        with ExitStack() as held:
+            for name, value in settings.items():
+                held.enter_context(env_setting(name, value))
+            gb = GossipBuffers.from_workload(wl)
+        for rounds in (1, 2, 3, 4):
+            B.pg_profile_enable(gb.ctx, True)
+            gb.run(rounds)
+            booked = sum(r["bytes"] for r in B.pg_profile_collect(gb.ctx))
+            B.pg_profile_enable(gb.ctx, False)
+            told = B.pg_run_bytes(gb.ctx, rounds)
+            assert abs(booked - told) <= 1e-9 * told, (rank, steps, rounds, booked, told)
+        gb.close()

@@ -9,6 +9,7 @@ import pytest
 
 from paper_2008_01425_amd import binding as B
 from paper_2008_01425_amd import workloads as W
+from parity_util import env_setting
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -138,9 +139,23 @@ def test_bytes_of_a_run_follow_the_path_it_takes():
     def passes(ctx, n, shapes, rounds):
         return B.pg_run_bytes(ctx, rounds) / (4.0 * n * sum(p * q for p, q in shapes))
     small = [(100, 100)]
-    ctx = _init(8, W.ring_edges(8), 1 / 3, small, 1, 2)
+    with env_setting("PG_EDGE", 0), env_setting("PG_SWEEP", 0):
+        ctx = _init(8, W.ring_edges(8), 1 / 3, small, 1, 2)
     assert [passes(ctx, 8, small, t) for t in (0, 1, 2, 5)] == [0, 6, 11, 26]
     assert B.pg_run_bytes(ctx, 1) == B.pg_round_bytes(ctx, False)
+    B.pg_destroy(ctx)
+    with env_setting("PG_EDGE", 0), env_setting("PG_SWEEP", 1):        # both products in one read: steps + 2
+        ctx = _init(8, W.ring_edges(8), 1 / 3, small, 1, 2)
+    assert [passes(ctx, 8, small, t) for t in (0, 1, 2, 5)] == [0, 4, 8, 20]
+    B.pg_destroy(ctx)
+    # edge kernels: every worker read by each of its two edges; an update of a round in between is one pass (the next
+    # round's kernel has read its operand), the last one two
+    ctx = _init(8, W.ring_edges(8), 1 / 3, small, 1, 2)
+    assert [passes(ctx, 8, small, t) for t in (0, 1, 2, 5)] == [0, 4, 7, 16]
+    B.pg_destroy(ctx)
+    path = [[0, 1], [1, 2]]                                            # worker 3 alone: no pass reads it
+    ctx = _init(4, path, 0.3, small, 1, 1)
+    assert [passes(ctx, 1, small, t) for t in (1, 2)] == [4 + 2 * 3, 2 * 4 + 3 * 3]
     B.pg_destroy(ctx)
     large = [(2048, 4608)]
     ctx = _init(16, W.ring_edges(16), 1 / 3, large, 1, 1)
@@ -148,7 +163,8 @@ def test_bytes_of_a_run_follow_the_path_it_takes():
     assert [passes(ctx, 16, large, t) for t in (0, 1, 2, 3, 4, 10)] == [0, 4, 6, 9, 11, 26]
     B.pg_destroy(ctx)
     hub = [(64, 64)]
-    ctx = _init(20, [[0, k] for k in range(1, 20)], 0.05, hub, 1, 1)   # 19 stacked columns: two passes for worker 0
+    with env_setting("PG_EDGE", 0), env_setting("PG_SWEEP", 0):
+        ctx = _init(20, [[0, k] for k in range(1, 20)], 0.05, hub, 1, 1)   # 19 stacked columns: two passes for worker 0
     assert B.pg_run_bytes(ctx, 3) == 3 * B.pg_round_bytes(ctx, False)
     B.pg_destroy(ctx)
 
