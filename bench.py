@@ -133,7 +133,7 @@ def measure_other(name: str, rounds: int):
     k_fused = kernel_table(B, gb, lambda: gb.run(kp))
     k_unfused = kernel_table(B, gb, lambda: [gb.round() for _ in range(kp)])
     nparam = wl.n_workers * wl.params_per_worker
-    bf, bu = moved(k_fused, kp), moved(k_unfused, kp)
+    bf, bu = B.pg_run_bytes(gb.ctx, rounds) / rounds, moved(k_unfused, kp)
     traffic, src = traffic_from_profiles(name)
     slim = lambda tab: {k: {"avg_ms": v["avg_ms"], "GBps": v["GBps"], "frac_of_peak": v["frac_of_peak"],
                             "launches": v["launches"]} for k, v in tab.items()}
@@ -292,7 +292,8 @@ def main():
 
     nparam = wl.n_workers * wl.params_per_worker
     bytes_fused = B.pg_run_bytes(gb.ctx, K) / K
-    bytes_unfused = moved(k_unfused, Kp)   # (edge sweeps read the parameters once for both products)
+    bytes_unfused = moved(k_unfused, Kp)
+    bytes_sgd = moved(k_sgd, min(Kp, 10))
     result = {
         "metric": "gossip rounds/sec + achieved HBM GB/s (% of peak), fp32, 1 MI355X",
         "value": K / dt,
@@ -321,7 +322,7 @@ def main():
                              "GBps": bytes_unfused / (stats_unfused["median"] * 1e-3) / 1e9,
                              "bytes_per_param_per_round": bytes_unfused / nparam},
         "pg_round_sgd": {"ms_per_step": stats_sgd, "rounds_per_s": 1e3 / stats_sgd["median"],
-                         "bytes_per_param_per_round": bytes_unfused / nparam + 4,
+                         "bytes_per_param_per_round": bytes_sgd / nparam,
                          "update_sgd_kernel": k_sgd.get("update_sgd")},
         "pg_iterate_1_sgd": {"ms_per_iteration": stats_it, "iterations_per_s": 1e3 / stats_it["median"],
                              "bytes_per_param_per_iteration": 16.0,
