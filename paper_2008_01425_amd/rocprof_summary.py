@@ -75,6 +75,17 @@ def kernel_kind(name: str):
         return "peek_sweep_q"
     if re.match(r"pg::(col_kernel|mcol_kernel|vec_col_kernel)<", name):
         return "sweep_q"
+    if re.match(r"pg::edge_(kernel|pending_kernel|iterate_kernel)<", name):
+        return "edge"
+    if re.match(r"pg::sweep_kernel<", name):
+        return "edge_sweep"
+    if re.match(r"pg::sweep_finish_kernel<", name):   # reads the parameters of layers with long rows
+        return "finish"
+    m = re.match(r"pg::(apply_kernel|apply_mixed_kernel)<(.*)>", name)
+    if m:
+        return "update_sgd" if m.group(2).endswith("true") else "update"
+    if name == "pg::sgd_only_kernel":
+        return "update_sgd"
     return None
 
 

@@ -350,8 +350,18 @@ def test_profile_summaries_classify_every_pass_kernel():
     assert kernel_kind("pg::row_pending_kernel<2, 8, 1, true, 1, false>") == "peek_sweep_p"
     assert kernel_kind("pg::row_pending_kernel<2, 8, 1, true, 2, false>") == "update_sweep_p"
     assert kernel_kind("pg::row_pending_kernel<2, 8, 1, false, 2, true>") == "update"
+    assert kernel_kind("pg::edge_kernel<256, 1>") == kernel_kind("pg::edge_pending_kernel<512, 4>") == "edge"
+    assert kernel_kind("pg::edge_iterate_kernel<256, 2>") == "edge"
+    assert kernel_kind("pg::sweep_kernel<256, 1>") == "edge_sweep"
+    assert kernel_kind("pg::sweep_finish_kernel<4>") == "finish"
+    assert kernel_kind("pg::apply_kernel<2, false>") == kernel_kind("pg::apply_mixed_kernel<false>") == "update"
+    assert kernel_kind("pg::apply_kernel<2, true>") == kernel_kind("pg::apply_mixed_kernel<true>") == "update_sgd"
     assert kernel_kind("pg::comb_kernel") is None
     assert kernel_kind("pg::orth_gram_kernel<256, 2>") is None
+    # and every kernel of the library: a pass over the parameters, or one of the vectors' own
+    import code_objects
+    for name in code_objects.kernels(B.LIB_PATH):
+        assert kernel_kind(name) is not None or re.match(r"pg::(orth|comb)_", name), name
     for wl in ("vgg16_r1", "vgg16_r2", "lstm", "resnet50"):
         path = os.path.join(ROOT, "profiles", f"{wl}_traffic_counters.txt")
         kinds = {line.split()[1] for line in open(path) if line.startswith("traffic ")}
