@@ -150,7 +150,8 @@ double pg_round_bytes(const pg_ctx *ctx, int fused);
 /*
  * Algorithmic bytes of parameter traffic of pg_run(ctx, ..., rounds), all rounds together, workers without
  * neighbours left out (no pass reads them).  Runs that write the parameters every second round (see
- * pg_run) make 5 passes over them for two rounds instead of 6.  Edge sweeps make power_steps + 2 per round.  Edge
+ * pg_run) make 5 passes over them for two rounds instead of 6.  Edge sweeps make power_steps + 2 per
+ * round, 2 * power_steps + 2 over layers whose rows do not fit a work-group's registers.  Edge
  * kernels read each worker's matrices once per edge and round, whatever power_steps; their updates make two passes, all
  * but a run's last one only one where the next round's kernel applies them.  The sum of the bytes that
  * pg_profile_collect reports for the same run.

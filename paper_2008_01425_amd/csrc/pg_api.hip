@@ -546,7 +546,7 @@ struct Launcher {
         check();
         end();
         if (status) return;
-        begin(K_FINISH, 0.0);
+        begin(K_FINISH, 4.0 * P.sweep_long_elems);
         launch_sweep_finish(l, c->d_finish, (unsigned)P.finish_tiles.size());
         check();
         end();
@@ -869,7 +869,7 @@ double pg_run_bytes(const pg_ctx *c, int rounds) {
     const double T = rounds;
     // edge kernels: each worker's matrix once per edge, and the updates (run_edge: all but the last one written from there)
     if (P.edge) return 4.0 * (T * P.edge_elems + (P.edge_run ? T + 1.0 : 2.0 * T) * P.pass_elems);
-    if (P.sweep && !P.lazy) return 4.0 * T * (P.steps * P.sweep_elems + 2.0 * P.pass_elems);
+    if (P.sweep && !P.lazy) return 4.0 * T * (P.steps * (P.sweep_elems + P.sweep_long_elems) + 2.0 * P.pass_elems);
     if (P.max_groups > 1) return T * pg_round_bytes(c, 0);
     double passes = 2.0 * P.steps * T + T + 1.0;  // both sweeps; every update also writes, the last one reads once more
     if (P.lazy && rounds > 1) passes = 2.0 * T + (rounds - 1) / 2 + 2.0;  // run_lazy: odd rounds from the third write

@@ -814,10 +814,14 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
         // Row blocks: two work-groups per CU take the whole set where it is small enough, at most 1.5 MB each.  The blocks' column sums
         // cost r / rows of the traffic and the time to add them up, so a block has 16 r rows, unless that leaves the chip idle.
         const int nt = P.sweep_threads;
-        P.sweep_elems = P.elems_per_worker * (double)std::count_if(P.incident.begin(), P.incident.end(), [](const std::vector<int> &e) { return !e.empty(); });
+        const double connected = (double)std::count_if(P.incident.begin(), P.incident.end(), [](const std::vector<int> &e) { return !e.empty(); });
+        P.sweep_elems = P.elems_per_worker * connected;
         const double all = 8.0 * n_edges * P.elems_per_worker;
         const size_t room = P.ws_pd - P.ws_pw, others = P.ws_bytes - room;
         auto long_rows = [&](int l) { return P.layers[l].q >= 4 && geometry[l].units == 0; };  // leave no column sums
+        P.sweep_long_elems = 0;
+        for (int l = 0; l < n_layers; ++l)
+            if (long_rows(l)) P.sweep_long_elems += (double)P.layers[l].p * P.layers[l].q * connected;
         std::vector<int> blk_rows(n_layers), nblk(n_layers);
         int64_t pe = 0, qe = 0, gr = 0;
         int least = 16, max_cols = 1;

@@ -132,6 +132,7 @@ struct Plan {
     bool sweep = false;
     int sweep_threads = 0, sweep_lds = 0;
     double sweep_elems = 0;                  // elements of the workers that have edges
+    double sweep_long_elems = 0;             // of that, rows too long for the registers: the finishing kernel reads them again
     std::vector<SweepDesc> sweep_descs;
     std::vector<SweepTile> sweep_tiles;      // slots of eight, one tile per die
     std::vector<FinishTile> finish_tiles;

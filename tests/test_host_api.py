@@ -148,6 +148,11 @@ def test_bytes_of_a_run_follow_the_path_it_takes():
         ctx = _init(8, W.ring_edges(8), 1 / 3, small, 1, 2)
     assert [passes(ctx, 8, small, t) for t in (0, 1, 2, 5)] == [0, 4, 8, 20]
     B.pg_destroy(ctx)
+    wide = [(40, 12001)]                                               # rows beyond the registers: read again for the column sums
+    with env_setting("PG_EDGE", 0), env_setting("PG_SWEEP", 1):
+        ctx = _init(8, W.ring_edges(8), 1 / 3, wide, 1, 2)
+    assert [passes(ctx, 8, wide, t) for t in (1, 2)] == [6, 12]
+    B.pg_destroy(ctx)
     # edge kernels: every worker read by each of its two edges; an update of a round in between is one pass (the next
     # round's kernel has read its operand), the last one two
     ctx = _init(8, W.ring_edges(8), 1 / 3, small, 1, 2)
