@@ -8,6 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 import numpy as np
 
 from oracle import pg_oracle as O
+from paper_2008_01425_amd import workloads as W
 
 TOL_1 = 1e-5     # relative error per element after one round
 TOL_10 = 1e-4    # after ten rounds
@@ -25,6 +26,38 @@ def env_setting(name, value):
             os.environ.pop(name, None)
         else:
             os.environ[name] = old
+
+
+@contextlib.contextmanager
+def env_settings(settings):
+    """env_setting for a dict of them."""
+    with contextlib.ExitStack() as held:
+        for name, value in settings.items():
+            held.enter_context(env_setting(name, value))
+        yield
+
+
+# Settings that hold a set on one kind of kernels (edge kernels: where it fits them; edge sweeps: up to rank 4).
+PATHS = {"streaming kernels": dict(PG_EDGE=0, PG_SWEEP=0), "edge kernels": dict(PG_EDGE=1), "edge sweeps": dict(PG_EDGE=0, PG_SWEEP=1)}
+
+
+def graph_workload(name, graph, shapes, rank, steps, seed):
+    """`graph`: (workers, edges); 1 / (1 + the larger degree of its ends) as an edge's weight."""
+    n, edges = graph
+    edges = np.asarray(edges, np.int32)
+    deg = np.bincount(edges.reshape(-1), minlength=n)
+    w = np.array([1.0 / (1 + max(deg[a], deg[b])) for a, b in edges], np.float32)
+    return W.Workload(name, n, edges, w, shapes, rank, steps, 0.05, 10, seed)
+
+
+def launched(gb, call):
+    """What `call` launches: {kind: launches}."""
+    from paper_2008_01425_amd import binding as B
+    B.pg_profile_enable(gb.ctx, True)
+    call()
+    kinds = {r["name"]: r["launches"] for r in B.pg_profile_collect(gb.ctx)}
+    B.pg_profile_enable(gb.ctx, False)
+    return kinds
 
 
 def rel_err(got: np.ndarray, ref: np.ndarray) -> float:

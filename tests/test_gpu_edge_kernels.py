@@ -4,8 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import pg_oracle as O
-from paper_2008_01425_amd import workloads as W
-from parity_util import TOL_1, TOL_10, compare_state, env_setting, oracle_problem, oracle_rounds
+from parity_util import TOL_1, TOL_10, compare_state, env_setting, graph_workload, launched, oracle_problem, oracle_rounds
 
 pytestmark = pytest.mark.gpu
 
@@ -20,11 +19,7 @@ GRAPHS = {"ring": (5, [(0, 1), (1, 2), (2, 3), (3, 4), (4, 0)]),
 
 
 def _workload(graph, shapes, rank, steps, seed=31):
-    n, edges = GRAPHS[graph]
-    edges = np.asarray(edges, np.int32)
-    deg = np.bincount(edges.reshape(-1), minlength=n)
-    w = np.array([1.0 / (1 + max(deg[a], deg[b])) for a, b in edges], np.float32)
-    return W.Workload(f"edge {graph} {len(shapes)} r{rank}", n, edges, w, shapes, rank, steps, 0.05, 10, seed)
+    return graph_workload(f"edge {graph} {len(shapes)} r{rank}", GRAPHS[graph], shapes, rank, steps, seed)
 
 
 def _buffers(wl, X, Q, edge):
@@ -33,15 +28,6 @@ def _buffers(wl, X, Q, edge):
         gb = GossipBuffers.from_workload(wl, fill=False)
     gb.fill_from_arrays(X, Q)
     return gb
-
-
-def _kinds(gb, call):
-    from paper_2008_01425_amd import binding as B
-    B.pg_profile_enable(gb.ctx, True)
-    call()
-    kinds = {r["name"]: r["launches"] for r in B.pg_profile_collect(gb.ctx)}
-    B.pg_profile_enable(gb.ctx, False)
-    return kinds
 
 
 @pytest.mark.parametrize("threads", SHAPES)
@@ -56,9 +42,9 @@ def test_rounds_runs_and_gradients_against_the_oracle(threads, graph, rank, step
         X[1][l] = X[0][l].copy()
     print(f"case {wl.name} {threads}", flush=True)
     a, b, c, d = (_buffers(wl, X, Q, 1) for _ in range(4))
-    kinds = _kinds(a, a.round)
+    kinds = launched(a, a.round)
     assert kinds == {"edge": 1, "update": 1}, kinds
-    kinds = _kinds(b, lambda: b.run(3))
+    kinds = launched(b, lambda: b.run(3))
     # one launch a round where the operands of a pending update fit beside each other, at high ranks two
     assert kinds["edge"] == 3 and kinds["update"] in ((1,) if graph == "ring" and rank == 1 else (1, 3)), kinds
     c.run(4)
@@ -120,7 +106,7 @@ def test_a_layer_that_does_not_fit_keeps_the_set_on_the_streaming_kernels():
     for shapes in ([(64, 32), (513, 4)], [(64, 32), (33, 576)], [(64, 32), (1, 18433)]):
         wl = _workload("ring", shapes, 1, 1)
         gb = _buffers(wl, wl.all_params(), wl.all_q(), 1)
-        assert "edge" not in _kinds(gb, gb.round), shapes
+        assert "edge" not in launched(gb, gb.round), shapes
         gb.close()
 
 
@@ -132,7 +118,7 @@ def test_runs_with_sixteen_columns_are_their_rounds(rounds):
     layers = list(range(len(wl.shapes)))
     print(f"case {wl.name} {rounds}", flush=True)
     a, b = _buffers(wl, X, Q, 1), _buffers(wl, X, Q, 1)
-    assert _kinds(a, lambda: a.run(rounds)) == {"edge": rounds, "update": 1}
+    assert launched(a, lambda: a.run(rounds)) == {"edge": rounds, "update": 1}
     for _ in range(rounds):
         b.round()
     assert all(bool((x == y).all()) for x, y in zip(a.x, b.x)) and bool((a.q == b.q).all())

@@ -4,8 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import pg_oracle as O
-from paper_2008_01425_amd import workloads as W
-from parity_util import TOL_1, TOL_10, compare_state, env_setting, oracle_problem, oracle_rounds
+from parity_util import TOL_1, TOL_10, compare_state, env_setting, env_settings, graph_workload, launched, oracle_problem, oracle_rounds
 
 pytestmark = pytest.mark.gpu
 
@@ -20,11 +19,7 @@ GRAPHS = {"ring": (5, [(0, 1), (1, 2), (2, 3), (3, 4), (4, 0)]),
 
 
 def _workload(graph, shapes, rank, steps, seed=41):
-    n, edges = GRAPHS[graph]
-    edges = np.asarray(edges, np.int32)
-    deg = np.bincount(edges.reshape(-1), minlength=n)
-    w = np.array([1.0 / (1 + max(deg[a], deg[b])) for a, b in edges], np.float32)
-    return W.Workload(f"sweep {graph} {len(shapes)} r{rank}", n, edges, w, shapes, rank, steps, 0.05, 10, seed)
+    return graph_workload(f"sweep {graph} {len(shapes)} r{rank}", GRAPHS[graph], shapes, rank, steps, seed)
 
 
 def _buffers(wl, X, Q):
@@ -33,15 +28,6 @@ def _buffers(wl, X, Q):
         gb = GossipBuffers.from_workload(wl, fill=False)
     gb.fill_from_arrays(X, Q)
     return gb
-
-
-def _kinds(gb, call):
-    from paper_2008_01425_amd import binding as B
-    B.pg_profile_enable(gb.ctx, True)
-    call()
-    kinds = {r["name"]: r["launches"] for r in B.pg_profile_collect(gb.ctx)}
-    B.pg_profile_enable(gb.ctx, False)
-    return kinds
 
 
 @pytest.mark.parametrize("graph", GRAPHS)
@@ -57,9 +43,9 @@ def test_rounds_runs_and_gradients_against_the_oracle(graph, rank, steps, wide):
         X[1][l] = X[0][l].copy()
     print(f"case {wl.name}", flush=True)
     a, b, c, d = (_buffers(wl, X, Q) for _ in range(4))
-    kinds = _kinds(a, a.round)
+    kinds = launched(a, a.round)
     assert kinds["edge_sweep"] == steps and kinds["finish"] == steps and "sweep_p" not in kinds, kinds
-    kinds = _kinds(b, lambda: b.run(3))
+    kinds = launched(b, lambda: b.run(3))
     assert kinds["edge_sweep"] == 3 * steps, kinds
     c.run(4)
     rng = np.random.default_rng(5)
@@ -103,7 +89,7 @@ def test_update_in_one_launch_is_the_row_kernels_update(graph, rank, wide):
         for i in range(wl.n_workers):
             for l in range(len(wl.shapes)):
                 gb.set_grad_layer(i, l, G[i][l])
-        kinds = _kinds(gb, gb.round)
+        kinds = launched(gb, gb.round)
         launches.append(kinds["update"])
         gb.round_sgd(0.05)
         gb.run(2)
@@ -183,7 +169,7 @@ def test_runs_that_write_every_second_round_are_their_rounds(graph, rank):
         with env_setting("PG_EDGE", 0), env_setting("PG_LIGHT", 0), env_setting("PG_LAZY", 1), env_setting("PG_SWEEP", 1):
             gb = GossipBuffers.from_workload(wl, fill=False)
         gb.fill_from_arrays(X, Q)
-        kinds.append(_kinds(gb, lambda: call(gb)))
+        kinds.append(launched(gb, lambda: call(gb)))
         got.append(gb)
     assert "peek_sweep_p" in kinds[0] and "peek_sweep_p" in kinds[2] and all("edge_sweep" not in k for k in kinds), kinds
     for other in got[1:]:
@@ -193,7 +179,7 @@ def test_runs_that_write_every_second_round_are_their_rounds(graph, rank):
     got[0].alloc_grads()
     for g in got[0].g:
         g.zero_()
-    assert "edge_sweep" in _kinds(got[0], lambda: got[0].round_sgd(0.0))
+    assert "edge_sweep" in launched(got[0], lambda: got[0].round_sgd(0.0))
     for gb in got:
         gb.close()
 
@@ -203,15 +189,12 @@ def test_runs_that_write_every_second_round_are_their_rounds(graph, rank):
                                       dict(PG_EDGE=0, PG_SWEEP=1, PG_MIXED=0), dict(PG_EDGE=0, PG_SWEEP=1, PG_MIXED=1),
                                       dict(PG_EDGE=0, PG_SWEEP=1, PG_LIGHT=0, PG_LAZY=1), dict(PG_EDGE=1)], ids=str)
 def test_bytes_of_a_run_are_those_of_its_launches(graph, settings):
-    from contextlib import ExitStack
     from paper_2008_01425_amd import binding as B
     from paper_2008_01425_amd.device import GossipBuffers
     for rank, steps in ((1, 1), (2, 2)):
-        wl = _workload(graph, [(64, 96), (33, 130), (100, 1), (7, 8)], rank, steps)
+        wl = _workload(graph, [(64, 96), (33, 130), (100, 1), (7, 8)] + ([(5, 12001)] if settings.get("PG_SWEEP") else []), rank, steps)
         print(f"case {wl.name} {settings}", flush=True)
-        with ExitStack() as held:
-            for name, value in settings.items():
-                held.enter_context(env_setting(name, value))
+        with env_settings(settings):
             gb = GossipBuffers.from_workload(wl)
         for rounds in (1, 2, 3, 4):
             B.pg_profile_enable(gb.ctx, True)

@@ -8,7 +8,7 @@ from paper_2008_01425_amd import workloads as W
 import os
 import time
 
-from parity_util import TOL_1, TOL_10, compare_state, oracle_rounds, rel_err
+from parity_util import PATHS, TOL_1, TOL_10, compare_state, env_settings, launched, oracle_rounds, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -434,6 +434,28 @@ def test_run_equals_repeated_round_bitwise():
     a.run(4)
     for _ in range(4):
         b.round()
+    for i in range(6):
+        assert np.array_equal(a.x[i].cpu().numpy(), b.x[i].cpu().numpy())
+    assert np.array_equal(a.q.cpu().numpy(), b.q.cpu().numpy())
+    a.close(); b.close()
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("rank,steps", [(1, 1), (2, 2)])
+def test_run_equals_repeated_round_bitwise_on_every_path(path, rank, steps):
+    """On the streaming kernels a run shares a pass between an update and the next product, on edge kernels it applies
+    an update in the next round's launch; edge sweeps run their rounds."""
+    wl = _custom("fuse_eq", 6, W.ring_edges(6), 1 / 3, [(60, 90) if path == "edge kernels" else (96, 260), (50, 1), (31, 27)], rank, steps)
+    with env_settings(PATHS[path]):
+        a, b = _gb(wl), _gb(wl)
+    print(f"case {path} rank {rank}", flush=True)
+    run, rounds = launched(a, lambda: a.run(4)), launched(b, lambda: [b.round() for _ in range(4)])
+    if path == "streaming kernels":
+        assert run["update_sweep_p"] > 0 and "update_sweep_p" not in rounds, (run, rounds)
+    elif path == "edge kernels":
+        assert run == {"edge": 4, "update": 1} and rounds == {"edge": 4, "update": 4}, (run, rounds)
+    else:
+        assert run == rounds and run["edge_sweep"] == 4 * steps, (run, rounds)
     for i in range(6):
         assert np.array_equal(a.x[i].cpu().numpy(), b.x[i].cpu().numpy())
     assert np.array_equal(a.q.cpu().numpy(), b.q.cpu().numpy())

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2008_01425_amd import workloads as W
-from parity_util import TOL_1, TOL_10, compare_state, env_setting, oracle_rounds
+from parity_util import PATHS, TOL_1, TOL_10, compare_state, env_settings, launched, oracle_rounds
 
 pytestmark = pytest.mark.gpu
 
@@ -41,22 +41,45 @@ def _random_problem(seed):
                       float(rng.choice([0.02, 0.1, 0.5])), 10, 1000 + seed)
 
 
+def _of_path(path, seed):
+    """The problem of this seed; for edge kernels of its small layers, at most rank 4."""
+    wl = _random_problem(seed)
+    if path == "edge kernels":
+        small = [s for s in wl.shapes if s[0] * s[1] <= 512 * 4 and s[0] <= 512] or [(40, 37)]
+        wl = W.Workload(wl.name, wl.n_workers, wl.edges, wl.edge_w, small, min(wl.rank, 4), wl.power_steps, wl.sigma, 10, 1000 + seed)
+    return wl
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_problem_one_round_and_a_short_fused_run(seed):
-    from paper_2008_01425_amd.device import GossipBuffers
-    wl = _random_problem(seed)
-    layers = list(range(len(wl.shapes)))
-    print(f"case {wl.name}: n={wl.n_workers} edges={wl.edges.tolist()} shapes={wl.shapes} rank={wl.rank} "
-          f"steps={wl.power_steps} sigma={wl.sigma}", flush=True)
-    X, Q = wl.all_params(), wl.all_q()
     # even seeds with the row blocking of large parameter sets, odd seeds with that of small ones
     # (by size all of these problems would get the latter)
-    with env_setting("PG_LIGHT", seed % 2):
+    _round_and_run(_random_problem(seed), dict(PG_LIGHT=seed % 2))
+
+
+@pytest.mark.parametrize("path", ["by rule", "edge kernels", "edge sweeps"])
+@pytest.mark.parametrize("seed", range(24))
+def test_random_problem_one_round_and_a_short_run_on_other_kernels(seed, path):
+    wl = _of_path(path, seed)
+    kinds = _round_and_run(wl, PATHS.get(path, {}))
+    if path == "edge kernels":
+        assert "edge" in kinds, kinds
+    if path == "edge sweeps" and wl.rank <= 4:
+        assert "edge_sweep" in kinds, kinds
+
+
+def _round_and_run(wl, settings):
+    from paper_2008_01425_amd.device import GossipBuffers
+    layers = list(range(len(wl.shapes)))
+    print(f"case {wl.name}: n={wl.n_workers} edges={wl.edges.tolist()} shapes={wl.shapes} rank={wl.rank} "
+          f"steps={wl.power_steps} sigma={wl.sigma} {settings}", flush=True)
+    X, Q = wl.all_params(), wl.all_q()
+    with env_settings(settings):
         a = GossipBuffers.from_workload(wl, fill=False)
         b = GossipBuffers.from_workload(wl, fill=False)
     a.fill_from_arrays(X, Q)
     b.fill_from_arrays(X, Q)
-    a.round()
+    kinds = launched(a, a.round)
     b.run(2)
     b.round()
     info, snaps = oracle_rounds(wl, X, Q, 3, layers, snap_at=(1,))
@@ -68,16 +91,26 @@ def test_random_problem_one_round_and_a_short_fused_run(seed):
     print("   worst rel err", w1, w3, flush=True)
     a.close()
     b.close()
+    return kinds
 
 
 @pytest.mark.parametrize("seed", range(100, 112))
 def test_random_problem_sgd_step_and_single_iterations(seed):
+    _sgd_and_iterations(_random_problem(seed), seed, dict(PG_LIGHT=seed % 2))
+
+
+@pytest.mark.parametrize("path", ["by rule", "edge kernels", "edge sweeps"])
+@pytest.mark.parametrize("seed", range(100, 112))
+def test_random_problem_sgd_step_and_single_iterations_on_other_kernels(seed, path):
+    _sgd_and_iterations(_of_path(path, seed), seed, PATHS.get(path, {}))
+
+
+def _sgd_and_iterations(wl, seed, settings):
     """The same random problems through Algorithm 1's step (gradient folded into the update) and
     through Algorithm 2 one iteration at a time (with and without a gradient)."""
     from oracle import pg_oracle as O
     from parity_util import oracle_problem, rel_err
     from paper_2008_01425_amd.device import GossipBuffers
-    wl = _random_problem(seed)
     L, E, n = len(wl.shapes), wl.n_edges, wl.n_workers
     layers = list(range(L))
     print(f"case {wl.name}: n={n} edges={wl.edges.tolist()} shapes={wl.shapes} rank={wl.rank} steps={wl.power_steps}",
@@ -88,7 +121,7 @@ def test_random_problem_sgd_step_and_single_iterations(seed):
     eta = 0.05
     # Algorithm 1's step
     X, Q = wl.all_params(), wl.all_q()
-    with env_setting("PG_LIGHT", seed % 2):
+    with env_settings(settings):
         gb = GossipBuffers.from_workload(wl, fill=False)
     gb.fill_from_arrays(X, Q)
     gb.alloc_grads()
@@ -102,7 +135,7 @@ def test_random_problem_sgd_step_and_single_iterations(seed):
     # Algorithm 2, iterations 1, 2 and 3 in two calls, the second with the gradient
     X, Vq = wl.all_params(), wl.all_q()
     Vp = [[np.zeros((wl.layer_rank(l), wl.shapes[l][0]), np.float32) for l in layers] for _ in range(E)]
-    with env_setting("PG_LIGHT", seed % 2):
+    with env_settings(settings):
         gb = GossipBuffers.from_workload(wl, fill=False)
     gb.fill_from_arrays(X, Vq)
     gb.alloc_pstate()

@@ -416,3 +416,21 @@ def test_wide_kernels_of_whole_units_keep_their_registers():
         used = (kernel[".vgpr_count"] + kernel.get(".agpr_count", 0) + 7) // 8 * 8
         assert 512 // used >= waves, (name, used)
         assert kernel[".vgpr_spill_count"] == 0, name
+
+
+def test_edge_kernels_and_sweeps_keep_their_registers():
+    """Two wavefronts per SIMD for every body of an edge kernel or a sweep, four for the updates and the finishing kernel that go
+    by the registers of up to four columns; none in scratch memory."""
+    import code_objects
+    kernels = code_objects.kernels(B.LIB_PATH)
+    waves = {"edge_kernel<": 2, "edge_pending_kernel<": 2, "edge_iterate_kernel<": 2, "sweep_kernel<": 2, "sweep_finish_kernel<": 4,
+             "apply_kernel<": 4, "apply_mixed_kernel<": 3}
+    found = dict.fromkeys(waves, 0)
+    for name, kernel in kernels.items():
+        for stem, least in waves.items():
+            if name.startswith("pg::" + stem):
+                used = (kernel[".vgpr_count"] + kernel.get(".agpr_count", 0) + 7) // 8 * 8
+                assert 512 // used >= least, (name, used)
+                assert kernel[".vgpr_spill_count"] == 0 and kernel[".private_segment_fixed_size"] == 0, name
+                found[stem] += 1
+    assert all(found.values()), found
