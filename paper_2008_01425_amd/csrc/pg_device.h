@@ -61,6 +61,15 @@ __device__ __forceinline__ void stgx(float *p, typename VecT<V>::T v) {
     }
 }
 __device__ __forceinline__ float ldg1(const float *p) { return *(const PG_GLOBAL float *)p; }
+// The same at a byte offset of 32 bits from a base of the whole wavefront.
+__device__ __forceinline__ void ld4_at(const float *base, uint32_t byte_off, float (&x)[4]) {
+    const float4_any t = *(const PG_GLOBAL float4_any *)((const PG_GLOBAL char *)base + byte_off);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = t[v];
+}
+__device__ __forceinline__ float ld1_at(const float *base, uint32_t byte_off) {
+    return *(const PG_GLOBAL float *)((const PG_GLOBAL char *)base + byte_off);
+}
 
 // Which tile this work-group takes: the tile list in order, or backwards, so that a pass can start
 // on the data the previous pass touched last (still resident in the memory-side cache).
@@ -124,6 +133,21 @@ __device__ __forceinline__ void group_sum_all(double (&v)[N], int width) {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], 32);
     }
+}
+
+// a and b, summed over the two halves of the wavefront: a's sums in the lower half's lanes, b's in the upper's
+__device__ __forceinline__ double fold32(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const u2 hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// the same over neighbouring rows of 16 lanes: a's sums in the even rows, b's in the odd ones
+__device__ __forceinline__ double fold16(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const u2 hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
 
 // One thread factors G = R^T R with the dropped-column rule (flags null: not stored); everyone waits for it.

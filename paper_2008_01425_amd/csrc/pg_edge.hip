@@ -24,29 +24,6 @@ namespace pg {
 // ---------------------------------------------------------------------------------------
 enum EdgeKind { kEdgeRound = 0, kEdgeIterate = 1 };
 
-__device__ __forceinline__ void ld4_at(const float *base, uint32_t byte_off, float (&x)[4]) {
-    const float4_any t = *(const PG_GLOBAL float4_any *)((const PG_GLOBAL char *)base + byte_off);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] = t[v];
-}
-__device__ __forceinline__ float ld1_at(const float *base, uint32_t byte_off) {
-    return *(const PG_GLOBAL float *)((const PG_GLOBAL char *)base + byte_off);
-}
-// a and b, summed over the two halves of the wavefront: a's sums in the lower half's lanes, b's in the upper's
-__device__ __forceinline__ double fold32(double a, double b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-    const u2 hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-// the same over neighbouring rows of 16 lanes: a's sums in the even rows, b's in the odd ones
-__device__ __forceinline__ double fold16(double a, double b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    const u2 hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-
 // Gram-Schmidt of r columns of `len` entries (value(k, i), double) by their Gram matrix G = R^T R, with the
 // dropped-column rule of gram_factor.  Every wavefront forms it for itself: no barrier.
 template <int RMAX>

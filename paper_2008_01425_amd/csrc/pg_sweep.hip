@@ -18,20 +18,6 @@
 
 namespace pg {
 
-// a and b, each summed over the two halves of the wavefront: a's sums in the lower lanes, b's in the upper
-__device__ __forceinline__ double sweep_fold32(double a, double b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-    const u2 hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-// the same over neighbouring rows of 16 lanes: a's sums in the even rows, b's in the odd ones
-__device__ __forceinline__ double sweep_fold16(double a, double b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    const u2 hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
 __device__ __forceinline__ double row16_sum(double z) {
     z += dpp_mov<0xB1>(z);
     z += dpp_mov<0x4E>(z);
@@ -47,20 +33,20 @@ template <int N>
 __device__ __forceinline__ void wave_sums(double (&v)[N]) {
 #pragma unroll
     for (int i = 0; i + 4 <= N; i += 4) {
-        const double z = row16_sum(sweep_fold16(sweep_fold32(v[i], v[i + 2]), sweep_fold32(v[i + 1], v[i + 3])));
+        const double z = row16_sum(fold16(fold32(v[i], v[i + 2]), fold32(v[i + 1], v[i + 3])));
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[i + k] = read_lane(z, 16 * k);
     }
     if constexpr (N % 4 >= 2) {
         constexpr int i = N / 4 * 4;
-        const double f = sweep_fold32(v[i], v[i + 1]);
-        const double z = row16_sum(sweep_fold16(f, f));
+        const double f = fold32(v[i], v[i + 1]);
+        const double z = row16_sum(fold16(f, f));
         v[i] = read_lane(z, 0);
         v[i + 1] = read_lane(z, 32);
     }
     if constexpr (N % 2 == 1) {
-        const double f = sweep_fold32(v[N - 1], v[N - 1]);
-        const double z = row16_sum(sweep_fold16(f, f));
+        const double f = fold32(v[N - 1], v[N - 1]);
+        const double z = row16_sum(fold16(f, f));
         v[N - 1] = read_lane(z, 0);
     }
 }
@@ -74,16 +60,6 @@ __device__ __forceinline__ double sweep_unit_gram(int i, const int *drop) {
     int k = 0;
     while ((k + 1) * (k + 2) / 2 <= i) ++k;
     return i == k * (k + 1) / 2 + k && !drop[k] ? 1.0 : 0.0;
-}
-
-template <bool NT>
-__device__ __forceinline__ void sweep_ld4(const float *base, uint32_t byte_off, float (&x)[4]) {
-    const PG_GLOBAL float4_any *p = (const PG_GLOBAL float4_any *)((const PG_GLOBAL char *)base + byte_off);
-    float4_any t;
-    if constexpr (NT) t = __builtin_nontemporal_load(p);
-    else t = *p;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] = t[v];
 }
 
 // One tile: rows [row0, row0 + nrows) of one (edge, layer).
@@ -137,8 +113,8 @@ __device__ __forceinline__ void sweep_body(const SweepTile &t, const SweepDesc &
             const uint32_t at = 4u * (uint32_t)min(row + m, row_end - 1) * (uint32_t)d.ld;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                sweep_ld4<false>(Xa, at + col[k], x.a[m][k]);
-                sweep_ld4<false>(Xb, at + col[k], x.b[m][k]);
+                ld4_at(Xa, at + col[k], x.a[m][k]);
+                ld4_at(Xb, at + col[k], x.b[m][k]);
             }
         }
     };
@@ -492,8 +468,8 @@ __device__ __forceinline__ void sweep_long_body(const SweepTile &t, const SweepD
     auto diff = [&](int row, int u, double (&D)[4]) {
         float a[4], b[4];
         const uint32_t at = 4u * ((uint32_t)row * (uint32_t)d.ld + (uint32_t)min(4 * u, last));
-        sweep_ld4<false>(Xa, at, a);
-        sweep_ld4<false>(Xb, at, b);
+        ld4_at(Xa, at, a);
+        ld4_at(Xb, at, b);
 #pragma unroll
         for (int v = 0; v < 4; ++v) D[v] = (double)a[v] - (double)b[v];
     };
@@ -512,7 +488,7 @@ __device__ __forceinline__ void sweep_long_body(const SweepTile &t, const SweepD
                 for (int j = 0; j < RM; ++j) {
                     if (j >= r) continue;
                     float w[4];
-                    sweep_ld4<false>(qin + d.q_off + (int64_t)j * q, 4u * (uint32_t)c, w);
+                    ld4_at(qin + d.q_off + (int64_t)j * q, 4u * (uint32_t)c, w);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) p[j] = fma(v < back ? 0.0 : D[i][v], (double)w[v], p[j]);
                 }
