@@ -766,7 +766,8 @@ int pg_init(pg_ctx **out, int n_workers, int n_edges, const int32_t *edges, cons
     if (const char *e = getenv("PG_VEC_KERNELS")) tune.vec_kernels = std::min(2, std::max(0, atoi(e)));
     // a setting of the streaming kernels keeps a small set on them
     for (const char *name : {"PG_MFMA_ROWS", "PG_MFMA_COLS", "PG_LAZY", "PG_STREAM", "PG_ODD_ROWS", "PG_WIDE_UNITS", "PG_LIGHT",
-                             "PG_VEC_KERNELS", "PG_MFMA_ROW_COLS", "PG_ROW_TILE_BYTES", "PG_COL_TILE_BYTES"})
+                             "PG_VEC_KERNELS", "PG_MFMA_ROW_COLS", "PG_ROW_TILE_BYTES", "PG_COL_TILE_BYTES", "PG_WIDE_TILE_BYTES",
+                             "PG_MCOL_TILE_BYTES", "PG_MCOL_STAGE"})
         if (getenv(name)) tune.edge = tune.sweep = 0;
     if (const char *e = getenv("PG_SWEEP")) tune.sweep = atoi(e) != 0;
     if (const char *e = getenv("PG_SWEEP_TILE_BYTES")) tune.sweep_tile_bytes = std::max(1024, atoi(e));

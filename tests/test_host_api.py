@@ -9,7 +9,7 @@ import pytest
 
 from paper_2008_01425_amd import binding as B
 from paper_2008_01425_amd import workloads as W
-from parity_util import env_setting
+from parity_util import env_setting, env_settings
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -172,6 +172,19 @@ def test_bytes_of_a_run_follow_the_path_it_takes():
         ctx = _init(20, [[0, k] for k in range(1, 20)], 0.05, hub, 1, 1)   # 19 stacked columns: two passes for worker 0
     assert B.pg_run_bytes(ctx, 3) == 3 * B.pg_round_bytes(ctx, False)
     B.pg_destroy(ctx)
+
+
+@pytest.mark.parametrize("name", ["PG_MFMA_ROWS", "PG_MFMA_COLS", "PG_STREAM", "PG_ODD_ROWS", "PG_WIDE_UNITS", "PG_LIGHT", "PG_VEC_KERNELS",
+                                  "PG_ROW_TILE_BYTES", "PG_COL_TILE_BYTES", "PG_WIDE_TILE_BYTES", "PG_MCOL_TILE_BYTES", "PG_MCOL_STAGE"])
+def test_a_setting_of_the_streaming_kernels_keeps_a_set_on_them(name):
+    for shapes in ([(100, 100)], [(300, 577), (64, 1)]):       # edge kernels; edge sweeps
+        moved = []
+        for settings in ({}, dict(PG_EDGE=0, PG_SWEEP=0), {name: 65536 if name.endswith("BYTES") else 1}):
+            with env_settings(settings):
+                ctx = _init(8, W.ring_edges(8), 1 / 3, shapes, 1, 2)
+            moved.append(B.pg_run_bytes(ctx, 1))
+            B.pg_destroy(ctx)
+        assert moved[0] < moved[1] == moved[2], (shapes, moved)
 
 
 def test_rows_are_padded_to_whole_lines_only_where_wavefronts_share_rows():
