@@ -194,12 +194,14 @@ struct MixedTile {
 constexpr int kSweepMaxRank = 4;
 constexpr int kSweepGram = 10;         // Gram sums per row block (rank 4)
 constexpr int kSweepVectorRows = 512;  // vectors up to this length are one wavefront's
-constexpr int kSweepExactSize = 10000; // elements up to which a layer is walked twice
-constexpr int kSweepExactRows = 2048;  // rows x rank of such a layer (its P lies in LDS)
+constexpr int kSweepExactSize = 10000; // elements up to which a layer is walked twice (rows under four floats: rows x rank as well)
+constexpr int kSweepExactRows = 2048;  // rows x rank of such a layer with longer rows (its P lies in LDS)
 constexpr int64_t kSweepMixedBytes = 160ll << 20;  // parameter bytes (all workers) up to which mixed degrees alone decide
 constexpr int kSweepLongRows = 8;      // most rows of a tile whose rows are too long for the registers
 constexpr int kSweepLdsBytes = 152 * 1024;
-constexpr double kSweepSpreadBytes = 8.0 * (1 << 20);  // sets up to which a row block's edges are spread over the dies
+// Sets (bytes read, both ends of every edge) up to which a row block's edges are spread over the dies, so that all of them have work:
+// rounds of 70 drawn sets, kept together over spread: up to this limit 0.99-1.07 (mean 1.02), above 0.92-1.08 (mean 0.97).
+constexpr double kSweepSpreadBytes = 8.0 * (1 << 20);
 struct SweepDesc {
     int32_t p, q, r, ld;
     int32_t wa, wb;          // the edge's workers

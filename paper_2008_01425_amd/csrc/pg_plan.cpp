@@ -117,8 +117,8 @@ static bool gains_sweeps(const Plan &P, size_t max_deg, double total_bytes) {
     return mixed || heavy <= 0.25 * P.elems_per_worker;
 }
 // Threads side by side over a row's units (log2) and units per thread of the edge sweeps: the split that covers the row with the
-// fewest idle units, of those the one with the most units per thread.  At rank 3 and 4 the sums of five units per
-// thread do not fit the registers.
+// fewest idle units, of those the one with the most units per thread.  Five units are compiled at rank 1 only: their sums in double are
+// 40 registers per column, at rank 3 and 4 more than half of what a thread has; at rank 2 they have not been tried.
 static bool sweep_split(const LayerInfo &L, int nt, int rank, int max_units, SweepDesc &d) {
     const int nv = (L.q + 3) / 4;
     int best = 0;
@@ -812,7 +812,8 @@ int build_plan(Plan &P, int n_workers, int n_edges, const int32_t *edges, const 
     }
     if (P.sweep) {
         // Row blocks: two work-groups per CU take the whole set where it is small enough, at most 1.5 MB each.  The blocks' column sums
-        // cost r / rows of the traffic and the time to add them up, so a block has 16 r rows, unless that leaves the chip idle.
+        // cost r / rows of the traffic and the time to add them up, so a block has 16 r rows, unless that leaves fewer
+        // blocks than CUs; then 8 r, then 4 r.  (Rounds of 70 drawn sets over this: always 16 r 0.98-1.40, always 8 r 0.89-1.11, 4 r 0.86-1.16.)
         const int nt = P.sweep_threads;
         const double connected = (double)std::count_if(P.incident.begin(), P.incident.end(), [](const std::vector<int> &e) { return !e.empty(); });
         P.sweep_elems = P.elems_per_worker * connected;
