@@ -173,6 +173,7 @@ def main():
                     help="hardware-counter run (under rocprofv3 --pmc): only pg_run and pg_round of the "
                          "headline workload, then 5 plain device copies of this many MiB (known traffic "
                          "that scales the byte counters)")
+    ap.add_argument("--counters-sgd", action="store_true", help="such a run over pg_round_sgd as well")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on ONE GPU (all simulated workers share its HBM); "
@@ -202,6 +203,10 @@ def main():
     if args.counters > 0:
         for _ in range(K):
             gb.round()
+        if args.counters_sgd:
+            gb.alloc_grads()
+            for _ in range(K):
+                gb.round_sgd(0.1)
         torch.cuda.synchronize()
         n = args.counters * (1 << 20) // 4
         src = torch.ones(n, dtype=torch.float32, device="cuda")
