@@ -547,7 +547,7 @@ struct Launcher {
         end();
         if (status) return;
         begin(K_FINISH, 4.0 * P.sweep_long_elems);
-        launch_sweep_finish(l, c->d_finish, (unsigned)P.finish_tiles.size());
+        launch_sweep_finish(l, c->d_finish, (unsigned)P.finish_tiles.size(), P.sweep_long_elems > 0);
         check();
         end();
         turn();

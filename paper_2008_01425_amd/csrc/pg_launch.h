@@ -39,6 +39,6 @@ struct SweepLaunch {
     int32_t *flags;
 };
 void launch_sweep(const SweepLaunch &l);
-void launch_sweep_finish(const SweepLaunch &l, const FinishTile *tiles, unsigned ntiles);
+void launch_sweep_finish(const SweepLaunch &l, const FinishTile *tiles, unsigned ntiles, bool long_rows);
 
 }  // namespace pg

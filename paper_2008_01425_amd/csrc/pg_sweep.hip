@@ -561,9 +561,9 @@ sweep_kernel(const SweepTile *__restrict__ tiles, int nslots, int reverse, const
 
 // What is left of a power step per (edge, layer): the factor R of the Gram matrix, Phat = P R^-1 and Q' = (D^T P) R^-1 by forward
 // substitution, rounded to float; the column of a dropped Phat is zero and its Q column keeps its old state.  A tile is a run of
-// the p rows of P followed by the q entries of Q', all r columns; the sums over the blocks run in a fixed order.  Of layers whose rows are too
-// long for the sweep's registers it forms D^T P itself, entry by entry over the rows.
-template <int RM>
+// the p rows of P followed by the q entries of Q', all r columns; the sums over the blocks run in a fixed order.  LONG (sets that have such):
+// of layers whose rows are too long for the sweep's registers it forms D^T P itself, entry by entry over the rows.
+template <int RM, bool LONG>
 __global__ void __launch_bounds__(kThreads)
 sweep_finish_kernel(const FinishTile *__restrict__ tiles, const SweepDesc *__restrict__ descs, float *const *__restrict__ xs,
                     const double *__restrict__ part, float *__restrict__ qstate, float *__restrict__ phat, int32_t *__restrict__ flags) {
@@ -581,7 +581,7 @@ sweep_finish_kernel(const FinishTile *__restrict__ tiles, const SweepDesc *__res
 #pragma unroll
             for (int k = 0; k < RM; ++k)
                 if (k < r) v[k] = part[d.pe_off + (int64_t)k * d.p + i];
-        } else if (i < d.p + d.q && d.units == 0 && d.q >= 4) {
+        } else if (LONG && i < d.p + d.q && d.units == 0 && d.q >= 4) {
             const float *Xa = xs[d.wa] + d.x_off + (i - d.p), *Xb = xs[d.wb] + d.x_off + (i - d.p);
             constexpr int U = 8;  // rows in flight
             for (int m = 0; m < d.p; m += U) {
@@ -686,8 +686,9 @@ void launch_sweep(const SweepLaunch &l) {
         else sweep_launch<512, 4>(l);
     }
 }
-void launch_sweep_finish(const SweepLaunch &l, const FinishTile *tiles, unsigned ntiles) {
-#define PG_FINISH(RM) sweep_finish_kernel<RM><<<dim3(ntiles), dim3(kThreads), 0, l.stream>>>(tiles, l.descs, l.xs, l.part, l.qstate, l.phat, l.flags)
+void launch_sweep_finish(const SweepLaunch &l, const FinishTile *tiles, unsigned ntiles, bool long_rows) {
+#define PG_FINISH(RM) do { if (long_rows) sweep_finish_kernel<RM, true><<<dim3(ntiles), dim3(kThreads), 0, l.stream>>>(tiles, l.descs, l.xs, l.part, l.qstate, l.phat, l.flags); \
+        else sweep_finish_kernel<RM, false><<<dim3(ntiles), dim3(kThreads), 0, l.stream>>>(tiles, l.descs, l.xs, l.part, l.qstate, l.phat, l.flags); } while (0)
     if (l.rank <= 1) PG_FINISH(1);
     else if (l.rank <= 2) PG_FINISH(2);
     else PG_FINISH(4);
