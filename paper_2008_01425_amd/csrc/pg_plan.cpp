@@ -207,10 +207,11 @@ static StepTimes step_times(const Plan &P) {
     T.fused = 4.4 * P.row_classes.size() + 0.4 * read;
     return T;
 }
-// What the streaming kernels' time has to be of the sweeps'.  Of 1364 drawn sets that the rule above takes, 230 were slower with the sweeps in some call by
-// more than 4 % (single rounds, SGD rounds, runs of two and five), 150 by more than 10 %; of the 997 that these lines leave, 38 and 13.  Sets of
-// few workers, whose streaming passes are short, and of many edges per worker are overrated by the estimate.
-constexpr double kSweepGain = 0.95, kSweepGainFew = 1.2;
+// What the streaming kernels' time has to be of the sweeps'.  2477 other drawn sets that the rule above takes, single rounds and runs of two and of five,
+// faster or slower by more than 4 % (10 %) in every call, or in some: all of them with the sweeps, 214 (126) slower; with the sets that these lines leave
+// on the streaming kernels, 93 (35) slower and 103 (68) left that would have been faster; at 0.95 and 1.2, 68 (20) and 275 (199).  Sets of few workers, whose
+// streaming passes are short, and of many edges per worker are overrated by the estimate.
+constexpr double kSweepGain = 0.85, kSweepGainFew = 1.0;
 static bool sweeps_are_faster(const Plan &P) {
     const StepTimes T = step_times(P);
     int workers = 0;
