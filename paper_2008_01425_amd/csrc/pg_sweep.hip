@@ -11,8 +11,8 @@
 // 2048 x 4608 on 16 workers, ring, 604 MB: 111 us, 5.4 TB/s of parameters read once (a plain read pass takes 101 us); with
 // the edges spread over the dies 163 us.
 //
-// Measured, streaming kernels -> sweeps: VGG-16 shapes, ring of 16, SGD round 812 -> 736 us (this kernel 225 us for 0.94 GB, issue of a row's chain and
-// HBM about even); ResNet-20 shapes, ring of 8, SGD round 29.8 -> 23.3 us; eight layers of odd lengths on a tree of 11 at rank 3 466 -> 329 us.
+// Measured, streaming kernels -> sweeps: VGG-16 shapes, ring of 16, SGD round 812 -> 735 us (this kernel 225 us for 0.94 GB, issue of a row's chain and
+// HBM about even); ResNet-20 shapes, ring of 8, SGD round 29.8 -> 23.9 us; eight layers of odd lengths on a tree of 11 at rank 3 466 -> 249 us, with the update in one launch.
 #include "pg_device.h"
 #include "pg_launch.h"
 
